@@ -48,7 +48,7 @@ def _run(cmd, verbose):
 
 def build(verbose: bool = True) -> str:
     common = [hipcc_path(), "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
-              # no packed-fp32 instruction forms on the test machines
+              # no packed-fp32 instruction forms (some have given wrong results on this hardware)
               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
               "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]
     os.makedirs(OBJ_DIR, exist_ok=True)

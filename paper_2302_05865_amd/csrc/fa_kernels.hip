@@ -132,6 +132,8 @@ __device__ __forceinline__ uint4 load16_guarded(const unsigned char* base, int64
 // T   = number of 16-column blocks (p <= 16 T)
 // CPL = columns covered by one load instruction (1: a wave reads 1 KiB of one column;
 //       4: 256 B of each of four columns, which keeps the LDS tile small for large p)
+// skip: worker-major storage only, the p columns are gradients 0 .. p without gradient `skip`,
+//       whose place is not read (skip >= p: the first p gradients)
 __device__ __forceinline__ void wave_lds_fence() {
   // orders this wavefront's LDS accesses for the compiler; the hardware executes one
   // wavefront's LDS instructions in order
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
                                                      int64_t ldg, int p, int64_t n,
                                                      int64_t ntiles,
                                                      double* __restrict__ partials,
-                                                     const int* __restrict__ gate) {
+                                                     const int* __restrict__ gate, int skip) {
   // as the stand-by of the bf16 matrix-core pass: nothing to do unless that one overflowed
   if (gate != nullptr && *gate == 0) return;
   constexpr int EPL = E::EPL;
@@ -199,7 +201,8 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   for (int cg = 0; cg < NCG; ++cg) {
     const int col = cg * CPL + lcol;
     colon[cg] = col < p;
-    colbase[cg] = G + (int64_t)(colon[cg] ? col : p - 1) * ldg * E::SIZE;
+    const int src = colon[cg] ? col : p - 1;
+    colbase[cg] = G + (int64_t)(src + (src >= skip ? 1 : 0)) * ldg * E::SIZE;
   }
 
   // interleaved storage: (row in tile, column) of the first element of each of this lane's
@@ -634,12 +637,16 @@ __global__ __launch_bounds__(256) void fa_restream_weights_kernel(const fa_info*
 // TM > 0: the tiles are the T x TM blocks of a p x m matrix (row-major, leading dimension m).
 // colscale (may be null; symmetric case only): entry (i, j) is multiplied by u_i u_j, which
 // makes the result the Gram matrix G^T W G of the columns scaled by u = W^(1/2).
+// add (symmetric case only): the sums are those of some rows of G and are added to K, whose
+// order is ldk; the pass behind them left out gradient `skip`, so column g of the tiles is
+// gradient g + (g >= skip).
 __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __restrict__ partials,
                                                               int nparts, int T, int p,
                                                               double* __restrict__ K, int TM,
                                                               int m,
                                                               const double* __restrict__ colscale,
-                                                              const int* __restrict__ gate) {
+                                                              const int* __restrict__ gate,
+                                                              int add, int ldk, int skip) {
   if (gate != nullptr && *gate == 0) return;   // stand-by of a pass that did not need it
   const int NTP = TM > 0 ? T * TM : T * (T + 1) / 2;
   const int ei = threadIdx.x & 63, g = threadIdx.x >> 6;   // entry, strand 0..15
@@ -681,6 +688,13 @@ __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __re
         if (k == tp) { ta = aa; tb = bb; }
     const int gi = ta * 16 + 4 * r + (l >> 4), gj = tb * 16 + (l & 15);
     if (gi < p && gj < p && gi <= gj) {
+      if (add) {
+        const int ki = gi + (gi >= skip ? 1 : 0), kj = gj + (gj >= skip ? 1 : 0);
+        const double v = K[ki * ldk + kj] + tot;   // (both triangles hold the same bits)
+        K[ki * ldk + kj] = v;
+        K[kj * ldk + ki] = v;
+        return;
+      }
       const double v = colscale ? tot * (colscale[gi] * colscale[gj]) : tot;
       K[gi * p + gj] = v;
       K[gj * p + gi] = v;
@@ -793,9 +807,10 @@ __global__ __launch_bounds__(256) void fa_combine_kernel(const unsigned char* __
 }
 
 // ------------------------------------------------------------------------------------------
-// One row of the Gram matrix: k_u = g_i . g_{cols[u]} for up to FA_ROW_JB resident gradients,
-// for a parameter server that extends K as the gradients arrive (Alg. 1: the server receives
-// the p workers' gradients) instead of waiting for all of them.  Each thread owns 16 bytes of
+// One row of the Gram matrix: k_u = g_i . g_{cols[u]} for up to FA_ROW_JB gradients: what is left
+// to do for some rows of a wide set (p > 16) when the last gradient to hold them lands and the
+// others' share of K is there already (Alg. 1: the server receives the p workers' gradients; see
+// fa_gram_update_rows).  Each thread owns 16 bytes of
 // gradient i and of every listed gradient per pass; products of the stored values are exact
 // in fp64 and are added in fp64.  Static chunk -> workgroup map, fixed-order sums inside the
 // workgroup: one partial row per workgroup, bitwise reproducible.
@@ -901,20 +916,16 @@ hipError_t fa_launch_zero(double* dst, int count, hipStream_t st) {
 }
 
 hipError_t fa_launch_gram_row(const void* G, int64_t ldg, int p, int64_t n, int dtype, int i,
-                              uint64_t resident, double* partials, int max_parts, double* Kd,
-                              hipStream_t st) {
+                              double* partials, int max_parts, double* Kd, hipStream_t st) {
   const int epl = dtype == FA_F32 ? 4 : 8;
   const int64_t ngroups = (n + epl - 1) / epl;
   int64_t blocks = (ngroups + 255) / 256;
   if (blocks > max_parts) blocks = max_parts;
-  // gradient i against itself and against every resident one, FA_ROW_JB of them per pass
-  int list[FA_P_MAX], nl = 0;
-  for (int j = 0; j < p; ++j)
-    if (j == i || ((resident >> j) & 1u)) list[nl++] = j;
-  for (int a0 = 0; a0 < nl; a0 += FA_ROW_JB) {
+  // gradient i against itself and against every other one, FA_ROW_JB of them per pass
+  for (int a0 = 0; a0 < p; a0 += FA_ROW_JB) {
     fa_row_cols cols;
-    const int nj = nl - a0 < FA_ROW_JB ? nl - a0 : FA_ROW_JB;
-    for (int u = 0; u < FA_ROW_JB; ++u) cols.idx[u] = list[a0 + (u < nj ? u : nj - 1)];
+    const int nj = p - a0 < FA_ROW_JB ? p - a0 : FA_ROW_JB;
+    for (int u = 0; u < FA_ROW_JB; ++u) cols.idx[u] = a0 + (u < nj ? u : nj - 1);
     if (dtype == FA_F32)
       hipLaunchKernelGGL((fa_gram_row_kernel<ElemF32>), dim3((unsigned)blocks), dim3(256), 0, st,
                          (const unsigned char*)G, ldg, n, i, cols, nj, partials);
@@ -1381,7 +1392,7 @@ size_t fa_irls_lds_bytes(int p, int* big_in_global) {
 template <int T, int CPL, typename E, int WAVES, bool ROWS>
 static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, int max_blocks,
                                 double* partials, int* nparts, hipStream_t st,
-                                const fa_ktime* tm, const int* gate) {
+                                const fa_ktime* tm, const int* gate, int skip = 1 << 30) {
   static_assert(WAVES <= FA_GRAM_WAVES_PER_CU, "partials buffer is sized for this many");
   constexpr int R = (64 / CPL) * E::EPL;
   constexpr int CS = R * E::SIZE + 16;
@@ -1395,7 +1406,7 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
   *nparts = (int)wgs;
   FA_LAUNCH(tm, (fa_gram_kernel<T, CPL, E, WAVES, ROWS>), dim3((unsigned)wgs),
             dim3(64 * WAVES), lds_bytes, st, (const unsigned char*)G, ldg, p, n, ntiles,
-            partials, gate);
+            partials, gate, skip);
   return hipGetLastError();
 }
 
@@ -1406,11 +1417,11 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
 template <typename E, bool ROWS>
 static hipError_t launch_gram_e(const void* G, int64_t ldg, int p, int64_t n, int max_blocks,
                                 double* partials, int* nparts, hipStream_t st,
-                                const fa_ktime* tm, const int* gate) {
+                                const fa_ktime* tm, const int* gate, int skip = 1 << 30) {
   switch ((p + 15) / 16) {
 #define FA_X(t, cpl, w)                                                                        \
     case t: return launch_gram_t<t, cpl, E, w, ROWS>(G, ldg, p, n, max_blocks, partials, nparts, \
-                                                     st, tm, gate);
+                                                     st, tm, gate, skip);
     FA_GRAM_TILINGS(FA_X)
 #undef FA_X
   }
@@ -1456,7 +1467,27 @@ hipError_t fa_launch_gram_reduce(const double* partials, int nparts, int p, doub
   const int T = (p + 15) / 16;
   const int NTP = T * (T + 1) / 2;
   FA_LAUNCH(tm, fa_gram_reduce_kernel, dim3(NTP * 4), dim3(1024), 0, st, partials, nparts, T, p,
-            Kd, 0, 0, colscale, gate);
+            Kd, 0, 0, colscale, gate, 0, p, p);
+  return hipGetLastError();
+}
+
+// K += the Gram matrix of n rows of the p gradients without gradient `skip` (skip >= p: of all of
+// them), products and sums in fp64.  Worker-major G, pointing at the first of the rows in
+// gradient 0; Kd is p x p.
+hipError_t fa_launch_gram_add(const void* G, int64_t ldg, int p, int64_t n, int dtype, int skip,
+                              int max_blocks, double* partials, double* Kd, hipStream_t st) {
+  const int cols = skip < p ? p - 1 : p;
+  int nparts = 0;
+  hipError_t e = dtype == FA_F32
+      ? launch_gram_e<ElemF32, false>(G, ldg, cols, n, max_blocks, partials, &nparts, st, nullptr,
+                                      nullptr, skip)
+      : launch_gram_e<ElemBF16, false>(G, ldg, cols, n, max_blocks, partials, &nparts, st, nullptr,
+                                       nullptr, skip);
+  if (e != hipSuccess) return e;
+  const int T = (cols + 15) / 16, NTP = T * (T + 1) / 2;
+  hipLaunchKernelGGL(fa_gram_reduce_kernel, dim3(NTP * 4), dim3(1024), 0, st,
+                     (const double*)partials, nparts, T, cols, Kd, 0, 0, (const double*)nullptr,
+                     (const int*)nullptr, 1, p, skip);
   return hipGetLastError();
 }
 
@@ -1498,7 +1529,7 @@ hipError_t fa_launch_proj_reduce(const double* partials, int nparts, int p, int 
                                  hipStream_t st, const fa_ktime* tm) {
   const int T = (p + 15) / 16, TM = (m + 15) / 16;
   FA_LAUNCH(tm, fa_gram_reduce_kernel, dim3(T * TM * 4), dim3(1024), 0, st, partials, nparts, T,
-            p, Td, TM, m, (const double*)nullptr, (const int*)nullptr);
+            p, Td, TM, m, (const double*)nullptr, (const int*)nullptr, 0, p, p);
   return hipGetLastError();
 }
 
@@ -1538,7 +1569,7 @@ hipError_t fa_launch_cross(const float* Y, int64_t ldy, int m, const void* G, in
   const int ncols = 16 * TMr + p;
   hipLaunchKernelGGL(fa_gram_reduce_kernel, dim3(TMr * TC * 4), dim3(1024), 0, st,
                      (const double*)partials, (int)stripes, TMr, m, Wd, TC, ncols,
-                     (const double*)nullptr, (const int*)nullptr);
+                     (const double*)nullptr, (const int*)nullptr, 0, m, m);
   return hipGetLastError();
 }
 
