@@ -155,9 +155,17 @@ __device__ __forceinline__ void unpack4(const unsigned char* src, double* x) {
 
 // ROWS: G is stored row by row ("interleaved": element i of coordinate k at G + (k*ldg + i)
 // * elem_size, ldg <= 16 T).  A tile of R rows is then one contiguous span of memory; it is
-// read with the same 16-byte coalesced loads, and each lane scatters the four (eight)
-// elements of its pieces to their [column][row] places in LDS.  Where the elements of a piece
-// go is the same for every tile, so it is worked out once.
+// read with the same 16-byte coalesced loads and goes to LDS as it is, and a lane reads the
+// elements of "its" column one by one; four rows are a group, and the groups are set apart so
+// that the sixteen elements each quarter wavefront reads lie in banks of their own.  The scatter
+// of every element to a [column][row] place on the way into LDS, eight 2-byte writes per 16 bytes
+// of bf16, bounded the pass: p = 32, bf16, 8M rows 390 -> 244 us, where the matrix core alone needs
+// 156; p = 64, bf16, 2M rows 444 -> 177; p = 20, fp32, 3M rows 95 -> 90; fp32 at the other widths
+// within 3 %.  What is left is the conversions: a SIMD does not overlap them with fp64 products.
+// LDS bytes of a tile of r interleaved rows, whatever their pitch (at most 16 t elements):
+constexpr int fa_rows_tile_bytes(int t, int es, int r) {
+  return r / 4 * ((64 * t * es + 255) / 256 * 256 + 16 * es);
+}
 template <int T, int CPL, typename E, int WAVES, bool ROWS>
 __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
                                                      const unsigned char* __restrict__ G,
@@ -174,9 +182,10 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   constexpr int CS = R * E::SIZE + 16;     // LDS bytes per column (+16: bank spread)
   constexpr int NTP = T * (T + 1) / 2;
   constexpr int NSTEP = R / 16;
+  constexpr int TILE = ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : T * 16 * CS;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
   const int wave = threadIdx.x >> 6;
-  unsigned char* lds = lds_all + wave * (T * 16 * CS);
+  unsigned char* lds = lds_all + wave * TILE;
   const int64_t wid = (int64_t)blockIdx.x * WAVES + wave;   // global wave index
   const int64_t nwaves = (int64_t)gridDim.x * WAVES;
 
@@ -190,7 +199,8 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   for (int i = 0; i < NTP; ++i) acc[i] = v4f64{0.0, 0.0, 0.0, 0.0};
 
   // zero the whole tile once: columns >= p stay zero for the life of the kernel
-  for (int off = lane * 16; off < T * 16 * CS; off += 64 * 16)
+  // (interleaved storage: the span of a tile overwrites what is read of it)
+  for (int off = lane * 16; !ROWS && off < TILE; off += 64 * 16)
     *reinterpret_cast<uint4*>(lds + off) = make_uint4(0u, 0u, 0u, 0u);
 
   // this lane's source column for each load instruction (clamped: lanes of columns >= p
@@ -205,34 +215,29 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
     colbase[cg] = G + (int64_t)(src + (src >= skip ? 1 : 0)) * ldg * E::SIZE;
   }
 
-  // interleaved storage: (row in tile, column) of the first element of each of this lane's
-  // pieces; the span of a tile is R * ldg elements (<= NCG * 64 pieces)
-  int prow[NCG], pcol[NCG];
-  bool pon[NCG];
+  // interleaved storage: where each of this lane's pieces goes (the span of a tile is R * ldg
+  // elements, <= NCG * 64 pieces).  A group of four rows takes gb bytes; where those are whole
+  // 16-byte pieces (always, but for bf16 rows of odd length) the next group starts gs >= gb bytes
+  // on, gs = 16 elements modulo the 256 bytes of the 64 banks.
   const int ldr = (int)ldg;
+  const int gb = 4 * ldr * E::SIZE;
+  const int gs = (gb & 15) ? gb : gb + ((16 * E::SIZE - gb) & 255);
+  const int tb = R * ldr * E::SIZE;        // bytes of a tile's span
+  int pdst[NCG];
 #pragma unroll
   for (int cg = 0; cg < NCG; ++cg) {
-    const int e0 = (cg * 64 + lane) * EPL;
-    pon[cg] = ROWS && e0 < R * ldr;
-    prow[cg] = ROWS ? e0 / ldr : 0;
-    pcol[cg] = ROWS ? e0 - prow[cg] * ldr : 0;
+    const int b = (cg * 64 + lane) * 16;
+    pdst[cg] = ROWS ? b + (b / gb) * (gs - gb) : 0;
   }
 
   uint4 regs[NCG];
   auto load_tile = [&](int64_t tl) {
     if constexpr (ROWS) {
-      const unsigned char* base = G + tl * R * ldr * E::SIZE;
-      const int64_t rows_here = n - tl * R < R ? n - tl * R : R;
-      const int lim = (int)rows_here * ldr;          // elements of this tile that exist
+      if ((tl + 1) * R > n) return;        // the ragged last tile: see store_tile_lds
+      const unsigned char* base = G + tl * tb + lane * 16;
 #pragma unroll
-      for (int cg = 0; cg < NCG; ++cg) {
-        regs[cg] = make_uint4(0u, 0u, 0u, 0u);
-        const int e0 = (cg * 64 + lane) * EPL;
-        if (pon[cg]) {
-          if (e0 + EPL <= lim) regs[cg] = load16_stream(base + (int64_t)e0 * E::SIZE);
-          else if (e0 < lim) regs[cg] = load16_guarded<E>(base, e0, lim);
-        }
-      }
+      for (int cg = 0; cg < NCG; ++cg)
+        if ((cg * 64 + lane) * 16 < tb) regs[cg] = load16_stream(base + cg * 1024);
       return;
     }
     const int64_t row0 = tl * R + lrow;
@@ -245,25 +250,21 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
       for (int cg = 0; cg < NCG; ++cg) regs[cg] = load16_guarded<E>(colbase[cg], row0, n);
     }
   };
-  auto store_tile_lds = [&]() {
+  auto store_tile_lds = [&](int64_t tl) {
     if constexpr (ROWS) {
-#pragma unroll
-      for (int cg = 0; cg < NCG; ++cg) {
-        if (!pon[cg]) continue;
-        int r = prow[cg], c = pcol[cg];
-        const uint32_t wds[4] = {regs[cg].x, regs[cg].y, regs[cg].z, regs[cg].w};
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-          if (c < p) {
-            if constexpr (E::SIZE == 4)
-              *reinterpret_cast<uint32_t*>(lds + c * CS + r * 4) = wds[j];
-            else
-              *reinterpret_cast<uint16_t*>(lds + c * CS + r * 2) =
-                  (uint16_t)(wds[j >> 1] >> (16 * (j & 1)));
-          }
-          if (++c == ldr) { c = 0; ++r; }
-        }
+      if ((tl + 1) * R > n) {
+        // the ragged last tile straight from memory, zero past the end (rolled: once per launch)
+        const unsigned char* base = G + tl * tb;
+        const int lim = (int)(n - tl * R) * ldr;     // elements of this tile that exist
+#pragma unroll 1
+        for (int b = lane * 16; b < tb; b += 64 * 16)
+          *reinterpret_cast<uint4*>(lds + b + (b / gb) * (gs - gb)) =
+              load16_guarded<E>(base, b / E::SIZE, lim);
+        return;
       }
+#pragma unroll
+      for (int cg = 0; cg < NCG; ++cg)
+        if ((cg * 64 + lane) * 16 < tb) *reinterpret_cast<uint4*>(lds + pdst[cg]) = regs[cg];
       return;
     }
 #pragma unroll
@@ -271,28 +272,46 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
       if (colon[cg])
         *reinterpret_cast<uint4*>(lds + (cg * CPL + lcol) * CS + lrow * E::SIZE) = regs[cg];
   };
-  auto operand = [&](const unsigned char* src, int tt, double* x) { unpack4<E>(src, x); };
+  // rows 16 t + 4 kq + j (j = 0..3) of this lane's column of tile column tt.  Interleaved storage:
+  // a column >= p reads whatever comes next in the tile's LDS (a row has at most 16 T elements, so
+  // that is never past its end); it only reaches entries of its own row and column, which the
+  // reduction does not look at.
+  const unsigned char* src =
+      ROWS ? lds + kq * gs + c16 * E::SIZE : lds + c16 * CS + 4 * kq * E::SIZE;
+  auto operand = [&](int t, int tt, double* x) {
+    if constexpr (ROWS) {
+      const unsigned char* at = src + t * (4 * gs) + tt * 16 * E::SIZE;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if constexpr (E::SIZE == 4)
+          x[j] = (double)*reinterpret_cast<const float*>(at + j * ldr * 4);
+        else
+          x[j] = (double)bf16_bits_to_f32(*reinterpret_cast<const uint16_t*>(at + j * ldr * 2));
+      }
+    } else {
+      unpack4<E>(src + tt * 16 * CS + 16 * t * E::SIZE, x);
+    }
+  };
 
   wave_lds_fence();
   int64_t tile = wid;
   if (tile < ntiles) load_tile(tile);
   for (; tile < ntiles; tile += nwaves) {
     wave_lds_fence();  // the previous tile's LDS reads precede these writes
-    store_tile_lds();
+    store_tile_lds(tile);
     wave_lds_fence();
     const int64_t next = tile + nwaves;
     if (next < ntiles) load_tile(next);
 
-    const unsigned char* src = lds + c16 * CS + 4 * kq * E::SIZE;
     double xc[T][4], xn[T][4];
 #pragma unroll
-    for (int tt = 0; tt < T; ++tt) operand(src + tt * 16 * CS, tt, xc[tt]);
+    for (int tt = 0; tt < T; ++tt) operand(0, tt, xc[tt]);
 #pragma unroll 4
     for (int t = 0; t < NSTEP; ++t) {
       // operands of the next step (the last step re-reads step 0; harmless)
       const int tn = (t + 1 < NSTEP) ? t + 1 : 0;
 #pragma unroll
-      for (int tt = 0; tt < T; ++tt) operand(src + tt * 16 * CS + 16 * tn * E::SIZE, tt, xn[tt]);
+      for (int tt = 0; tt < T; ++tt) operand(tn, tt, xn[tt]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         int tp = 0;
@@ -1396,7 +1415,8 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
   static_assert(WAVES <= FA_GRAM_WAVES_PER_CU, "partials buffer is sized for this many");
   constexpr int R = (64 / CPL) * E::EPL;
   constexpr int CS = R * E::SIZE + 16;
-  constexpr size_t tile_bytes = (size_t)T * 16 * CS;
+  constexpr size_t tile_bytes =
+      ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : (size_t)T * 16 * CS;
   static_assert(WAVES * tile_bytes <= 160 * 1024, "LDS tiles of one workgroup must fit a CU");
   // more than half of the CU's 160 KiB, so that no second workgroup fits beside this one
   const size_t lds_bytes = WAVES * tile_bytes > 84 * 1024 ? WAVES * tile_bytes : 84 * 1024;
