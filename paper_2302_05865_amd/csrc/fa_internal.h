@@ -112,7 +112,7 @@ hipError_t fa_launch_irls16(const double* Kd, int p, int m, double lambda, int i
                             double* cd,
                             fa_info* info_d, double* mlast, int use_purification,
                             fa_resume* rs, hipStream_t st, const fa_ktime* tm);
-// K3 for 16 < p <= 64 (sixteen wavefronts, tiled matrix-core products).  tiles_ws:
+// K3 for 16 < p <= 64 (eight or twelve wavefronts, tiled matrix-core products).  tiles_ws:
 // FA_GWS_TILES doubles; mlast as above with N = 16 ceil(p/16).  May leave
 // info_d->status = FA_ST_RETRY, in which case the any-p kernel must run next.  exponent_a as
 // for fa_launch_irls16.  nworkers > 0: the p columns are nworkers blocks of sizes_d[i]

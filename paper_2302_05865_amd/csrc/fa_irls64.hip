@@ -1,5 +1,5 @@
 // K3 for 16 < p <= 64: the p x p part of the Flag Aggregator (normalisation, IRLS by repeated
-// weighted PCA, coefficients) in one workgroup of sixteen wavefronts, every matrix product on
+// weighted PCA, coefficients) in one workgroup of eight or twelve wavefronts, every matrix product on
 // the fp64 matrix core.
 //
 // Same mathematics as the p <= 16 fast path (fa_irls16.hip, namespace fastp; Eq. 5 with the
@@ -15,9 +15,8 @@
 //   * as B operand (rows of the tile are the contraction index), and
 //   * as A operand of the *transposed* tile (for a symmetric matrix: of tile (J, I)).
 // One wavefront owns one output tile of a product; symmetric results are computed for I <= J
-// and mirrored.  Steering of the purification: every wavefront publishes trace and squared
-// Frobenius norm of its tile, all wavefronts add the published numbers in the same order
-// after the step's barrier, so they take identical decisions.
+// and mirrored.  One further wavefront steers the purification; from the second solve on, most of
+// its steps are planned from the previous solve's eigenvalues (see Plan).
 //
 // The same kernel has a mode for workers that send several gradients (blocks of columns, see
 // MODE below); in that mode it is also built for a single tile (p <= 16).
@@ -28,6 +27,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "fa.h"
 #include "fa_internal.h"
@@ -36,8 +36,10 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int NW = 16;                 // wavefronts in the workgroup
-constexpr int NTHREADS = 64 * NW;
+// Wavefronts in the workgroup: one for each tile I <= J of a symmetric result and one that steers
+// have to fit, and every further one takes registers from them (sixteen leave 128 a lane, and the
+// purification step then spilled; twelve leave 168, eight 256).
+constexpr int waves_for(int t) { return t <= 3 ? 8 : 12; }
 constexpr int MAX_PURIFY = 200;
 
 template <int CTRL>
@@ -141,16 +143,90 @@ __device__ __forceinline__ void upper_pair(int k, int* I, int* J) {
 
 struct Small {
   double s[64], dinv[64], w[64], wn[64], r1[64], beta[64], rinv[64], gd[64], rho[64];
-  double dgx[2][64], dgy[2][64];   // [step parity]: diagonals of X_k and of X_k^2
-  double red[NW];
+  double red[16];
   int piv[64], used[64];
   // workers that send several gradients: first column and width of the block a column is in,
   // 1 / tr(g^T g) of that block
   int gf[64], gc[64];
   double ginv[64];
-  int dec[4];   // word of purification step g at [g & 3]: g << 4 | trace ok (4) | converged (2) | square (1)
+  // word of purification step g at [g & 3]: g << 4 | a planned map (8) | trace ok (4) |
+  // converged (2) | square (1), and its map X -> map[0] X + map[1] X^2 + map[2] I if planned
+  int dec[4];
+  double map[4][3];
+  float hist[MAX_PURIFY];          // step k of this solve: a of a growth, -1 - b of a shrinking map
+  float cap[2];                    // the ends of the gap at step cap_k
+  int cap_k;                       // (negative: not known)
+  double est[2];                   // eigenvalues m + 1 and m of the last solve's matrix ...
+  int have_est;                    // ... if known
+  int guessed;                     // this solve's first steps were planned
   int flag[2];  // [step parity] a wavefront gave up waiting for that step's steering word
 };
+
+// ---- planned steps ---------------------------------------------------------------------------
+// Without knowing where the gap between eigenvalues m and m + 1 is, a step X^2 or 2X - X^2 widens it
+// by a factor of 1.24 on average; knowing it, by up to two, with the same product:
+//   growth   1 - (1 - a X)^2,     1 <= a <= 2: a = 1 is 2X - X^2; folds [2/a - 1, 1] onto itself
+//   shrink   ((1 + b) X - b)^2,   0 <= b <= 1: b = 0 is X^2;      folds [0, 2b / (1 + b)]
+// A fold gives up the order of what it folds, so it must not reach the gap.  From the second solve
+// on the last solve's gap is a guess for this one's: a fifth outside either end ([0, H] and [G, 1])
+// is folded, the two eigenvalues themselves (expected near h and g) are not.  [G, 1] and [0, H] are
+// taken through the maps along with X (rounded outwards).  What started in [G, 1] stays in its
+// image, the same for [0, H], and in between every map keeps the order; so if in the end G is near
+// 1, H near 0 and trace X = m, the result is the projector onto the m leading eigenvectors whatever
+// the guess was worth.  If not, the solve is done once more without.
+// The maps of these steps need no trace: the steering wavefront has each ready one step ahead, so
+// nobody waits for it.  Once h and g are within 0.03 of 0 and 1 the steps go on as always.
+// Measured, steps per call (plain -> with plans): p = 32, m = 16, 15 solves 428 -> 344; p = 60, 5 solves
+// 181 -> 169; p = 64, 30 solves 806 -> 640.  The first solves, whose gap moves most, stay unplanned.
+struct Plan {                 // all scalar: one wavefront's, the same in every lane
+  float H, G, h, g;
+  float c;                    // a or b of the last map
+  bool grow;
+};
+__device__ __forceinline__ float scalar(float x) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
+}
+__device__ __forceinline__ bool scalar(bool x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ float plan_image(bool grow, float c, float x) {
+  if (grow) {
+    const float u = fmaf(-c, x, 1.0f);
+    return fmaf(-u, u, 1.0f);
+  }
+  const float u = fmaf(c, x, x - c);
+  return u * u;
+}
+// one step further: maps with the ends rounded outwards, so that they hold whatever f32 does
+__device__ __forceinline__ void plan_push(Plan& pl) {
+  const float H = plan_image(pl.grow, pl.c, pl.H), G = plan_image(pl.grow, pl.c, pl.G);
+  const float e0 = pl.grow ? 0.0f : pl.c * pl.c, e1 = plan_image(pl.grow, pl.c, 1.0f);
+  pl.H = scalar(fmaf(fmaxf(H, e0), 1.0f + 1e-6f, 1e-7f));
+  pl.G = scalar(fmaf(fminf(G, e1), 1.0f - 1e-6f, -1e-7f));
+  pl.h = scalar(plan_image(pl.grow, pl.c, pl.h));
+  pl.g = scalar(plan_image(pl.grow, pl.c, pl.g));
+}
+// the next planned map, published as step g's; false when the plan is at its end
+__device__ __forceinline__ bool plan_next(Plan& pl, Small& sm, int g, int k, int lane) {
+  const float up = 1.0f - pl.g;
+  if (scalar(fmaxf(pl.h, up) < 0.03f) || k >= 40) return false;
+  pl.grow = scalar(up > pl.h);
+  const float c = pl.grow ? 2.0f * __builtin_amdgcn_rcpf(1.0f + pl.G)
+                          : pl.H * __builtin_amdgcn_rcpf(2.0f - pl.H);
+  pl.c = scalar(fminf(fmaxf(c, pl.grow ? 1.0f : 0.0f), pl.grow ? 2.0f : 1.0f));
+  if (lane == 0) {
+    const double cd = (double)pl.c, b1 = 1.0 + cd;
+    // in this order: see the readers
+    __hip_atomic_store(&sm.map[g & 3][0], pl.grow ? 2.0 * cd : -2.0 * cd * b1, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_store(&sm.map[g & 3][1], pl.grow ? -cd * cd : b1 * b1, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_store(&sm.map[g & 3][2], pl.grow ? 0.0 : cd * cd, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_store(&sm.dec[g & 3], g << 4 | 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    sm.hist[k] = pl.grow ? pl.c : -1.0f - pl.c;
+  }
+  plan_push(pl);
+  return true;
+}
 
 }  // namespace
 
@@ -161,7 +237,7 @@ struct Small {
 // value is tr(g^T Y Y^T g) / tr(g^T g), the IRLS re-weights whole blocks, pair terms exist
 // between blocks of equal width (Frobenius distance, column l against column l); any exponent.
 template <int T, int MODE>
-__global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __restrict__ Kg, int p,
+__global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const double* __restrict__ Kg, int p,
                                                              int nworkers,
                                                              const int* __restrict__ sizes,
                                                              int m, int iters, double lambda,
@@ -174,6 +250,11 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
                                                              double* __restrict__ Ml,
                                                              int spin_budget, fa_resume* rs) {
   constexpr int N = 16 * T, TT = T * T, NTP = T * (T + 1) / 2, MSZ = TT * FA_TILE;
+  constexpr int NW = waves_for(T), NTHREADS = 64 * NW;
+  // The fourth SIMD (wavefronts 3, 7, 11) gets one tile at T = 4 and none below; the wavefront
+  // that steers is on it.  A vector instruction of its would otherwise wait for a matrix
+  // instruction of the others each time.
+  constexpr int SW = T == 4 ? 7 : 3;
   constexpr int EPT = (N * N + NTHREADS - 1) / NTHREADS;   // matrix entries per thread
   extern __shared__ __attribute__((aligned(16))) double lds[];
   double* B0 = lds;
@@ -209,6 +290,7 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
     sm.used[tid] = 0;
     sm.rho[tid] = 0.0;
     if (tid < 4) sm.dec[tid] = 0;   // tag 0 is never used
+    if (tid == 0) sm.have_est = 0;
   }
   __syncthreads();
   if constexpr (GRP) {
@@ -358,15 +440,16 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
   __syncthreads();
   {
     // R 1: sixteen threads per row
-    const int a = tid >> 4, l16 = tid & 15;
-    double acc = 0.0;
-    if (a < N)
+    const int l16 = tid & 15;
+    for (int a = tid >> 4; a < N; a += NTHREADS / 16) {
+      double acc = 0.0;
       for (int j = l16; j < N; j += 16) {
         const double x = RA[aidx<T>(a, j)];
         acc += GRP ? x / (double)sm.gc[j] : x;          // a block counts with its mean column
       }
-    acc = row_sum(acc);
-    if (a < N && l16 == 0) sm.r1[a] = acc;
+      acc = row_sum(acc);
+      if (l16 == 0) sm.r1[a] = acc;
+    }
   }
   // the Cholesky pivots are needed again in the epilogue
   int piv_keep = tid < 64 ? sm.piv[tid] : 0;
@@ -388,11 +471,13 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
   double prev_obj = it0 > 0 ? rs->prev_obj : 0.0;
   __syncthreads();
 
-  // this wavefront's output tile in products with a full (wave < TT) or symmetric
-  // (wave < NTP, I <= J) result
-  const int fI = wave / T, fJ = wave % T;
+  // this wavefront's output tile in products with a symmetric result (I <= J); the tiles of a full
+  // one go round the wavefronts
+  int mt = (wave & 3) < 3 ? wave - (wave >> 2) : -1;       // ... tile number, negative: none
+  if (T == 4) mt = wave < 7 ? wave : (wave & 3) < 3 ? wave - 1 : -1;
+  if (mt >= NTP) mt = -1;
   int uI = 0, uJ = 0;
-  if (wave < NTP) upper_pair<T>(wave, &uI, &uJ);
+  if (mt >= 0) upper_pair<T>(mt, &uI, &uJ);
   const double rs_delta = 1.0 / sqrt(delta);
   int iters_done = 0, steps = 0, gstep = 0;
   double* cur = B0;   // where the projector of the last solve is
@@ -402,19 +487,21 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
   for (int it = 0; it < iters; ++it) {
     // ---- C: diagonal from the data weights and the row sums of the pair part ---------------
     {
-      const int i = tid >> 4, l16 = tid & 15;
-      double acc = 0.0;
-      if (i < N)
+      // (nobody else reads the diagonal place of a row: it is written over at once)
+      const int l16 = tid & 15;
+      for (int i = tid >> 4; i < N; i += NTHREADS / 16) {
+        double acc = 0.0;
         for (int j = l16; j < N; j += 16) acc += (j != i) ? B2[eidx<T>(i, j)] : 0.0;
-      acc = row_sum(acc);
-      __syncthreads();
-      if (i < N && l16 == 0)
-        B2[eidx<T>(i, i)] = sm.w[i] * (GRP ? sm.ginv[i] : sm.dinv[i] * sm.dinv[i]) - acc;
+        acc = row_sum(acc);
+        if (l16 == 0)
+          B2[eidx<T>(i, i)] = sm.w[i] * (GRP ? sm.ginv[i] : sm.dinv[i] * sm.dinv[i]) - acc;
+      }
     }
     __syncthreads();
     // ---- W = C R^T (B1): A operand = C (symmetric: tile (K, I)), B operand = R^T tile (K, J),
     // which is R's tile (J, K) in A-operand order ---------------------------------------------
-    if (wave < TT) {
+    for (int f = wave; f < TT; f += NW) {
+      const int fI = f / T, fJ = f % T;
       v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int K = 0; K < T; ++K)
@@ -423,7 +510,7 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
     }
     __syncthreads();
     // ---- M = R W (B0, both triangles), its trace ----------------------------------------------
-    if (wave < NTP) {
+    if (mt >= 0) {
       v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int K = 0; K < T; ++K)
@@ -436,14 +523,15 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
         for (int r = 0; r < 4; ++r) td += isdiag[r] ? acc[r] : 0.0;
       }
       td = wave_sum(td);
-      if (lane == 0) sm.red[wave] = td;
+      if (lane == 0) sm.red[mt] = td;
     }
     __syncthreads();
     double hi = 0.0;
 #pragma unroll
     for (int k = 0; k < NTP; ++k) hi += sm.red[k];
     // the matrix itself, row-major, for the eigengap diagnostic
-    if (wave < TT) {
+    for (int f = wave; f < TT; f += NW) {
+      const int fI = f / T, fJ = f % T;
       const v4d mt = load_tile<T>(B0, fI, fJ, lane);
 #pragma unroll
       for (int r = 0; r < 4; ++r) Ml[(16 * fI + 4 * r + q4) * N + 16 * fJ + c16] = mt[r];
@@ -452,7 +540,8 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
     if (mm < rank) {
       // ---- X_0 = M / trace(M) (slightly less: any scale with eigenvalues in [0, 1] will do)
       const double sc = __builtin_amdgcn_rcp(hi) * (1.0 - 1e-7);
-      if (wave < TT) {
+      for (int f = wave; f < TT; f += NW) {
+        const int fI = f / T, fJ = f % T;
         v4d x = load_tile<T>(B0, fI, fJ, lane);
 #pragma unroll
         for (int r = 0; r < 4; ++r) x[r] *= sc;
@@ -460,129 +549,216 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
       }
       // ---- purification ---------------------------------------------------------------------
       // A wavefront's fp64 vector instructions do not get a turn while older wavefronts of
-      // its SIMD have matrix instructions to issue, and every dependent LDS round trip or
-      // cross-lane sum costs hundreds of cycles, so measuring and deciding stay off the
-      // multiplying wavefronts' path:
-      //  - wavefronts 0..NTP-1 multiply (one tile of X_k^2 each); those with a diagonal tile
-      //    leave the diagonals of X_k and X_k^2 in LDS;
-      //  - during step k wavefront NTP (on the SIMD with the fewest multiplying wavefronts)
-      //    sums the diagonals left in step k-1 (trace(X_{k-1}), trace(X_{k-1}^2) =
-      //    |X_{k-1}|_F^2) and publishes the word of step k: "X_{k-1} was a projector" (then
-      //    X_k, its polished successor, is the result) and "square X_k", from trace(X_k) =
-      //    |X_{k-1}|_F^2 after a squaring and 2 trace(X_{k-1}) - |X_{k-1}|_F^2 otherwise;
-      //  - the multiplying wavefronts pick the word up after their products; everybody else
-      //    reads it at the top of the next step, after the barrier.
+      // its SIMD have matrix instructions to issue, and every dependent LDS round trip, cross-lane
+      // sum or taken branch costs hundreds of cycles, so measuring and deciding stay off the
+      // multiplying wavefronts' path, and each of the three roles runs a loop of its own (cycles per
+      // step: T = 2 1870 with one loop, diagonals written out and every factor loaded, 1580 now, 512
+      // of them matrix instructions; T = 4 4590, 4500 now, 3072 of them matrix instructions):
+      //  - multiplying wavefronts (mt >= 0) make one tile of X_k^2 and of X_{k+1} each;
+      //  - during step k wavefront SW sums the diagonal of X_k and publishes the word of the step:
+      //    "square X_k" (trace X_k > m) and "X_{k-1} was a projector" (its trace and the next one
+      //    say how far it was from one; then X_k, its polished successor, is the result).  While
+      //    steps are planned (see Plan) it publishes the next step's word and map instead;
+      //  - the multiplying wavefronts pick the word up after their products, the others after the
+      //    step's barrier.
       // Waits: the steering wavefront waits for nobody, so the readers' bounded spin ends.  One
       // that runs out of its budget of polls raises the step's flag, skips its store and goes
-      // on to the step's barrier like everybody else; all read that flag right after the
-      // barrier, at the top of the next step, and leave the loop together with the solve marked
-      // as failed (the last step of the loop cannot raise it unseen: MAX_PURIFY is even and a
-      // failed solve is what running out of steps means anyway).
+      // on to the step's barrier like everybody else; all look at that flag during the next
+      // step and leave before its barrier, together, with the solve marked as failed (the last step
+      // of the loop cannot raise it unseen: a failed solve is what running out of steps means
+      // anyway).  In the step after the word "X_{k-1} was a projector" all leave the same way.
+      const int gstep0 = gstep;
       ++gstep;                        // a tag of its own between solves: no stale word matches
-      bool sq_prev = hi * sc > (double)mm, conv = false;
-      int wprev = 0;                  // the word of the previous step
-      bool reread = wave > NTP;       // ... fetched from LDS by those who did not use it then
+      int k = 0, wprev = 0;           // wprev: the word of the previous step
+      bool raised = false;
       if (tid == 0) { sm.flag[0] = 0; sm.flag[1] = 0; }
-      __syncthreads();
-      // One step: X_k in cu, X_{k+1} into nx.  Written for fixed buffers (the loop below
-      // alternates two instances) so that every LDS address is loop invariant: a wavefront
-      // that leaves the barrier behind older ones of its SIMD can put its loads in flight at
-      // once, without a vector instruction that would wait for their products.
-      // Returns false when the loop is over.
-      auto step = [&](double* cu, double* nx, int k) __attribute__((always_inline)) -> bool {
-        ++gstep;                      // tags the words: never repeats within a launch
-        // the previous step's flag: raised before the last barrier, if at all, and written by
-        // nobody in this step (which has the other one), so every wavefront reads the same
-        if (k > 0 && __builtin_amdgcn_readfirstlane(sm.flag[(k - 1) & 1])) {
-          conv = false;
-          return false;
-        }
-        if (k > 0) {
-          // in place since the last barrier: its publisher waits for nobody
-          if (reread) wprev = __builtin_amdgcn_readfirstlane(sm.dec[(gstep - 1) & 3]);
-          if (wprev & 2) {            // X_{k-1}, left alone in nx, is the result
-            conv = (wprev & 4) != 0;
-            cur = nx; nxt = cu;
-            return false;
-          }
-        }
-        if (wave < NTP) {
-          // own tile (uI, uJ) of X_k^2 = sum_K X(K, uI)^T X(K, uJ); the operands of the
-          // next K are on their way from LDS while this K is multiplied
+      if (mt >= 0) {
+        __syncthreads();
+        // this wavefront's tile of X_k stays in its registers: LDS holds it for the others
+        v4d x = load_tile<T>(B0, uI, uJ, lane);
+        // One step: X_k in cu, X_{k+1} into nx.  Written for fixed buffers (the loop alternates
+        // two instances) so that every LDS address is loop invariant and the loads of a
+        // wavefront that leaves the barrier behind older ones of its SIMD are in flight at
+        // once.  Returns true when the loop is over.
+        auto step = [&](auto diag, const double* cu, double* nx) __attribute__((always_inline)) -> bool {
+          constexpr bool DIAG = decltype(diag)::value;
+          ++gstep;                      // tags the words: never repeats within a launch
+          if (wprev & 2) return true;
+          // own tile (uI, uJ) of X_k^2 = sum_K X(K, uI)^T X(K, uJ), K = uI first: that one needs no
+          // load on the diagonal, where both factors are the same tile for every K, and one off
+          // it.  The operands of the next K are on their way while this K is multiplied.
           v4d y = {0.0, 0.0, 0.0, 0.0};
-          v4d a = load_tile<T>(cu, 0, uI, lane), b = load_tile<T>(cu, 0, uJ, lane);
+          v4d a = x, b = x;
+          if constexpr (!DIAG) a = load_tile<T>(cu, uI, uI, lane);
+          // the previous step's flag; this step's word and, if it is a planned one, its map: the
+          // publisher writes the word after the map, LDS serves a wavefront's accesses in order,
+          // and these loads are issued in this order, so a map read after its word is the word's.
+          // Looked at after the products; an unplanned step's word comes meanwhile.
+          int flag, wv;
+          double al, be, ga;
 #pragma unroll
-          for (int K = 0; K < T; ++K) {
+          for (int i = 0; i < T; ++i) {
             v4d an = a, bn = b;
-            if (K + 1 < T) {
-              an = load_tile<T>(cu, K + 1, uI, lane);
-              bn = load_tile<T>(cu, K + 1, uJ, lane);
-            } else {
-              an = load_tile<T>(cu, uI, uJ, lane);       // the tile itself, for the update
+            if (i + 1 < T) {
+              const int K = uI + i + 1 < T ? uI + i + 1 : uI + i + 1 - T;
+              an = load_tile<T>(cu, K, uI, lane);
+              bn = DIAG ? an : load_tile<T>(cu, K, uJ, lane);
+            }
+            if (i + 2 == T || T == 1) {
+              flag = sm.flag[(k & 1) ^ 1];
+              wv = __hip_atomic_load(&sm.dec[gstep & 3], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+              al = __hip_atomic_load(&sm.map[gstep & 3][0], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+              be = __hip_atomic_load(&sm.map[gstep & 3][1], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+              ga = __hip_atomic_load(&sm.map[gstep & 3][2], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             __builtin_amdgcn_sched_barrier(0);           // keep those loads ahead of the products
             y = mma4(a, b, y);
             a = an; b = bn;
           }
-          const v4d x = a;
-          if (uI == uJ) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (isdiag[r]) {
-                sm.dgx[k & 1][16 * uI + c16] = x[r];
-                sm.dgy[k & 1][16 * uI + c16] = y[r];
-              }
-          }
-          // this step's word (there already, as a rule)
-          int word = 0;               // tag 0 is never used
+          raised = k > 0 && __builtin_amdgcn_readfirstlane(flag) != 0;
+          if (raised) return true;
+          int word = spin_budget > 0 ? __builtin_amdgcn_readfirstlane(wv) : 0;   // tag 0: never used
           for (int tries = 0; (word >> 4) != gstep && tries < spin_budget; ++tries)
             word = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
                 &sm.dec[gstep & 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-          const bool gave_up = (word >> 4) != gstep;
-          if (gave_up) { sm.flag[k & 1] = 1; reread = true; }
           wprev = word;
-          if (!gave_up && !(word & 2)) {
-            v4d xn;
-            if (word & 1) {
-              xn = y;
+          if ((word >> 4) != gstep) {
+            sm.flag[k & 1] = 1;
+            wprev = 0;
+          } else if (!(word & 2)) {
+            if (word & 8) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                x[r] = fma(be, y[r], fma(al, x[r], DIAG && isdiag[r] ? ga : 0.0));
+            } else if (word & 1) {
+              x = y;
             } else {
 #pragma unroll
-              for (int r = 0; r < 4; ++r) xn[r] = fma(2.0, x[r], -y[r]);
+              for (int r = 0; r < 4; ++r) x[r] = fma(2.0, x[r], -y[r]);
             }
-            store_tile<T>(nx, uI, uJ, lane, xn);
-            if (uI != uJ) store_tile_transposed<T>(nx, uI, uJ, lane, xn);
+            store_tile<T>(nx, uI, uJ, lane, x);
+            if constexpr (!DIAG) store_tile_transposed<T>(nx, uI, uJ, lane, x);
           }
-        } else if (wave == NTP) {
-          int word = gstep << 4;
-          if (k == 0) {
-            word |= sq_prev ? 1 : 0;
-          } else {
-            // both sums in one pass: the lower half wavefront adds up one diagonal, the
-            // upper half the other (entries N..63 are never written: masked)
-            const double* dg = lane < 32 ? sm.dgx[(k - 1) & 1] : sm.dgy[(k - 1) & 1];
-            const int l32 = lane & 31;
-            const double d0 = l32 < N ? dg[l32] : 0.0, d1 = l32 + 32 < N ? dg[l32 + 32] : 0.0;
-            const double hs = row_sum(d0 + d1);
-            const double trx = lane_bcast(hs, 0) + lane_bcast(hs, 16);
-            const double fro = lane_bcast(hs, 32) + lane_bcast(hs, 48);
-            if (trx - fro < 1e-10) word |= 2 | (fabs(trx - (double)mm) < 0.25 ? 4 : 0);
-            if ((sq_prev ? fro : fma(2.0, trx, -fro)) > (double)mm) word |= 1;
-            sq_prev = (word & 1) != 0;
-          }
-          if (lane == 0) __hip_atomic_store(&sm.dec[gstep & 3], word, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_WORKGROUP);
-          wprev = word;
+          ++k;
+          __syncthreads();
+          return false;
+        };
+        if (uI == uJ) {
+          while (k < MAX_PURIFY)
+            if (step(std::true_type{}, B0, B1) || step(std::true_type{}, B1, B0)) break;
+        } else {
+          while (k < MAX_PURIFY)
+            if (step(std::false_type{}, B0, B1) || step(std::false_type{}, B1, B0)) break;
         }
-        steps = steps + 1;
+      } else if (wave == SW) {
+        // everything that is decided here is scalar
+        const double lo = sm.est[0] * sc, up = sm.est[1] * sc, dm = (double)mm;
+        const bool guessed = scalar(sm.have_est != 0 && up > 1.2 * lo);
+        double t = hi * sc;                 // trace X_k
+        bool sq = t > dm, planned = false, mapped = false, have_cap = false;
+        Plan pl = {0.0f, 1.0f, 0.0f, 1.0f, 1.0f, true};
+        if (lane == 0) { sm.guessed = guessed; sm.cap_k = -1; }
+        if (guessed) {
+          pl.H = scalar((float)(0.8 * lo)); pl.G = scalar((float)fmin(1.0, 1.25 * up));
+          pl.h = scalar((float)(1.05 * lo)); pl.g = scalar((float)(0.95 * up));
+          planned = plan_next(pl, sm, gstep + 1, 0, lane);
+        }
+        __builtin_amdgcn_s_setprio(3);      // ahead of the matrix instructions of its SIMD
         __syncthreads();
-        return true;
-      };
-      for (int k = 0; k < MAX_PURIFY; k += 2)
-        if (!step(B0, B1, k) || !step(B1, B0, k + 1)) break;
-      if (!conv) { failed = 1; break; }
+        for (; k < MAX_PURIFY; ++k) {
+          ++gstep;
+          if (wprev & 2) break;
+          const int flag = sm.flag[(k & 1) ^ 1];
+          int word = gstep << 4;
+          if (planned) {
+            // this step's map is out: the next one's
+            mapped = true;
+            word |= 8;
+            planned = plan_next(pl, sm, gstep + 1, k + 1, lane);
+          } else {
+            double s = 1.0, t1 = t;                 // t1: trace X_{k-1}
+            if (k > 0) {
+              const double* cu = k & 1 ? B1 : B0;
+              const int d = lane < N ? lane : 0;
+              const double hs = row_sum(lane < N ? cu[eidx<T>(d, d)] : 0.0);
+              t = (lane_bcast(hs, 0) + lane_bcast(hs, 16)) + (lane_bcast(hs, 32) + lane_bcast(hs, 48));
+              if (!mapped) {
+                // X_k is X^2 or 2X - X^2 of X = X_{k-1}: sum x (1 - x) over its eigenvalues
+                s = sq ? t1 - t : t - t1;
+                if (scalar(s < 1e-10)) {
+                  word |= 2;
+                  if (scalar(fabs(t1 - dm) < 0.25) && (!guessed || (pl.G > 0.9f && pl.H < 0.1f)))
+                    word |= 4;
+                }
+              }
+              sq = scalar(t > dm);
+              mapped = false;
+              if (guessed && k >= 64) word = (word & ~4) | 2;      // the guess is no good
+            }
+            word |= sq ? 1 : 0;
+            if (lane == 0) {
+              __hip_atomic_store(&sm.dec[gstep & 3], word, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+              sm.hist[k] = sq ? -1.0f : 1.0f;
+            }
+            // While the others multiply.  All eigenvalues of X_{k-1} near 0 or 1: the sums of the
+            // lower ones and of the upper ones' distance from 1 bound the ends of the gap (1.02 s
+            // stands for the s = sum x (1 - x) without the squares)
+            if (!have_cap && scalar(s < 0.02)) {
+              have_cap = true;
+              if (lane == 0) {
+                sm.cap_k = k - 1;
+                sm.cap[0] = (float)fmin(0.5, fmax(1e-4, 0.5 * (1.02 * s + t1 - dm)));
+                sm.cap[1] = 1.0f - (float)fmin(0.5, fmax(1e-4, 0.5 * (1.02 * s - t1 + dm)));
+              }
+            }
+            if (guessed) {
+              pl.grow = !sq;
+              pl.c = sq ? 0.0f : 1.0f;
+              plan_push(pl);
+            }
+          }
+          wprev = word;
+          raised = k > 0 && __builtin_amdgcn_readfirstlane(flag) != 0;
+          if (raised) break;
+          __syncthreads();
+        }
+        __builtin_amdgcn_s_setprio(0);
+      } else {
+        __syncthreads();
+        for (; k < MAX_PURIFY; ++k) {
+          if (k > 0) {
+            raised = __builtin_amdgcn_readfirstlane(sm.flag[(k - 1) & 1]) != 0;
+            wprev = __builtin_amdgcn_readfirstlane(sm.dec[gstep & 3]);
+            if (raised || (wprev & 2)) break;
+          }
+          ++gstep;
+          __syncthreads();
+        }
+      }
+      steps += k;
+      // the last word is the one of step k - 1 and says that X_{k-1} is the result
+      const bool conv = k < MAX_PURIFY && !raised && (wprev & 6) == 6;
+      cur = k & 1 ? B0 : B1;
+      nxt = k & 1 ? B1 : B0;
+      gstep = gstep0 + MAX_PURIFY + 2;     // the same in all roles
+      if (!conv) {
+        // a guess that did not hold: the solve once more without
+        if (!sm.guessed) { failed = 1; break; }
+        __syncthreads();
+        if (tid == 0) sm.have_est = 0;
+        --it;
+        continue;
+      }
     } else {
       // m >= rank: Y spans all of span(G)
-      if (wave < TT) {
+      if (tid == 0) sm.have_est = 0;
+      for (int f = wave; f < TT; f += NW) {
+        const int fI = f / T, fJ = f % T;
         v4d x;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -592,7 +768,8 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
       __syncthreads();
     }
     // ---- Z = (I - P) R (nxt): A operand = I - P (symmetric), B operand = R from global -------
-    if (wave < TT) {
+    for (int f = wave; f < TT; f += NW) {
+      const int fI = f / T, fJ = f % T;
       v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int K = 0; K < T; ++K) {
@@ -606,7 +783,7 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
     __syncthreads();
     // ---- Gq = Z^T Z (symmetric; tile (I, J) = sum_K Z(K, I)^T Z(K, J)); its diagonal ----------
     v4d gq = {0.0, 0.0, 0.0, 0.0};
-    if (wave < NTP) {
+    if (mt >= 0) {
 #pragma unroll
       for (int K = 0; K < T; ++K)
         gq = mma4(load_tile<T>(nxt, K, uI, lane), load_tile<T>(nxt, K, uJ, lane), gq);
@@ -615,12 +792,27 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
         for (int r = 0; r < 4; ++r)
           if (isdiag[r]) sm.gd[16 * uI + c16] = gq[r];
       }
+    } else if (wave == SW && mm < rank && sm.cap_k >= 0) {
+      // where the two ends of the gap lay in this solve's matrix, for the next one's folds: the
+      // bounds of step cap_k taken back through the maps before it (even lanes: the lower end)
+      float yv = sm.cap[lane & 1];
+      for (int k = sm.cap_k - 1; k >= 0; --k) {
+        const float h = sm.hist[k];
+        if (h > 0.0f) {
+          const float u = 1.0f - yv;
+          yv = yv * __builtin_amdgcn_rcpf(h * (1.0f + __builtin_amdgcn_sqrtf(u > 0.0f ? u : 0.0f)));
+        } else {
+          yv = (__builtin_amdgcn_sqrtf(yv) - (h + 1.0f)) * __builtin_amdgcn_rcpf(-h);
+        }
+      }
+      if (lane < 2) sm.est[lane] = hi * (double)yv;
+      if (lane == 0) sm.have_est = 1;
     }
     __syncthreads();
     if constexpr (GRP) {
       // a block's residual adds entries of Gq that other wavefronts hold: all of it into LDS
       // (over Z, which nobody reads any more)
-      if (wave < NTP) {
+      if (mt >= 0) {
         store_tile<T>(nxt, uI, uJ, lane, gq);
         if (uI != uJ) store_tile_transposed<T>(nxt, uI, uJ, lane, gq);
       }
@@ -628,7 +820,7 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
     }
     // ---- residuals, objective, next weights (pair part straight into C = B2) -------------------
     double part = 0.0;
-    if (wave < NTP) {
+    if (mt >= 0) {
       v4d cpn;
       if constexpr (!GEN) {
 #pragma unroll
@@ -715,7 +907,7 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
       store_tile<T>(B2, uI, uJ, lane, cpn);
       if (uI != uJ) store_tile_transposed<T>(B2, uI, uJ, lane, cpn);
       part = wave_sum(part);
-      if (lane == 0) sm.red[wave] = part;
+      if (lane == 0) sm.red[mt] = part;
     }
     __syncthreads();
     double obj = 0.0;
@@ -728,6 +920,7 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
     __syncthreads();   // red[] is reused by the next solve
     if (stop) break;
     if (tid < 64) sm.w[tid] = sm.wn[tid];
+    __syncthreads();
   }
   if (failed) {
     if (tid == 0) info->status = FA_ST_RETRY;
@@ -751,12 +944,13 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
   }
   // beta = U_m (R 1)   (U_m rows k, columns a)
   {
-    const int k = tid >> 4, l16 = tid & 15;
-    double acc = 0.0;
-    if (k < N)
+    const int l16 = tid & 15;
+    for (int k = tid >> 4; k < N; k += NTHREADS / 16) {
+      double acc = 0.0;
       for (int a = l16; a < N; a += 16) acc = fma(Um[k * N + a], sm.r1[a], acc);
-    acc = row_sum(acc);
-    if (k < N && l16 == 0) sm.beta[k] = k < mm ? acc : 0.0;
+      acc = row_sum(acc);
+      if (l16 == 0) sm.beta[k] = k < mm ? acc : 0.0;
+    }
   }
   // restore the first factorisation's pivots and reciprocal diagonal
   __syncthreads();
@@ -803,20 +997,18 @@ __global__ __launch_bounds__(NTHREADS) void fa_irls64_kernel(const double* __res
   // A[piv[a]][k] = dinv[piv[a]] * solution[a][k];  c = A beta / p
   for (int idx = tid; idx < p * m; idx += NTHREADS) info->A[idx] = 0.0;
   __syncthreads();
-  if (tid < N * 16) {
-    const int a = tid >> 4, l16 = tid & 15;
+  for (int a = tid >> 4; a < rank; a += NTHREADS / 16) {
+    const int l16 = tid & 15;
     double acc = 0.0;
-    if (a < rank) {
-      const int i = sm.piv[a];
-      const double di = sm.dinv[i];
-      for (int k = l16; k < mm; k += 16) {
-        const double av = Bs[a * N + k] * di;
-        if (i < p && k < m) info->A[i * m + k] = av;
-        acc = fma(av, sm.beta[k], acc);
-      }
+    const int i = sm.piv[a];
+    const double di = sm.dinv[i];
+    for (int k = l16; k < mm; k += 16) {
+      const double av = Bs[a * N + k] * di;
+      if (i < p && k < m) info->A[i * m + k] = av;
+      acc = fma(av, sm.beta[k], acc);
     }
     acc = row_sum(acc);
-    if (a < rank && l16 == 0) sm.gd[sm.piv[a]] = acc / (double)P;     // c of that column
+    if (l16 == 0) sm.gd[sm.piv[a]] = acc / (double)P;     // c of that column
   }
   if (tid < 64) sm.used[tid] = 0;
   __syncthreads();
@@ -865,7 +1057,7 @@ static hipError_t launch_tm(const double* Kd, int p, int nworkers, const int* si
                             double rank_tol, double pair_tol, double* cd, fa_info* info_d,
                             double* tiles_ws, double* mlast, int spin_budget, fa_resume* rs,
                             hipStream_t st, const fa_ktime* tm) {
-  FA_LAUNCH(tm, (fa_irls64_kernel<T, MODE>), dim3(1), dim3(NTHREADS), lds_bytes<T>(), st, Kd, p,
+  FA_LAUNCH(tm, (fa_irls64_kernel<T, MODE>), dim3(1), dim3(64 * waves_for(T)), lds_bytes<T>(), st, Kd, p,
             nworkers, sizes_d, m, iters, lambda, tol, delta, expo, rank_tol, pair_tol, cd, info_d,
             tiles_ws, mlast, spin_budget, rs);
   return hipGetLastError();
