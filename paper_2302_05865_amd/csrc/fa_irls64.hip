@@ -145,6 +145,8 @@ struct Small {
   double s[64], dinv[64], w[64], wn[64], r1[64], beta[64], rinv[64], gd[64], rho[64];
   double red[16];
   int piv[64], used[64];
+  int cstop[2], crank;   // of the factorisation: the step is the end, by parity; rows
+  double cpart[4][64];   // tile columns' parts of c
   // workers that send several gradients: first column and width of the block a column is in,
   // 1 / tr(g^T g) of that block
   int gf[64], gc[64];
@@ -261,6 +263,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   double* B1 = lds + MSZ;
   double* B2 = lds + 2 * MSZ;
   double* RA = lds + 3 * MSZ;
+  constexpr int LP = N + 1;         // row pitch of the factors (N LP <= MSZ)
   Small& sm = *reinterpret_cast<Small*>(lds + 4 * MSZ);
   double* Rb = gws;                 // R in tile order (B operand), global
   double* D2I = gws + MSZ;          // 1 / D_ij^2 in tile order, 0 for dropped pairs
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       bad = bad || !(fabs(kv) <= 1.79e308);
       const double si = sm.s[i], sj = sm.s[j];
       live = live || (i == j && si > 0.0);
-      B0[e] = (i == j) ? (si > 0.0 ? 1.0 : 0.0) : kv * sm.dinv[i] * sm.dinv[j];   // K~, row-major
+      B0[eidx<T>(i, j)] = (i == j) ? (si > 0.0 ? 1.0 : 0.0) : kv * sm.dinv[i] * sm.dinv[j];   // K~
       double d2 = si + sj - 2.0 * kv;
       bool livep = in && i != j && d2 > pair_tol * (si + sj);
       if constexpr (GRP) {
@@ -366,56 +369,75 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     return;
   }
 
-  // ---- pivoted Cholesky of K~ (B0, row-major) -> rows in B1; right-looking: after a pivot
-  // row is taken the whole remaining matrix is updated at once, by all threads ----------------
-  auto pivoted_cholesky = [&](double* S, double* rows, double tolv, int max_rank) -> int {
-    int rank = 0;
-    for (int k = 0; k < max_rank; ++k) {
-      // every wavefront finds the pivot for itself (same data, same answer): the largest
-      // remaining diagonal entry as seen in fp32, ties to the lowest index
-      const double d = (lane < N && !sm.used[lane]) ? S[lane * N + lane] : 0.0;
-      const float df = d > 0.0 ? (float)d : 0.0f;
-      unsigned key = (__float_as_uint(df) & ~63u) | (unsigned)(63 - lane);
-      key = max(key, dpp_u32<0x128>(key));
-      key = max(key, dpp_u32<0x124>(key));
-      key = max(key, dpp_u32<0x122>(key));
-      key = max(key, dpp_u32<0x121>(key));
-      const unsigned k0 = (unsigned)__builtin_amdgcn_readlane((int)key, 0);
-      const unsigned k1 = (unsigned)__builtin_amdgcn_readlane((int)key, 16);
-      const unsigned k2 = (unsigned)__builtin_amdgcn_readlane((int)key, 32);
-      const unsigned k3 = (unsigned)__builtin_amdgcn_readlane((int)key, 48);
-      const unsigned kmax = max(max(k0, k1), max(k2, k3));
-      const int pv = 63 - (int)(kmax & 63u);
-      const double dp = (pv < N && !sm.used[pv]) ? S[pv * N + pv] : 0.0;
-      if (!(dp > tolv)) break;                       // uniform: everyone read the same value
-      const double rsv = rsq2(dp);
-      double ai[EPT], aj[EPT];
+  // ---- greedy diagonal-pivoted Cholesky of S (tile order) -> rows (row-major, pitch LP) ---------
+  // Right-looking on the matrix core: wavefront w < T keeps tile row w of what is left of S in its
+  // registers and every diagonal entry in a lane, so each finds the pivot for itself (same data,
+  // same answer: the largest remaining entry as seen in fp32, ties to the lowest index); the one
+  // that holds the pivot row writes it out scaled, and after the step's one barrier one matrix
+  // instruction per tile takes the rank-one term off (only contraction index 0 is used).  The other
+  // wavefronts keep the barrier.  Latency bound: 1730 cycles a pivot at T = 4 where the update of
+  // all of S in LDS by all threads, three barriers a pivot, took 3100 (T = 2: 1400, 1900).
+  auto pivoted_cholesky = [&](const double* S, double* rows, double tolv, int max_rank) -> int {
+    if (wave < T) {
+      v4d st[T];
 #pragma unroll
-      for (int q = 0; q < EPT; ++q) {
-        const int e = tid + q * NTHREADS;
-        const int i = e < N * N ? e / N : 0, j = e < N * N ? e - i * N : 0;
-        ai[q] = S[pv * N + i] * rsv;
-        aj[q] = S[pv * N + j] * rsv;
-      }
-      const double rk = (tid < N && !sm.used[tid]) ? S[pv * N + tid] * rsv : 0.0;
-      __syncthreads();                               // row pv has been read by everyone
-#pragma unroll
-      for (int q = 0; q < EPT; ++q) {
-        const int e = tid + q * NTHREADS;
-        if (e < N * N) {
-          const int i = e / N, j = e - i * N;
-          const bool dead = i == pv || j == pv || sm.used[i] || sm.used[j];
-          S[e] = dead ? 0.0 : fma(-ai[q], aj[q], S[e]);
+      for (int J = 0; J < T; ++J) st[J] = load_tile<T>(S, wave, J, lane);
+      const int dl = lane < N ? lane : 0;
+      double d = lane < N ? S[eidx<T>(dl, dl)] : 0.0;
+      unsigned long long used = 0;
+      for (int k = 0;; ++k) {
+        const float df = d > 0.0 ? (float)d : 0.0f;
+        unsigned key = (__float_as_uint(df) & ~63u) | (unsigned)(63 - lane);
+        key = max(key, dpp_u32<0x128>(key));
+        key = max(key, dpp_u32<0x124>(key));
+        key = max(key, dpp_u32<0x122>(key));
+        key = max(key, dpp_u32<0x121>(key));
+        const unsigned k0 = (unsigned)__builtin_amdgcn_readlane((int)key, 0);
+        const unsigned k1 = (unsigned)__builtin_amdgcn_readlane((int)key, 16);
+        const unsigned k2 = (unsigned)__builtin_amdgcn_readlane((int)key, 32);
+        const unsigned k3 = (unsigned)__builtin_amdgcn_readlane((int)key, 48);
+        const int pv = 63 - (int)(max(max(k0, k1), max(k2, k3)) & 63u);
+        const double dp = lane_bcast(d, pv);
+        const bool stop = k == max_rank || !scalar(dp > tolv);
+        if (wave == 0 && lane == 0) sm.cstop[k & 1] = stop;
+        if (stop) {
+          if (wave == 0 && lane == 0) sm.crank = k;
+          __syncthreads();
+          break;
         }
+        if (wave == pv >> 4) {
+          const double rsv = rsq2(dp);
+          const int e = (pv & 15) >> 2;
+#pragma unroll
+          for (int J = 0; J < T; ++J) {
+            const int j = 16 * J + c16;
+            double v = e == 0 ? st[J][0] : e == 1 ? st[J][1] : e == 2 ? st[J][2] : st[J][3];
+            v = j == pv ? dp : v;
+            // (columns that are done with hold rounding noise)
+            if (q4 == (pv & 3)) rows[k * LP + j] = (used >> j) & 1 ? 0.0 : v * rsv;
+          }
+          if (lane == 0) { sm.piv[k] = pv; sm.rinv[k] = rsv; }
+        }
+        __syncthreads();
+        const double* row = rows + k * LP;
+        const double aw = q4 == 0 ? row[16 * wave + c16] : 0.0;
+#pragma unroll
+        for (int J = 0; J < T; ++J)
+          st[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(-aw, q4 == 0 ? row[16 * J + c16] : 0.0, st[J],
+                                                       0, 0, 0);
+        const double rd = row[dl];
+        d = lane == pv ? 0.0 : fma(-rd, rd, d);
+        used |= 1ull << pv;
       }
-      if (tid < N) rows[k * N + tid] = rk;
-      __syncthreads();                               // used[] is read above, written below
-      if (tid == 0) { sm.piv[k] = pv; sm.rinv[k] = rsv; sm.used[pv] = 1; }
-      rank = k + 1;
-      __syncthreads();
+    } else {
+      for (int k = 0;; ++k) {
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(sm.cstop[k & 1])) break;
+      }
     }
-    for (int e = tid; e < N * N; e += NTHREADS)
-      if (e / N >= rank) rows[e] = 0.0;
+    const int rank = __builtin_amdgcn_readfirstlane(sm.crank);
+    for (int e = tid; e < N * LP; e += NTHREADS)
+      if (e / LP >= rank) rows[e] = 0.0;
     if (tid < N && tid >= rank) { sm.piv[tid] = 0; sm.rinv[tid] = 0.0; }
     __syncthreads();
     return rank;
@@ -429,14 +451,13 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     const int e = tid + q * NTHREADS;
     if (e < N * N) {
       const int a = e / N, j = e - a * N;
-      const double rt = B1[e];
+      const double rt = B1[a * LP + j];
       const double rv = rt * sqrt(sm.s[j]);
       RA[aidx<T>(a, j)] = rv;
       Rb[eidx<T>(a, j)] = rv;
       RtG[e] = rt;
     }
   }
-  if (tid < 64) sm.used[tid] = 0;   // the second factorisation (epilogue) starts afresh
   __syncthreads();
   {
     // R 1: sixteen threads per row
@@ -897,7 +918,16 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
               }
             }
           }
-          const double tv = fa_term_pow(rho, expo), wv = fa_weight_pow(rho, delta, expo);
+          double tv, wv;
+          if (GRP && expo == 0.5) {
+            // Eq. 5: one reciprocal square root instead of two powers
+            const double rsv = rsq2(rho > 1e-300 ? rho : 1e-300);
+            tv = rho * rsv;
+            wv = rsv < rs_delta ? rsv : rs_delta;
+          } else {
+            tv = fa_term_pow(rho, expo);
+            wv = fa_weight_pow(rho, delta, expo);
+          }
           if (use) part += scale * tv;
           if (diag) { sm.rho[j] = rho; sm.wn[j] = use ? wv : 0.0; }
           const double cv = (!diag && use) ? -2.0 * coef * d2i * wv : 0.0;
@@ -927,17 +957,10 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     return;
   }
   // ---- epilogue ----------------------------------------------------------------------------
-  // P (cur, tile order) -> row-major copy in nxt, its pivoted Cholesky rows U_m -> RA's place
-  double* Sp = nxt;
+  // pivoted Cholesky rows U_m of P (cur) -> RA's place
   double* Um = RA;      // R in A order is no longer needed
-#pragma unroll
-  for (int q = 0; q < EPT; ++q) {
-    const int e = tid + q * NTHREADS;
-    if (e < N * N) Sp[e] = cur[eidx<T>(e / N, e % N)];
-  }
-  __syncthreads();
   // pivots of the first factorisation survive in registers; the second one overwrites sm.piv
-  const int nb = pivoted_cholesky(Sp, Um, 1e-6, mm);
+  const int nb = pivoted_cholesky(cur, Um, 1e-6, mm);
   if (nb != mm) {
     if (tid == 0) info->status = FA_ST_RETRY;
     return;
@@ -947,7 +970,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     const int l16 = tid & 15;
     for (int k = tid >> 4; k < N; k += NTHREADS / 16) {
       double acc = 0.0;
-      for (int a = l16; a < N; a += 16) acc = fma(Um[k * N + a], sm.r1[a], acc);
+      for (int a = l16; a < N; a += 16) acc = fma(Um[k * LP + a], sm.r1[a], acc);
       acc = row_sum(acc);
       if (l16 == 0) sm.beta[k] = k < mm ? acc : 0.0;
     }
@@ -955,60 +978,85 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   // restore the first factorisation's pivots and reciprocal diagonal
   __syncthreads();
   if (tid < 64) { sm.piv[tid] = piv_keep; sm.rinv[tid] = rinv_keep; }
-  // right-hand sides B[a][k] = U_m[k][a] into B2's place (row-major N x N), then back
-  // substitution with the upper triangular U_R[a][l] = R~[a][piv[l]] (rows from global):
-  // column-oriented, all threads: once row a of the solution is known it is taken out of all
-  // earlier rows at once.  The solution row a belongs to worker piv[a].
-  // (B2 still holds the pair part of C, which the resume state wants)
-  double* Bs = cur;     // the projector's tiles are no longer needed
+  for (int idx = tid; idx < p * m; idx += NTHREADS) info->A[idx] = 0.0;
   __syncthreads();
-#pragma unroll
-  for (int q = 0; q < EPT; ++q) {
-    const int e = tid + q * NTHREADS;
-    if (e < N * N) {
-      const int a = e / N, k = e - a * N;
-      Bs[e] = (a < rank && k < mm) ? Um[k * N + a] : 0.0;
-    }
-  }
-  __syncthreads();
+  // A = D^-1/2 X, U X = U_m^T, with the upper triangular U[a][l] = R~[a][piv[l]] (rows from global;
+  // row a of X belongs to worker piv[a]).  By tiles: the T diagonal tiles of U are inverted, one
+  // wavefront each, lane c column c; then wavefront J takes tile column J of X from the bottom up
+  // on the matrix core, without a barrier.  (B2 still holds the pair part of C, which the resume
+  // state wants.)  T = 4: 19 thousand cycles; substitution by all threads, two barriers a row, 53.
+  double* Us = nxt;                 // row-major, pitch LP
+  double* Ui = cur;                 // inverses of the diagonal tiles, pitch 17
 #pragma unroll
   for (int q = 0; q < EPT; ++q) {
     const int e = tid + q * NTHREADS;
     if (e < N * N) {
       const int a = e / N, l = e - a * N;
-      Sp[e] = (a < rank && l < rank) ? RtG[a * N + sm.piv[l]] : 0.0;   // Sp is free again
+      Us[a * LP + l] = (a < rank && l < rank) ? RtG[a * N + sm.piv[l]] : 0.0;
     }
   }
   __syncthreads();
-  for (int a = rank - 1; a >= 0; --a) {
-    const double ri = sm.rinv[a];
-    if (tid < N) Bs[a * N + tid] *= ri;            // solution row a
-    __syncthreads();
+  if (wave < T) {
+    const int o = 16 * wave;
+    double bcol[16];
 #pragma unroll
-    for (int q = 0; q < EPT; ++q) {
-      const int e = tid + q * NTHREADS;
-      if (e < N * N) {
-        const int i = e / N, k = e - i * N;
-        if (i < a) Bs[e] = fma(-Sp[i * N + a], Bs[a * N + k], Bs[e]);
+    for (int i = 0; i < 16; ++i) bcol[i] = (i == c16) ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 15; k >= 0; --k) {
+      if (o + k < rank) {
+        const double xk = bcol[k] * sm.rinv[o + k];
+#pragma unroll
+        for (int i = 0; i < k; ++i) bcol[i] = fma(-Us[(o + i) * LP + o + k], xk, bcol[i]);
+        bcol[k] = xk;
+      } else {
+        bcol[k] = 0.0;
       }
     }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (lane < 16) Ui[wave * FA_TILE + k * 17 + c16] = bcol[k];
   }
-  // A[piv[a]][k] = dinv[piv[a]] * solution[a][k];  c = A beta / p
-  for (int idx = tid; idx < p * m; idx += NTHREADS) info->A[idx] = 0.0;
   __syncthreads();
-  for (int a = tid >> 4; a < rank; a += NTHREADS / 16) {
-    const int l16 = tid & 15;
-    double acc = 0.0;
-    const int i = sm.piv[a];
-    const double di = sm.dinv[i];
-    for (int k = l16; k < mm; k += 16) {
-      const double av = Bs[a * N + k] * di;
-      if (i < p && k < m) info->A[i * m + k] = av;
-      acc = fma(av, sm.beta[k], acc);
+  if (wave < T) {
+    v4d X[T];
+#pragma unroll
+    for (int I = T - 1; I >= 0; --I) {
+      v4d acc, u;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = Um[(16 * wave + c16) * LP + 16 * I + 4 * r + q4];
+#pragma unroll
+      for (int K = I + 1; K < T; ++K) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) u[r] = -Us[(16 * I + c16) * LP + 16 * K + 4 * r + q4];
+        acc = mma4(u, X[K], acc);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) u[r] = Ui[I * FA_TILE + c16 * 17 + 4 * r + q4];
+      X[I] = mma4(u, acc, v4d{0.0, 0.0, 0.0, 0.0});
     }
-    acc = row_sum(acc);
-    if (l16 == 0) sm.gd[sm.piv[a]] = acc / (double)P;     // c of that column
+    // A[piv[a]][k] = dinv[piv[a]] X[a][k];  this tile column's part of c = A beta / p
+    const int k = 16 * wave + c16;
+#pragma unroll
+    for (int I = 0; I < T; ++I)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int a = 16 * I + 4 * r + q4;
+        double av = 0.0;
+        if (a < rank) {
+          const int i = sm.piv[a];
+          av = X[I][r] * sm.dinv[i];
+          if (i < p && k < mm) info->A[i * m + k] = av;
+        }
+        const double t = row_sum(k < mm ? av * sm.beta[k] : 0.0);
+        if (c16 == 0) sm.cpart[wave][a] = t;
+      }
+  }
+  __syncthreads();
+  if (tid < rank) {
+    double acc = sm.cpart[0][tid];
+#pragma unroll
+    for (int J = 1; J < T; ++J) acc += sm.cpart[J][tid];
+    sm.gd[sm.piv[tid]] = acc / (double)P;               // c of that column
   }
   if (tid < 64) sm.used[tid] = 0;
   __syncthreads();
