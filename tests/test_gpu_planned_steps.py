@@ -1,5 +1,6 @@
-"""Purification steps planned from the previous solve's gap (16 < p <= 64): where the guess holds, where
-it does not and the solve is done again, and at every tile count."""
+"""Purification steps that need no trace: planned from the previous solve's gap (16 < p <= 64: where the
+guess holds, where it does not and the solve is done again, every tile count) and the folded first
+growth steps (p <= 16: every width class of the solver)."""
 import numpy as np
 import pytest
 
@@ -27,6 +28,18 @@ def gram_of(p, seed, n=200):
     (17, 16, 1.0, 1), (32, 1, 1.0, 2), (33, 17, 1.0, 3), (48, 24, 0.1, 4), (48, 47, 1.0, 5),
     (49, 3, 1.0, 6), (64, 32, 0.1, 7), (64, 63, 4.0, 8), (64, 1, 0.0, 9)])
 def test_planned_steps_give_the_jacobi_solvers_answer(p, m, lam, seed):
+    _compare_with_jacobi(p, m, lam, seed)
+
+
+@pytest.mark.parametrize("p", [2, 4, 5, 8, 9, 12, 13, 16])
+def test_folded_growth_gives_the_jacobi_solvers_answer(p):
+    """m = 1 (no folded step: the bound is 1/2 already) to m = p (no purification at all); widths on
+    both sides of every count of matrix instructions per product."""
+    for m in sorted({1, 2, p // 2, p - 1, p}):
+        _compare_with_jacobi(p, m, 0.3, 11 * p + m)
+
+
+def _compare_with_jacobi(p, m, lam, seed):
     """Both solvers start from the same K in fp64.  Each solve's projector is good to eps p / gap,
     and passes that on to the next solve's weights; the objective after every solve and the
     coefficients agree to 1e-8 where the relative gap at m stays above 1e-5."""
