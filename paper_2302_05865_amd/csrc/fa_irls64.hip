@@ -178,11 +178,14 @@ struct Small {
 // the guess was worth.  If not, the solve is done once more without.
 // The maps of these steps need no trace: the steering wavefront has each ready one step ahead, so
 // nobody waits for it.  Once h and g are within 0.03 of 0 and 1 the steps go on as always.
-// Measured, steps per call (plain -> with plans): p = 32, m = 16, 15 solves 428 -> 344; p = 60, 5 solves
-// 181 -> 169; p = 64, 30 solves 806 -> 640.  The first solves, whose gap moves most, stay unplanned.
+// Where there is no guess - the first solve, a gap of less than a fifth, a guess that failed - only the
+// first growth steps are planned, from a bound that always holds (trace X_0 = 1).
+// Measured, steps per call (plain -> with plans): p = 32, m = 16, 15 solves 428 -> 342; p = 60, 5 solves
+// 181 -> 163; p = 64, 30 solves 806 -> 639.
 struct Plan {                 // all scalar: one wavefront's, the same in every lane
   float H, G, h, g;
   float c;                    // a or b of the last map
+  float end;                  // the plan ends when h and 1 - g are below this
   bool grow;
 };
 __device__ __forceinline__ float scalar(float x) {
@@ -209,7 +212,7 @@ __device__ __forceinline__ void plan_push(Plan& pl) {
 // the next planned map, published as step g's; false when the plan is at its end
 __device__ __forceinline__ bool plan_next(Plan& pl, Small& sm, int g, int k, int lane) {
   const float up = 1.0f - pl.g;
-  if (scalar(fmaxf(pl.h, up) < 0.03f) || k >= 40) return false;
+  if (scalar(fmaxf(pl.h, up) < pl.end) || k >= 40) return false;
   pl.grow = scalar(up > pl.h);
   const float c = pl.grow ? 2.0f * __builtin_amdgcn_rcpf(1.0f + pl.G)
                           : pl.H * __builtin_amdgcn_rcpf(2.0f - pl.H);
@@ -681,13 +684,18 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         const bool guessed = scalar(sm.have_est != 0 && up > 1.2 * lo);
         double t = hi * sc;                 // trace X_k
         bool sq = t > dm, planned = false, mapped = false, have_cap = false;
-        Plan pl = {0.0f, 1.0f, 0.0f, 1.0f, 1.0f, true};
+        Plan pl = {0.0f, 1.0f, 0.0f, 1.0f, 1.0f, 0.03f, true};
         if (lane == 0) { sm.guessed = guessed; sm.cap_k = -1; }
         if (guessed) {
           pl.H = scalar((float)(0.8 * lo)); pl.G = scalar((float)fmin(1.0, 1.25 * up));
           pl.h = scalar((float)(1.05 * lo)); pl.g = scalar((float)(0.95 * up));
-          planned = plan_next(pl, sm, gstep + 1, 0, lane);
+        } else {
+          // no guess, but trace X_0 = 1 bounds x_{m+1} by 1 / (m + 1) (with a margin for rounding):
+          // growth may fold what is above that, while it is small
+          pl.G = pl.g = scalar(1.0001f / (float)(mm + 1));
+          pl.end = 0.5f;
         }
+        planned = plan_next(pl, sm, gstep + 1, 0, lane);
         __builtin_amdgcn_s_setprio(3);      // ahead of the matrix instructions of its SIMD
         __syncthreads();
         for (; k < MAX_PURIFY; ++k) {
