@@ -253,14 +253,6 @@ pthread_mutex_t g_static_mu = PTHREAD_MUTEX_INITIALIZER;
 
 static __device__ __align__(256) unsigned char scratch[FA_STATIC_SCRATCH_BYTES];
 
-// the record of the previous call must not be mistaken for this one's
-__global__ void fa_static_clear_kernel(fa_info* info) {
-  if (threadIdx.x == 0) {
-    info->status = 0; info->p = 0; info->m = 0; info->rank = 0; info->iters_done = 0;
-    info->sweeps = 0;
-  }
-}
-
 // Once per device, with that device current: the address of its copy of the array, its
 // compute-unit count, the kernels' launch attributes.  None of these allocates.
 static fa_status static_setup(int dev, StaticDev* out) {
@@ -307,8 +299,7 @@ extern "C" fa_status fa_aggregate_static(const void* G, int64_t ldg, int p, int6
   fa_info* info_d = reinterpret_cast<fa_info*>(sd.base + kOffInfo);
   fa_config cfg;
   fa_default_config(&cfg);
-  hipLaunchKernelGGL(fa_static_clear_kernel, dim3(1), dim3(64), 0, st, info_d);
-  if (hipGetLastError() != hipSuccess) return FA_ERR_DEVICE;
+  // (the solvers write every field of the record that a later kernel reads: nothing to clear)
   int nparts = 0;
   int* flag_d = reinterpret_cast<int*>(sd.base + kOffFlag);
   if (fa_launch_gram(G, ldg, p, n, dtype, FA_WORKER_MAJOR, cfg.gram, sd.blocks, partials, Kd,
