@@ -1047,38 +1047,61 @@ __global__ __launch_bounds__(256) void fa_combine_multi_kernel(
 // Sec. 3 "Baselines", Sec. 2.3; rule of Blanchard et al., 2017): D_ij^2 = K_ii + K_jj - 2 K_ij,
 // worker i is scored by the sum of its k = p - f - 2 smallest distances to the others (added
 // in ascending order), the q smallest scores are selected (ties: smaller index), and the
-// coefficients of out = G c are 1/q on the selected workers.  One thread per worker; p <= 64.
-__global__ __launch_bounds__(64) void fa_krum_kernel(const double* __restrict__ K, int p, int k,
-                                                     int q, double* __restrict__ c,
-                                                     double* __restrict__ scores,
-                                                     int* __restrict__ selected) {
+// coefficients of out = G c are 1/q on the selected workers.  A distance's place in its row is
+// counted, one thread per distance, and the row's thread adds the first k up in order (an insertion
+// sort by one thread per worker took 13.6 us at p = 15 and 185 at p = 64; 4.4 and 28 now).
+// p <= 64; scores and selected may be host memory the device can write.
+__global__ __launch_bounds__(1024) void fa_krum_kernel(const double* __restrict__ K, int p, int k,
+                                                       int q, double* __restrict__ c,
+                                                       double* __restrict__ scores,
+                                                       int* __restrict__ selected) {
   __shared__ double sc[FA_P_MAX];
   __shared__ double dist[FA_P_MAX][FA_P_MAX + 1];
-  const int i = threadIdx.x;
-  double s = 0.0;
-  if (i < p) {
-    double* d = dist[i];
-    const double kii = K[i * p + i];
-    int cnt = 0;
-    for (int j = 0; j < p; ++j) {
-      if (j == i) continue;
-      double x = kii + K[j * p + j] - 2.0 * K[i * p + j];
-      x = x > 0.0 ? x : 0.0;
-      int pos = cnt++;                       // insertion sort, ascending
-      while (pos > 0 && d[pos - 1] > x) { d[pos] = d[pos - 1]; --pos; }
-      d[pos] = x;
+  constexpr int PER = FA_P_MAX * FA_P_MAX / 1024;
+  const int tid = threadIdx.x, j = tid & 63, i0 = tid >> 6;      // entries (i0 + 16 u, j)
+  double x[PER];
+  int pos[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = i0 + 16 * u;
+    x[u] = 0.0;
+    if (i < p && j < p) {
+      const double d = K[i * p + i] + K[j * p + j] - 2.0 * K[i * p + j];
+      x[u] = d > 0.0 ? d : 0.0;
+      dist[i][j] = x[u];
     }
-    for (int t = 0; t < k; ++t) s += d[t];
-    sc[i] = s;
-    scores[i] = s;
   }
   __syncthreads();
-  if (i < p) {
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = i0 + 16 * u;
+    pos[u] = 0;
+    if (i < p && j < p && j != i)
+      for (int t = 0; t < p; ++t) {
+        const double y = dist[i][t];
+        pos[u] += t != i && (y < x[u] || (y == x[u] && t < j)) ? 1 : 0;
+      }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = i0 + 16 * u;
+    if (i < p && j < p && j != i) dist[i][pos[u]] = x[u];       // ascending
+  }
+  __syncthreads();
+  double s = 0.0;
+  if (tid < p) {
+    for (int t = 0; t < k; ++t) s += dist[tid][t];
+    sc[tid] = s;
+    scores[tid] = s;
+  }
+  __syncthreads();
+  if (tid < p) {
     int rank = 0;
-    for (int j = 0; j < p; ++j) rank += (sc[j] < s || (sc[j] == s && j < i)) ? 1 : 0;
+    for (int t = 0; t < p; ++t) rank += (sc[t] < s || (sc[t] == s && t < tid)) ? 1 : 0;
     const int sel = rank < q ? 1 : 0;
-    selected[i] = sel;
-    c[i] = sel ? 1.0 / (double)q : 0.0;
+    selected[tid] = sel;
+    c[tid] = sel ? 1.0 / (double)q : 0.0;
   }
 }
 
@@ -1132,7 +1155,7 @@ hipError_t fa_launch_combine_multi(const void* G, int64_t ldg, int p, int64_t n,
 
 hipError_t fa_launch_krum(const double* Kd, int p, int f, int q, double* cd, double* scores_d,
                           int* selected_d, hipStream_t st) {
-  hipLaunchKernelGGL(fa_krum_kernel, dim3(1), dim3(64), 0, st, Kd, p, p - f - 2, q, cd, scores_d,
+  hipLaunchKernelGGL(fa_krum_kernel, dim3(1), dim3(1024), 0, st, Kd, p, p - f - 2, q, cd, scores_d,
                      selected_d);
   return hipGetLastError();
 }
