@@ -587,10 +587,12 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       //    step's barrier.
       // Waits: the steering wavefront waits for nobody, so the readers' bounded spin ends.  One
       // that runs out of its budget of polls raises the step's flag, skips its store and goes
-      // on to the step's barrier like everybody else; all look at that flag during the next
-      // step and leave before its barrier, together, with the solve marked as failed (the last step
-      // of the loop cannot raise it unseen: a failed solve is what running out of steps means
-      // anyway).  In the step after the word "X_{k-1} was a projector" all leave the same way.
+      // on to the step's barrier like everybody else; all leave the next step before its
+      // barrier, together, with the solve marked as failed (the last step of the loop cannot raise
+      // it unseen: a failed solve is what running out of steps means anyway).  In the step after
+      // the word "X_{k-1} was a projector" all leave the same way, some on the word and some on
+      // the flag if somebody ran out of polls on that very word: so the flag is looked at once more
+      // behind the loops, where it wins over the word in every role.
       const int gstep0 = gstep;
       ++gstep;                        // a tag of its own between solves: no stale word matches
       int k = 0, wprev = 0;           // wprev: the word of the previous step
@@ -770,6 +772,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         }
       }
       steps += k;
+      // the flag of step k - 1 (step k, which nobody finished, has the other one)
+      if (k > 0) raised = __builtin_amdgcn_readfirstlane(sm.flag[(k & 1) ^ 1]) != 0;
       // the last word is the one of step k - 1 and says that X_{k-1} is the result
       const bool conv = k < MAX_PURIFY && !raised && (wprev & 6) == 6;
       cur = k & 1 ? B0 : B1;
