@@ -241,10 +241,10 @@ fa_status fa_basis(fa_ctx* ctx, const void* G, int64_t ldg, int p, int64_t n, in
  *   fa_gram_update_rows  the same for a gradient that lands piece by piece: elements
  *                   [row0, row0 + nrows) of gradient i are now in place.  For p <= 16 one pass over
  *                   a piece of all gradients adds its share to K when the last of them lands; for
- *                   p > 16 the share of the other gradients is added when only one is missing,
- *                   and that one's row and column of K when it lands.  The pieces of one gradient
- *                   are announced
- *                   in order (row0 = the end of the previous piece, 0 first); a piece starts
+ *                   p > 16 the share of the other gradients is added when only one is missing
+ *                   (in rounds whose first piece has 2^22 rows or more, the share of the first
+ *                   16 (32, 48) gradients is added when these are there), and that one's row and
+ *                   column of K when it lands.  The pieces of one gradient are announced in order (row0 = the end of the previous piece, 0 first); a piece starts
  *                   on a 16-byte boundary of the gradient (row0 * elem_size a multiple of 16);
  *                   all gradients are cut at the same places: FA_ERR_ARG if another gradient's
  *                   landed part ends inside the piece.  K is the fp64 Gram matrix to rounding
@@ -256,7 +256,7 @@ fa_status fa_basis(fa_ctx* ctx, const void* G, int64_t ldg, int p, int64_t n, in
  * When the last gradient lands whole, a pass that reads what the one-shot Gram pass reads is
  * still to do.  When it lands in pieces, only its last piece is: after the last byte the server is
  * a pass over (piece) x p elements away from the p x p solve, instead of a pass over all of G.
- * In total the updates read every gradient once (p <= 16) or twice.
+ * In total the updates read every gradient once (p <= 16), twice or three times.
  * Worker-major contexts only (a gradient arrives as one contiguous vector).
  */
 fa_status fa_gram_begin(fa_ctx* ctx, int p, int64_t n);

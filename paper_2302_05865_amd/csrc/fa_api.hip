@@ -41,6 +41,8 @@ struct fa_ctx {
   int64_t arr_n;
   uint64_t arrived;   // bit j: gradient j is complete
   int64_t arr_rows[FA_P_MAX];   // rows of gradient j announced so far (a prefix)
+  uint64_t arr_early;           // the gradients whose pairs are worked off ahead of the others' ...
+  int arr_n_early;              // ... and how many there will be (negative: nothing landed yet)
 };
 
 static int elem_size(int dtype) { return dtype == FA_F32 ? 4 : 2; }
@@ -437,10 +439,15 @@ extern "C" fa_status fa_gram_begin(fa_ctx* c, int p, int64_t n) {
   if (fa_launch_zero(c->Kd, FA_P_MAX * FA_P_MAX, c->stream) != hipSuccess) return FA_ERR_DEVICE;
   c->arr_p = p;
   c->arr_n = n;
+  c->arr_early = 0;
+  c->arr_n_early = -1;
   c->arrived = 0;
   for (int j = 0; j < FA_P_MAX; ++j) c->arr_rows[j] = 0;
   return FA_OK;
 }
+
+// rows of a round's first piece from which on the first gradients' pairs are worked off ahead
+#define FA_EARLY_MIN_ROWS ((int64_t)1 << 22)
 
 extern "C" fa_status fa_gram_update_rows(fa_ctx* c, const void* G, int64_t ldg, int i,
                                          int64_t row0, int64_t nrows) {
@@ -458,29 +465,58 @@ extern "C" fa_status fa_gram_update_rows(fa_ctx* c, const void* G, int64_t ldg, 
     if (c->arr_rows[j] >= row1) resident |= (uint64_t)1 << j;
     else if (c->arr_rows[j] > row0) return FA_ERR_ARG;
   }
-  // What these rows add to K is added when the gradients that are needed for it hold them: one
-  // pass over all of them instead of one over gradient i and its predecessors at every arrival.
-  // p <= 16: when the last gradient lands, all pairs at once (the pass is HBM bound, so it is as
-  // quick as the last gradient's own pairs would be: both read the same rows of all gradients).
-  // p > 16: the fp64 matrix core bounds that pass, so the pairs of the others are done as soon as
-  // only one gradient is missing, and its own row of K when it lands.  Measured at p = 15,
-  // n = 11.2M, 4 pieces per gradient: 60 passes over gradient i and its predecessors 2.1 ms,
-  // 4 passes over all gradients 0.14 ms.
-  const unsigned char* first = reinterpret_cast<const unsigned char*>(G) + row0 * es;
-  const int p = c->arr_p, holders = __builtin_popcountll(resident) + 1;
+  // What these rows add to K is added when the gradients that are needed for it hold them, in few
+  // passes over many gradients instead of one over gradient i and its predecessors at every arrival.
+  // p <= 16: one pass over all when the last gradient lands.  p > 16: the last gradient's row and
+  // column when it lands, the others' pairs when only one is missing; but that pass is long where the
+  // last two land together, so in rounds of large pieces the pairs among as many of the first
+  // gradients as fill whole tiles (`early`, in order of their first piece) are worked off when these
+  // hold the rows, which leaves tiles of the other 16 or fewer for it.
+  // Last data landed -> K there, us, 8M rows in whole gradients, the last one alone / the last two
+  // together (every arrival for itself; without `early`; now):
+  //   p = 16 f32 103, 192;  90,  95;  the same      p = 16 bf16  69, 122;  92,  96;  the same
+  //   p = 32 f32 200, 383; 200, 413; 202, 365       p = 32 bf16 125, 234; 123, 335; 124, 279
+  //   p = 48 f32 298, 572; 296, 699; 296, 536       p = 48 bf16 186, 354; 184, 579; 181, 404
+  //   p = 64 f32 400, 785; 395,1043; 397, 715       p = 64 bf16 244, 471; 242, 871; 240, 541
+  // and a whole round at p = 64 f32 13.4, 1.35 and 1.35 ms.  From 4M rows a piece on: there the last
+  // two together take 312 us with and 398 without (p = 48 f32), a round at p = 20 bf16 486 and 460; at
+  // 2M rows 204 and 245, 617 and 563.
+  const unsigned char* at = reinterpret_cast<const unsigned char*>(G) + row0 * es;
+  const int p = c->arr_p;
+  const uint64_t me = (uint64_t)1 << i, holders = resident | me;
+  const uint64_t all = p == 64 ? ~(uint64_t)0 : (((uint64_t)1 << p) - 1);
+  const int nh = __builtin_popcountll(holders);
+  if (c->arr_n_early < 0) c->arr_n_early = nrows >= FA_EARLY_MIN_ROWS ? (p - 2) / 16 * 16 : 0;
+  const int n_early = c->arr_n_early;
+  if (__builtin_popcountll(c->arr_early) < n_early) c->arr_early |= me;
+  const uint64_t early = c->arr_early;
+  const bool early_full = n_early > 0 && __builtin_popcountll(early) == n_early;
+  // If all of `early` held these rows before gradient i brings them, their pairs are there already:
+  // the last of them to announce the rows (each does so once) found `early` complete and, unless
+  // all but one held the rows with it, added them then.
+  const bool early_there = early_full && (early & ~resident) == 0;
+  uint64_t first = 0, then = 0;
+  bool row = false;
+  if (p <= 16) {
+    if (holders == all) then = all;
+  } else if (holders == all) {
+    row = true;
+  } else if (nh == p - 1) {
+    first = early_there ? early : 0;
+    then = holders & ~first;
+  } else if (early_full && (early & me) && (early & ~holders) == 0) {
+    then = early;
+  }
   hipError_t e = hipSuccess;
-  if (p <= 16 ? holders == p : holders == p - 1) {
-    int missing = p;                                          // nobody, where holders == p
-    for (int j = 0; j < p; ++j)
-      if (j != i && !((resident >> j) & 1u)) missing = j;
-    e = fa_launch_gram_add(first, ldg, p, nrows, c->cfg.dtype, missing, c->gram_max_blocks,
-                           c->partials, c->Kd, c->stream);
-  } else if (holders == p) {
+  if (row) {
     // partial rows go to the Gram pass's partial buffer (at least 256 doubles per compute unit)
     int max_parts = c->gram_max_blocks * 256 / FA_ROW_JB;
     if (max_parts > 1024) max_parts = 1024;
-    e = fa_launch_gram_row(first, ldg, p, nrows, c->cfg.dtype, i, c->partials, max_parts, c->Kd,
+    e = fa_launch_gram_row(at, ldg, p, nrows, c->cfg.dtype, i, c->partials, max_parts, c->Kd,
                            c->stream);
+  } else if (then) {
+    e = fa_launch_gram_add(at, ldg, p, nrows, c->cfg.dtype, first, then, c->gram_max_blocks,
+                           c->partials, c->Kd, c->stream);
   }
   if (e != hipSuccess) return FA_ERR_DEVICE;
   c->arr_rows[i] = row1;

@@ -53,11 +53,14 @@ hipError_t fa_launch_gram_lp_partials(const void* G, int64_t ldg, int p, int64_t
                                       int max_blocks, double* partials, int* nparts,
                                       hipStream_t st, const fa_ktime* tm);
 hipError_t fa_gram_lp_prepare(void);
-// K += the Gram matrix of n rows of all p gradients, or of all but gradient `skip` (skip < p),
-// whose place is not read; fp64 products and sums.  G points at the first of the rows in
-// gradient 0; worker-major.  partials and max_blocks as for fa_launch_gram_partials.
-hipError_t fa_launch_gram_add(const void* G, int64_t ldg, int p, int64_t n, int dtype, int skip,
-                              int max_blocks, double* partials, double* Kd, hipStream_t st);
+// K (p x p) += over n rows, the products of every gradient in the set `then` (bit j: gradient j)
+// with every one in `first` and in `then`, fp64 products and sums; no other gradient's place is
+// read.  `first` is empty or holds a multiple of 16 gradients, with at most 16 in `then`.  G points
+// at the first of the rows in gradient 0; worker-major.  partials and max_blocks as for
+// fa_launch_gram_partials.
+hipError_t fa_launch_gram_add(const void* G, int64_t ldg, int p, int64_t n, int dtype,
+                              uint64_t first, uint64_t then, int max_blocks, double* partials,
+                              double* Kd, hipStream_t st);
 // Row and column i of K from one pass over n rows of gradient i and of all others: K[i][j] and
 // K[j][i] += g_i . g_j over those rows, in fp64.  G points at the first of the rows in gradient
 // 0.  partials: max_parts * FA_ROW_JB doubles of scratch.  Worker-major G.

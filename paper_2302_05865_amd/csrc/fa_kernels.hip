@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <initializer_list>
 #include <type_traits>
 
 #include "fa.h"
@@ -108,6 +109,12 @@ __device__ __forceinline__ uint4 load16_guarded(const unsigned char* base, int64
   return v;
 }
 
+// which gradients the columns of a Gram pass are, where they are not simply the first p
+struct fa_gram_cols {
+  int listed;
+  uint8_t idx[FA_P_MAX];
+};
+
 // ------------------------------------------------------------------------------------------
 // K1: Gram matrix by fp64 matrix-core accumulation.
 //
@@ -132,8 +139,9 @@ __device__ __forceinline__ uint4 load16_guarded(const unsigned char* base, int64
 // T   = number of 16-column blocks (p <= 16 T)
 // CPL = columns covered by one load instruction (1: a wave reads 1 KiB of one column;
 //       4: 256 B of each of four columns, which keeps the LDS tile small for large p)
-// skip: worker-major storage only, the p columns are gradients 0 .. p without gradient `skip`,
-//       whose place is not read (skip >= p: the first p gradients)
+// LAST = only the tiles of the last block of columns with all blocks, itself included (the others'
+//       entries of K are there already: see fa_gram_update_rows)
+// cols: worker-major storage only, which gradients the p columns are; no other place is read
 __device__ __forceinline__ void wave_lds_fence() {
   // orders this wavefront's LDS accesses for the compiler; the hardware executes one
   // wavefront's LDS instructions in order
@@ -166,13 +174,14 @@ __device__ __forceinline__ void unpack4(const unsigned char* src, double* x) {
 constexpr int fa_rows_tile_bytes(int t, int es, int r) {
   return r / 4 * ((64 * t * es + 255) / 256 * 256 + 16 * es);
 }
-template <int T, int CPL, typename E, int WAVES, bool ROWS>
+template <int T, int CPL, typename E, int WAVES, bool ROWS, bool LAST>
 __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
                                                      const unsigned char* __restrict__ G,
                                                      int64_t ldg, int p, int64_t n,
                                                      int64_t ntiles,
                                                      double* __restrict__ partials,
-                                                     const int* __restrict__ gate, int skip) {
+                                                     const int* __restrict__ gate,
+                                                     fa_gram_cols cols) {
   // as the stand-by of the bf16 matrix-core pass: nothing to do unless that one overflowed
   if (gate != nullptr && *gate == 0) return;
   constexpr int EPL = E::EPL;
@@ -180,7 +189,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   constexpr int R = LPC * EPL;             // rows per tile
   constexpr int NCG = T * 16 / CPL;        // load instructions per tile
   constexpr int CS = R * E::SIZE + 16;     // LDS bytes per column (+16: bank spread)
-  constexpr int NTP = T * (T + 1) / 2;
+  constexpr int NTP = LAST ? T : T * (T + 1) / 2;
   constexpr int NSTEP = R / 16;
   constexpr int TILE = ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : T * 16 * CS;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
@@ -212,7 +221,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
     const int col = cg * CPL + lcol;
     colon[cg] = col < p;
     const int src = colon[cg] ? col : p - 1;
-    colbase[cg] = G + (int64_t)(src + (src >= skip ? 1 : 0)) * ldg * E::SIZE;
+    colbase[cg] = G + (int64_t)(cols.listed ? cols.idx[src] : src) * ldg * E::SIZE;
   }
 
   // interleaved storage: where each of this lane's pieces goes (the span of a tile is R * ldg
@@ -318,7 +327,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
 #pragma unroll
         for (int a = 0; a < T; ++a)
 #pragma unroll
-          for (int b = a; b < T; ++b) {
+          for (int b = LAST ? T - 1 : a; b < T; ++b) {
             acc[tp] = __builtin_amdgcn_mfma_f64_16x16x4f64(xc[a][j], xc[b][j], acc[tp], 0, 0, 0);
             ++tp;
           }
@@ -656,18 +665,18 @@ __global__ __launch_bounds__(256) void fa_restream_weights_kernel(const fa_info*
 // TM > 0: the tiles are the T x TM blocks of a p x m matrix (row-major, leading dimension m).
 // colscale (may be null; symmetric case only): entry (i, j) is multiplied by u_i u_j, which
 // makes the result the Gram matrix G^T W G of the columns scaled by u = W^(1/2).
-// add (symmetric case only): the sums are those of some rows of G and are added to K, whose
-// order is ldk; the pass behind them left out gradient `skip`, so column g of the tiles is
-// gradient g + (g >= skip).
+// cols (symmetric case only): where the columns are listed, the sums are those of some rows of G
+// and are added to K, whose order is ldk; last: the tiles are those of the LAST pass.
 __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __restrict__ partials,
                                                               int nparts, int T, int p,
                                                               double* __restrict__ K, int TM,
                                                               int m,
                                                               const double* __restrict__ colscale,
                                                               const int* __restrict__ gate,
-                                                              int add, int ldk, int skip) {
+                                                              int last, int ldk,
+                                                              fa_gram_cols cols) {
   if (gate != nullptr && *gate == 0) return;   // stand-by of a pass that did not need it
-  const int NTP = TM > 0 ? T * TM : T * (T + 1) / 2;
+  const int NTP = TM > 0 ? T * TM : last ? T : T * (T + 1) / 2;
   const int ei = threadIdx.x & 63, g = threadIdx.x >> 6;   // entry, strand 0..15
   const int E = blockIdx.x * 64 + ei;                      // entry in [0, NTP*256)
   const int64_t stride = (int64_t)NTP * 256;
@@ -703,12 +712,12 @@ __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __re
     }
     int ta = 0, tb = 0;
     for (int aa = 0, k = 0; aa < T; ++aa)
-      for (int bb = aa; bb < T; ++bb, ++k)
+      for (int bb = last ? T - 1 : aa; bb < T; ++bb, ++k)
         if (k == tp) { ta = aa; tb = bb; }
     const int gi = ta * 16 + 4 * r + (l >> 4), gj = tb * 16 + (l & 15);
     if (gi < p && gj < p && gi <= gj) {
-      if (add) {
-        const int ki = gi + (gi >= skip ? 1 : 0), kj = gj + (gj >= skip ? 1 : 0);
+      if (cols.listed) {
+        const int ki = cols.idx[gi], kj = cols.idx[gj];
         const double v = K[ki * ldk + kj] + tot;   // (both triangles hold the same bits)
         K[ki * ldk + kj] = v;
         K[kj * ldk + ki] = v;
@@ -1431,10 +1440,10 @@ size_t fa_irls_lds_bytes(int p, int* big_in_global) {
 
 // ------------------------------------------------------------------------------------------
 // launchers (host).  Shapes are validated by the callers in fa_api.hip.
-template <int T, int CPL, typename E, int WAVES, bool ROWS>
+template <int T, int CPL, typename E, int WAVES, bool ROWS, bool LAST = false>
 static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, int max_blocks,
                                 double* partials, int* nparts, hipStream_t st,
-                                const fa_ktime* tm, const int* gate, int skip = 1 << 30) {
+                                const fa_ktime* tm, const int* gate, const fa_gram_cols& cols) {
   static_assert(WAVES <= FA_GRAM_WAVES_PER_CU, "partials buffer is sized for this many");
   constexpr int R = (64 / CPL) * E::EPL;
   constexpr int CS = R * E::SIZE + 16;
@@ -1447,9 +1456,9 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
   int64_t wgs = (ntiles + WAVES - 1) / WAVES;
   if (wgs > max_blocks) wgs = max_blocks;
   *nparts = (int)wgs;
-  FA_LAUNCH(tm, (fa_gram_kernel<T, CPL, E, WAVES, ROWS>), dim3((unsigned)wgs),
+  FA_LAUNCH(tm, (fa_gram_kernel<T, CPL, E, WAVES, ROWS, LAST>), dim3((unsigned)wgs),
             dim3(64 * WAVES), lds_bytes, st, (const unsigned char*)G, ldg, p, n, ntiles,
-            partials, gate, skip);
+            partials, gate, cols);
   return hipGetLastError();
 }
 
@@ -1460,11 +1469,17 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
 template <typename E, bool ROWS>
 static hipError_t launch_gram_e(const void* G, int64_t ldg, int p, int64_t n, int max_blocks,
                                 double* partials, int* nparts, hipStream_t st,
-                                const fa_ktime* tm, const int* gate, int skip = 1 << 30) {
+                                const fa_ktime* tm, const int* gate,
+                                const fa_gram_cols& cols = fa_gram_cols{}, bool last = false) {
   switch ((p + 15) / 16) {
 #define FA_X(t, cpl, w)                                                                        \
-    case t: return launch_gram_t<t, cpl, E, w, ROWS>(G, ldg, p, n, max_blocks, partials, nparts, \
-                                                     st, tm, gate, skip);
+    case t:                                                                                    \
+      if constexpr (!ROWS && t > 1)                                                            \
+        if (last)                                                                              \
+          return launch_gram_t<t, cpl, E, w, false, true>(G, ldg, p, n, max_blocks, partials,  \
+                                                          nparts, st, tm, gate, cols);         \
+      return launch_gram_t<t, cpl, E, w, ROWS>(G, ldg, p, n, max_blocks, partials, nparts, st, \
+                                               tm, gate, cols);
     FA_GRAM_TILINGS(FA_X)
 #undef FA_X
   }
@@ -1477,8 +1492,13 @@ static hipError_t prepare_gram_e() {
 #define FA_X(t, cpl, w)                                                                          \
   if (e == hipSuccess)                                                                           \
     e = hipFuncSetAttribute(                                                                     \
-        reinterpret_cast<const void*>(fa_gram_kernel<t, cpl, E, w, ROWS>),                       \
-        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        reinterpret_cast<const void*>(fa_gram_kernel<t, cpl, E, w, ROWS, false>),                \
+        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);                                 \
+  if constexpr (!ROWS && t > 1)                                                                  \
+    if (e == hipSuccess)                                                                         \
+      e = hipFuncSetAttribute(                                                                   \
+          reinterpret_cast<const void*>(fa_gram_kernel<t, cpl, E, w, false, true>),              \
+          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   FA_GRAM_TILINGS(FA_X)
 #undef FA_X
   return e;
@@ -1510,27 +1530,31 @@ hipError_t fa_launch_gram_reduce(const double* partials, int nparts, int p, doub
   const int T = (p + 15) / 16;
   const int NTP = T * (T + 1) / 2;
   FA_LAUNCH(tm, fa_gram_reduce_kernel, dim3(NTP * 4), dim3(1024), 0, st, partials, nparts, T, p,
-            Kd, 0, 0, colscale, gate, 0, p, p);
+            Kd, 0, 0, colscale, gate, 0, p, fa_gram_cols{});
   return hipGetLastError();
 }
 
-// K += the Gram matrix of n rows of the p gradients without gradient `skip` (skip >= p: of all of
-// them), products and sums in fp64.  Worker-major G, pointing at the first of the rows in
-// gradient 0; Kd is p x p.
-hipError_t fa_launch_gram_add(const void* G, int64_t ldg, int p, int64_t n, int dtype, int skip,
-                              int max_blocks, double* partials, double* Kd, hipStream_t st) {
-  const int cols = skip < p ? p - 1 : p;
+hipError_t fa_launch_gram_add(const void* G, int64_t ldg, int p, int64_t n, int dtype,
+                              uint64_t first, uint64_t then, int max_blocks, double* partials,
+                              double* Kd, hipStream_t st) {
+  fa_gram_cols cols{};
+  cols.listed = 1;
+  int ncols = 0;
+  for (const uint64_t set : {first, then})
+    for (int j = 0; j < p; ++j)
+      if ((set >> j) & 1u) cols.idx[ncols++] = (uint8_t)j;
+  const int T = (ncols + 15) / 16;
+  const bool last = first != 0;
   int nparts = 0;
   hipError_t e = dtype == FA_F32
-      ? launch_gram_e<ElemF32, false>(G, ldg, cols, n, max_blocks, partials, &nparts, st, nullptr,
-                                      nullptr, skip)
-      : launch_gram_e<ElemBF16, false>(G, ldg, cols, n, max_blocks, partials, &nparts, st, nullptr,
-                                       nullptr, skip);
+      ? launch_gram_e<ElemF32, false>(G, ldg, ncols, n, max_blocks, partials, &nparts, st, nullptr,
+                                      nullptr, cols, last)
+      : launch_gram_e<ElemBF16, false>(G, ldg, ncols, n, max_blocks, partials, &nparts, st, nullptr,
+                                       nullptr, cols, last);
   if (e != hipSuccess) return e;
-  const int T = (cols + 15) / 16, NTP = T * (T + 1) / 2;
-  hipLaunchKernelGGL(fa_gram_reduce_kernel, dim3(NTP * 4), dim3(1024), 0, st,
-                     (const double*)partials, nparts, T, cols, Kd, 0, 0, (const double*)nullptr,
-                     (const int*)nullptr, 1, p, skip);
+  hipLaunchKernelGGL(fa_gram_reduce_kernel, dim3((last ? T : T * (T + 1) / 2) * 4), dim3(1024), 0,
+                     st, (const double*)partials, nparts, T, ncols, Kd, 0, 0,
+                     (const double*)nullptr, (const int*)nullptr, last ? 1 : 0, p, cols);
   return hipGetLastError();
 }
 
@@ -1572,7 +1596,7 @@ hipError_t fa_launch_proj_reduce(const double* partials, int nparts, int p, int 
                                  hipStream_t st, const fa_ktime* tm) {
   const int T = (p + 15) / 16, TM = (m + 15) / 16;
   FA_LAUNCH(tm, fa_gram_reduce_kernel, dim3(T * TM * 4), dim3(1024), 0, st, partials, nparts, T,
-            p, Td, TM, m, (const double*)nullptr, (const int*)nullptr, 0, p, p);
+            p, Td, TM, m, (const double*)nullptr, (const int*)nullptr, 0, p, fa_gram_cols{});
   return hipGetLastError();
 }
 
@@ -1612,7 +1636,7 @@ hipError_t fa_launch_cross(const float* Y, int64_t ldy, int m, const void* G, in
   const int ncols = 16 * TMr + p;
   hipLaunchKernelGGL(fa_gram_reduce_kernel, dim3(TMr * TC * 4), dim3(1024), 0, st,
                      (const double*)partials, (int)stripes, TMr, m, Wd, TC, ncols,
-                     (const double*)nullptr, (const int*)nullptr, 0, m, m);
+                     (const double*)nullptr, (const int*)nullptr, 0, m, fa_gram_cols{});
   return hipGetLastError();
 }
 

@@ -50,3 +50,59 @@ def test_gram_from_pieces_at_every_width_class(p, dtype):
         assert np.max(np.abs(K - ref) / scale) <= 1e-12
         assert np.array_equal(K, K.T)
     agg.close()
+
+
+@pytest.mark.parametrize("p,n,dtype", [
+    *((p, 20_011, d) for p in (17, 18, 33, 64) for d in ("f32", "bf16")),
+    *((p, (1 << 22) + 20_011, d) for p in (18, 33, 34) for d in ("f32", "bf16")),
+    (50, (1 << 22) + 20_011, "bf16"), (64, (1 << 22) + 20_011, "bf16")])
+def test_gram_from_pieces_in_any_order(p, n, dtype):
+    """p > 16.  Small pieces: the pairs of all but one gradient, then the last one's row.  A first
+    piece of 2^22 rows or more: the pairs of the first gradients ahead of the others', of all but one
+    at once where one of the first is the last or the last but one to hold the rows.  Whole
+    gradients and pieces in random order, one worker far behind with its later pieces, pieces of
+    eight rows and of many tiles.  fp64 sums as above, in blocks."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("gram from pieces: orders", p, n, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(p)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    pitch = (n + 7) // 8 * 8
+    full = torch.zeros((p, pitch), dtype=tdt, device="cuda")
+    for i in range(p):
+        full[i, :n] = torch.randn(n, generator=gen, device="cuda").to(tdt)
+    ref = np.zeros((p, p))
+    for a in range(0, n, 1 << 20):
+        x = full[:, a:min(a + (1 << 20), n)].to(torch.float64)
+        ref += (x @ x.t().contiguous()).cpu().numpy()
+    scale = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
+    buf = torch.empty_like(full)
+    agg = FlagAggregator(n_max=n, p_max=p, dtype=dtype)
+    r = np.random.default_rng(p)
+    base = n - 20_011
+    cuts = [0, base + 4096, base + 4104, base + 16_384, n]
+    pieces = list(zip(cuts, cuts[1:]))
+    for kind in ("whole", "pieces", "straggler", "mixed"):
+        todo = {i: [(0, n)] if kind == "whole" or (kind == "mixed" and i % 3 == 0) else pieces[:]
+                for i in range(p)}
+        behind = int(r.integers(p)) if kind == "straggler" else -1
+        buf.fill_(float("nan"))
+        agg.fa_gram_begin(p, n)
+        started = False
+        while any(todo.values()):
+            ready = [i for i in todo if todo[i]]
+            # the one behind lands its first piece at once, the others when all are done
+            if behind in ready and len(ready) > 1 and started:
+                ready.remove(behind)
+            i = behind if behind in ready and not started else int(r.choice(ready))
+            started = True
+            a, b = todo[i].pop(0)
+            held = [n if not todo[j] else todo[j][0][0] for j in range(p) if j != i]
+            for e in sorted({h for h in held if a < h < b} | {b}):   # cut where others' rows end
+                buf[i, a:e] = full[i, a:e]
+                agg.fa_gram_update_rows(buf[:, :n], i, a, e - a)
+                a = e
+        agg.fa_aggregate_arrived(buf[:, :n], p // 2, 1.0, 1, 0.0)
+        K = agg.fa_get_info().K
+        assert np.max(np.abs(K - ref) / scale) <= 1e-12, kind
+        assert np.array_equal(K, K.T)
+    agg.close()
