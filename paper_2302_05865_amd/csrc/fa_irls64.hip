@@ -158,6 +158,7 @@ struct Small {
   float hist[MAX_PURIFY];          // step k of this solve: a of a growth, -1 - b of a shrinking map
   float cap[2];                    // the ends of the gap at step cap_k
   int cap_k;                       // (negative: not known)
+  int cap_in;                      // bit e: end e may lie in what was folded
   double est[2];                   // eigenvalues m + 1 and m of the last solve's matrix ...
   int have_est;                    // ... if known
   int guessed;                     // this solve's first steps were planned
@@ -169,7 +170,7 @@ struct Small {
 // by a factor of 1.24 on average; knowing it, by up to two, with the same product:
 //   growth   1 - (1 - a X)^2,     1 <= a <= 2: a = 1 is 2X - X^2; folds [2/a - 1, 1] onto itself
 //   shrink   ((1 + b) X - b)^2,   0 <= b <= 1: b = 0 is X^2;      folds [0, 2b / (1 + b)]
-// A fold gives up the order of what it folds, so it must not reach the gap.  From the second solve
+// A fold gives up the order of what it folds, so it must not reach the gap.  From the third solve
 // on the last solve's gap is a guess for this one's: a fifth outside either end ([0, H] and [G, 1])
 // is folded, the two eigenvalues themselves (expected near h and g) are not.  [G, 1] and [0, H] are
 // taken through the maps along with X (rounded outwards).  What started in [G, 1] stays in its
@@ -178,10 +179,13 @@ struct Small {
 // the guess was worth.  If not, the solve is done once more without.
 // The maps of these steps need no trace: the steering wavefront has each ready one step ahead, so
 // nobody waits for it.  Once h and g are within 0.03 of 0 and 1 the steps go on as always.
-// Where there is no guess - the first solve, a gap of less than a fifth, a guess that failed - only the
-// first growth steps are planned, from a bound that always holds (trace X_0 = 1).
-// Measured, steps per call (plain -> with plans): p = 32, m = 16, 15 solves 428 -> 342; p = 60, 5 solves
-// 181 -> 163; p = 64, 30 solves 806 -> 639.
+// Where there is no guess - the first two solves (the first weights move the gap most: guesses failed
+// there), a gap of less than a fifth or of more than 32 (where the plain steps need few), a guess that
+// failed - only the first growth steps are planned, from a bound that always holds (trace X_0 = 1).
+// Measured, steps per call (plain -> with plans): p = 32, m = 16, 15 solves 400 -> 313; p = 64,
+// m = 32, 30 solves 764 -> 639; p = 60, m = 31, 5 solves 170 -> 161.  Where a guess from the second solve
+// on and ends that stay below a fold cost up to 1.7 times the plain steps (m = 1 or close to p, a = 4: 137
+// for 81), it is 85 now; the worst of 8000 problems of that kind drawn at random is 1.35 times.
 struct Plan {                 // all scalar: one wavefront's, the same in every lane
   float H, G, h, g;
   float c;                    // a or b of the last map
@@ -683,14 +687,15 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       } else if (wave == SW) {
         // everything that is decided here is scalar
         const double lo = sm.est[0] * sc, up = sm.est[1] * sc, dm = (double)mm;
-        const bool guessed = scalar(sm.have_est != 0 && up > 1.2 * lo);
+        const bool guessed = scalar(it > 1 && sm.have_est != 0 && up > 1.2 * lo && up < 32.0 * lo);
         double t = hi * sc;                 // trace X_k
         bool sq = t > dm, planned = false, mapped = false, have_cap = false;
         Plan pl = {0.0f, 1.0f, 0.0f, 1.0f, 1.0f, 0.03f, true};
+        float Hp = 0.0f, Gp = 1.0f;         // pl.H, pl.G of X_{k-1} (looked at behind unplanned steps)
         if (lane == 0) { sm.guessed = guessed; sm.cap_k = -1; }
         if (guessed) {
           pl.H = scalar((float)(0.8 * lo)); pl.G = scalar((float)fmin(1.0, 1.25 * up));
-          pl.h = scalar((float)(1.05 * lo)); pl.g = scalar((float)(0.95 * up));
+          pl.h = scalar((float)(1.05 * lo)); pl.g = scalar((float)fmin(0.99, 0.95 * up));
         } else {
           // no guess, but trace X_0 = 1 bounds x_{m+1} by 1 / (m + 1) (with a margin for rounding):
           // growth may fold what is above that, while it is small
@@ -728,7 +733,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
               }
               sq = scalar(t > dm);
               mapped = false;
-              if (guessed && k >= 64) word = (word & ~4) | 2;      // the guess is no good
+              // the guess is no good: nearly a projector, but with another trace
+              if (guessed && (k >= 64 || scalar(s < 1e-3 && fabs(t1 - dm) > 0.5))) word = (word & ~4) | 2;
             }
             word |= sq ? 1 : 0;
             if (lane == 0) {
@@ -742,12 +748,17 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
             if (!have_cap && scalar(s < 0.02)) {
               have_cap = true;
               if (lane == 0) {
+                const double cl = 0.5 * (1.02 * s + t1 - dm), cu1 = 0.5 * (1.02 * s - t1 + dm);
                 sm.cap_k = k - 1;
-                sm.cap[0] = (float)fmin(0.5, fmax(1e-4, 0.5 * (1.02 * s + t1 - dm)));
-                sm.cap[1] = 1.0f - (float)fmin(0.5, fmax(1e-4, 0.5 * (1.02 * s - t1 + dm)));
+                sm.cap[0] = (float)fmin(0.5, fmax(1e-4, cl));
+                sm.cap[1] = 1.0f - (float)fmin(0.5, fmax(1e-4, cu1));
+                // (both are sums, good to 0.02 s)
+                const double zl = 0.5 * (double)(rank - mm) * Hp, zu = 0.5 * dm * (1.0 - Gp);
+                sm.cap_in = !guessed ? 0 : (cl <= zl + 0.02 * s ? 1 : 0) | (cu1 <= zu + 0.02 * s ? 2 : 0);
               }
             }
             if (guessed) {
+              Hp = pl.H; Gp = pl.G;
               pl.grow = !sq;
               pl.c = sq ? 0.0f : 1.0f;
               plan_push(pl);
@@ -827,7 +838,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       }
     } else if (wave == SW && mm < rank && sm.cap_k >= 0) {
       // where the two ends of the gap lay in this solve's matrix, for the next one's folds: the
-      // bounds of step cap_k taken back through the maps before it (even lanes: the lower end)
+      // bounds of step cap_k taken back through the maps before it (even lanes: the lower end).  An
+      // end that was folded could have come from either side of the fold: then further out.
       float yv = sm.cap[lane & 1];
       for (int k = sm.cap_k - 1; k >= 0; --k) {
         const float h = sm.hist[k];
@@ -838,7 +850,10 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
           yv = (__builtin_amdgcn_sqrtf(yv) - (h + 1.0f)) * __builtin_amdgcn_rcpf(-h);
         }
       }
-      if (lane < 2) sm.est[lane] = hi * (double)yv;
+      double e = hi * (double)yv;
+      if ((sm.cap_in >> (lane & 1)) & 1)
+        e = lane & 1 ? fmin(hi, fmax(e, 2.0 * sm.est[1])) : fmin(e, 0.5 * sm.est[0]);
+      if (lane < 2) sm.est[lane] = e;
       if (lane == 0) sm.have_est = 1;
     }
     __syncthreads();

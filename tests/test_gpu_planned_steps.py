@@ -1,6 +1,7 @@
 """Purification steps that need no trace: planned from the previous solve's gap (16 < p <= 64: where the
-guess holds, where it does not and the solve is done again, every tile count) and the folded first
-growth steps (p <= 16: every width class of the solver)."""
+guess holds, where it does not and the solve is done again, every tile count, single columns and
+blocks, a general exponent) and the folded first growth steps (p <= 16: every width class of the
+solver).  info.sweeps counts steps, those of a solve that is done again among them."""
 import numpy as np
 import pytest
 
@@ -10,17 +11,22 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def gram_of(p, seed, n=200):
+def grads_of(p, seed, n=200):
     """Workers around a common direction (or none), some of them replaced by scaled noise or
     copies: the gap at m moves by orders of magnitude from one solve to the next."""
     r = np.random.default_rng(seed)
     G = r.standard_normal((p, n)) * 0.5 + (r.standard_normal((1, n)) if r.random() < 0.7 else 0)
     for i in range(r.integers(0, p // 2)):
         G[i] = r.choice([-4, 5, 0.01]) * r.standard_normal(n) + r.choice([0, 1]) * G[-1]
+    return G
+
+
+def gram_of(p, seed):
+    G = grads_of(p, seed)
     return G @ G.T
 
 
-# the first nine: a NumPy model of the steps says that a guess fails in one of the solves
+# the first nine: the gap moves by orders of magnitude between the first two solves
 @pytest.mark.parametrize("p,m,lam,seed", [
     (17, 5, 0.1, 636078391), (27, 6, 0.1, 604592858), (25, 23, 0.0, 746945520),
     (21, 20, 4.0, 614711476), (26, 23, 0.1, 651383795), (23, 8, 0.0, 515711975),
@@ -53,8 +59,77 @@ def _compare_with_jacobi(p, m, lam, seed):
         got.append(agg.fa_get_info())
         agg.close()
     a, j = got
+    assert m >= a.rank or a.sweeps != j.sweeps          # the Jacobi solver did not do it
     assert a.status == 0 and j.status == 0 and a.rank == j.rank and a.iters_done == 8
     assert np.max(np.abs(a.objective - j.objective) / (1.0 + np.abs(j.objective))) <= 1e-8
     scale = np.sqrt(np.diag(K))
     assert np.linalg.norm((a.c - j.c) * scale) <= 1e-8 * np.linalg.norm(j.c * scale)
     assert np.max(np.abs(a.A.T @ K @ a.A - np.eye(m))) <= 1e-9
+
+
+def _steps(p, m, lam, seed, mode):
+    """Steps of each of eight solves, as planned and (from launches of one solve each, which know no
+    previous gap) without; the answer after them and the Jacobi solver's."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("steps", p, m, lam, seed, mode)
+    G = torch.from_numpy(grads_of(p, seed).astype(np.float32)).cuda()
+    a = 4.0 if mode == "exponent" else 2.0
+    agg, ref = (FlagAggregator(n_max=256, p_max=64, exponent_a=a, solver=s) for s in ("auto", "jacobi"))
+
+    def call(ctx, iters):
+        if mode == "blocks":
+            ctx.fa_aggregate_grouped(G, [1] * p, m, lam, iters, 0.0)
+        else:
+            ctx.fa_aggregate(G, m, lam, iters, 0.0)
+        return ctx.fa_get_info()
+
+    steps, plain, before = [], [], 0
+    for iters in range(1, 9):
+        info = call(agg, iters)
+        steps.append(info.sweeps - before)
+        before = info.sweeps
+        agg.fa_aggregate_restream(G, m, lam, iters)
+        plain.append(agg.fa_get_info().sweeps)
+    j = call(ref, 8)
+    # projectors good to eps p / gap and the relative gap at m above 1e-7 throughout
+    assert info.status == 0 and j.status == 0 and info.rank == j.rank and info.sweeps != j.sweeps
+    assert np.max(np.abs(info.objective - j.objective) / (1.0 + np.abs(j.objective))) <= 1e-7
+    scale = np.sqrt(np.diag(j.K))
+    assert np.linalg.norm((info.c - j.c) * scale) <= 1e-7 * np.linalg.norm(j.c * scale)
+    agg.close()
+    ref.close()
+    return np.array(steps), np.array(plain)
+
+
+# a gap that closes in or opens up; ends beyond the last solve's folds; the second solve's gap elsewhere
+@pytest.mark.parametrize("p,m,lam,seed,mode", [
+    (54, 1, 0.0, 759667580, "exponent"), (48, 47, 1.0, 5, "plain"), (48, 47, 1.0, 5, "blocks"),
+    (17, 16, 1.0, 1, "plain"), (64, 63, 4.0, 8, "plain"), (21, 20, 4.0, 614711476, "plain"),
+    (17, 5, 0.1, 636078391, "plain"), (27, 6, 0.1, 604592858, "blocks"), (23, 8, 0.0, 515711975, "exponent"),
+    (18, 2, 0.0, 981457606, "plain")])
+def test_planned_steps_cost_no_more_than_plain_ones(p, m, lam, seed, mode):
+    """Rounding moves a solve by a step or so; 10 % covers that and the last check of a plan."""
+    steps, plain = _steps(p, m, lam, seed, mode)
+    assert steps.sum() <= 1.1 * plain.sum(), (steps, plain)
+
+
+@pytest.mark.parametrize("p,m,lam,seed", [(17, 5, 0.1, 636078391), (27, 6, 0.1, 604592858),
+                                          (23, 8, 0.0, 515711975), (17, 5, 0.1, 403139253)])
+@pytest.mark.parametrize("mode", ["plain", "blocks"])
+def test_planned_steps_are_taken_and_fewer(p, m, lam, seed, mode):
+    steps, plain = _steps(p, m, lam, seed, mode)
+    assert np.all(np.abs(steps[:2] - plain[:2]) <= 1)                 # no guess yet
+    assert steps[2:].sum() <= 0.9 * plain[2:].sum(), (steps, plain)
+
+
+@pytest.mark.parametrize("p,m,lam,seed,mode", [
+    (25, 23, 0.0, 195971021, "plain"), (31, 30, 0.1, 926618490, "plain"), (27, 24, 0.0, 822271859, "plain"),
+    (17, 14, 0.0, 574192913, "blocks"), (31, 28, 0.0, 1042215544, "blocks"),
+    (64, 62, 0.0, 233228967, "exponent"), (37, 36, 0.0, 172104776, "exponent"),
+    (25, 21, 4.0, 611524802, "exponent")])
+def test_a_guess_that_fails_costs_one_more_solve(p, m, lam, seed, mode):
+    """The third solve's gap is not near the second's: that solve takes its plain steps and the
+    planned ones before them, and is over well before the 64 steps after which a guess is dropped."""
+    steps, plain = _steps(p, m, lam, seed, mode)
+    assert 12 <= steps[2] - plain[2] <= 45, (steps, plain)
+    assert np.all(steps[3:] <= plain[3:] + 10), (steps, plain)
