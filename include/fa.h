@@ -116,8 +116,8 @@ typedef struct {
   int p, m;        /* as passed */
   int rank;        /* numerical rank of G */
   int iters_done;  /* IRLS solves performed (<= iters; fewer if tol stopped it) */
-  int sweeps;      /* eigen-iteration count in total (diagnostic): purification steps on the
-                      p <= 16 fast path, Jacobi sweeps otherwise */
+  int sweeps;      /* eigen-iteration count in total (diagnostic): purification steps of the
+                      matrix-core solvers, Jacobi sweeps where the Jacobi solver did the work */
   double eigengap; /* (mu_m - mu_{m+1}) / mu_1 of the last weighted PCA (inf if m >= rank) */
   double objective[FA_ITERS_MAX]; /* Eq. 5 value after each solve */
   double s[FA_P_MAX];  /* |g_i|^2 */

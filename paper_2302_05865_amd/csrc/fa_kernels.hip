@@ -121,15 +121,16 @@ struct fa_gram_cols {
 // Each wavefront owns a private LDS tile and walks the row tiles w, w + W, w + 2W, ... (w its
 // index among the W wavefronts of the launch: a fixed assignment, so results are
 // reproducible).  Per tile: 16-byte coalesced global loads (next tile's loads are in flight while this
-// tile is multiplied) -> LDS laid out [column][row] -> each lane reads the four rows of "its"
-// column -> v_mfma_f64_16x16x4_f64, whose A and B operands are the same register for a
+// tile is multiplied) -> LDS laid out [column][row] (interleaved storage: as the rows are, see ROWS) ->
+// each lane reads the four rows of "its" column -> v_mfma_f64_16x16x4_f64, whose A and B operands are the same register for a
 // diagonal 16x16 block of G^T G: lane (c, k) supplies G[row_k][c].
 // Products of fp32 (or bf16) inputs are exact in fp64 and the accumulation is fp64, which the
 // small differences 1 - v_i of the IRLS weights need.
 //
 // The operands of step t+1 are read from LDS and converted before the matrix instructions
 // of step t are issued, so their LDS latency is hidden behind those.
-// LDS columns p..16T-1 are zeroed once and never written, so no masking is needed.
+// No masking: over worker-major storage the LDS columns p..16T-1 are zeroed once and never written, over
+// interleaved storage they read what lies there, which only reaches entries of K that nobody reads.
 //
 // Launch shape: one workgroup of WAVES wavefronts (a multiple of the four SIMDs) per compute
 // unit, each wavefront with its private LDS tile; the workgroup's LDS request is sized so

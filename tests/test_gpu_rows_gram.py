@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 def test_interleaved_gram_matches_worker_major(p, pitch, dtype):
     """Same tiles, same order of rows and sums as over worker-major storage: the same bits, whatever
     the pitch; the places between the rows hold NaN and reach nothing.  Sizes around one tile
-    (64 rows fp32, 128 bf16) and around one round of all wavefronts of the widest tiling."""
+    (64 rows fp32, 128 bf16) and less than a round of all wavefronts."""
     from paper_2302_05865_amd import FlagAggregator
     announce("interleaved gram", p, pitch, dtype)
     for n in (1, 63, 64, 65, 127, 129, 2049, 262_145 if p == 17 else 20_003):
@@ -29,6 +29,32 @@ def test_interleaved_gram_matches_worker_major(p, pitch, dtype):
         a = FlagAggregator(n_max=n, p_max=p, dtype=dtype, layout="row_major")
         b = FlagAggregator(n_max=n, p_max=p, dtype=dtype, gram="fp64")
         K, W = a.fa_gram(rows[:, :p]), b.fa_gram(by_worker)
+        assert np.all(np.isfinite(K)) and np.array_equal(K, W), n
+        a.close()
+        b.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("p,pitch,waves", [(9, 9, 12), (15, 16, 12), (17, 17, 16), (30, 32, 16),
+                                           (33, 33, 8), (45, 48, 8), (51, 51, 8), (64, 64, 8)])
+def test_interleaved_gram_in_its_steady_state(p, pitch, waves, dtype):
+    """Two rounds of all wavefronts and a ragged tail: every wavefront has a full tile in LDS while the
+    next full one is on its way to its registers, some have a third and one the ragged one (waves: per
+    compute unit, of that width's tiling)."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("interleaved gram, rounds", p, pitch, dtype)
+    tile = 64 if dtype == "f32" else 128
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    gen = torch.Generator(device="cuda").manual_seed(p)
+    for n in (2 * units * waves * tile, 2 * units * waves * tile + 5 * tile + 3):
+        by_worker = torch.zeros((p, -(-n // 8) * 8), device="cuda",
+                                dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+        by_worker[:, :n] = torch.randn((p, n), generator=gen, device="cuda")
+        rows = torch.full((n, pitch), float("nan"), dtype=by_worker.dtype, device="cuda")
+        rows[:, :p] = by_worker[:, :n].t()
+        a = FlagAggregator(n_max=n, p_max=p, dtype=dtype, layout="row_major")
+        b = FlagAggregator(n_max=n, p_max=p, dtype=dtype, gram="fp64")
+        K, W = a.fa_gram(rows[:, :p]), b.fa_gram(by_worker[:, :n])
         assert np.all(np.isfinite(K)) and np.array_equal(K, W), n
         a.close()
         b.close()
