@@ -1059,7 +1059,7 @@ __global__ __launch_bounds__(256) void fa_combine_multi_kernel(
 // in ascending order), the q smallest scores are selected (ties: smaller index), and the
 // coefficients of out = G c are 1/q on the selected workers.  A distance's place in its row is
 // counted, one thread per distance, and the row's thread adds the first k up in order (an insertion
-// sort by one thread per worker took 13.6 us at p = 15 and 185 at p = 64; 4.4 and 28 now).
+// sort by one thread per worker took 13.6 us at p = 15 and 185 at p = 64; 4.6 and 28 now).
 // p <= 64; scores and selected may be host memory the device can write.
 __global__ __launch_bounds__(1024) void fa_krum_kernel(const double* __restrict__ K, int p, int k,
                                                        int q, double* __restrict__ c,
