@@ -567,12 +567,20 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     cur = B0; nxt = B1;
     if (mm < rank) {
       // ---- X_0 = M / trace(M) (slightly less: any scale with eigenvalues in [0, 1] will do)
+      // Exactly symmetric: the diagonal tiles take their lower triangle twice (the others are mirrored
+      // already).  The steps keep that bit for bit, X^T X being symmetric; an antisymmetric rest would
+      // only ever see a map's linear coefficient, up to 4 in a planned step, and no planned step
+      // takes it out as a square does: 1e-17 of M was 5e-4 of X after 40 of them.
       const double sc = __builtin_amdgcn_rcp(hi) * (1.0 - 1e-7);
       for (int f = wave; f < TT; f += NW) {
         const int fI = f / T, fJ = f % T;
         v4d x = load_tile<T>(B0, fI, fJ, lane);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] *= sc;
+        for (int r = 0; r < 4; ++r) {
+          const int i = 4 * r + q4;
+          if (fI == fJ && i < c16) x[r] = B0[eidx<T>(16 * fI + c16, 16 * fI + i)];
+          x[r] *= sc;
+        }
         store_tile<T>(B0, fI, fJ, lane, x);
       }
       // ---- purification ---------------------------------------------------------------------
@@ -725,7 +733,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
               if (!mapped) {
                 // X_k is X^2 or 2X - X^2 of X = X_{k-1}: sum x (1 - x) over its eigenvalues
                 s = sq ? t1 - t : t - t1;
-                if (scalar(s < 1e-10)) {
+                if (scalar(fabs(s) < 1e-10)) {
                   word |= 2;
                   if (scalar(fabs(t1 - dm) < 0.25) && (!guessed || (pl.G > 0.9f && pl.H < 0.1f)))
                     word |= 4;

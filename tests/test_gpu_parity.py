@@ -926,7 +926,7 @@ def test_grouped_with_single_columns_is_fa_aggregate(name, n):
     b = gen.fa_aggregate(dev, w.m, w.lam, 5, 0.0).clone()
     assert torch.equal(a, b)
     gen.close()
-    # on the default route the block kernel takes powers where the plain one has square roots
+    # the default route: the block kernel against the plain one
     plain = FlagAggregator(n_max=w.n, p_max=w.p, dtype=w.dtype)
     c = plain.fa_aggregate_grouped(dev, [1] * w.p, w.m, w.lam, 5, 0.0).clone()
     info_c = plain.fa_get_info()

@@ -133,3 +133,29 @@ def test_a_guess_that_fails_costs_one_more_solve(p, m, lam, seed, mode):
     steps, plain = _steps(p, m, lam, seed, mode)
     assert 12 <= steps[2] - plain[2] <= 45, (steps, plain)
     assert np.all(steps[3:] <= plain[3:] + 10), (steps, plain)
+
+
+@pytest.mark.parametrize("p,m,lam,iters,seed,a", [
+    (59, 55, 1.0, 14, 954815241, 2.0), (51, 47, 0.1, 14, 801768823, 2.0), (59, 57, 0.1, 14, 636697993, 4.0),
+    (26, 22, 4.0, 9, 556645660, 2.0)])
+def test_long_plans_keep_the_projector_symmetric(p, m, lam, iters, seed, a):
+    """Eigenvalues m and m + 1 at 1e-7 of the trace: up to forty planned steps with no square among
+    them, so whatever is not symmetric in X_0 meets the maps' linear coefficients only (product 1e13
+    here; the objective was wrong by 6e-4 in the first case).  Workers with two gradients.  Both
+    projectors are good to eps p / gap, 1e-15 * 64 / 5e-8 = 1e-6 at worst in a single vector pair;
+    weights and coefficients see its square and its product with a small component."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("long plans", p, m, lam, iters, seed, a)
+    G = torch.from_numpy(grads_of(p, seed).astype(np.float32)).cuda()
+    got = []
+    for solver in ("auto", "jacobi"):
+        agg = FlagAggregator(n_max=256, p_max=64, exponent_a=a, solver=solver)
+        agg.fa_aggregate_grouped(G, [2] * (p // 2) + [1] * (p % 2), m, lam, iters, 0.0)
+        got.append(agg.fa_get_info())
+        agg.close()
+    x, j = got
+    assert x.status == 0 and j.status == 0 and x.sweeps != j.sweeps
+    scale = np.sqrt(np.diag(j.K))
+    assert np.max(np.abs(x.objective - j.objective) / (1.0 + np.abs(j.objective))) <= 1e-9
+    assert np.linalg.norm((x.c - j.c) * scale) <= 2e-9 * np.linalg.norm(j.c * scale)
+    assert np.max(np.abs(x.A.T @ x.K @ x.A - np.eye(m))) <= 1e-9
