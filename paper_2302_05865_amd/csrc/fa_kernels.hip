@@ -109,6 +109,9 @@ __device__ __forceinline__ uint4 load16_guarded(const unsigned char* base, int64
   return v;
 }
 
+// how G lies in memory and goes to LDS: worker-major; interleaved as it is; interleaved, scattered
+enum { FA_MEM_WORKER, FA_MEM_ROWS, FA_MEM_SCATTER };
+
 // which gradients the columns of a Gram pass are, where they are not simply the first p
 struct fa_gram_cols {
   int listed;
@@ -169,13 +172,18 @@ __device__ __forceinline__ void unpack4(const unsigned char* src, double* x) {
 // that the sixteen elements each quarter wavefront reads lie in banks of their own.  The scatter
 // of every element to a [column][row] place on the way into LDS, eight 2-byte writes per 16 bytes
 // of bf16, bounded the pass: p = 32, bf16, 8M rows 390 -> 244 us, where the matrix core alone needs
-// 156; p = 64, bf16, 2M rows 444 -> 177; p = 20, fp32, 3M rows 95 -> 90; fp32 at the other widths
-// within 3 %.  What is left is the conversions: a SIMD does not overlap them with fp64 products.
+// 156; p = 64, bf16, 2M rows 444 -> 177; p = 20, fp32, 3M rows 95 -> 90; fp32, 4M rows at p = 47 262 -> 281
+// and at p = 64 443 -> 464, but at 300 thousand 39.6 -> 38.9 and 72 -> 55 (the reads are four where a
+// column's rows lie side by side).  What is left is the conversions: a SIMD does not overlap them with
+// fp64 products.
+// With one tile and many rows the scatter is the quicker one (FA_MEM_SCATTER; the same order of sums, the
+// same bits): as they are / scattered, p = 4 bf16 12M rows 138 / 122 us, 4M 56 / 51, 1M 22 / 22, 300 thousand
+// 13 / 14; p = 16 fp32 12M 136 / 129, 4M 53 / 52, 1M 22 / 23.
 // LDS bytes of a tile of r interleaved rows, whatever their pitch (at most 16 t elements):
 constexpr int fa_rows_tile_bytes(int t, int es, int r) {
   return r / 4 * ((64 * t * es + 255) / 256 * 256 + 16 * es);
 }
-template <int T, int CPL, typename E, int WAVES, bool ROWS, bool LAST>
+template <int T, int CPL, typename E, int WAVES, int ST, bool LAST>
 __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
                                                      const unsigned char* __restrict__ G,
                                                      int64_t ldg, int p, int64_t n,
@@ -185,6 +193,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
                                                      fa_gram_cols cols) {
   // as the stand-by of the bf16 matrix-core pass: nothing to do unless that one overflowed
   if (gate != nullptr && *gate == 0) return;
+  constexpr bool ROWS = ST == FA_MEM_ROWS;
   constexpr int EPL = E::EPL;
   constexpr int LPC = 64 / CPL;            // lanes per column in one load instruction
   constexpr int R = LPC * EPL;             // rows per tile
@@ -233,15 +242,27 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   const int gb = 4 * ldr * E::SIZE;
   const int gs = (gb & 15) ? gb : gb + ((16 * E::SIZE - gb) & 255);
   const int tb = R * ldr * E::SIZE;        // bytes of a tile's span
-  int pdst[NCG];
+  int pdst[NCG], prow[NCG], pcol[NCG];     // (scattered: row and column of a piece's first element)
 #pragma unroll
   for (int cg = 0; cg < NCG; ++cg) {
     const int b = (cg * 64 + lane) * 16;
     pdst[cg] = ROWS ? b + (b / gb) * (gs - gb) : 0;
+    prow[cg] = ST == FA_MEM_SCATTER ? (b / E::SIZE) / ldr : 0;
+    pcol[cg] = b / E::SIZE - prow[cg] * ldr;
   }
 
   uint4 regs[NCG];
   auto load_tile = [&](int64_t tl) {
+    if constexpr (ST == FA_MEM_SCATTER) {
+      const unsigned char* base = G + tl * tb;
+      const int lim = (int)(n - tl * R < R ? n - tl * R : R) * ldr;   // elements that exist
+#pragma unroll
+      for (int cg = 0; cg < NCG; ++cg) {
+        const int e0 = (cg * 64 + lane) * EPL;
+        if (e0 < R * ldr) regs[cg] = load16_guarded<E>(base, e0, lim);
+      }
+      return;
+    }
     if constexpr (ROWS) {
       if ((tl + 1) * R > n) return;        // the ragged last tile: see store_tile_lds
       const unsigned char* base = G + tl * tb + lane * 16;
@@ -275,6 +296,26 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
 #pragma unroll
       for (int cg = 0; cg < NCG; ++cg)
         if ((cg * 64 + lane) * 16 < tb) *reinterpret_cast<uint4*>(lds + pdst[cg]) = regs[cg];
+      return;
+    }
+    if constexpr (ST == FA_MEM_SCATTER) {
+#pragma unroll
+      for (int cg = 0; cg < NCG; ++cg) {
+        if ((cg * 64 + lane) * EPL >= R * ldr) continue;
+        int r = prow[cg], c = pcol[cg];
+        const uint32_t w[4] = {regs[cg].x, regs[cg].y, regs[cg].z, regs[cg].w};
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) {
+          if (c < p) {
+            if constexpr (E::SIZE == 4)
+              *reinterpret_cast<uint32_t*>(lds + c * CS + r * 4) = w[j];
+            else
+              *reinterpret_cast<uint16_t*>(lds + c * CS + r * 2) =
+                  (uint16_t)(w[j >> 1] >> (16 * (j & 1)));
+          }
+          if (++c == ldr) { c = 0; ++r; }
+        }
+      }
       return;
     }
 #pragma unroll
@@ -1441,7 +1482,7 @@ size_t fa_irls_lds_bytes(int p, int* big_in_global) {
 
 // ------------------------------------------------------------------------------------------
 // launchers (host).  Shapes are validated by the callers in fa_api.hip.
-template <int T, int CPL, typename E, int WAVES, bool ROWS, bool LAST = false>
+template <int T, int CPL, typename E, int WAVES, int ST, bool LAST = false>
 static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, int max_blocks,
                                 double* partials, int* nparts, hipStream_t st,
                                 const fa_ktime* tm, const int* gate, const fa_gram_cols& cols) {
@@ -1449,7 +1490,7 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
   constexpr int R = (64 / CPL) * E::EPL;
   constexpr int CS = R * E::SIZE + 16;
   constexpr size_t tile_bytes =
-      ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : (size_t)T * 16 * CS;
+      ST == FA_MEM_ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : (size_t)T * 16 * CS;
   static_assert(WAVES * tile_bytes <= 160 * 1024, "LDS tiles of one workgroup must fit a CU");
   // more than half of the CU's 160 KiB, so that no second workgroup fits beside this one
   const size_t lds_bytes = WAVES * tile_bytes > 84 * 1024 ? WAVES * tile_bytes : 84 * 1024;
@@ -1457,11 +1498,14 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
   int64_t wgs = (ntiles + WAVES - 1) / WAVES;
   if (wgs > max_blocks) wgs = max_blocks;
   *nparts = (int)wgs;
-  FA_LAUNCH(tm, (fa_gram_kernel<T, CPL, E, WAVES, ROWS, LAST>), dim3((unsigned)wgs),
+  FA_LAUNCH(tm, (fa_gram_kernel<T, CPL, E, WAVES, ST, LAST>), dim3((unsigned)wgs),
             dim3(64 * WAVES), lds_bytes, st, (const unsigned char*)G, ldg, p, n, ntiles,
             partials, gate, cols);
   return hipGetLastError();
 }
+
+// interleaved storage, p <= 16: rows from which on the elements are scattered (see ROWS)
+#define FA_SCATTER_MIN_ROWS ((int64_t)1 << 22)
 
 // the tiling of each width class: T -> (columns per load, wavefronts per CU)
 #define FA_GRAM_TILINGS(X) \
@@ -1477,10 +1521,16 @@ static hipError_t launch_gram_e(const void* G, int64_t ldg, int p, int64_t n, in
     case t:                                                                                    \
       if constexpr (!ROWS && t > 1)                                                            \
         if (last)                                                                              \
-          return launch_gram_t<t, cpl, E, w, false, true>(G, ldg, p, n, max_blocks, partials,  \
-                                                          nparts, st, tm, gate, cols);         \
-      return launch_gram_t<t, cpl, E, w, ROWS>(G, ldg, p, n, max_blocks, partials, nparts, st, \
-                                               tm, gate, cols);
+          return launch_gram_t<t, cpl, E, w, FA_MEM_WORKER, true>(G, ldg, p, n, max_blocks,     \
+                                                                 partials, nparts, st, tm,     \
+                                                                 gate, cols);                  \
+      if constexpr (ROWS && t == 1)                                                            \
+        if (n >= FA_SCATTER_MIN_ROWS)                                                          \
+          return launch_gram_t<t, cpl, E, w, FA_MEM_SCATTER>(G, ldg, p, n, max_blocks,          \
+                                                            partials, nparts, st, tm, gate,    \
+                                                            cols);                             \
+      return launch_gram_t<t, cpl, E, w, ROWS ? FA_MEM_ROWS : FA_MEM_WORKER>(                    \
+          G, ldg, p, n, max_blocks, partials, nparts, st, tm, gate, cols);
     FA_GRAM_TILINGS(FA_X)
 #undef FA_X
   }
@@ -1490,18 +1540,17 @@ static hipError_t launch_gram_e(const void* G, int64_t ldg, int p, int64_t n, in
 template <typename E, bool ROWS>
 static hipError_t prepare_gram_e() {
   hipError_t e = hipSuccess;
-#define FA_X(t, cpl, w)                                                                          \
+#define FA_SET(...)                                                                               \
   if (e == hipSuccess)                                                                           \
-    e = hipFuncSetAttribute(                                                                     \
-        reinterpret_cast<const void*>(fa_gram_kernel<t, cpl, E, w, ROWS, false>),                \
-        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);                                 \
-  if constexpr (!ROWS && t > 1)                                                                  \
-    if (e == hipSuccess)                                                                         \
-      e = hipFuncSetAttribute(                                                                   \
-          reinterpret_cast<const void*>(fa_gram_kernel<t, cpl, E, w, false, true>),              \
-          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_gram_kernel<__VA_ARGS__>),          \
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+#define FA_X(t, cpl, w)                                                                          \
+  FA_SET(t, cpl, E, w, ROWS ? FA_MEM_ROWS : FA_MEM_WORKER, false)                                  \
+  if constexpr (!ROWS && t > 1) { FA_SET(t, cpl, E, w, FA_MEM_WORKER, true) }                     \
+  if constexpr (ROWS && t == 1) { FA_SET(t, cpl, E, w, FA_MEM_SCATTER, false) }
   FA_GRAM_TILINGS(FA_X)
 #undef FA_X
+#undef FA_SET
   return e;
 }
 

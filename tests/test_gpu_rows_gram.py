@@ -58,3 +58,25 @@ def test_interleaved_gram_in_its_steady_state(p, pitch, waves, dtype):
         assert np.all(np.isfinite(K)) and np.array_equal(K, W), n
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("p,pitch", [(1, 1), (1, 16), (4, 4), (7, 9), (11, 11), (15, 16), (16, 16)])
+def test_interleaved_gram_of_many_rows(p, pitch, dtype):
+    """p <= 16 from 2^22 rows on: elements scattered to their columns on the way into LDS.  A last tile
+    of one row, of all rows but one and none; one row below the rule's line."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("interleaved gram, many rows", p, pitch, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(p)
+    for n in ((1 << 22) - 1, 1 << 22, (1 << 22) + 1, (1 << 22) + 127):
+        by_worker = torch.zeros((p, -(-n // 8) * 8), device="cuda",
+                                dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+        by_worker[:, :n] = torch.randn((p, n), generator=gen, device="cuda")
+        rows = torch.full((n, pitch), float("nan"), dtype=by_worker.dtype, device="cuda")
+        rows[:, :p] = by_worker[:, :n].t()
+        a = FlagAggregator(n_max=n, p_max=p, dtype=dtype, layout="row_major")
+        b = FlagAggregator(n_max=n, p_max=p, dtype=dtype, gram="fp64")
+        K, W = a.fa_gram(rows[:, :p]), b.fa_gram(by_worker[:, :n])
+        assert np.all(np.isfinite(K)) and np.array_equal(K, W), n
+        a.close()
+        b.close()
