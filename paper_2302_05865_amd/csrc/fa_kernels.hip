@@ -112,9 +112,10 @@ __device__ __forceinline__ uint4 load16_guarded(const unsigned char* base, int64
 // how G lies in memory and goes to LDS: worker-major; interleaved as it is; interleaved, scattered
 enum { FA_MEM_WORKER, FA_MEM_ROWS, FA_MEM_SCATTER };
 
-// which gradients the columns of a Gram pass are, where they are not simply the first p
+// a pass over some rows of some gradients, whose sums are added to K: which gradients its columns are,
+// where they are not simply the first p
 struct fa_gram_cols {
-  int listed;
+  int add, listed;
   uint8_t idx[FA_P_MAX];
 };
 
@@ -707,8 +708,8 @@ __global__ __launch_bounds__(256) void fa_restream_weights_kernel(const fa_info*
 // TM > 0: the tiles are the T x TM blocks of a p x m matrix (row-major, leading dimension m).
 // colscale (may be null; symmetric case only): entry (i, j) is multiplied by u_i u_j, which
 // makes the result the Gram matrix G^T W G of the columns scaled by u = W^(1/2).
-// cols (symmetric case only): where the columns are listed, the sums are those of some rows of G
-// and are added to K, whose order is ldk; last: the tiles are those of the LAST pass.
+// cols (symmetric case only): the sums may be those of some rows of G, to be added to K, whose order
+// is ldk, at the places of the listed columns; last: the tiles are those of the LAST pass.
 __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __restrict__ partials,
                                                               int nparts, int T, int p,
                                                               double* __restrict__ K, int TM,
@@ -758,8 +759,8 @@ __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __re
         if (k == tp) { ta = aa; tb = bb; }
     const int gi = ta * 16 + 4 * r + (l >> 4), gj = tb * 16 + (l & 15);
     if (gi < p && gj < p && gi <= gj) {
-      if (cols.listed) {
-        const int ki = cols.idx[gi], kj = cols.idx[gj];
+      if (cols.add) {
+        const int ki = cols.listed ? cols.idx[gi] : gi, kj = cols.listed ? cols.idx[gj] : gj;
         const double v = K[ki * ldk + kj] + tot;   // (both triangles hold the same bits)
         K[ki * ldk + kj] = v;
         K[kj * ldk + ki] = v;
@@ -1588,11 +1589,12 @@ hipError_t fa_launch_gram_add(const void* G, int64_t ldg, int p, int64_t n, int 
                               uint64_t first, uint64_t then, int max_blocks, double* partials,
                               double* Kd, hipStream_t st) {
   fa_gram_cols cols{};
-  cols.listed = 1;
+  cols.add = 1;
   int ncols = 0;
   for (const uint64_t set : {first, then})
     for (int j = 0; j < p; ++j)
       if ((set >> j) & 1u) cols.idx[ncols++] = (uint8_t)j;
+  cols.listed = ncols < p;
   const int T = (ncols + 15) / 16;
   const bool last = first != 0;
   int nparts = 0;
