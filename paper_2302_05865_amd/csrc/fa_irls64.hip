@@ -697,7 +697,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         const double lo = sm.est[0] * sc, up = sm.est[1] * sc, dm = (double)mm;
         const bool guessed = scalar(it > 1 && sm.have_est != 0 && up > 1.2 * lo && up < 32.0 * lo);
         double t = hi * sc;                 // trace X_k
-        bool sq = t > dm, planned = false, mapped = false, have_cap = false;
+        bool sq = t > dm, planned = false, mapped = false, have_cap = false, drop = false;
         Plan pl = {0.0f, 1.0f, 0.0f, 1.0f, 1.0f, 0.03f, true};
         float Hp = 0.0f, Gp = 1.0f;         // pl.H, pl.G of X_{k-1} (looked at behind unplanned steps)
         if (lane == 0) { sm.guessed = guessed; sm.cap_k = -1; }
@@ -741,8 +741,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
               }
               sq = scalar(t > dm);
               mapped = false;
-              // the guess is no good: nearly a projector, but with another trace
-              if (guessed && (k >= 64 || scalar(s < 1e-3 && fabs(t1 - dm) > 0.5))) word = (word & ~4) | 2;
+              if (drop) word = (word & ~4) | 2;                    // the guess is no good
             }
             word |= sq ? 1 : 0;
             if (lane == 0) {
@@ -766,6 +765,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
               }
             }
             if (guessed) {
+              // nearly a projector, but with another trace (or never one)
+              drop = k >= 63 || scalar(s < 1e-3 && fabs(t1 - dm) > 0.5);
               Hp = pl.H; Gp = pl.G;
               pl.grow = !sq;
               pl.c = sq ? 0.0f : 1.0f;
