@@ -102,11 +102,10 @@ typedef struct {
                          values (powers in place of the square roots; same passes over G). */
   int layout;         /* fa_layout of every G this context sees; default FA_WORKER_MAJOR */
   int solver;         /* fa_solver: which p x p solver runs the IRLS; default FA_SOLVER_AUTO */
-  int wide_spin_budget; /* 16 < p <= 64 matrix-core solver: how many times a wavefront may poll
-                         for a purification step's steering word before it gives up and the
-                         Jacobi solver redoes the solve.  Default 1 << 22 (never reached in
-                         practice); 0 = give up without polling, which makes every such solve
-                         take the stand-by route (for testing it).  >= 0. */
+  int wide_spin_budget; /* 16 < p <= 64 matrix-core solver: 0 = give up before the first purification
+                         step, which makes every such solve take the stand-by route, the Jacobi
+                         solver (for testing it).  Any other value runs the solver (in which no
+                         wavefront polls any more).  Default 1 << 22; >= 0. */
   int gram;           /* fa_gram_mode; default FA_GRAM_AUTO */
 } fa_config;
 

@@ -240,7 +240,7 @@ constexpr size_t kOffInfo = kOffGws + sizeof(double) * FA_GWS_DOUBLES;
 constexpr size_t kOffFlag = kOffInfo + ((sizeof(fa_info) + 63) / 64) * 64;
 constexpr size_t kStaticUsed = kOffFlag + 64;
 static_assert(kStaticUsed <= FA_STATIC_SCRATCH_BYTES, "the static workspace is too small");
-static_assert(kOffK % 256 == 0 && kOffC % 8 == 0 && kOffGws % 8 == 0 && kOffInfo % 8 == 0,
+static_assert(kOffK % 256 == 0 && kOffC % 8 == 0 && kOffGws % 16 == 0 && kOffInfo % 8 == 0,
               "alignment of the parts of the static workspace");
 
 constexpr int kMaxDevices = 64;

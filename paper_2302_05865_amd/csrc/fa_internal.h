@@ -16,8 +16,9 @@
 
 // layout of the p x p solvers' global workspace (doubles)
 #define FA_GWS_GENERIC (2 * FA_P_MAX * (FA_P_MAX + 1))    // any-p Jacobi kernel: D2inv, Vt
-// 16 < p <= 64 matrix-core kernel: three matrices as (p_max/16)^2 tiles of 272 doubles
-#define FA_GWS_TILES (3 * (FA_P_MAX / 16) * (FA_P_MAX / 16) * 272)
+// 16 < p <= 64 matrix-core kernel: three matrices as (p_max/16)^2 tiles
+#define FA_TILE_DOUBLES 288   // 16 x 16 entries and padding
+#define FA_GWS_TILES (3 * (FA_P_MAX / 16) * (FA_P_MAX / 16) * FA_TILE_DOUBLES)
 #define FA_GWS_MLAST_OFF (FA_GWS_GENERIC + FA_GWS_TILES)  // last weighted-PCA matrix N x N, rank, m
 #define FA_GWS_DOUBLES (FA_GWS_MLAST_OFF + FA_P_MAX * FA_P_MAX + 2)
 

@@ -40,7 +40,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // have to fit, and every further one takes registers from them (sixteen leave 128 a lane, and the
 // purification step then spilled; twelve leave 168, eight 256).
 constexpr int waves_for(int t) { return t <= 3 ? 8 : 12; }
-constexpr int MAX_PURIFY = 200;
+constexpr int MAX_PURIFY = 200;   // steps of one solve
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double x) {
@@ -71,6 +71,20 @@ __device__ __forceinline__ double wave_sum(double x) {
   x = row_sum(x);
   return ((lane_bcast(x, 0) + lane_bcast(x, 16)) + lane_bcast(x, 32)) + lane_bcast(x, 48);
 }
+// about the same in f32, ~80 instead of ~200 cycles: row totals, then along the rows into lane 63
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float add_dpp(float x) {
+  return x + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum_f32(float x) {
+  x = add_dpp<0x128, 0xf>(x);   // row_ror:8
+  x = add_dpp<0x124, 0xf>(x);   // row_ror:4
+  x = add_dpp<0x122, 0xf>(x);   // row_ror:2
+  x = add_dpp<0x121, 0xf>(x);   // row_ror:1
+  x = add_dpp<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+  x = add_dpp<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
+  return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+}
 // 1/sqrt(x): hardware estimate plus two Newton steps
 __device__ __forceinline__ double rsq2(double x) {
   double y = __builtin_amdgcn_rsq(x);
@@ -85,23 +99,27 @@ __device__ __forceinline__ double rsq2(double x) {
 
 // ---- tiles ---------------------------------------------------------------------------------
 // A matrix is stored as T x T tiles of 16 x 16.  Lane l = 16 q + c of a wavefront holds rows
-// 4e + q (e = 0..3), column c of a tile, as the matrix instruction delivers them; entry e of
-// lane l sits at e * FA_ES + sw(l) doubles into the tile.  Both the lane-parallel access
-// (fixed e) and the transposed store (lane (q, c), fixed source entry r, goes to entry c / 4,
-// lane 16 (c % 4) + 4 r + q) then touch every LDS bank once per half wavefront: the entry
-// stride 68 spreads the four destination entries over banks, and sw() moves the bit of c
-// that would otherwise be lost into the bit that q leaves constant within a half wavefront.
-constexpr int FA_ES = 68, FA_TILE = 272;
-__device__ __forceinline__ int sw(int l) { return l ^ ((l >> 5) << 1); }
-template <int T, typename P>
-__device__ __forceinline__ v4d load_tile(P base, int I, int J, int lane) {
-  const double* t = base + (I * T + J) * FA_TILE + sw(lane);
-  return v4d{t[0], t[FA_ES], t[2 * FA_ES], t[3 * FA_ES]};
+// 4e + q (e = 0..3), column c of a tile, as the matrix instruction delivers them.  Entries 2h and
+// 2h + 1 of a lane are neighbours, in half h of the tile at 2 l doubles and four more for every
+// sixteen lanes, so that a tile is two 16-byte accesses per lane, without bank conflicts; and the
+// transposed store (lane (q, c), source entry r, goes to entry c / 4 of lane 16 (c % 4) + 4 r + q)
+// touches every bank once per half wavefront: q and the parity of c / 4 stay within 32 bytes, c % 4
+// moves by 288 bytes and the half by 1152.  (Four 8-byte accesses per lane, entries 68 doubles apart:
+// 937 against 853 cycles a purification step at T = 2.)
+constexpr int FA_TILE = FA_TILE_DOUBLES, FA_HALF = FA_TILE / 2;
+typedef double v2d __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int at(int l) { return 2 * l + 4 * (l >> 4); }
+template <int T>
+__device__ __forceinline__ v4d load_tile(const double* base, int I, int J, int lane) {
+  const double* t = base + (I * T + J) * FA_TILE + at(lane);
+  const v2d a = *reinterpret_cast<const v2d*>(t), b = *reinterpret_cast<const v2d*>(t + FA_HALF);
+  return v4d{a[0], a[1], b[0], b[1]};
 }
 template <int T>
 __device__ __forceinline__ void store_tile(double* base, int I, int J, int lane, const v4d& v) {
-  double* t = base + (I * T + J) * FA_TILE + sw(lane);
-  t[0] = v[0]; t[FA_ES] = v[1]; t[2 * FA_ES] = v[2]; t[3 * FA_ES] = v[3];
+  double* t = base + (I * T + J) * FA_TILE + at(lane);
+  *reinterpret_cast<v2d*>(t) = v2d{v[0], v[1]};
+  *reinterpret_cast<v2d*>(t + FA_HALF) = v2d{v[2], v[3]};
 }
 // the same values written as the transposed tile (J, I): element (4r + q, c) of (I, J) is
 // element (c, 4r + q) of (J, I), i.e. entry c / 4 of lane 16 (c % 4) + 4r + q
@@ -109,26 +127,34 @@ template <int T>
 __device__ __forceinline__ void store_tile_transposed(double* base, int I, int J, int lane,
                                                       const v4d& v) {
   const int c16 = lane & 15, q4 = lane >> 4;
-  double* t = base + (J * T + I) * FA_TILE + (c16 >> 2) * FA_ES + sw((c16 & 3) * 16 + q4);
+  double* t = base + (J * T + I) * FA_TILE + (c16 >> 3) * FA_HALF + ((c16 >> 2) & 1) +
+              at((c16 & 3) * 16 + q4);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) t[4 * r] = v[r];
+  for (int r = 0; r < 4; ++r) t[8 * r] = v[r];
 }
+// offset of entry e of lane l
+__device__ __forceinline__ int entry(int e, int l) { return (e >> 1) * FA_HALF + (e & 1) + at(l); }
 // offset of element (i, j) in the tiled storage
 template <int T>
 __device__ __forceinline__ int eidx(int i, int j) {
-  return ((i >> 4) * T + (j >> 4)) * FA_TILE + ((i & 15) >> 2) * FA_ES +
-         sw((i & 3) * 16 + (j & 15));
+  return ((i >> 4) * T + (j >> 4)) * FA_TILE + entry((i & 15) >> 2, (i & 3) * 16 + (j & 15));
 }
 // offset of element (a, j) of a matrix kept in A-operand order: tile (a/16, j/16), entry
 // (j%16)/4 of lane ((j%16)%4) * 16 + a%16   [lane (i, k) supplies element (i, 4s + k)]
 template <int T>
 __device__ __forceinline__ int aidx(int a, int j) {
-  return ((a >> 4) * T + (j >> 4)) * FA_TILE + ((j & 15) >> 2) * FA_ES +
-         sw((j & 3) * 16 + (a & 15));
+  return ((a >> 4) * T + (j >> 4)) * FA_TILE + entry((j & 15) >> 2, (j & 3) * 16 + (a & 15));
 }
 __device__ __forceinline__ v4d mma4(const v4d& a, const v4d& b, v4d acc) {
 #pragma unroll
   for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+  return acc;
+}
+// the first NS of those: what the others would add is zero
+template <int NS>
+__device__ __forceinline__ v4d mma_first(const v4d& a, const v4d& b, v4d acc) {
+#pragma unroll
+  for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
   return acc;
 }
 // the k-th pair (I <= J) of the upper triangle: the T diagonal tiles first (the wavefronts
@@ -141,6 +167,13 @@ __device__ __forceinline__ void upper_pair(int k, int* I, int* J) {
   *I = i; *J = i + 1 + rem;
 }
 
+// what a purification step does: X -> al X + be X^2 + ga I, or end the loop
+enum { OFF_DIAGONAL, DIAGONAL, LAST_DIAGONAL };   // tiles by what their purification step needs
+enum { STEP_GO = 0, STEP_DONE = 1, STEP_FAILED = 2 };
+struct __attribute__((aligned(16))) Step {
+  double al, be, ga;
+  int end, pad;
+};
 struct Small {
   double s[64], dinv[64], w[64], wn[64], r1[64], beta[64], rinv[64], gd[64], rho[64];
   double red[16];
@@ -151,10 +184,7 @@ struct Small {
   // 1 / tr(g^T g) of that block
   int gf[64], gc[64];
   double ginv[64];
-  // word of purification step g at [g & 3]: g << 4 | a planned map (8) | trace ok (4) |
-  // converged (2) | square (1), and its map X -> map[0] X + map[1] X^2 + map[2] I if planned
-  int dec[4];
-  double map[4][3];
+  Step step[2];                    // of purification step k at [k & 1]
   float hist[MAX_PURIFY];          // step k of this solve: a of a growth, -1 - b of a shrinking map
   float cap[2];                    // the ends of the gap at step cap_k
   int cap_k;                       // (negative: not known)
@@ -162,7 +192,6 @@ struct Small {
   double est[2];                   // eigenvalues m + 1 and m of the last solve's matrix ...
   int have_est;                    // ... if known
   int guessed;                     // this solve's first steps were planned
-  int flag[2];  // [step parity] a wavefront gave up waiting for that step's steering word
 };
 
 // ---- planned steps ---------------------------------------------------------------------------
@@ -177,8 +206,7 @@ struct Small {
 // image, the same for [0, H], and in between every map keeps the order; so if in the end G is near
 // 1, H near 0 and trace X = m, the result is the projector onto the m leading eigenvectors whatever
 // the guess was worth.  If not, the solve is done once more without.
-// The maps of these steps need no trace: the steering wavefront has each ready one step ahead, so
-// nobody waits for it.  Once h and g are within 0.03 of 0 and 1 the steps go on as always.
+// Once h and g are within 0.03 of 0 and 1 the steps go on as always.
 // Where there is no guess - the first two solves (the first weights move the gap most: guesses failed
 // there), a gap of less than a fifth or of more than 32 (where the plain steps need few), a guess that
 // failed - only the first growth steps are planned, from a bound that always holds (trace X_0 = 1).
@@ -186,54 +214,53 @@ struct Small {
 // m = 32, 30 solves 764 -> 639; p = 60, m = 31, 5 solves 170 -> 161.  Where a guess from the second solve
 // on and ends that stay below a fold cost up to 1.7 times the plain steps (m = 1 or close to p, a = 4: 137
 // for 81), it is 85 now; the worst of 8000 problems of that kind drawn at random is 1.35 times.
-struct Plan {                 // all scalar: one wavefront's, the same in every lane
-  float H, G, h, g;
-  float c;                    // a or b of the last map
+// All of it is one wavefront's and uniform; the ends are kept in its lanes, so that one image takes all of
+// them a step further: lane 0 H, 1 G, 2 h, 3 g, 4 the image of 0, 5 that of 1.
+struct Plan {
+  float x;                    // this lane's end
+  float mul, add;             // H and G are rounded outwards, so that they hold whatever f32 does
+  float dn, up;               // 0 in lane 0 / lane 1, beyond every number elsewhere
   float end;                  // the plan ends when h and 1 - g are below this
-  bool grow;
+  double al, be, ga;          // the last step's map: X -> al X + be X^2 + ga I
 };
-__device__ __forceinline__ float scalar(float x) {
-  return __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
+__device__ __forceinline__ float lane_of(float x, int l) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), l));
 }
 __device__ __forceinline__ bool scalar(bool x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ float plan_image(bool grow, float c, float x) {
-  if (grow) {
-    const float u = fmaf(-c, x, 1.0f);
-    return fmaf(-u, u, 1.0f);
-  }
-  const float u = fmaf(c, x, x - c);
-  return u * u;
+__device__ __forceinline__ double scalar(double x) { return lane_bcast(x, 0); }
+__device__ __forceinline__ void plan_begin(Plan& pl, float H, float G, float h, float g, float end, int lane) {
+  pl.x = lane == 0 ? H : lane == 1 ? G : lane == 2 ? h : lane == 3 ? g : lane == 5 ? 1.0f : 0.0f;
+  pl.mul = lane == 0 ? 1.0f + 1e-6f : lane == 1 ? 1.0f - 1e-6f : lane < 4 ? 1.0f : 0.0f;
+  pl.add = lane == 0 ? 1e-7f : lane == 1 ? -1e-7f : lane == 5 ? 1.0f : 0.0f;
+  pl.dn = lane == 0 ? 0.0f : -__builtin_inff();
+  pl.up = lane == 1 ? 0.0f : __builtin_inff();
+  pl.end = end;
 }
-// one step further: maps with the ends rounded outwards, so that they hold whatever f32 does
-__device__ __forceinline__ void plan_push(Plan& pl) {
-  const float H = plan_image(pl.grow, pl.c, pl.H), G = plan_image(pl.grow, pl.c, pl.G);
-  const float e0 = pl.grow ? 0.0f : pl.c * pl.c, e1 = plan_image(pl.grow, pl.c, 1.0f);
-  pl.H = scalar(fmaf(fmaxf(H, e0), 1.0f + 1e-6f, 1e-7f));
-  pl.G = scalar(fmaf(fminf(G, e1), 1.0f - 1e-6f, -1e-7f));
-  pl.h = scalar(plan_image(pl.grow, pl.c, pl.h));
-  pl.g = scalar(plan_image(pl.grow, pl.c, pl.g));
+// the ends through the growth or shrinking map of parameter c
+__device__ __forceinline__ void plan_push(Plan& pl, bool grow, float c) {
+  const float u = fmaf(grow ? -c : 1.0f + c, pl.x, grow ? 1.0f : -c);
+  float y = grow ? fmaf(-u, u, 1.0f) : u * u;
+  y = fminf(fmaxf(y, lane_of(y, 4) + pl.dn), lane_of(y, 5) + pl.up);
+  pl.x = fmaf(y, pl.mul, pl.add);
 }
-// the next planned map, published as step g's; false when the plan is at its end
-__device__ __forceinline__ bool plan_next(Plan& pl, Small& sm, int g, int k, int lane) {
-  const float up = 1.0f - pl.g;
-  if (scalar(fmaxf(pl.h, up) < pl.end) || k >= 40) return false;
-  pl.grow = scalar(up > pl.h);
-  const float c = pl.grow ? 2.0f * __builtin_amdgcn_rcpf(1.0f + pl.G)
-                          : pl.H * __builtin_amdgcn_rcpf(2.0f - pl.H);
-  pl.c = scalar(fminf(fmaxf(c, pl.grow ? 1.0f : 0.0f), pl.grow ? 2.0f : 1.0f));
+// step k's map; false when the plan is at its end
+__device__ __forceinline__ bool plan_next(Plan& pl, Small& sm, int k, int lane) {
+  const float H = lane_of(pl.x, 0), G = lane_of(pl.x, 1), h = lane_of(pl.x, 2);
+  const float up = 1.0f - lane_of(pl.x, 3);
+  if (fmaxf(h, up) < pl.end || k >= 40) return false;
+  const bool grow = up > h;
+  float c = (grow ? 2.0f : H) * __builtin_amdgcn_rcpf(grow ? 1.0f + G : 2.0f - H);
+  c = fminf(fmaxf(c, grow ? 1.0f : 0.0f), grow ? 2.0f : 1.0f);
+  const double cd = (double)c, b1 = 1.0 + cd;
+  pl.al = grow ? 2.0 * cd : -2.0 * cd * b1;
+  pl.be = grow ? -cd * cd : b1 * b1;
+  pl.ga = grow ? 0.0 : cd * cd;
   if (lane == 0) {
-    const double cd = (double)pl.c, b1 = 1.0 + cd;
-    // in this order: see the readers
-    __hip_atomic_store(&sm.map[g & 3][0], pl.grow ? 2.0 * cd : -2.0 * cd * b1, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_store(&sm.map[g & 3][1], pl.grow ? -cd * cd : b1 * b1, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_store(&sm.map[g & 3][2], pl.grow ? 0.0 : cd * cd, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_store(&sm.dec[g & 3], g << 4 | 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    sm.hist[k] = pl.grow ? pl.c : -1.0f - pl.c;
+    Step& st = sm.step[k & 1];
+    st.al = pl.al; st.be = pl.be; st.ga = pl.ga; st.end = STEP_GO;
+    sm.hist[k] = grow ? c : -1.0f - c;
   }
-  plan_push(pl);
+  plan_push(pl, grow, c);
   return true;
 }
 
@@ -299,7 +326,6 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     sm.w[tid] = si > 0.0 ? 1.0 : 0.0;
     sm.used[tid] = 0;
     sm.rho[tid] = 0.0;
-    if (tid < 4) sm.dec[tid] = 0;   // tag 0 is never used
     if (tid == 0) sm.have_est = 0;
   }
   __syncthreads();
@@ -507,7 +533,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   int uI = 0, uJ = 0;
   if (mt >= 0) upper_pair<T>(mt, &uI, &uJ);
   const double rs_delta = 1.0 / sqrt(delta);
-  int iters_done = 0, steps = 0, gstep = 0;
+  int iters_done = 0, steps = 0;
   double* cur = B0;   // where the projector of the last solve is
   double* nxt = B1;
   int failed = 0;
@@ -587,218 +613,234 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       // A wavefront's fp64 vector instructions do not get a turn while older wavefronts of
       // its SIMD have matrix instructions to issue, and every dependent LDS round trip, cross-lane
       // sum or taken branch costs hundreds of cycles, so measuring and deciding stay off the
-      // multiplying wavefronts' path, and each of the three roles runs a loop of its own (cycles per
-      // step: T = 2 1870 with one loop, diagonals written out and every factor loaded, 1580 now, 512
-      // of them matrix instructions; T = 4 4590, 4500 now, 3072 of them matrix instructions):
+      // multiplying wavefronts' path, and each of the three roles runs a loop of its own:
       //  - multiplying wavefronts (mt >= 0) make one tile of X_k^2 and of X_{k+1} each;
-      //  - during step k wavefront SW sums the diagonal of X_k and publishes the word of the step:
-      //    "square X_k" (trace X_k > m) and "X_{k-1} was a projector" (its trace and the next one
-      //    say how far it was from one; then X_k, its polished successor, is the result).  While
-      //    steps are planned (see Plan) it publishes the next step's word and map instead;
-      //  - the multiplying wavefronts pick the word up after their products, the others after the
-      //    step's barrier.
-      // Waits: the steering wavefront waits for nobody, so the readers' bounded spin ends.  One
-      // that runs out of its budget of polls raises the step's flag, skips its store and goes
-      // on to the step's barrier like everybody else; all leave the next step before its
-      // barrier, together, with the solve marked as failed (the last step of the loop cannot raise
-      // it unseen: a failed solve is what running out of steps means anyway).  In the step after
-      // the word "X_{k-1} was a projector" all leave the same way, some on the word and some on
-      // the flag if somebody ran out of polls on that very word: so the flag is looked at once more
-      // behind the loops, where it wins over the word in every role.
-      const int gstep0 = gstep;
-      ++gstep;                        // a tag of its own between solves: no stale word matches
-      int k = 0, wprev = 0;           // wprev: the word of the previous step
-      bool raised = false;
-      if (tid == 0) { sm.flag[0] = 0; sm.flag[1] = 0; }
+      //  - during step k wavefront SW decides on step k + 1: the next planned map (see Plan), or from
+      //    t = trace X_k and |X_k|_F^2, which give trace X_{k+1}: X^2 where that is above m, 2X - X^2
+      //    below; and that X_{k+1} is the result where X_k is a projector already;
+      //  - everybody else keeps the barrier, one a step.
+      // So a step's map is there before the barrier in front of it and nobody waits for it.  Cycles a
+      // step, begin and end of a solve included: T = 2 1070 to 1130 (512 of them matrix instructions),
+      // T = 4 3700 to 4100 (3072); 1480 and 4370 with the trace of X_k itself, published during step k
+      // and waited for behind its products.  (p = 32 bf16, 15 solves: 314 -> 263 us.)
+      int k = 0, end = STEP_GO;
       if (mt >= 0) {
-        __syncthreads();
         // this wavefront's tile of X_k stays in its registers: LDS holds it for the others
-        v4d x = load_tile<T>(B0, uI, uJ, lane);
+        v4d x;
+        double live[4];                                  // the identity's place in a diagonal tile
+#pragma unroll
+        for (int r = 0; r < 4; ++r) live[r] = isdiag[r] && 16 * uJ + c16 < rank ? 1.0 : 0.0;
         // One step: X_k in cu, X_{k+1} into nx.  Written for fixed buffers (the loop alternates
         // two instances) so that every LDS address is loop invariant and the loads of a
         // wavefront that leaves the barrier behind older ones of its SIMD are in flight at
-        // once.  Returns true when the loop is over.
-        auto step = [&](auto diag, const double* cu, double* nx) __attribute__((always_inline)) -> bool {
-          constexpr bool DIAG = decltype(diag)::value;
-          ++gstep;                      // tags the words: never repeats within a launch
-          if (wprev & 2) return true;
-          // own tile (uI, uJ) of X_k^2 = sum_K X(K, uI)^T X(K, uJ), K = uI first: that one needs no
-          // load on the diagonal, where both factors are the same tile for every K, and one off
-          // it.  The operands of the next K are on their way while this K is multiplied.
+        // once.  Own tile (uI, uJ) of X_k^2 = sum_K X(K, uI)^T X(K, uJ), K = uI first and K = T - 1,
+        // where NL of the four matrix instructions suffice (X is zero from index rank on; p = 20: 700
+        // cycles, p = 32: 850), last.  On the diagonal the part K = uI needs nobody else's tile: it is
+        // multiplied ahead of the barrier (853 against 937 cycles at T = 2, 3556 against 3809 at
+        // T = 4).  Returns true when the loop is over.
+        auto step = [&](auto kind, auto nl, const double* cu, double* nx) __attribute__((always_inline)) -> bool {
+          constexpr int KIND = decltype(kind)::value, NL = decltype(nl)::value;
+          constexpr bool DIAG = KIND != OFF_DIAGONAL;
           v4d y = {0.0, 0.0, 0.0, 0.0};
-          v4d a = x, b = x;
-          if constexpr (!DIAG) a = load_tile<T>(cu, uI, uI, lane);
-          // the previous step's flag; this step's word and, if it is a planned one, its map: the
-          // publisher writes the word after the map, LDS serves a wavefront's accesses in order,
-          // and these loads are issued in this order, so a map read after its word is the word's.
-          // Looked at after the products; an unplanned step's word comes meanwhile.
-          int flag, wv;
-          double al, be, ga;
-#pragma unroll
-          for (int i = 0; i < T; ++i) {
-            v4d an = a, bn = b;
-            if (i + 1 < T) {
-              const int K = uI + i + 1 < T ? uI + i + 1 : uI + i + 1 - T;
-              an = load_tile<T>(cu, K, uI, lane);
-              bn = DIAG ? an : load_tile<T>(cu, K, uJ, lane);
-            }
-            if (i + 2 == T || T == 1) {
-              flag = sm.flag[(k & 1) ^ 1];
-              wv = __hip_atomic_load(&sm.dec[gstep & 3], __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-              al = __hip_atomic_load(&sm.map[gstep & 3][0], __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-              be = __hip_atomic_load(&sm.map[gstep & 3][1], __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-              ga = __hip_atomic_load(&sm.map[gstep & 3][2], __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-            __builtin_amdgcn_sched_barrier(0);           // keep those loads ahead of the products
-            y = mma4(a, b, y);
-            a = an; b = bn;
+          if constexpr (DIAG) {
+            y = mma_first<KIND == LAST_DIAGONAL ? NL : 4>(x, x, y);
+            __builtin_amdgcn_sched_barrier(0);
           }
-          raised = k > 0 && __builtin_amdgcn_readfirstlane(flag) != 0;
-          if (raised) return true;
-          int word = spin_budget > 0 ? __builtin_amdgcn_readfirstlane(wv) : 0;   // tag 0: never used
-          for (int tries = 0; (word >> 4) != gstep && tries < spin_budget; ++tries)
-            word = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
-                &sm.dec[gstep & 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-          wprev = word;
-          if ((word >> 4) != gstep) {
-            sm.flag[k & 1] = 1;
-            wprev = 0;
-          } else if (!(word & 2)) {
-            if (word & 8) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                x[r] = fma(be, y[r], fma(al, x[r], DIAG && isdiag[r] ? ga : 0.0));
-            } else if (word & 1) {
-              x = y;
-            } else {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) x[r] = fma(2.0, x[r], -y[r]);
-            }
-            store_tile<T>(nx, uI, uJ, lane, x);
-            if constexpr (!DIAG) store_tile_transposed<T>(nx, uI, uJ, lane, x);
-          }
-          ++k;
           __syncthreads();
+          const Step& st = sm.step[k & 1];
+          const int e = st.end;
+          v4d a[T], b[T];
+#pragma unroll
+          for (int i = DIAG ? 1 : 0; i < T; ++i) {
+            const int K = KIND == LAST_DIAGONAL ? i - 1 : i == T - 1 ? T - 1 : uI + i < T - 1 ? uI + i : uI + i - (T - 1);
+            a[i] = load_tile<T>(cu, K, uI, lane);
+            b[i] = DIAG ? a[i] : i == 0 ? x : load_tile<T>(cu, K, uJ, lane);
+          }
+          const double al = st.al, be = st.be, ga = st.ga;
+          __builtin_amdgcn_sched_barrier(0);             // all of them ahead of the products
+          end = __builtin_amdgcn_readfirstlane(e);
+          if (end != STEP_GO) return true;
+#pragma unroll
+          for (int i = DIAG ? 1 : 0; i < T; ++i)
+            y = i == T - 1 && KIND != LAST_DIAGONAL ? mma_first<NL>(a[i], b[i], y) : mma4(a[i], b[i], y);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[r] = fma(be, y[r], DIAG ? fma(al, x[r], ga * live[r]) : al * x[r]);
+          store_tile<T>(nx, uI, uJ, lane, x);
+          if constexpr (!DIAG) store_tile_transposed<T>(nx, uI, uJ, lane, x);
+          ++k;
           return false;
         };
-        if (uI == uJ) {
-          while (k < MAX_PURIFY)
-            if (step(std::true_type{}, B0, B1) || step(std::true_type{}, B1, B0)) break;
-        } else {
-          while (k < MAX_PURIFY)
-            if (step(std::false_type{}, B0, B1) || step(std::false_type{}, B1, B0)) break;
-        }
+        __syncthreads();
+        x = load_tile<T>(B0, uI, uJ, lane);
+        auto steps_of = [&](auto kind, auto nl) __attribute__((always_inline)) {
+          while (!step(kind, nl, B0, B1) && !step(kind, nl, B1, B0)) {}
+        };
+        auto run = [&](auto nl) __attribute__((always_inline)) {
+          if (uI != uJ) {
+            if constexpr (T > 1) steps_of(std::integral_constant<int, OFF_DIAGONAL>{}, nl);
+          } else if (uI != T - 1) {
+            if constexpr (T > 1) steps_of(std::integral_constant<int, DIAGONAL>{}, nl);
+          } else {
+            steps_of(std::integral_constant<int, LAST_DIAGONAL>{}, nl);
+          }
+        };
+        const int nl = (rank + 3) / 4 - 4 * (T - 1);
+        if (nl <= 1) run(std::integral_constant<int, 1>{});
+        else if (nl == 2) run(std::integral_constant<int, 2>{});
+        else if (nl == 3) run(std::integral_constant<int, 3>{});
+        else run(std::integral_constant<int, 4>{});
       } else if (wave == SW) {
-        // everything that is decided here is scalar
-        const double lo = sm.est[0] * sc, up = sm.est[1] * sc, dm = (double)mm;
-        const bool guessed = scalar(it > 1 && sm.have_est != 0 && up > 1.2 * lo && up < 32.0 * lo);
-        double t = hi * sc;                 // trace X_k
-        bool sq = t > dm, planned = false, mapped = false, have_cap = false, drop = false;
-        Plan pl = {0.0f, 1.0f, 0.0f, 1.0f, 1.0f, 0.03f, true};
-        float Hp = 0.0f, Gp = 1.0f;         // pl.H, pl.G of X_{k-1} (looked at behind unplanned steps)
+        // Everything here is uniform, and its chain has to stay under a step's products (planned 470
+        // cycles, steered 710 at T = 2).  Three stages:
+        // planned steps; steps steered by f32 values of trace X_k and |X_k|_F^2 (which way does not
+        // matter to what is right, both maps keep the eigenvalues' order); and from where all
+        // eigenvalues are near 0 or 1, with those two measured in f64, as many steps as it takes to
+        // square what the sums of the lower ones and of the upper ones' distances from 1 leave away.
+        const double lo = scalar(sm.est[0] * sc), up = scalar(sm.est[1] * sc), dm = (double)mm;
+        const bool guessed = it > 1 && __builtin_amdgcn_readfirstlane(sm.have_est) != 0 && up > 1.2 * lo &&
+                             up < 32.0 * lo;
+        Plan pl;
         if (lane == 0) { sm.guessed = guessed; sm.cap_k = -1; }
         if (guessed) {
-          pl.H = scalar((float)(0.8 * lo)); pl.G = scalar((float)fmin(1.0, 1.25 * up));
-          pl.h = scalar((float)(1.05 * lo)); pl.g = scalar((float)fmin(0.99, 0.95 * up));
+          plan_begin(pl, (float)(0.8 * lo), (float)fmin(1.0, 1.25 * up), (float)(1.05 * lo),
+                     (float)fmin(0.99, 0.95 * up), 0.03f, lane);
         } else {
           // no guess, but trace X_0 = 1 bounds x_{m+1} by 1 / (m + 1) (with a margin for rounding):
           // growth may fold what is above that, while it is small
-          pl.G = pl.g = scalar(1.0001f / (float)(mm + 1));
-          pl.end = 0.5f;
+          const float bound = 1.0001f / (float)(mm + 1);
+          plan_begin(pl, 0.0f, bound, 0.0f, bound, 0.5f, lane);
         }
-        planned = plan_next(pl, sm, gstep + 1, 0, lane);
+        float Hp = lane_of(pl.x, 0), Gp = lane_of(pl.x, 1);   // the ends' images at X_k (pl is at X_{k+1})
+        bool sq = false;
+        // the plain map of step j
+        auto publish = [&](int j) {
+          pl.al = sq ? 0.0 : 2.0; pl.be = sq ? 1.0 : -1.0; pl.ga = 0.0;
+          if (lane == 0) {
+            Step& st = sm.step[j & 1];
+            st.al = pl.al; st.be = pl.be; st.ga = 0.0; st.end = end;
+            sm.hist[j] = sq ? -1.0f : 1.0f;
+          }
+          if (guessed) {
+            Hp = lane_of(pl.x, 0); Gp = lane_of(pl.x, 1);
+            plan_push(pl, !sq, sq ? 0.0f : 1.0f);
+          }
+        };
+        if (spin_budget <= 0) end = STEP_FAILED;
+        bool planned = plan_next(pl, sm, 0, lane);
+        const bool any = planned && end == STEP_GO;
+        if (!any) publish(0);
+        __syncthreads();
         __builtin_amdgcn_s_setprio(3);      // ahead of the matrix instructions of its SIMD
         __syncthreads();
-        for (; k < MAX_PURIFY; ++k) {
-          ++gstep;
-          if (wprev & 2) break;
-          const int flag = sm.flag[(k & 1) ^ 1];
-          int word = gstep << 4;
-          if (planned) {
-            // this step's map is out: the next one's
-            mapped = true;
-            word |= 8;
-            planned = plan_next(pl, sm, gstep + 1, k + 1, lane);
-          } else {
-            double s = 1.0, t1 = t;                 // t1: trace X_{k-1}
-            if (k > 0) {
-              const double* cu = k & 1 ? B1 : B0;
-              const int d = lane < N ? lane : 0;
-              const double hs = row_sum(lane < N ? cu[eidx<T>(d, d)] : 0.0);
-              t = (lane_bcast(hs, 0) + lane_bcast(hs, 16)) + (lane_bcast(hs, 32) + lane_bcast(hs, 48));
-              if (!mapped) {
-                // X_k is X^2 or 2X - X^2 of X = X_{k-1}: sum x (1 - x) over its eigenvalues
-                s = sq ? t1 - t : t - t1;
-                if (scalar(fabs(s) < 1e-10)) {
-                  word |= 2;
-                  if (scalar(fabs(t1 - dm) < 0.25) && (!guessed || (pl.G > 0.9f && pl.H < 0.1f)))
-                    word |= 4;
-                }
+        if (any) {
+          for (;;) {                        // step k, whose map is a planned one
+            const float H = lane_of(pl.x, 0), G = lane_of(pl.x, 1);
+            planned = plan_next(pl, sm, k + 1, lane);
+            Hp = H; Gp = G;
+            if (!planned) break;
+            ++k;
+            __syncthreads();
+          }
+          // the first plain one goes by the guess: what is behind it can be measured and bounded
+          sq = lane_of(pl.x, 2) > 1.0f - lane_of(pl.x, 3);
+          publish(k + 1);
+          ++k;
+          __syncthreads();
+        }
+        bool near = true, settled = false, have_cap = false;
+        float t = 0.0f, F = 0.0f;           // of X_k
+        float A = 0.0f, B = 0.0f;           // the lower eigenvalues' sum, the upper ones' distance from 1
+        while (end == STEP_GO) {            // step k, whose map is a plain one
+          const double* cu = k & 1 ? B1 : B0;
+          if (!settled && !near) {
+            double f0 = 0.0, f1 = 0.0;
+            v4d v[NTP];
+#pragma unroll
+            for (int q = 0; q < NTP; ++q) {
+              int I, J;
+              upper_pair<T>(q, &I, &J);
+              v[q] = load_tile<T>(cu, I, J, lane);
+            }
+#pragma unroll
+            for (int q = 0; q < NTP; ++q) {
+              double& f = q < T ? f0 : f1;
+#pragma unroll
+              for (int r = 0; r < 4; ++r) f = fma(v[q][r], v[q][r], f);
+            }
+            F = wave_sum_f32((float)fma(2.0, f1, f0));
+            near = t - F < 0.04f;
+          }
+          if (!settled && near) {
+            // (behind a plan, where the trace is not known, and from the first sign on)
+            double fd = 0.0;
+#pragma unroll 1
+            for (int I = 0; I < T; ++I)
+#pragma unroll 1
+              for (int J = I; J < T; ++J) {
+                const v4d v = load_tile<T>(cu, I, J, lane);
+                const double f = fma(v[0], v[0], v[1] * v[1]) + fma(v[2], v[2], v[3] * v[3]);
+                fd = fma(I == J ? 1.0 : 2.0, f, fd);
               }
-              sq = scalar(t > dm);
-              mapped = false;
-              if (drop) word = (word & ~4) | 2;                    // the guess is no good
-            }
-            word |= sq ? 1 : 0;
-            if (lane == 0) {
-              __hip_atomic_store(&sm.dec[gstep & 3], word, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-              sm.hist[k] = sq ? -1.0f : 1.0f;
-            }
-            // While the others multiply.  All eigenvalues of X_{k-1} near 0 or 1: the sums of the
-            // lower ones and of the upper ones' distance from 1 bound the ends of the gap (1.02 s
-            // stands for the s = sum x (1 - x) without the squares)
-            if (!have_cap && scalar(s < 0.02)) {
-              have_cap = true;
-              if (lane == 0) {
-                const double cl = 0.5 * (1.02 * s + t1 - dm), cu1 = 0.5 * (1.02 * s - t1 + dm);
-                sm.cap_k = k - 1;
+            const int d = lane < N ? lane : 0;
+            const double td = wave_sum(lane < N ? cu[eidx<T>(d, d)] : 0.0);
+            fd = wave_sum(fd);
+            t = (float)td; F = (float)fd;
+            const double s = td - fd;       // sum x (1 - x) over the eigenvalues of X_k
+            near = s < 0.04;
+            if (s < 0.02) {
+              // All eigenvalues of X_k near 0 or 1: the sums of the lower ones and of the upper ones'
+              // distance from 1 bound the ends of the gap (1.02 s stands for the s = sum x (1 - x)
+              // without the squares)
+              const double cl = 0.5 * (1.02 * s + td - dm), cu1 = 0.5 * (1.02 * s - td + dm);
+              if (!have_cap && lane == 0) {
+                sm.cap_k = k;
                 sm.cap[0] = (float)fmin(0.5, fmax(1e-4, cl));
                 sm.cap[1] = 1.0f - (float)fmin(0.5, fmax(1e-4, cu1));
                 // (both are sums, good to 0.02 s)
                 const double zl = 0.5 * (double)(rank - mm) * Hp, zu = 0.5 * dm * (1.0 - Gp);
                 sm.cap_in = !guessed ? 0 : (cl <= zl + 0.02 * s ? 1 : 0) | (cu1 <= zu + 0.02 * s ? 2 : 0);
               }
-            }
-            if (guessed) {
-              // nearly a projector, but with another trace (or never one)
-              drop = k >= 63 || scalar(s < 1e-3 && fabs(t1 - dm) > 0.5);
-              Hp = pl.H; Gp = pl.G;
-              pl.grow = !sq;
-              pl.c = sq ? 0.0f : 1.0f;
-              plan_push(pl);
+              have_cap = true;
+              if (fabs(td - dm) < 0.25) {
+                settled = true;
+                A = fmaxf((float)cl, 1e-15f);
+                B = fmaxf((float)cu1, 1e-15f);
+              } else if (fabs(s) < 1e-10 || (guessed && s < 1e-3)) {
+                end = STEP_FAILED;          // nearly a projector, but with another trace
+              }
             }
           }
-          wprev = word;
-          raised = k > 0 && __builtin_amdgcn_readfirstlane(flag) != 0;
-          if (raised) break;
+          // on to X_{k+1}
+          bool next;
+          if (settled) {
+            A = sq ? A * A : 2.0f * A;
+            B = sq ? 2.0f * B : B * B;
+            next = A > B;
+            if (fmaxf(A, B) < 1e-12f)
+              end = !guessed || (lane_of(pl.x, 1) > 0.9f && lane_of(pl.x, 0) < 0.1f) ? STEP_DONE : STEP_FAILED;
+          } else {
+            t = sq ? F : 2.0f * t - F;
+            next = t > (float)mm;
+          }
+          ++k;
+          if (end == STEP_GO && k >= (guessed ? 64 : MAX_PURIFY - 1)) end = STEP_FAILED;
+          sq = next;
+          publish(k);
           __syncthreads();
         }
         __builtin_amdgcn_s_setprio(0);
       } else {
         __syncthreads();
-        for (; k < MAX_PURIFY; ++k) {
-          if (k > 0) {
-            raised = __builtin_amdgcn_readfirstlane(sm.flag[(k - 1) & 1]) != 0;
-            wprev = __builtin_amdgcn_readfirstlane(sm.dec[gstep & 3]);
-            if (raised || (wprev & 2)) break;
-          }
-          ++gstep;
+        for (;; ++k) {
           __syncthreads();
+          end = __builtin_amdgcn_readfirstlane(sm.step[k & 1].end);
+          if (end != STEP_GO) break;
         }
       }
       steps += k;
-      // the flag of step k - 1 (step k, which nobody finished, has the other one)
-      if (k > 0) raised = __builtin_amdgcn_readfirstlane(sm.flag[(k & 1) ^ 1]) != 0;
-      // the last word is the one of step k - 1 and says that X_{k-1} is the result
-      const bool conv = k < MAX_PURIFY && !raised && (wprev & 6) == 6;
-      cur = k & 1 ? B0 : B1;
-      nxt = k & 1 ? B1 : B0;
-      gstep = gstep0 + MAX_PURIFY + 2;     // the same in all roles
+      const bool conv = end == STEP_DONE;
+      cur = k & 1 ? B1 : B0;
+      nxt = k & 1 ? B0 : B1;
       if (!conv) {
         // a guess that did not hold: the solve once more without
         if (!sm.guessed) { failed = 1; break; }
@@ -1132,7 +1174,9 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
 
 template <int T>
 static constexpr size_t lds_bytes() {
-  return (size_t)4 * T * T * FA_TILE * sizeof(double) + sizeof(Small);
+  constexpr size_t bytes = (size_t)4 * T * T * FA_TILE * sizeof(double) + sizeof(Small);
+  static_assert(bytes <= 160 * 1024, "more than a compute unit's LDS");
+  return bytes;
 }
 
 template <int T, int MODE>

@@ -159,3 +159,34 @@ def test_long_plans_keep_the_projector_symmetric(p, m, lam, iters, seed, a):
     assert np.max(np.abs(x.objective - j.objective) / (1.0 + np.abs(j.objective))) <= 1e-9
     assert np.linalg.norm((x.c - j.c) * scale) <= 2e-9 * np.linalg.norm(j.c * scale)
     assert np.max(np.abs(x.A.T @ x.K @ x.A - np.eye(m))) <= 1e-9
+
+
+def _with_copies(p, rank, seed):
+    """Gram matrix of `rank` gradients and p - rank exact copies of them."""
+    r = np.random.default_rng(seed)
+    G = r.standard_normal((rank, 200)) * 0.5 + r.standard_normal((1, 200))
+    G = G[np.concatenate([np.arange(rank), r.integers(0, rank, p - rank)])[r.permutation(p)]]
+    return G @ G.T
+
+
+@pytest.mark.parametrize("p,rank", [(p, p) for p in (17, 20, 21, 24, 25, 28, 29, 32, 33, 37, 41, 45, 48, 49, 53,
+                                                    57, 61, 64)] +
+                         [(20, 16), (32, 7), (40, 32), (48, 20), (64, 48), (64, 33), (60, 61 - 16)])
+def test_every_remainder_of_the_last_tile(p, rank):
+    """A product stops at the rank: one to four matrix instructions of the last tile, or none of it
+    needed.  Against the Jacobi solver from the same K: projectors good to eps p / gap with gaps above
+    1e-5, so 1e-8 on the objective and the aggregate (copies' coefficients are not unique, K c is)."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("last tile", p, rank)
+    K = _with_copies(p, rank, 5 * p + rank)
+    m, got = (rank + 2) // 2, []
+    for solver in ("auto", "jacobi"):
+        agg = FlagAggregator(n_max=1 << 20, p_max=64, solver=solver)
+        agg.fa_irls(K, m, 0.5, 6, 0.0)
+        got.append(agg.fa_get_info())
+        agg.close()
+    a, j = got
+    assert a.status == 0 and j.status == 0 and a.rank == j.rank == rank and a.sweeps != j.sweeps
+    assert np.max(np.abs(a.objective - j.objective) / (1.0 + np.abs(j.objective))) <= 1e-8
+    scale = np.sqrt(np.diag(K))
+    assert np.linalg.norm(K @ (a.c - j.c) / scale) <= 1e-8 * np.linalg.norm(K @ j.c / scale)
