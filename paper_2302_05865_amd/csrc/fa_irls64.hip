@@ -49,9 +49,9 @@ __device__ __forceinline__ double dpp_f64(double x) {
   hi = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
 }
-template <int CTRL>
+template <int CTRL, int ROWS = 0xf>
 __device__ __forceinline__ unsigned dpp_u32(unsigned x) {
-  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
 }
 // sum over each 16-lane row; every lane of the row gets it
 __device__ __forceinline__ double row_sum(double x) {
@@ -178,7 +178,7 @@ struct Small {
   double s[64], dinv[64], w[64], wn[64], r1[64], beta[64], rinv[64], gd[64], rho[64];
   double red[16];
   int piv[64], used[64];
-  int cstop[2], crank;   // of the factorisation: the step is the end, by parity; rows
+  int cstop, crank;      // of the factorisation: its end; rows
   double cpart[4][64];   // tile columns' parts of c
   // workers that send several gradients: first column and width of the block a column is in,
   // 1 / tr(g^T g) of that block
@@ -402,71 +402,75 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     return;
   }
 
-  // ---- greedy diagonal-pivoted Cholesky of S (tile order) -> rows (row-major, pitch LP) ---------
-  // Right-looking on the matrix core: wavefront w < T keeps tile row w of what is left of S in its
-  // registers and every diagonal entry in a lane, so each finds the pivot for itself (same data,
-  // same answer: the largest remaining entry as seen in fp32, ties to the lowest index); the one
-  // that holds the pivot row writes it out scaled, and after the step's one barrier one matrix
-  // instruction per tile takes the rank-one term off (only contraction index 0 is used).  The other
-  // wavefronts keep the barrier.  Latency bound: 1730 cycles a pivot at T = 4 where the update of
-  // all of S in LDS by all threads, three barriers a pivot, took 3100 (T = 2: 1400, 1900).
-  auto pivoted_cholesky = [&](const double* S, double* rows, double tolv, int max_rank) -> int {
-    if (wave < T) {
-      v4d st[T];
+  // this wavefront's output tile in products with a symmetric result (I <= J); the tiles of a full
+  // one go round the wavefronts
+  int mt = (wave & 3) < 3 ? wave - (wave >> 2) : -1;       // ... tile number, negative: none
+  if (T == 4) mt = wave < 7 ? wave : (wave & 3) < 3 ? wave - 1 : -1;
+  if (mt >= NTP) mt = -1;
+  int uI = 0, uJ = 0;
+  if (mt >= 0) upper_pair<T>(mt, &uI, &uJ);
+
+  // ---- greedy diagonal-pivoted Cholesky of S (tile order; overwritten) -> rows (row-major, pitch LP)
+  // Eight pivots at a time by one wavefront, lane j = column j: the pivot is the largest remaining
+  // diagonal entry as seen in fp32, ties to the lowest index; its row of S comes from LDS as it was
+  // before these eight, what they have taken off since is subtracted from registers, and the diagonal
+  // is kept up in the lanes.  Then all wavefronts take the eight rows off S on the matrix core.  Two
+  // barriers in eight pivots.  Latency bound, 640 to 740 cycles a pivot; 1400 and 1730 with
+  // S in the registers of T wavefronts, a barrier and a rank-one update on the matrix core per pivot.
+  auto pivoted_cholesky = [&](double* S, double* rows, double tolv, int max_rank) -> int {
+    constexpr int NB = 8;
+    const int jl = lane < N ? lane : 0;
+    const double* col = S + (jl >> 4) * FA_TILE + 2 * (jl & 15);      // + row_offset: element (row, jl)
+    double d = lane < N ? S[eidx<T>(jl, jl)] : 0.0, open = 1.0;       // open: not a pivot yet
+    for (int k0 = 0;; k0 += NB) {
+      if (wave == 0) {
+        int k = k0, last = 0;
+        double r[NB];
 #pragma unroll
-      for (int J = 0; J < T; ++J) st[J] = load_tile<T>(S, wave, J, lane);
-      const int dl = lane < N ? lane : 0;
-      double d = lane < N ? S[eidx<T>(dl, dl)] : 0.0;
-      unsigned long long used = 0;
-      for (int k = 0;; ++k) {
-        const float df = d > 0.0 ? (float)d : 0.0f;
-        unsigned key = (__float_as_uint(df) & ~63u) | (unsigned)(63 - lane);
-        key = max(key, dpp_u32<0x128>(key));
-        key = max(key, dpp_u32<0x124>(key));
-        key = max(key, dpp_u32<0x122>(key));
-        key = max(key, dpp_u32<0x121>(key));
-        const unsigned k0 = (unsigned)__builtin_amdgcn_readlane((int)key, 0);
-        const unsigned k1 = (unsigned)__builtin_amdgcn_readlane((int)key, 16);
-        const unsigned k2 = (unsigned)__builtin_amdgcn_readlane((int)key, 32);
-        const unsigned k3 = (unsigned)__builtin_amdgcn_readlane((int)key, 48);
-        const int pv = 63 - (int)(max(max(k0, k1), max(k2, k3)) & 63u);
-        const double dp = lane_bcast(d, pv);
-        const bool stop = k == max_rank || !scalar(dp > tolv);
-        if (wave == 0 && lane == 0) sm.cstop[k & 1] = stop;
-        if (stop) {
-          if (wave == 0 && lane == 0) sm.crank = k;
-          __syncthreads();
-          break;
-        }
-        if (wave == pv >> 4) {
-          const double rsv = rsq2(dp);
-          const int e = (pv & 15) >> 2;
+        for (int b = 0; b < NB; ++b) {
+          if (!last) {
+            const float df = d > 0.0 ? (float)d : 0.0f;
+            unsigned key = (__float_as_uint(df) & ~63u) | (unsigned)(63 - lane);
+            key = max(key, dpp_u32<0x128>(key));
+            key = max(key, dpp_u32<0x124>(key));
+            key = max(key, dpp_u32<0x122>(key));
+            key = max(key, dpp_u32<0x121>(key));
+            key = max(key, dpp_u32<0x142, 0xa>(key));
+            key = max(key, dpp_u32<0x143, 0xc>(key));
+            const int pv = 63 - (__builtin_amdgcn_readlane((int)key, 63) & 63);
+            const double dp = lane_bcast(d, pv);
+            if (k == max_rank || !(dp > tolv)) {
+              last = 1;
+            } else {
+              double row = col[(pv >> 4) * T * FA_TILE + entry((pv & 15) >> 2, (pv & 3) * 16)];
+              const double rsv = rsq2(dp);
 #pragma unroll
-          for (int J = 0; J < T; ++J) {
-            const int j = 16 * J + c16;
-            double v = e == 0 ? st[J][0] : e == 1 ? st[J][1] : e == 2 ? st[J][2] : st[J][3];
-            v = j == pv ? dp : v;
-            // (columns that are done with hold rounding noise)
-            if (q4 == (pv & 3)) rows[k * LP + j] = (used >> j) & 1 ? 0.0 : v * rsv;
+              for (int c = 0; c < b; ++c) row = fma(-lane_bcast(r[c], pv), r[c], row);
+              // (columns that are done with hold rounding noise)
+              r[b] = (lane == pv ? dp : row * open) * rsv;
+              if (lane < N) rows[k * LP + lane] = r[b];
+              if (lane == 0) { sm.piv[k] = pv; sm.rinv[k] = rsv; }
+              d = lane == pv ? 0.0 : fma(-r[b], r[b], d);
+              open = lane == pv ? 0.0 : open;
+              ++k;
+            }
           }
-          if (lane == 0) { sm.piv[k] = pv; sm.rinv[k] = rsv; }
         }
-        __syncthreads();
-        const double* row = rows + k * LP;
-        const double aw = q4 == 0 ? row[16 * wave + c16] : 0.0;
+        if (lane == 0) { sm.cstop = last || k == max_rank; sm.crank = k; }
+      }
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(sm.cstop)) break;
+      if (mt >= 0) {
+        v4d acc = load_tile<T>(S, uI, uJ, lane);
 #pragma unroll
-        for (int J = 0; J < T; ++J)
-          st[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(-aw, q4 == 0 ? row[16 * J + c16] : 0.0, st[J],
-                                                       0, 0, 0);
-        const double rd = row[dl];
-        d = lane == pv ? 0.0 : fma(-rd, rd, d);
-        used |= 1ull << pv;
+        for (int s = 0; s < NB / 4; ++s) {
+          const double* rk = rows + (k0 + 4 * s + q4) * LP + c16;
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-rk[16 * uI], rk[16 * uJ], acc, 0, 0, 0);
+        }
+        store_tile<T>(S, uI, uJ, lane, acc);
+        if (uI != uJ) store_tile_transposed<T>(S, uI, uJ, lane, acc);
       }
-    } else {
-      for (int k = 0;; ++k) {
-        __syncthreads();
-        if (__builtin_amdgcn_readfirstlane(sm.cstop[k & 1])) break;
-      }
+      __syncthreads();
     }
     const int rank = __builtin_amdgcn_readfirstlane(sm.crank);
     for (int e = tid; e < N * LP; e += NTHREADS)
@@ -525,13 +529,6 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   double prev_obj = it0 > 0 ? rs->prev_obj : 0.0;
   __syncthreads();
 
-  // this wavefront's output tile in products with a symmetric result (I <= J); the tiles of a full
-  // one go round the wavefronts
-  int mt = (wave & 3) < 3 ? wave - (wave >> 2) : -1;       // ... tile number, negative: none
-  if (T == 4) mt = wave < 7 ? wave : (wave & 3) < 3 ? wave - 1 : -1;
-  if (mt >= NTP) mt = -1;
-  int uI = 0, uJ = 0;
-  if (mt >= 0) upper_pair<T>(mt, &uI, &uJ);
   const double rs_delta = 1.0 / sqrt(delta);
   int iters_done = 0, steps = 0;
   double* cur = B0;   // where the projector of the last solve is
