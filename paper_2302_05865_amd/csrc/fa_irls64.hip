@@ -66,6 +66,23 @@ __device__ __forceinline__ double lane_bcast(double x, int srclane) {
   const int hi = __builtin_amdgcn_readlane(__double2hiint(x), srclane);
   return __hiloint2double(hi, lo);
 }
+// Sum over the four lanes c, 16 + c, 32 + c, 48 + c, in every one of them: (t0 + t1) + (t2 + t3).
+// v_permlane16_swap / v_permlane32_swap with both operands the same value return the even rows
+// (the lower half) and the odd rows (the upper half) side by side.
+__device__ __forceinline__ double rows_sum(double t) {
+  int lo = __double2loint(t), hi = __double2hiint(t);
+  auto a = __builtin_amdgcn_permlane16_swap((unsigned)lo, (unsigned)lo, false, false);
+  auto b = __builtin_amdgcn_permlane16_swap((unsigned)hi, (unsigned)hi, false, false);
+  const double s = __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+  lo = __double2loint(s); hi = __double2hiint(s);
+  a = __builtin_amdgcn_permlane32_swap((unsigned)lo, (unsigned)lo, false, false);
+  b = __builtin_amdgcn_permlane32_swap((unsigned)hi, (unsigned)hi, false, false);
+  return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+}
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 // deterministic sum over the wavefront, same value in every lane
 __device__ __forceinline__ double wave_sum(double x) {
   x = row_sum(x);
@@ -175,8 +192,8 @@ struct __attribute__((aligned(16))) Step {
   int end, pad;
 };
 struct Small {
-  double s[64], dinv[64], w[64], wn[64], r1[64], beta[64], rinv[64], gd[64], rho[64];
-  double red[16];
+  double s[64], dinv[64], w[2][64], r1[64], beta[64], rinv[64], gd[64], rho[64];
+  double red[16], redw[16];
   int piv[64], used[64];
   int cstop, crank;      // of the factorisation: its end; rows
   double cpart[4][64];   // tile columns' parts of c
@@ -186,11 +203,6 @@ struct Small {
   double ginv[64];
   Step step[2];                    // of purification step k at [k & 1]
   float hist[MAX_PURIFY];          // step k of this solve: a of a growth, -1 - b of a shrinking map
-  float cap[2];                    // the ends of the gap at step cap_k
-  int cap_k;                       // (negative: not known)
-  int cap_in;                      // bit e: end e may lie in what was folded
-  double est[2];                   // eigenvalues m + 1 and m of the last solve's matrix ...
-  int have_est;                    // ... if known
   int guessed;                     // this solve's first steps were planned
 };
 
@@ -226,7 +238,6 @@ struct Plan {
 __device__ __forceinline__ float lane_of(float x, int l) {
   return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), l));
 }
-__device__ __forceinline__ bool scalar(bool x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ double scalar(double x) { return lane_bcast(x, 0); }
 __device__ __forceinline__ void plan_begin(Plan& pl, float H, float G, float h, float g, float end, int lane) {
   pl.x = lane == 0 ? H : lane == 1 ? G : lane == 2 ? h : lane == 3 ? g : lane == 5 ? 1.0f : 0.0f;
@@ -290,7 +301,11 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   // The fourth SIMD (wavefronts 3, 7, 11) gets one tile at T = 4 and none below; the wavefront
   // that steers is on it.  A vector instruction of its would otherwise wait for a matrix
   // instruction of the others each time.
-  constexpr int SW = T == 4 ? 7 : 3;
+  constexpr int SW = 7;
+  // R as B operand: a fifth matrix in LDS where there is room, in global memory (a second-level cache's
+  // latency in front of a product) otherwise.
+  constexpr bool RB_LDS = T < 4;
+  constexpr int BACK = T < 3 ? 2 : T < 4 ? 6 : 10;         // see take_back
   constexpr int EPT = (N * N + NTHREADS - 1) / NTHREADS;   // matrix entries per thread
   extern __shared__ __attribute__((aligned(16))) double lds[];
   double* B0 = lds;
@@ -298,8 +313,9 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   double* B2 = lds + 2 * MSZ;
   double* RA = lds + 3 * MSZ;
   constexpr int LP = N + 1;         // row pitch of the factors (N LP <= MSZ)
-  Small& sm = *reinterpret_cast<Small*>(lds + 4 * MSZ);
-  double* Rb = gws;                 // R in tile order (B operand), global
+  Small& sm = *reinterpret_cast<Small*>(lds + (RB_LDS ? 5 : 4) * MSZ);
+  double* Rb = gws;                 // R in tile order (B operand)
+  if constexpr (RB_LDS) Rb = lds + 4 * MSZ;
   double* D2I = gws + MSZ;          // 1 / D_ij^2 in tile order, 0 for dropped pairs
   double* RtG = gws + 2 * MSZ;      // rows of the Cholesky factor of K~, row-major N x N
   // Ml: last weighted-PCA matrix, row-major N x N, then rank, m (for the eigengap diagnostic)
@@ -323,10 +339,9 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     if (tid < p && scaled) si *= rs->uinv[tid] * rs->uinv[tid];
     sm.s[tid] = si;
     sm.dinv[tid] = si > 0.0 ? 1.0 / sqrt(si) : 0.0;
-    sm.w[tid] = si > 0.0 ? 1.0 : 0.0;
+    sm.w[0][tid] = si > 0.0 ? 1.0 : 0.0;
     sm.used[tid] = 0;
     sm.rho[tid] = 0.0;
-    if (tid == 0) sm.have_est = 0;
   }
   __syncthreads();
   if constexpr (GRP) {
@@ -344,7 +359,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       for (int l = 0; l < cnt; ++l) gs += sm.s[first + l];
       sm.gf[tid] = first; sm.gc[tid] = cnt;
       sm.ginv[tid] = gs > 0.0 ? 1.0 / gs : 0.0;
-      sm.w[tid] = gs > 0.0 ? 1.0 : 0.0;
+      sm.w[0][tid] = gs > 0.0 ? 1.0 : 0.0;
     }
     __syncthreads();
   }
@@ -525,7 +540,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       B2[eidx<T>(i, j)] = v;
     }
   }
-  if (it0 > 0 && tid < p) sm.w[tid] = sm.s[tid] > 0.0 ? rs->w[tid] : 0.0;
+  if (it0 > 0 && tid < p) sm.w[0][tid] = sm.s[tid] > 0.0 ? rs->w[tid] : 0.0;
   double prev_obj = it0 > 0 ? rs->prev_obj : 0.0;
   __syncthreads();
 
@@ -534,77 +549,168 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   double* cur = B0;   // where the projector of the last solve is
   double* nxt = B1;
   int failed = 0;
-
-  for (int it = 0; it < iters; ++it) {
-    // ---- C: diagonal from the data weights and the row sums of the pair part ---------------
-    {
-      // (nobody else reads the diagonal place of a row: it is written over at once)
-      const int l16 = tid & 15;
-      for (int i = tid >> 4; i < N; i += NTHREADS / 16) {
-        double acc = 0.0;
-        for (int j = l16; j < N; j += 16) acc += (j != i) ? B2[eidx<T>(i, j)] : 0.0;
-        acc = row_sum(acc);
-        if (l16 == 0)
-          B2[eidx<T>(i, i)] = sm.w[i] * (GRP ? sm.ginv[i] : sm.dinv[i] * sm.dinv[i]) - acc;
-      }
+  int wi = 0;         // sm.w[wi]: the weights of this solve
+  double hi = 0.0;    // trace M
+  // the steering wavefront's: eigenvalues m + 1 (even lanes) and m (odd lanes) of the last solve's
+  // matrix, if known
+  double est = 0.0;
+  bool have_est = false;
+  // Of this wavefront's tile: 1 / D^2 (0: no such term); in the Eq. 5 kernel with 1 / |g|^2 on the diagonal.
+  double d2i[4] = {0.0, 0.0, 0.0, 0.0};
+  if (mt >= 0) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * uI + 4 * r + q4, j = 16 * uJ + c16;
+      d2i[r] = coef > 0.0 ? D2I[eidx<T>(i, j)] : 0.0;
+      if (!GEN && i == j) d2i[r] = sm.dinv[j] * sm.dinv[j];
     }
-    __syncthreads();
+  }
+
+  // Between two purifications stand four products and the residuals.  What is not on their path stays off
+  // it: the trace of M is the sum of the weights, C's diagonal is put in on the way to the first
+  // product, M goes into X_0 from the accumulators, the steering wavefront plans the first step and takes
+  // the gap's ends back beside the products, the residuals' chains overlap.  (With a phase and a barrier for
+  // each of these, ten solves at p = 20 took 206 us instead of 165, fifteen at p = 32 263 instead of 207.)
+  for (int it = 0; it < iters; ++it) {
+    int k = 0, end = STEP_GO;
+    // the steering wavefront's
+    Plan pl;
+    float Hp = 0.0f, Gp = 1.0f;             // the ends' images at X_k (pl is at X_{k+1})
+    bool guessed = false, planned = false, sq = false;
+    const double dm = (double)mm;
+    // Where the two ends of the gap lie in this solve's matrix, for the next one's folds: bounds of both
+    // (even lanes: the lower end) where the eigenvalues are all near 0 or 1, taken back through the maps
+    // of the steps bk - 1, ..., 0 before that.
+    float yv = 0.5f;
+    int bk = -1, cap_in = 0;                // (negative: not known); bit e: end e may lie in what was folded
+    auto take_back = [&](int down_to) {
+      float hv = 0.0f;
+      for (bool first = true; bk > down_to; first = false) {
+        --bk;
+        if (first || (bk & 63) == 63) hv = sm.hist[(bk & ~63) + lane];
+        const float h = lane_of(hv, bk & 63);
+        const bool grow = h > 0.0f;
+        const float r = __builtin_amdgcn_sqrtf(fmaxf(grow ? 1.0f - yv : yv, 0.0f));
+        yv = (grow ? yv : r - (h + 1.0f)) * __builtin_amdgcn_rcpf(grow ? fmaf(h, r, h) : -h);
+      }
+    };
     // ---- W = C R^T (B1): A operand = C (symmetric: tile (K, I)), B operand = R^T tile (K, J),
-    // which is R's tile (J, K) in A-operand order ---------------------------------------------
+    // which is R's tile (J, K) in A-operand order.  C's diagonal, w / s minus the row sum of the pair
+    // part, is put in on the way: a column of the A operand is spread over the four lanes c, c + 16, ...
     for (int f = wave; f < TT; f += NW) {
       const int fI = f / T, fJ = f % T;
+      v4d a[T];
+      double sum = 0.0;
+#pragma unroll
+      for (int K = 0; K < T; ++K) {
+        a[K] = load_tile<T>(B2, K, fI, lane);
+        sum += (a[K][0] + a[K][1]) + (a[K][2] + a[K][3]);
+      }
+      const int j = 16 * fI + c16;
+      const double cd = sm.w[wi][j] * (GRP ? sm.ginv[j] : sm.dinv[j] * sm.dinv[j]) - rows_sum(sum);
       v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int K = 0; K < T; ++K)
-        acc = mma4(load_tile<T>(B2, K, fI, lane), load_tile<T>(RA, fJ, K, lane), acc);
+      for (int K = 0; K < T; ++K) {
+        if (K == fI) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) a[K][r] = isdiag[r] ? cd : a[K][r];
+        }
+        acc = mma4(a[K], load_tile<T>(RA, fJ, K, lane), acc);
+      }
       store_tile<T>(B1, fI, fJ, lane, acc);
     }
     __syncthreads();
-    // ---- M = R W (B0, both triangles), its trace ----------------------------------------------
+    // the unplanned map of step j
+    bool tracked = false;                   // H and G are taken along
+    auto publish = [&](int j) {
+      pl.al = sq ? 0.0 : 2.0; pl.be = sq ? 1.0 : -1.0; pl.ga = 0.0;
+      if (lane == 0) {
+        Step& st = sm.step[j & 1];
+        st.al = pl.al; st.be = pl.be; st.ga = 0.0; st.end = end;
+        sm.hist[j] = sq ? -1.0f : 1.0f;
+      }
+      if (tracked) {
+        Hp = lane_of(pl.x, 0); Gp = lane_of(pl.x, 1);
+        plan_push(pl, !sq, sq ? 0.0f : 1.0f);
+      }
+    };
+    if (wave == SW && mm < rank) {
+      // while the others multiply: the first step's map (2000 cycles)
+      const double is = scalar(__builtin_amdgcn_rcp(hi) * (1.0 - 1e-7));
+      const double lo = lane_bcast(est, 0) * is, up = lane_bcast(est, 1) * is;
+      tracked = guessed = it > 1 && have_est && up > 1.2 * lo && up < 32.0 * lo;
+      if (lane == 0) sm.guessed = guessed;
+      if (guessed) {
+        plan_begin(pl, (float)(0.8 * lo), (float)fmin(1.0, 1.25 * up), (float)(1.05 * lo),
+                   (float)fmin(0.99, 0.95 * up), 0.03f, lane);
+      } else {
+        // no guess, but trace X_0 = 1 bounds x_{m+1} by 1 / (m + 1) (with a margin for rounding):
+        // growth may fold what is above that, while it is small
+        const float bound = 1.0001f / (float)(mm + 1);
+        plan_begin(pl, 0.0f, bound, 0.0f, bound, 0.5f, lane);
+      }
+      Hp = lane_of(pl.x, 0); Gp = lane_of(pl.x, 1);
+      if (spin_budget <= 0) end = STEP_FAILED;
+      planned = plan_next(pl, sm, 0, lane) && end == STEP_GO;
+      if (!planned) publish(0);
+    }
+    // ---- M = R W, and X_0 = M / trace M (slightly less: any scale with eigenvalues in [0, 1] will do)
+    v4d x = {0.0, 0.0, 0.0, 0.0};           // this wavefront's tile of X_k
     if (mt >= 0) {
-      v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int K = 0; K < T; ++K)
-        acc = mma4(load_tile<T>(RA, uI, K, lane), load_tile<T>(B1, K, uJ, lane), acc);
-      store_tile<T>(B0, uI, uJ, lane, acc);
-      if (uI != uJ) store_tile_transposed<T>(B0, uI, uJ, lane, acc);
-      double td = 0.0;
-      if (uI == uJ) {
+        x = mma4(load_tile<T>(RA, uI, K, lane), load_tile<T>(B1, K, uJ, lane), x);
+      // the matrix itself, row-major, for the eigengap diagnostic (only a last solve's is looked at)
+      if (it + 1 == iters || tol > 0.0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) td += isdiag[r] ? acc[r] : 0.0;
+        for (int r = 0; r < 4; ++r) {
+          const int i = 16 * uI + 4 * r + q4, j = 16 * uJ + c16;
+          Ml[i * N + j] = x[r];
+          if (uI != uJ) Ml[j * N + i] = x[r];
+        }
       }
-      td = wave_sum(td);
-      if (lane == 0) sm.red[mt] = td;
     }
-    __syncthreads();
-    double hi = 0.0;
+    if (it == 0) {
+      // (later on the residuals' weights give it)
+      if (mt >= 0) {
+        double td = 0.0;
+        if (uI == uJ) {
 #pragma unroll
-    for (int k = 0; k < NTP; ++k) hi += sm.red[k];
-    // the matrix itself, row-major, for the eigengap diagnostic
-    for (int f = wave; f < TT; f += NW) {
-      const int fI = f / T, fJ = f % T;
-      const v4d mt = load_tile<T>(B0, fI, fJ, lane);
+          for (int r = 0; r < 4; ++r) td += isdiag[r] ? x[r] : 0.0;
+        }
+        td = wave_sum(td);
+        if (lane == 0) sm.red[mt] = td;
+      }
+      __syncthreads();
+      hi = 0.0;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Ml[(16 * fI + 4 * r + q4) * N + 16 * fJ + c16] = mt[r];
+      for (int q = 0; q < NTP; ++q) hi += sm.red[q];
     }
     cur = B0; nxt = B1;
     if (mm < rank) {
-      // ---- X_0 = M / trace(M) (slightly less: any scale with eigenvalues in [0, 1] will do)
-      // Exactly symmetric: the diagonal tiles take their lower triangle twice (the others are mirrored
-      // already).  The steps keep that bit for bit, X^T X being symmetric; an antisymmetric rest would
-      // only ever see a map's linear coefficient, up to 4 in a planned step, and no planned step
-      // takes it out as a square does: 1e-17 of M was 5e-4 of X after 40 of them.
-      const double sc = __builtin_amdgcn_rcp(hi) * (1.0 - 1e-7);
-      for (int f = wave; f < TT; f += NW) {
-        const int fI = f / T, fJ = f % T;
-        v4d x = load_tile<T>(B0, fI, fJ, lane);
+      if (mt >= 0) {
+        const double sc = __builtin_amdgcn_rcp(hi) * (1.0 - 1e-7);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 4 * r + q4;
-          if (fI == fJ && i < c16) x[r] = B0[eidx<T>(16 * fI + c16, 16 * fI + i)];
-          x[r] *= sc;
+        for (int r = 0; r < 4; ++r) x[r] *= sc;
+        store_tile<T>(B0, uI, uJ, lane, x);
+        if (uI != uJ) {
+          store_tile_transposed<T>(B0, uI, uJ, lane, x);
+        } else {
+          // Exactly symmetric: a diagonal tile takes its lower triangle twice (the others are mirrored).
+          // The steps keep that bit for bit, X^T X being symmetric; an antisymmetric rest would
+          // only ever see a map's linear coefficient, up to 4 in a planned step, and no planned step
+          // takes it out as a square does: 1e-17 of M was 5e-4 of X after 40 of them.
+          wave_fence();
+          const double* tp = B0 + (uI * T + uI) * FA_TILE + (c16 >> 3) * FA_HALF + ((c16 >> 2) & 1) +
+                             at((c16 & 3) * 16 + q4);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const double below = tp[8 * r];
+            if (4 * r + q4 < c16) x[r] = below;
+          }
+          wave_fence();
+          store_tile<T>(B0, uI, uI, lane, x);
         }
-        store_tile<T>(B0, fI, fJ, lane, x);
       }
       // ---- purification ---------------------------------------------------------------------
       // A wavefront's fp64 vector instructions do not get a turn while older wavefronts of
@@ -616,14 +722,11 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       //    t = trace X_k and |X_k|_F^2, which give trace X_{k+1}: X^2 where that is above m, 2X - X^2
       //    below; and that X_{k+1} is the result where X_k is a projector already;
       //  - everybody else keeps the barrier, one a step.
-      // So a step's map is there before the barrier in front of it and nobody waits for it.  Cycles a
-      // step, begin and end of a solve included: T = 2 1070 to 1130 (512 of them matrix instructions),
-      // T = 4 3700 to 4100 (3072); 1480 and 4370 with the trace of X_k itself, published during step k
-      // and waited for behind its products.  (p = 32 bf16, 15 solves: 314 -> 263 us.)
-      int k = 0, end = STEP_GO;
+      // So a step's map is there before the barrier in front of it and nobody waits for it.  A step, us at
+      // 2.4 GHz: T = 2 0.4 (512 of about 950 cycles matrix instructions), T = 4 1.6 (3072 of 3900); 0.6
+      // and 1.8 with the trace of X_k itself, published during step k and waited for behind its products.
       if (mt >= 0) {
         // this wavefront's tile of X_k stays in its registers: LDS holds it for the others
-        v4d x;
         double live[4];                                  // the identity's place in a diagonal tile
 #pragma unroll
         for (int r = 0; r < 4; ++r) live[r] = isdiag[r] && 16 * uJ + c16 < rank ? 1.0 : 0.0;
@@ -667,8 +770,6 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
           ++k;
           return false;
         };
-        __syncthreads();
-        x = load_tile<T>(B0, uI, uJ, lane);
         auto steps_of = [&](auto kind, auto nl) __attribute__((always_inline)) {
           while (!step(kind, nl, B0, B1) && !step(kind, nl, B1, B0)) {}
         };
@@ -693,43 +794,9 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         // matter to what is right, both maps keep the eigenvalues' order); and from where all
         // eigenvalues are near 0 or 1, with those two measured in f64, as many steps as it takes to
         // square what the sums of the lower ones and of the upper ones' distances from 1 leave away.
-        const double lo = scalar(sm.est[0] * sc), up = scalar(sm.est[1] * sc), dm = (double)mm;
-        const bool guessed = it > 1 && __builtin_amdgcn_readfirstlane(sm.have_est) != 0 && up > 1.2 * lo &&
-                             up < 32.0 * lo;
-        Plan pl;
-        if (lane == 0) { sm.guessed = guessed; sm.cap_k = -1; }
-        if (guessed) {
-          plan_begin(pl, (float)(0.8 * lo), (float)fmin(1.0, 1.25 * up), (float)(1.05 * lo),
-                     (float)fmin(0.99, 0.95 * up), 0.03f, lane);
-        } else {
-          // no guess, but trace X_0 = 1 bounds x_{m+1} by 1 / (m + 1) (with a margin for rounding):
-          // growth may fold what is above that, while it is small
-          const float bound = 1.0001f / (float)(mm + 1);
-          plan_begin(pl, 0.0f, bound, 0.0f, bound, 0.5f, lane);
-        }
-        float Hp = lane_of(pl.x, 0), Gp = lane_of(pl.x, 1);   // the ends' images at X_k (pl is at X_{k+1})
-        bool sq = false;
-        // the plain map of step j
-        auto publish = [&](int j) {
-          pl.al = sq ? 0.0 : 2.0; pl.be = sq ? 1.0 : -1.0; pl.ga = 0.0;
-          if (lane == 0) {
-            Step& st = sm.step[j & 1];
-            st.al = pl.al; st.be = pl.be; st.ga = 0.0; st.end = end;
-            sm.hist[j] = sq ? -1.0f : 1.0f;
-          }
-          if (guessed) {
-            Hp = lane_of(pl.x, 0); Gp = lane_of(pl.x, 1);
-            plan_push(pl, !sq, sq ? 0.0f : 1.0f);
-          }
-        };
-        if (spin_budget <= 0) end = STEP_FAILED;
-        bool planned = plan_next(pl, sm, 0, lane);
-        const bool any = planned && end == STEP_GO;
-        if (!any) publish(0);
-        __syncthreads();
         __builtin_amdgcn_s_setprio(3);      // ahead of the matrix instructions of its SIMD
         __syncthreads();
-        if (any) {
+        if (planned) {
           for (;;) {                        // step k, whose map is a planned one
             const float H = lane_of(pl.x, 0), G = lane_of(pl.x, 1);
             planned = plan_next(pl, sm, k + 1, lane);
@@ -744,12 +811,12 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
           ++k;
           __syncthreads();
         }
-        bool near = true, settled = false, have_cap = false;
+        bool near = true, settled = false;
         float t = 0.0f, F = 0.0f;           // of X_k
         float A = 0.0f, B = 0.0f;           // the lower eigenvalues' sum, the upper ones' distance from 1
         while (end == STEP_GO) {            // step k, whose map is a plain one
           const double* cu = k & 1 ? B1 : B0;
-          if (!settled && !near) {
+          if (!settled) {
             double f0 = 0.0, f1 = 0.0;
             v4d v[NTP];
 #pragma unroll
@@ -764,23 +831,16 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
 #pragma unroll
               for (int r = 0; r < 4; ++r) f = fma(v[q][r], v[q][r], f);
             }
-            F = wave_sum_f32((float)fma(2.0, f1, f0));
-            near = t - F < 0.04f;
-          }
-          if (!settled && near) {
+            f0 = fma(2.0, f1, f0);
+            if (!near) {
+              F = wave_sum_f32((float)f0);
+              near = t - F < 0.04f;
+            }
+            if (near) {
             // (behind a plan, where the trace is not known, and from the first sign on)
-            double fd = 0.0;
-#pragma unroll 1
-            for (int I = 0; I < T; ++I)
-#pragma unroll 1
-              for (int J = I; J < T; ++J) {
-                const v4d v = load_tile<T>(cu, I, J, lane);
-                const double f = fma(v[0], v[0], v[1] * v[1]) + fma(v[2], v[2], v[3] * v[3]);
-                fd = fma(I == J ? 1.0 : 2.0, f, fd);
-              }
             const int d = lane < N ? lane : 0;
             const double td = wave_sum(lane < N ? cu[eidx<T>(d, d)] : 0.0);
-            fd = wave_sum(fd);
+            const double fd = wave_sum(f0);
             t = (float)td; F = (float)fd;
             const double s = td - fd;       // sum x (1 - x) over the eigenvalues of X_k
             near = s < 0.04;
@@ -789,22 +849,23 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
               // distance from 1 bound the ends of the gap (1.02 s stands for the s = sum x (1 - x)
               // without the squares)
               const double cl = 0.5 * (1.02 * s + td - dm), cu1 = 0.5 * (1.02 * s - td + dm);
-              if (!have_cap && lane == 0) {
-                sm.cap_k = k;
-                sm.cap[0] = (float)fmin(0.5, fmax(1e-4, cl));
-                sm.cap[1] = 1.0f - (float)fmin(0.5, fmax(1e-4, cu1));
+              if (bk < 0) {
+                bk = k;
+                yv = lane & 1 ? 1.0f - (float)fmin(0.5, fmax(1e-4, cu1)) : (float)fmin(0.5, fmax(1e-4, cl));
                 // (both are sums, good to 0.02 s)
                 const double zl = 0.5 * (double)(rank - mm) * Hp, zu = 0.5 * dm * (1.0 - Gp);
-                sm.cap_in = !guessed ? 0 : (cl <= zl + 0.02 * s ? 1 : 0) | (cu1 <= zu + 0.02 * s ? 2 : 0);
+                cap_in = !guessed ? 0 : (cl <= zl + 0.02 * s ? 1 : 0) | (cu1 <= zu + 0.02 * s ? 2 : 0);
               }
-              have_cap = true;
               if (fabs(td - dm) < 0.25) {
                 settled = true;
+                // where H and G are near 0 and 1 as well, the order is kept from here on
+                tracked = tracked && !(Hp < 0.1f && Gp > 0.9f);
                 A = fmaxf((float)cl, 1e-15f);
                 B = fmaxf((float)cu1, 1e-15f);
               } else if (fabs(s) < 1e-10 || (guessed && s < 1e-3)) {
                 end = STEP_FAILED;          // nearly a projector, but with another trace
               }
+            }
             }
           }
           // on to X_{k+1}
@@ -814,7 +875,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
             B = sq ? 2.0f * B : B * B;
             next = A > B;
             if (fmaxf(A, B) < 1e-12f)
-              end = !guessed || (lane_of(pl.x, 1) > 0.9f && lane_of(pl.x, 0) < 0.1f) ? STEP_DONE : STEP_FAILED;
+              end = !tracked || (lane_of(pl.x, 1) > 0.9f && lane_of(pl.x, 0) < 0.1f) ? STEP_DONE : STEP_FAILED;
           } else {
             t = sq ? F : 2.0f * t - F;
             next = t > (float)mm;
@@ -823,11 +884,11 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
           if (end == STEP_GO && k >= (guessed ? 64 : MAX_PURIFY - 1)) end = STEP_FAILED;
           sq = next;
           publish(k);
+          if (settled) take_back(bk > BACK ? bk - BACK : 0);      // (there is time beside these steps)
           __syncthreads();
         }
         __builtin_amdgcn_s_setprio(0);
       } else {
-        __syncthreads();
         for (;; ++k) {
           __syncthreads();
           end = __builtin_amdgcn_readfirstlane(sm.step[k & 1].end);
@@ -842,13 +903,12 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         // a guess that did not hold: the solve once more without
         if (!sm.guessed) { failed = 1; break; }
         __syncthreads();
-        if (tid == 0) sm.have_est = 0;
+        have_est = false;
         --it;
         continue;
       }
     } else {
       // m >= rank: Y spans all of span(G)
-      if (tid == 0) sm.have_est = 0;
       for (int f = wave; f < TT; f += NW) {
         const int fI = f / T, fJ = f % T;
         v4d x;
@@ -868,9 +928,17 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         v4d q = load_tile<T>(cur, K, fI, lane);
 #pragma unroll
         for (int r = 0; r < 4; ++r) q[r] = (K == fI && isdiag[r]) ? 1.0 - q[r] : -q[r];
-        acc = mma4(q, load_tile<T>((const double*)Rb, K, fJ, lane), acc);
+        acc = mma4(q, load_tile<T>(Rb, K, fJ, lane), acc);
       }
       store_tile<T>(nxt, fI, fJ, lane, acc);
+    }
+    if (wave == SW && bk >= 0) {
+      take_back(0);
+      // an end that was folded could have come from either side of the fold: then further out
+      double e = hi * (double)yv;
+      if ((cap_in >> (lane & 1)) & 1) e = lane & 1 ? fmin(hi, fmax(e, 2.0 * est)) : fmin(e, 0.5 * est);
+      est = e;
+      have_est = true;
     }
     __syncthreads();
     // ---- Gq = Z^T Z (symmetric; tile (I, J) = sum_K Z(K, I)^T Z(K, J)); its diagonal ----------
@@ -884,25 +952,6 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         for (int r = 0; r < 4; ++r)
           if (isdiag[r]) sm.gd[16 * uI + c16] = gq[r];
       }
-    } else if (wave == SW && mm < rank && sm.cap_k >= 0) {
-      // where the two ends of the gap lay in this solve's matrix, for the next one's folds: the
-      // bounds of step cap_k taken back through the maps before it (even lanes: the lower end).  An
-      // end that was folded could have come from either side of the fold: then further out.
-      float yv = sm.cap[lane & 1];
-      for (int k = sm.cap_k - 1; k >= 0; --k) {
-        const float h = sm.hist[k];
-        if (h > 0.0f) {
-          const float u = 1.0f - yv;
-          yv = yv * __builtin_amdgcn_rcpf(h * (1.0f + __builtin_amdgcn_sqrtf(u > 0.0f ? u : 0.0f)));
-        } else {
-          yv = (__builtin_amdgcn_sqrtf(yv) - (h + 1.0f)) * __builtin_amdgcn_rcpf(-h);
-        }
-      }
-      double e = hi * (double)yv;
-      if ((sm.cap_in >> (lane & 1)) & 1)
-        e = lane & 1 ? fmin(hi, fmax(e, 2.0 * sm.est[1])) : fmin(e, 0.5 * sm.est[0]);
-      if (lane < 2) sm.est[lane] = e;
-      if (lane == 0) sm.have_est = 1;
     }
     __syncthreads();
     if constexpr (GRP) {
@@ -915,36 +964,34 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       __syncthreads();
     }
     // ---- residuals, objective, next weights (pair part straight into C = B2) -------------------
-    double part = 0.0;
+    double part = 0.0, wsum = 0.0;          // of the objective; of the next M's trace
     if (mt >= 0) {
       v4d cpn;
       if constexpr (!GEN) {
+        // |(I - P) r_j|^2 / |g_j|^2 = 1 - v_j on the diagonal, |z_i - z_j|^2 / D_ij^2 elsewhere; ordered
+        // pairs: an off-diagonal tile stands for its mirror image too.  All four without a branch, so
+        // that their chains overlap.
+        const int j = 16 * uJ + c16;
+        const double gj = sm.gd[j], pair = (uI == uJ ? 1.0 : 2.0) * coef;
+        double rho[4], wv[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int i = 16 * uI + 4 * r + q4, j = 16 * uJ + c16;
-          double cv = 0.0;
-          if (i == j) {
-            // |(I - P) r_j|^2 / |g_j|^2 = 1 - v_j
-            const double rho = gq[r] * sm.dinv[j] * sm.dinv[j];
-            const bool livej = sm.s[j] > 0.0;
-            const double rsj = rsq2(rho > 1e-300 ? rho : 1e-300);
-            if (livej) part += rho * rsj;
-            sm.rho[j] = rho;
-            sm.wn[j] = livej ? (rsj < rs_delta ? rsj : rs_delta) : 0.0;
-          } else {
-            const double d2i = D2I[eidx<T>(i, j)];
-            if (d2i > 0.0 && coef > 0.0) {
-              double num = sm.gd[i] + sm.gd[j] - 2.0 * gq[r];
-              num = num > 0.0 ? num : 0.0;
-              const double rho = num * d2i;
-              const double rsv = rsq2(rho > 1e-300 ? rho : 1e-300);
-              // ordered pairs: an off-diagonal tile stands for its mirror image too
-              part += (uI == uJ ? 1.0 : 2.0) * coef * (rho * rsv);
-              cv = -2.0 * coef * d2i * (rsv < rs_delta ? rsv : rs_delta);
-            }
-          }
-          cpn[r] = cv;
+          const bool diag = uI == uJ && isdiag[r];
+          const double num = diag ? gq[r] : fma(-2.0, gq[r], sm.gd[16 * uI + 4 * r + q4] + gj);
+          rho[r] = fmax(num, 0.0) * d2i[r];
+          const double rsv = rsq2(rho[r] > 1e-300 ? rho[r] : 1e-300);
+          const double f = d2i[r] > 0.0 ? (diag ? 1.0 : pair) : 0.0;
+          wv[r] = fmin(rsv, rs_delta);
+          part = fma(f, rho[r] * rsv, part);
+          wsum = fma(f, wv[r], wsum);
+          cpn[r] = diag ? 0.0 : -2.0 * coef * d2i[r] * wv[r];
         }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (uI == uJ && isdiag[r]) {
+            sm.rho[j] = rho[r];
+            sm.w[wi ^ 1][j] = d2i[r] > 0.0 ? wv[r] : 0.0;
+          }
       } else {
         // the general exponent: same places, powers instead of square roots (rolled: once per
         // solve, and inlined copies of pow() are long)
@@ -954,18 +1001,17 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
           const double gqr = r == 0 ? gq[0] : r == 1 ? gq[1] : r == 2 ? gq[2] : gq[3];
           double rho = 0.0, scale = 0.0;       // residual; factor of its term in the objective
           bool diag = i == j, use = false;
-          double d2i = 0.0;
+          const double di = r == 0 ? d2i[0] : r == 1 ? d2i[1] : r == 2 ? d2i[2] : d2i[3];
           if constexpr (!GRP) {
             if (diag) {
               rho = gqr * sm.dinv[j] * sm.dinv[j];
               use = sm.s[j] > 0.0;
               scale = 1.0;
             } else {
-              d2i = D2I[eidx<T>(i, j)];
-              if (d2i > 0.0 && coef > 0.0) {
+              if (di > 0.0 && coef > 0.0) {
                 double num = sm.gd[i] + sm.gd[j] - 2.0 * gqr;
                 num = num > 0.0 ? num : 0.0;
-                rho = num * d2i;
+                rho = num * di;
                 use = true;
                 scale = (uI == uJ ? 1.0 : 2.0) * coef;
               }
@@ -981,13 +1027,12 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
               use = sm.ginv[j] > 0.0;
               scale = j == fj ? 1.0 : 0.0;
             } else {
-              d2i = D2I[eidx<T>(i, j)];
-              if (d2i > 0.0 && coef > 0.0) {
+              if (di > 0.0 && coef > 0.0) {
                 double num = 0.0;
                 for (int l = 0; l < kj; ++l)
                   num += sm.gd[fi + l] + sm.gd[fj + l] - 2.0 * nxt[eidx<T>(fi + l, fj + l)];
                 num = num > 0.0 ? num : 0.0;
-                rho = num * d2i;
+                rho = num * di;
                 use = true;
                 scale = i == fi ? (uI == uJ ? 1.0 : 2.0) * coef : 0.0;
               }
@@ -1003,30 +1048,31 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
             tv = fa_term_pow(rho, expo);
             wv = fa_weight_pow(rho, delta, expo);
           }
-          if (use) part += scale * tv;
-          if (diag) { sm.rho[j] = rho; sm.wn[j] = use ? wv : 0.0; }
-          const double cv = (!diag && use) ? -2.0 * coef * d2i * wv : 0.0;
+          if (use) { part += scale * tv; wsum += scale * wv; }
+          if (diag) { sm.rho[j] = rho; sm.w[wi ^ 1][j] = use ? wv : 0.0; }
+          const double cv = (!diag && use) ? -2.0 * coef * di * wv : 0.0;
           if (r == 0) cpn[0] = cv; else if (r == 1) cpn[1] = cv; else if (r == 2) cpn[2] = cv; else cpn[3] = cv;
         }
       }
       store_tile<T>(B2, uI, uJ, lane, cpn);
       if (uI != uJ) store_tile_transposed<T>(B2, uI, uJ, lane, cpn);
       part = wave_sum(part);
-      if (lane == 0) sm.red[mt] = part;
+      wsum = wave_sum(wsum);
+      if (lane == 0) { sm.red[mt] = part; sm.redw[mt] = wsum; }
     }
     __syncthreads();
     double obj = 0.0;
+    hi = 0.0;         // trace M = sum of the weights: its columns are normalised
 #pragma unroll
-    for (int k = 0; k < NTP; ++k) obj += sm.red[k];
+    for (int q = 0; q < NTP; ++q) { obj += sm.red[q]; hi += sm.redw[q]; }
     if (tid == 0 && it0 + it < FA_ITERS_MAX) info->objective[it0 + it] = obj;
     iters_done = it + 1;
     const bool stop = it0 + it > 0 && fabs(prev_obj - obj) < tol;
     prev_obj = obj;
-    __syncthreads();   // red[] is reused by the next solve
     if (stop) break;
-    if (tid < 64) sm.w[tid] = sm.wn[tid];
-    __syncthreads();
+    wi ^= 1;
   }
+  __syncthreads();
   if (failed) {
     if (tid == 0) info->status = FA_ST_RETRY;
     return;
@@ -1143,7 +1189,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     info->c[tid] = cv;
     info->s[tid] = sm.s[tid];
     info->v[tid] = (GRP ? sm.ginv[tid] > 0.0 : sm.s[tid] > 0.0) ? 1.0 - sm.rho[tid] : 0.0;
-    info->w[tid] = sm.w[tid];
+    info->w[tid] = sm.w[wi][tid];
   }
   if (rs) {
     // weights for the solve that would come next
@@ -1155,7 +1201,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         if (i < p && j < p) rs->cp[i * p + j] = i != j ? B2[eidx<T>(i, j)] : 0.0;
       }
     }
-    if (tid < p) rs->w[tid] = sm.w[tid];
+    if (tid < p) rs->w[tid] = sm.w[wi][tid];
     if (tid == 0) { rs->prev_obj = prev_obj; rs->it0 = it0 + iters_done; }
   }
   if (tid == 0) {
@@ -1171,7 +1217,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
 
 template <int T>
 static constexpr size_t lds_bytes() {
-  constexpr size_t bytes = (size_t)4 * T * T * FA_TILE * sizeof(double) + sizeof(Small);
+  constexpr size_t bytes = (size_t)(T < 4 ? 5 : 4) * T * T * FA_TILE * sizeof(double) + sizeof(Small);
   static_assert(bytes <= 160 * 1024, "more than a compute unit's LDS");
   return bytes;
 }
