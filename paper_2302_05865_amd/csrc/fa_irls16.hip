@@ -230,7 +230,7 @@ __device__ __forceinline__ double block_sum(double x, Smem& sm) {
 // one 16 x 16 fp64 product = four v_mfma_f64_16x16x4_f64 on registers: for a symmetric X the
 // accumulator layout (register r of lane l = entry (4r + l/16, l%16)) is at once the A- and
 // the B-operand layout, so the iteration never leaves the register file.  trace(X^2) =
-// |X|_F^2 is reduced on the vector ALU while the matrix core multiplies.
+// |X|_F^2 is summed up beside the products.
 // R comes from a pivoted Cholesky factorisation of the normalised Gram matrix (R^T R = K~,
 // rank-revealing), so no eigen-decomposition is needed at set-up either.
 // If the purification does not converge (eigenvalues m and m+1 tie), the Jacobi path below
@@ -240,6 +240,7 @@ namespace fastp {
 constexpr int LDF = 17;
 constexpr int LDZ = 18;          // column pitch of Zs (16-byte aligned rows of 16 doubles)
 constexpr int MAX_PURIFY = 128;
+constexpr double NEAR = 0.12;    // sum x (1 - x) below which the trace and |X|_F^2 are measured exactly
 
 struct Fmem {
   double Kt[16 * LDF];   // Gram, then normalised Gram
@@ -264,58 +265,43 @@ __device__ __forceinline__ double dpp_f64(double x) {
   hi = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
 }
-// sum / max over each 16-lane row (lanes l with equal l/16); every lane of the row gets it
-__device__ __forceinline__ double row_sum(double x) {
-  x += dpp_f64<0x128>(x);   // row_ror:8
-  x += dpp_f64<0x124>(x);   // row_ror:4
-  x += dpp_f64<0x122>(x);   // row_ror:2
-  x += dpp_f64<0x121>(x);   // row_ror:1
-  return x;
-}
-__device__ __forceinline__ double row_max(double x) {
-  x = fmax(x, dpp_f64<0x128>(x));
-  x = fmax(x, dpp_f64<0x124>(x));
-  x = fmax(x, dpp_f64<0x122>(x));
-  x = fmax(x, dpp_f64<0x121>(x));
-  return x;
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, false));
 }
 __device__ __forceinline__ double lane_bcast(double x, int srclane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(x), srclane);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(x), srclane);
   return __hiloint2double(hi, lo);
 }
-// Sum over the four lanes c, 16 + c, 32 + c, 48 + c, in every one of them: (t0 + t1) + (t2 + t3).
-// v_permlane16_swap / v_permlane32_swap with both operands the same value return the even rows
-// (the lower half) and the odd rows (the upper half) side by side.
-__device__ __forceinline__ double rows_sum(double t) {
-  int lo = __double2loint(t), hi = __double2hiint(t);
-  auto a = __builtin_amdgcn_permlane16_swap((unsigned)lo, (unsigned)lo, false, false);
-  auto b = __builtin_amdgcn_permlane16_swap((unsigned)hi, (unsigned)hi, false, false);
-  const double s = __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
-  lo = __double2loint(s); hi = __double2hiint(s);
-  a = __builtin_amdgcn_permlane32_swap((unsigned)lo, (unsigned)lo, false, false);
-  b = __builtin_amdgcn_permlane32_swap((unsigned)hi, (unsigned)hi, false, false);
-  return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+// Deterministic sum over the wavefront, same bits in every lane, in two stages.  A 4 x 4 x 4 matrix
+// instruction with four blocks sums over the lanes l, l + 16, l + 32, l + 48 where one operand is
+// all ones (first stage), and a second one over the other index of a block; two additions are left.
+// That is 8 instructions behind the first value instead of 23 with DPP moves and readlanes, and
+// beside a chain of matrix instructions every one costs 8 cycles.
+__device__ __forceinline__ double sum_stage1(double t) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(t, 1.0, 0.0, 0, 0, 0);
 }
-// deterministic sum over the wavefront, same value in every lane
-__device__ __forceinline__ double wave_sum(double x) {
-  x = row_sum(x);
-  return ((lane_bcast(x, 0) + lane_bcast(x, 16)) + lane_bcast(x, 32)) + lane_bcast(x, 48);
-}
-
-// |X|_F^2 over the wavefront in two stages, so that the second stage of one purification
-// step can be issued next to the first stage of the following one (fp64 vector operations
-// have a long dependent latency; two interleaved chains fit under one 16 x 16 product).
-__device__ __forceinline__ double fro2_stage1(const v4d& x) {
-  double t = fma(x[0], x[0], x[1] * x[1]) + fma(x[2], x[2], x[3] * x[3]);
-  t += dpp_f64<0x128>(t);
-  t += dpp_f64<0x124>(t);
+__device__ __forceinline__ double sum_stage2(double t) {
+  t = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, t, 0.0, 0, 0, 0);
+  t += dpp_f64<0x128>(t);   // row_ror:8
+  t += dpp_f64<0x124>(t);   // row_ror:4
   return t;
 }
-__device__ __forceinline__ double fro2_stage2(double t) {
-  t += dpp_f64<0x122>(t);
-  t += dpp_f64<0x121>(t);
-  return (lane_bcast(t, 0) + lane_bcast(t, 16)) + (lane_bcast(t, 32) + lane_bcast(t, 48));
+__device__ __forceinline__ double wave_sum(double x) { return lane_bcast(sum_stage2(sum_stage1(x)), 0); }
+// |X|_F^2, trace X (eye: the identity): the first stage of these sums
+__device__ __forceinline__ double fro2_stage1(const v4d& x) {
+  return sum_stage1(fma(x[3], x[3], fma(x[2], x[2], fma(x[1], x[1], x[0] * x[0]))));
+}
+__device__ __forceinline__ double trace_stage1(const v4d& x, const v4d& eye) {
+  return sum_stage1(fma(x[3], eye[3], fma(x[2], eye[2], fma(x[1], eye[1], x[0] * eye[0]))));
+}
+// c + the sum in f32
+__device__ __forceinline__ float sum_stage2_f32(double t, double quarter_c) {
+  float v = (float)__builtin_amdgcn_mfma_f64_4x4x4f64(1.0, t, quarter_c, 0, 0, 0);
+  v += dpp_f32<0x128>(v);
+  v += dpp_f32<0x124>(v);
+  return v;
 }
 
 // NS: matrix instructions, four contraction indices each; all that is multiplied here is zero from
@@ -323,6 +309,14 @@ __device__ __forceinline__ double fro2_stage2(double t) {
 template <int NS>
 __device__ __forceinline__ v4d mm16(const v4d& a, const v4d& b) {
   v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+  return acc;
+}
+
+// C + A B
+template <int NS>
+__device__ __forceinline__ v4d mm16_plus(const v4d& a, const v4d& b, v4d acc) {
 #pragma unroll
   for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
   return acc;
@@ -523,8 +517,12 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
   double rhoj = 0.0, rsj = 0.0;
   const double rs_delta = 1.0 / sqrt(delta);          // the weight floor, as a cap on 1/sqrt(rho)
   v4d cp;                                              // pair part of C, entry (4r+q4, c16)
+  double cp1[4], coefr[4];                             // the same of unit weights; coef where there is a pair
 #pragma unroll
-  for (int r = 0; r < 4; ++r) cp[r] = -2.0 * coef * d2inv[r];
+  for (int r = 0; r < 4; ++r) {
+    cp[r] = cp1[r] = -2.0 * coef * d2inv[r];
+    coefr[r] = d2inv[r] > 0.0 ? coef : 0.0;
+  }
   double prev_obj = 0.0;
   if (it0 > 0) {
     // continue from the weights the previous launch (or the streamed residuals) left
@@ -552,42 +550,51 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
       bound = ga[g] > 0.0 ? (1.0 - u * u) * 1.0001 : bound;
     }
   }
+  v4d eye, less;                                       // the identity, and its negative
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    eye[r] = isdiag[r] && c16 < rank ? 1.0 : 0.0;
+    less[r] = -eye[r];
+  }
+  double hi = 0.0;                                     // trace of M
   v4d x = {0.0, 0.0, 0.0, 0.0}, mk = {0.0, 0.0, 0.0, 0.0};
   int iters_done = 0, steps = 0;
   for (int it = 0; it < iters; ++it) {
     // C = diag(w/s) + Laplacian of the pair part;  M = R C R^T via W = C R^T, M = R W
     // (the pair part is symmetric, bit for bit: the sum of row j is the sum of column j, which
-    // is spread over the four lanes that hold column j)
+    // is spread over the four lanes that hold column j.  The first stage of a sum adds these up and leaves
+    // column 4 b + q in the lanes (q, 4 b + i): the diagonal entries' lanes have their own)
     v4d c;
-    const double csum = rows_sum((cp[0] + cp[1]) + (cp[2] + cp[3]));
+    const double csum = sum_stage1((cp[0] + cp[1]) + (cp[2] + cp[3]));
 #pragma unroll
     for (int r = 0; r < 4; ++r) c[r] = isdiag[r] ? wj * dj * dj - csum : cp[r];
     const v4d wmat = mm16<NS>(c, ra);
     mk = mm16<NS>(ra, wmat);
     if (mm < rank) {
-      // scale into [0, 1]: M is PSD, so 0 <= eigenvalues <= trace(M)
-      double tr = 0.0;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) tr += isdiag[r] ? mk[r] : 0.0;
-      const double hi = wave_sum(tr);
-      // any scale that keeps the eigenvalues in [0, 1] will do: the hardware reciprocal,
-      // shaded down by more than its error
-      const double sc = __builtin_amdgcn_rcp(hi) * (1.0 - 1e-7);
+      // Scale into [0, 1]: M is PSD, so 0 <= eigenvalues <= trace(M), which is the sum of the
+      // weights (a pair of nearly equal gradients adds its weight to 1e-4, rounding in D^2).  Any scale
+      // that keeps the eigenvalues in [0, 1] will do: the hardware reciprocal, shaded down.
+      if (it == 0) {
+        hi = lane_bcast(sum_stage2(trace_stage1(mk, eye)), 0);
+      }
+      const double sc = __builtin_amdgcn_rcp(hi) * (1.0 - 1e-3);
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] = mk[r] * sc;
-      // Steering: square when trace(X) > m, else X <- 2X - X^2.  trace(X) is carried along
-      // (after a square it is the previous |X|_F^2, otherwise 2 trace(X) - |X|_F^2), so the
-      // only reduction per step is |X|_F^2, and its result is not needed before the end of
-      // the *next* step: the reduction is split in two halves (second half for X_{k-1},
-      // first half for X_k) issued beside the four matrix-core instructions of X_k^2.
-      // The same numbers, one step late, say when X is nearly a projector:
-      // trace(X_{k-1}) - |X_{k-1}|_F^2 is the distance of X_{k-1} from idempotency.  The flag
-      // is acted upon at the top of the next step (a branch on a value computed long before
-      // costs nothing; a branch on the end of the reduction chain would stall every step):
-      // two steps after the distance fell below 1e-8 the iterate has converged (each step
-      // squares the error at one end of the spectrum and doubles it at the other), and there
-      // trace and |X|_F^2 are measured exactly, because the carried trace drifts by rounding.
-      double tX = hi * sc;                 // trace(X_k)
+      // Steering: square when trace(X) > m, else X <- 2X - X^2.  With E = 2X - I both are
+      // E <- E + sigma (E^2 - I), sigma = 1/2 or -1/2: the accumulators start at -I, and four multiply-adds
+      // are all that follows a product (twelve instructions with X itself, for the selects).
+      // trace(E) is carried along in f32 (E_{k+1}: trace(E_k) + sigma (|E_k|_F^2 - r); it only steers), so
+      // the only reduction per step is |E|_F^2, and its result is not needed before the end of
+      // the *next* step: the reduction is split in two halves (second half for E_{k-1},
+      // first half for E_k) issued beside the four matrix-core instructions of E_k^2.
+      // The same number says when X was nearly a projector: (r - |E_{k-1}|_F^2) / 4 is the distance
+      // of X_{k-1} from idempotency.  The flag is looked at every second step and
+      // acted upon at the top of the next one (a branch on a value computed long before
+      // costs nothing; a branch on the end of the reduction chain would stall every step);
+      // there trace and |E|_F^2 are measured exactly, because the carried trace drifts by
+      // rounding, and the steps behind that need no steering.
+      const double dm = (double)mm;
+      double tX = hi * sc;                 // trace(X)
       if (ga[0] > 0.0) {
 #pragma unroll
         for (int g = 0; g < 3; ++g) {
@@ -599,72 +606,89 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
             steps = steps + 1;
           }
         }
-        double tg = 0.0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tg += isdiag[r] ? x[r] : 0.0;
-        tX = wave_sum(tg);
+        tX = sum_stage2(trace_stage1(x, eye));
       }
-      double tXp = 64.0;                   // trace(X_{k-1}) (dummy for the first step: not "near")
-      double pend = tX * (1.0 / 16.0);     // stage-1 partial of |X_{k-1}|_F^2: stage 2 gives tX
-      bool sqp = true;                     // with the above, step 0 computes trace(X_0) = tX
+      const double dr = (double)rank;
+      const float cut = (float)(2 * mm - rank);            // trace(E) of the projector
+      // the dummies give the first step the trace it is told and "not near"
+      float tE = (float)(tX + tX - dr);
+      double sg = 0.0, pend = -1.0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[r] = fma(2.0, x[r], less[r]);
       bool conv = false;
       int k_end = MAX_PURIFY;
+      float A = 0.0f, B = 0.0f;            // the lower eigenvalues' sum, the upper ones' distance from 1
       // Two loops: the steps run in an inner loop of their own until the iterate is nearly
       // idempotent, the exact test sits outside it.  (With the test inside one loop, never
       // taken until the end, every step was a quarter slower: 700 against 534 cycles.)
-      // One step X_k (xi) -> X_{k+1} (xo); returns "X_{k-1} was nearly idempotent".  The loop
+      // One step E_k (xi) -> E_{k+1} (xo); returns |E_{k-1}|_F^2 - r.  The loop
       // runs two of them per pass, from x into a second set of registers and back, which
-      // spares the copies of a rotated loop and gives the scheduler two steps to interleave
-      // (522 against 593 cycles per step on a stand-alone copy of the loop).
-      auto one_step = [&](const v4d& xi, v4d& xo) __attribute__((always_inline)) -> bool {
-        const v4d y = mm16<NS>(xi, xi);
-        const double tYp = fro2_stage2(pend);              // |X_{k-1}|_F^2
+      // spares the copies of a rotated loop and gives the scheduler two steps to interleave.
+      // A step at p = 15: 455 cycles, 264 of them the four matrix instructions (598 with X itself, a reduction
+      // in f64 with DPP moves and readlanes and a way out behind either step); p = 7: 317 (506).
+      const double r4 = -0.25 * dr;
+      auto one_step = [&](const v4d& xi, v4d& xo) __attribute__((always_inline)) -> float {
+        const v4d y = mm16_plus<NS>(xi, xi, less);
+        const float q = sum_stage2_f32(pend, r4);
         pend = fro2_stage1(xi);
-        tX = sqp ? tYp : fma(2.0, tXp, -tYp);              // trace(X_k)
-        const bool nr = (tXp - tYp < 1e-8);
-        const bool sq = tX > (double)mm;
-        if (sq) {
+        tE = fmaf((float)sg, q, tE);                       // trace(E_k)
+        sg = tE > cut ? 0.5 : -0.5;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) xo[r] = y[r];
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) xo[r] = fma(2.0, xi[r], -y[r]);
-        }
-        tXp = tX;
-        sqp = sq;
+        for (int r = 0; r < 4; ++r) xo[r] = fma(sg, y[r], xi[r]);
         steps = steps + 1;
-        return nr;
+        return q;
       };
       for (int k = 0; k < MAX_PURIFY;) {
-        bool near = false;
+        bool near;
         do {
           v4d x2;
-          near = one_step(x, x2);
-          ++k;
-          if (near || k >= MAX_PURIFY) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = x2[r];
-            break;
-          }
-          near = one_step(x2, x);
-          ++k;
+          one_step(x, x2);
+          const float q = one_step(x2, x);
+          near = __ballot(q > (float)(-4.0 * NEAR)) != 0ull;
+          k += 2;
         } while (!near && k < MAX_PURIFY);
         if (!near) break;
-        double td = 0.0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) td += isdiag[r] ? x[r] : 0.0;
-        tX = wave_sum(td);
-        if (tX - fro2_stage2(fro2_stage1(x)) < 1e-12) {
-          // idempotent; it is the wanted projector only if its trace is m (the maps are
-          // monotone, so the eigenvalue order is kept whatever the steering did)
-          conv = fabs(tX - (double)mm) < 0.25;
-          k_end = k;
-          break;
+        const double t1 = trace_stage1(x, eye), f1 = fro2_stage1(x);
+        // trace X - m and sum x (1 - x)
+        const double dt = lane_bcast(0.5 * (sum_stage2(t1) + dr) - dm, 0);
+        const double s = lane_bcast(0.25 * (dr - sum_stage2(f1)), 0);
+        if (s < 0.03) {
+          // All eigenvalues are near 0 or 1.  The wanted projector only if the trace is near m (the
+          // maps are monotone, so the eigenvalue order is kept whatever the steering did); then s and
+          // trace X - m are the sum and the difference of the lower ones' sum and the upper
+          // ones' distances from 1, up to the squares (1.04).
+          if (fabs(dt) < 0.25) {
+            A = fmaxf((float)(0.5 * (1.04 * s + dt)), 1e-15f);
+            B = fmaxf((float)(0.5 * (1.04 * s - dt)), 1e-15f);
+            conv = true;
+          }
+          if (conv || s < 1e-12) { k_end = k; break; }
         }
         // not yet: go on from the exact trace
-        tXp = 64.0; sqp = true; pend = tX * (1.0 / 16.0);
+        tE = (float)(2.0 * (dt + dm) - dr);
+        sg = 0.0;
+        pend = -1.0;
       }
       if (!conv) return -(1000 + it * 1000 + k_end);
+      // ---- the last steps: plain ones in turn, as many as square those two sums away.  Nothing is measured any
+      // more, and with X = F or X - I = F up to sign, whichever the next map squares, a step is F^2 - I:
+      // 300 cycles at p = 15, 200 at p = 7.  (With 2e-12 for 2e-15 the aggregate's error doubles, to 2e-15.)
+      {
+        const bool sq = A > B;             // X^2 first: 2 A^2 and 4 B^2 after two steps
+        const float e = sq ? fmaxf(2.0f * A, 4.0f * B) : fmaxf(4.0f * A, 2.0f * B);
+        const int pairs = e < 4e-8f ? 1 : e < 2e-4f ? 2 : e < 1.4e-2f ? 3 : e < 0.12f ? 4 : 5;   // e^(2^pairs) < 2e-15
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = fma(0.5, x[r], (sq ? 0.5 : -0.5) * eye[r]);
+#pragma unroll 1
+        for (int k = 0; k < pairs; ++k) {
+          x = mm16_plus<NS>(x, x, less);
+          x = mm16_plus<NS>(x, x, less);
+        }
+        // behind 2X - X^2 it is I - X, behind X^2 X - I
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = sq ? -x[r] : x[r] + eye[r];
+        steps += 2 * pairs;
+      }
     } else {
       // m >= rank: Y spans all of span(G)
 #pragma unroll
@@ -689,26 +713,29 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     rhoj = qjj * dj * dj;                                // 1 - v_j
     // sqrt(rho) = rho * rsqrt(rho) and max(rho, delta)^(-1/2) = min(rsqrt(rho), delta^(-1/2)):
     // one reciprocal square root per residual, no division
-    double part, wnext;
+    double part, wnext, wsum;                            // wsum: trace of the next M
     if (expo == 0.5) {
-      rsj = rsq_nr<2>(rhoj > 1e-300 ? rhoj : 1e-300);
+      // (a pair that is none has rho = 0: nothing is selected)
+      rsj = rsq_nr<2>(fmax(rhoj, 1e-300));
       part = (q4 == 0 && livej) ? rhoj * rsj : 0.0;
-      wnext = rsj < rs_delta ? rsj : rs_delta;
+      wnext = fmin(rsj, rs_delta);
+      wsum = (q4 == 0 && livej) ? wnext : 0.0;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const double qii = fm.Zs[4 * r + q4];
-        const double dz2 = fma(-2.0, qz[r], qii + qjj);
-        const double rho = (dz2 > 0.0 ? dz2 : 0.0) * d2inv[r];
-        const bool lp = d2inv[r] > 0.0;
-        const double rs = rsq_nr<2>(rho > 1e-300 ? rho : 1e-300);
-        part += lp ? coef * (rho * rs) : 0.0;            // ordered pair (i, j)
-        cp[r] = lp ? -2.0 * coef * d2inv[r] * (rs < rs_delta ? rs : rs_delta) : 0.0;
+        const double rho = fmax(fma(-2.0, qz[r], qii + qjj), 0.0) * d2inv[r];
+        const double rs = rsq_nr<2>(fmax(rho, 1e-300));
+        const double wp = fmin(rs, rs_delta);
+        part = fma(coefr[r], rho * rs, part);              // ordered pair (i, j)
+        wsum = fma(coefr[r], wp, wsum);
+        cp[r] = cp1[r] * wp;
       }
     } else {
       // the general exponent: same places, powers instead of square roots (rolled: this code
       // runs once per solve, and five inlined copies of pow() are a thousand instructions)
       part = (q4 == 0 && livej) ? fa_term_pow(rhoj, expo) : 0.0;
       wnext = fa_weight_pow(rhoj, delta, expo);
+      wsum = (q4 == 0 && livej) ? wnext : 0.0;
 #pragma unroll 1
       for (int r = 0; r < 4; ++r) {
         const double qii = fm.Zs[4 * r + q4];
@@ -718,7 +745,9 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
         const double rho = (dz2 > 0.0 ? dz2 : 0.0) * di2;
         const bool lp = di2 > 0.0;
         part += lp ? coef * fa_term_pow(rho, expo) : 0.0;
-        const double cv = lp ? -2.0 * coef * di2 * fa_weight_pow(rho, delta, expo) : 0.0;
+        const double wp = lp ? coef * fa_weight_pow(rho, delta, expo) : 0.0;
+        wsum += wp;
+        const double cv = -2.0 * di2 * wp;
         if (r == 0) cp[0] = cv; else if (r == 1) cp[1] = cv; else if (r == 2) cp[2] = cv; else cp[3] = cv;
       }
     }
@@ -726,10 +755,13 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     const double obj = wave_sum(part);
     if (lane == 0 && it0 + it < FA_ITERS_MAX) info->objective[it0 + it] = obj;
     iters_done = it + 1;
-    const bool stop = it0 + it > 0 && fabs(prev_obj - obj) < tol;
+    const double was = prev_obj;
     prev_obj = obj;
-    if (stop) break;
+    if (tol > 0.0) {
+      if (it0 + it > 0 && fabs(was - obj) < tol) break;
+    }
     wj = livej ? wnext : 0.0;
+    hi = wave_sum(wsum);
   }
 
   // ---- epilogue: basis of range(P), A = B U_m, c = A (U_m^T R 1) / p ---------------------
@@ -802,8 +834,10 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
 
 // NS = ceil(p / 4): a product of the purification is NS dependent matrix instructions of 64 cycles
 // (p = 7, ten solves: 70.8 -> 60.7 us with two instead of four; p = 11, 87 -> 77 with three).
+// (Two wavefronts a SIMD, of which there is one: with at most 256 registers a lane the compiler keeps the
+// accumulators among them and copies none.)
 template <int NS>
-__global__ __launch_bounds__(256) void fa_irls16_kernel(const double* __restrict__ Kg,
+__global__ __launch_bounds__(256, 2) void fa_irls16_kernel(const double* __restrict__ Kg,
                                                         int p, int m, int iters, double lambda,
                                                         double tol, double delta, double expo,
                                                         double rank_tol,

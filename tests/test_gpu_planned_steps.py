@@ -45,6 +45,28 @@ def test_folded_growth_gives_the_jacobi_solvers_answer(p):
         _compare_with_jacobi(p, m, 0.3, 11 * p + m)
 
 
+@pytest.mark.parametrize("p,rank", [(16, 16), (16, 13), (16, 9), (15, 4), (12, 11), (9, 8), (8, 5), (7, 7), (5, 2),
+                                    (4, 4), (3, 2)])
+def test_steering_with_and_without_copies(p, rank):
+    """p <= 16: the steps run on 2X - I with the identity of the rank, which need not be p; the last ones
+    are counted from the measured distance.  Same bounds as test_every_remainder_of_the_last_tile."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("steering", p, rank)
+    K = _with_copies(p, rank, 7 * p + rank)
+    scale = np.sqrt(np.diag(K))
+    for m in sorted({1, (rank + 1) // 2, rank - 1}):
+        got = []
+        for solver in ("auto", "jacobi"):
+            agg = FlagAggregator(n_max=1 << 20, p_max=16, solver=solver)
+            agg.fa_irls(K, m, 0.5, 9, 0.0)
+            got.append(agg.fa_get_info())
+            agg.close()
+        a, j = got
+        assert a.status == 0 and j.status == 0 and a.rank == j.rank == rank and a.sweeps != j.sweeps, m
+        assert np.max(np.abs(a.objective - j.objective) / (1.0 + np.abs(j.objective))) <= 1e-8, m
+        assert np.linalg.norm(K @ (a.c - j.c) / scale) <= 1e-8 * np.linalg.norm(K @ j.c / scale), m
+
+
 def _compare_with_jacobi(p, m, lam, seed):
     """Both solvers start from the same K in fp64.  Each solve's projector is good to eps p / gap,
     and passes that on to the next solve's weights; the objective after every solve and the
