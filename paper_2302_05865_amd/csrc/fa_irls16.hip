@@ -253,7 +253,7 @@ struct Fmem {
   double Am[16 * LDF];   // A (p x m)
   __attribute__((aligned(16))) double Zs[16 * LDZ];   // [0..15]: diag(Z^T Z), Z = (I-P) R
   double s[16], dinv[16], r1[16], beta[16], rinv[16];
-  int piv[16];
+  int piv[16], rank;     // rank: 0 where there was no factorisation
 };
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -348,15 +348,20 @@ __device__ FA_CHOL_ATTR int pivoted_cholesky(const double* S, double* rows, int*
   v4d s;
 #pragma unroll
   for (int r = 0; r < 4; ++r) s[r] = S[(4 * r + q4) * LDF + c16];
-  // element (c, c) is entry c / 4 of the lane (c % 4, c)
+#pragma unroll
+  for (int r = 0; r < 4; ++r) rows[(4 * r + q4) * LDF + c16] = 0.0;
+  if (lane < 16) { piv[lane] = 0; rinv[lane] = 0.0; }
+  // element (c, c) is entry c / 4 of the lane (c % 4, c); open: column c has not been a pivot yet (what the
+  // update leaves in the row and column of one that has is rounding noise, and not looked at)
   const bool hasd = (c16 & 3) == q4;
+  bool open = true;
   const int rd = c16 >> 2;
   int rank = 0;
 #pragma unroll 1
   for (int k = 0; k < max_rank; ++k) {
     const double d = rd == 0 ? s[0] : rd == 1 ? s[1] : rd == 2 ? s[2] : s[3];
     const float df = (hasd && d > 0.0) ? (float)d : 0.0f;
-    unsigned key = hasd ? ((__float_as_uint(df) & ~15u) | (unsigned)(15 - c16)) : 0u;
+    unsigned key = hasd && open ? ((__float_as_uint(df) & ~15u) | (unsigned)(15 - c16)) : 0u;
     key = max(key, dpp_u32<0x128>(key));   // row_ror:8
     key = max(key, dpp_u32<0x124>(key));   // row_ror:4
     key = max(key, dpp_u32<0x122>(key));   // row_ror:2
@@ -372,26 +377,62 @@ __device__ FA_CHOL_ATTR int pivoted_cholesky(const double* S, double* rows, int*
     const double dp = lane_bcast(rowv, 16 * qp + pv);
     if (!(dp > tol)) break;
     const double rs = rsq_nr<2>(dp);
-    const double a = q4 == qp ? rowv * rs : 0.0;
-    if (q4 == qp) rows[k * LDF + c16] = a;
-    if (lane == 0) { piv[k] = pv; rinv[k] = rs; }
+    const double a = q4 == qp && open ? rowv * rs : 0.0;
+    if (q4 == qp) { rows[k * LDF + c16] = a; piv[k] = pv; rinv[k] = rs; }
     s = __builtin_amdgcn_mfma_f64_16x16x4f64(-a, a, s, 0, 0, 0);
-    // row and column pv are done with (what the update leaves there is rounding noise)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) s[r] = (c16 == pv || (q4 == qp && rp == r)) ? 0.0 : s[r];
+    open = open && c16 != pv;
     rank = k + 1;
-  }
-  wave_fence();
-  for (int k = rank; k < 16; ++k) {
-    if (lane < 16) rows[k * LDF + c16] = 0.0;
-    if (lane == 0) { piv[k] = 0; rinv[k] = 0.0; }
   }
   wave_fence();
   return rank;
 }
 
+// Wavefront 1, while wavefront 0 iterates (5000 cycles at rank 15): the right inverse B of R, R B = I, and the
+// row sums R 1, which only the epilogue needs.
+__device__ __forceinline__ void right_inverse(Fmem& fm, int rank, int lane) {
+  const int c16 = lane & 15, q4 = lane >> 4;
+  // Xi = inverse of the (upper triangular, in pivot order) block U = R~[:, piv]; lane c16
+  // solves U x = e_c16 by back substitution, column-oriented: once x_k is known it is taken
+  // out of all earlier equations at once (independent multiply-adds, no dependent chain)
+  {
+    double bcol[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bcol[i] = (i == c16) ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 15; k >= 0; --k) {
+      if (k < rank) {
+        const double xk = bcol[k] * fm.rinv[k];
+        const int pk = fm.piv[k];
+#pragma unroll
+        for (int i = 0; i < k; ++i) bcol[i] = fma(-fm.Rt[i * LDF + pk], xk, bcol[i]);
+        bcol[k] = xk;
+      } else {
+        bcol[k] = 0.0;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (lane < 16) fm.Xi[k * LDF + c16] = (c16 < rank) ? bcol[k] : 0.0;
+    wave_fence();
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) fm.Bm[(4 * r + q4) * LDF + c16] = 0.0;
+  wave_fence();
+  for (int k = q4; k < rank; k += 4) {
+    const int i = fm.piv[k];
+    fm.Bm[i * LDF + c16] = (c16 < rank) ? fm.Xi[k * LDF + c16] * fm.dinv[i] : 0.0;
+  }
+  if (lane < 16) {
+    double a4[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int jj = 0; jj < 16; ++jj) a4[jj & 3] += fm.Rr[lane * LDF + jj];
+    fm.r1[lane] = (a4[0] + a4[1]) + (a4[2] + a4[3]);   // R 1
+  }
+}
+
 // Returns 1 when the solve was completed here (including the error statuses), 0 when the
-// caller must fall back to the Jacobi path.
+// caller must fall back to the Jacobi path.  Every way out passes two workgroup barriers: behind
+// the factorisation, and before what wavefront 1 has made of it is used.
 template <int NS>
 __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, double lambda,
                      double tol, double delta, double expo, double rank_tol, double pair_tol,
@@ -433,7 +474,10 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     if (lane == 0) {
       info->status = st; info->p = p; info->m = m; info->rank = 0; info->iters_done = 0;
       info->sweeps = 0; info->eigengap = 0.0;
+      fm.rank = 0;
     }
+    __syncthreads();
+    __syncthreads();
     return 1;
   }
 
@@ -456,57 +500,19 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
 
   // ---- R from the pivoted Cholesky factorisation of K~; rank; right inverse --------------
   const int rank = pivoted_cholesky(fm.Kt, fm.Rt, fm.piv, fm.rinv, rank_tol, 16, lane);
-  // Xi = inverse of the (upper triangular, in pivot order) block U = R~[:, piv]; lane c16
-  // solves U x = e_c16 by back substitution, column-oriented: once x_k is known it is taken
-  // out of all earlier equations at once (independent multiply-adds, no dependent chain)
-  {
-    double bcol[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) bcol[i] = (i == c16) ? 1.0 : 0.0;
-#pragma unroll
-    for (int k = 15; k >= 0; --k) {
-      if (k < rank) {
-        const double xk = bcol[k] * fm.rinv[k];
-        const int pk = fm.piv[k];
-#pragma unroll
-        for (int i = 0; i < k; ++i) bcol[i] = fma(-fm.Rt[i * LDF + pk], xk, bcol[i]);
-        bcol[k] = xk;
-      } else {
-        bcol[k] = 0.0;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-      if (lane < 16) fm.Xi[k * LDF + c16] = (c16 < rank) ? bcol[k] : 0.0;
-    wave_fence();
-  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = 4 * r + q4;
-    fm.Bm[i * LDF + c16] = 0.0;
     fm.Rr[i * LDF + c16] = (i < rank) ? fm.Rt[i * LDF + c16] * sqrt(sj) : 0.0;
-    fm.Um[i * LDF + c16] = 0.0;
   }
-  wave_fence();
-  for (int k = lane >> 4; k < rank; k += 4) {
-    const int i = fm.piv[k];
-    fm.Bm[i * LDF + c16] = (c16 < rank) ? fm.Xi[k * LDF + c16] * fm.dinv[i] : 0.0;
-  }
-  wave_fence();
+  if (lane == 0) fm.rank = rank;
+  __syncthreads();                                     // wavefront 1: right_inverse
   v4d ra, rb;   // R as A operand (entry (c16, 4s+q4)) and as B operand (entry (4s+q4, c16))
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     ra[s] = fm.Rr[c16 * LDF + 4 * s + q4];
     rb[s] = fm.Rr[(4 * s + q4) * LDF + c16];
   }
-  if (lane < 16) {
-    double a4[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) a4[jj & 3] += fm.Rr[lane * LDF + jj];
-    fm.r1[lane] = (a4[0] + a4[1]) + (a4[2] + a4[3]);   // R 1
-  }
-  wave_fence();
-
   // ---- IRLS ------------------------------------------------------------------------------
   const int mm = m < rank ? m : rank;
   bool isdiag[4];
@@ -669,7 +675,10 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
         sg = 0.0;
         pend = -1.0;
       }
-      if (!conv) return -(1000 + it * 1000 + k_end);
+      if (!conv) {
+        __syncthreads();
+        return -(1000 + it * 1000 + k_end);
+      }
       // ---- the last steps: plain ones in turn, as many as square those two sums away.  Nothing is measured any
       // more, and with X = F or X - I = F up to sign, whichever the next map squares, a step is F^2 - I:
       // 300 cycles at p = 15, 200 at p = 7.  (With 2e-12 for 2e-15 the aggregate's error doubles, to 2e-15.)
@@ -771,7 +780,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     fm.Ps[i * LDF + c16] = x[r];
     mlast[i * 16 + c16] = mk[r];
   }
-  wave_fence();
+  __syncthreads();                                     // B and R 1 are there
   // P = U U^T with orthonormal U: the rows produced by the pivoted Cholesky of a projector
   const int nb = pivoted_cholesky(fm.Ps, fm.Um, fm.piv, fm.rinv, 1e-6, mm, lane);
   if (nb != mm) return -2;
@@ -854,6 +863,11 @@ __global__ __launch_bounds__(256, 2) void fa_irls16_kernel(const double* __restr
       const int ok = fastp::solve<NS>(Kg, p, m, iters, lambda, tol, delta, expo, rank_tol, pair_tol, cg,
                                   info, mlast, fm, rs);
       if (tid == 0) fast_done = ok;
+    } else {
+      __syncthreads();
+      const int rank = __builtin_amdgcn_readfirstlane(fm.rank);
+      if (tid < 128 && rank > 0) fastp::right_inverse(fm, rank, tid & 63);
+      __syncthreads();
     }
     __syncthreads();
     if (fast_done > 0) return;
