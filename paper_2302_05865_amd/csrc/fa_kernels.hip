@@ -109,8 +109,10 @@ __device__ __forceinline__ uint4 load16_guarded(const unsigned char* base, int64
   return v;
 }
 
-// how G lies in memory and goes to LDS: worker-major; interleaved as it is; interleaved, scattered
-enum { FA_MEM_WORKER, FA_MEM_ROWS, FA_MEM_SCATTER };
+// how G lies in memory and goes to LDS: worker-major; interleaved as it is; interleaved, scattered;
+// interleaved as it is with at most four, at most eight columns in the last block of sixteen
+enum { FA_MEM_WORKER, FA_MEM_ROWS, FA_MEM_SCATTER, FA_MEM_ROWS_LAST4, FA_MEM_ROWS_LAST8 };
+constexpr bool fa_mem_rows(int st) { return st == FA_MEM_ROWS || st >= FA_MEM_ROWS_LAST4; }
 
 // a pass over some rows of some gradients, whose sums are added to K: which gradients its columns are,
 // where they are not simply the first p
@@ -154,6 +156,13 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// the value of the lane n on within its row of sixteen (CTRL 0x120 + n)
+template <int CTRL>
+__device__ __forceinline__ double row_ror(double x) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, false),
+                          __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, false));
+}
+
 template <typename E>
 __device__ __forceinline__ void unpack4(const unsigned char* src, double* x) {
   if constexpr (E::SIZE == 4) {
@@ -180,6 +189,15 @@ __device__ __forceinline__ void unpack4(const unsigned char* src, double* x) {
 // With one tile and many rows the scatter is the quicker one (FA_MEM_SCATTER; the same order of sums, the
 // same bits): as they are / scattered, p = 4 bf16 12M rows 138 / 122 us, 4M 56 / 51, 1M 22 / 22, 300 thousand
 // 13 / 14; p = 16 fp32 12M 136 / 129, 4M 53 / 52, 1M 22 / 23.
+//
+// With few columns in the last block most of what is multiplied for it is thrown away.  v_mfma_f64_4x4x4_4b
+// multiplies four pairs of blocks of four columns at the rate of the 16 x 16 instruction (18 cycles against 64),
+// block b of an operand being columns 4 b .. 4 b + 3: sixteen columns times four, in all four blocks, are one of
+// them (FA_MEM_ROWS_LAST4), times eight, in two blocks each and in turn, two (FA_MEM_ROWS_LAST8; with twelve columns
+// nothing is left of the gain).  The order of an entry's sums, and so its bits, are those of the other instruction.
+// Multi-Krum calls over 3 M rows (this pass, the aggregate's and 12 us between them), us: fp32 p = 20 173 -> 149,
+// 24 167 -> 153, 36 292 -> 251, 40 320 -> 301, 52 512 -> 457, 56 524 -> 472; bf16 152 -> 124, 153 -> 151, 238 -> 190,
+// 305 -> 265, 348 -> 292, 364 -> 332.
 // LDS bytes of a tile of r interleaved rows, whatever their pitch (at most 16 t elements):
 constexpr int fa_rows_tile_bytes(int t, int es, int r) {
   return r / 4 * ((64 * t * es + 255) / 256 * 256 + 16 * es);
@@ -194,7 +212,9 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
                                                      fa_gram_cols cols) {
   // as the stand-by of the bf16 matrix-core pass: nothing to do unless that one overflowed
   if (gate != nullptr && *gate == 0) return;
-  constexpr bool ROWS = ST == FA_MEM_ROWS;
+  constexpr bool ROWS = fa_mem_rows(ST);
+  constexpr int NB = ST == FA_MEM_ROWS_LAST4 ? 4 : ST == FA_MEM_ROWS_LAST8 ? 8 : 16;   // columns of the last block
+  constexpr int NQ = NB / 4;
   constexpr int EPL = E::EPL;
   constexpr int LPC = 64 / CPL;            // lanes per column in one load instruction
   constexpr int R = LPC * EPL;             // rows per tile
@@ -217,6 +237,10 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   v4f64 acc[NTP];
 #pragma unroll
   for (int i = 0; i < NTP; ++i) acc[i] = v4f64{0.0, 0.0, 0.0, 0.0};
+
+  double accl[T][2];                       // the last block's pairs, where it is narrow
+#pragma unroll
+  for (int i = 0; i < T; ++i) accl[i][0] = accl[i][1] = 0.0;
 
   // zero the whole tile once: columns >= p stay zero for the life of the kernel
   // (interleaved storage: the span of a tile overwrites what is read of it)
@@ -332,7 +356,8 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
       ROWS ? lds + kq * gs + c16 * E::SIZE : lds + c16 * CS + 4 * kq * E::SIZE;
   auto operand = [&](int t, int tt, double* x) {
     if constexpr (ROWS) {
-      const unsigned char* at = src + t * (4 * gs) + tt * 16 * E::SIZE;
+      const unsigned char* at =
+          src + t * (4 * gs) + (tt * 16 + (NB < 16 && tt == T - 1 ? (c16 & (NB - 1)) - c16 : 0)) * E::SIZE;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if constexpr (E::SIZE == 4)
@@ -366,12 +391,24 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
       for (int tt = 0; tt < T; ++tt) operand(tn, tt, xn[tt]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
+        if constexpr (NB < 16) {
+          const double y = xc[T - 1][j];
+          double z = 0.0;
+          if constexpr (NQ == 2) z = row_ror<0x124>(y);
+#pragma unroll
+          for (int a = 0; a < T; ++a) {
+            accl[a][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(xc[a][j], y, accl[a][0], 0, 0, 0);
+            if constexpr (NQ == 2)
+              accl[a][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(xc[a][j], z, accl[a][1], 0, 0, 0);
+          }
+        }
         int tp = 0;
 #pragma unroll
         for (int a = 0; a < T; ++a)
 #pragma unroll
           for (int b = LAST ? T - 1 : a; b < T; ++b) {
-            acc[tp] = __builtin_amdgcn_mfma_f64_16x16x4f64(xc[a][j], xc[b][j], acc[tp], 0, 0, 0);
+            if (NB == 16 || b < T - 1)
+              acc[tp] = __builtin_amdgcn_mfma_f64_16x16x4f64(xc[a][j], xc[b][j], acc[tp], 0, 0, 0);
             ++tp;
           }
       }
@@ -390,8 +427,26 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   double* dst = partials + (int64_t)blockIdx.x * NTP * 256;
 #pragma unroll
   for (int tp = 0; tp < NTP; ++tp) {
+    // the tile of a block a and the last one; (a, T - 1) is where block a's row of tiles ends
+    int narrow = -1;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) red[wave * 256 + r * 64 + lane] = acc[tp][r];
+    for (int a = 0, end = -1; a < T; ++a) {
+      end += T - a;
+      if (NB < 16 && tp == end) narrow = a;
+    }
+    if (narrow >= 0) {
+      // entry i of lane (i, 4 b + j) belongs to column 4 b + i of the left operand and to the right one's of
+      // this lane; the places of columns that the block does not have stay as they are, nobody reads them
+#pragma unroll
+      for (int q = 0; q < NQ && q < 2; ++q) {
+        const int from = q == 0 ? c16 : __builtin_amdgcn_mov_dpp(c16, 0x124, 0xf, 0xf, false);
+        const int left = (c16 & ~3) + kq, row = narrow == T - 1 ? left & (NB - 1) : left;
+        red[wave * 256 + (row >> 2) * 64 + (row & 3) * 16 + (from & (NB - 1))] = accl[narrow < 0 ? 0 : narrow][q];
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave * 256 + r * 64 + lane] = acc[tp][r];
+    }
     __syncthreads();
     for (int e = threadIdx.x; e < 256; e += 64 * WAVES) {
       double tot = 0.0;
@@ -1491,7 +1546,7 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
   constexpr int R = (64 / CPL) * E::EPL;
   constexpr int CS = R * E::SIZE + 16;
   constexpr size_t tile_bytes =
-      ST == FA_MEM_ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : (size_t)T * 16 * CS;
+      fa_mem_rows(ST) ? fa_rows_tile_bytes(T, E::SIZE, R) : (size_t)T * 16 * CS;
   static_assert(WAVES * tile_bytes <= 160 * 1024, "LDS tiles of one workgroup must fit a CU");
   // more than half of the CU's 160 KiB, so that no second workgroup fits beside this one
   const size_t lds_bytes = WAVES * tile_bytes > 84 * 1024 ? WAVES * tile_bytes : 84 * 1024;
@@ -1530,6 +1585,16 @@ static hipError_t launch_gram_e(const void* G, int64_t ldg, int p, int64_t n, in
           return launch_gram_t<t, cpl, E, w, FA_MEM_SCATTER>(G, ldg, p, n, max_blocks,          \
                                                             partials, nparts, st, tm, gate,    \
                                                             cols);                             \
+      if constexpr (ROWS && t > 1) {                                                           \
+        if (p <= 16 * t - 12)                                                                  \
+          return launch_gram_t<t, cpl, E, w, FA_MEM_ROWS_LAST4>(G, ldg, p, n, max_blocks,       \
+                                                               partials, nparts, st, tm, gate, \
+                                                               cols);                          \
+        if (p <= 16 * t - 8)                                                                   \
+          return launch_gram_t<t, cpl, E, w, FA_MEM_ROWS_LAST8>(G, ldg, p, n, max_blocks,       \
+                                                               partials, nparts, st, tm, gate, \
+                                                               cols);                          \
+      }                                                                                        \
       return launch_gram_t<t, cpl, E, w, ROWS ? FA_MEM_ROWS : FA_MEM_WORKER>(                    \
           G, ldg, p, n, max_blocks, partials, nparts, st, tm, gate, cols);
     FA_GRAM_TILINGS(FA_X)
@@ -1548,7 +1613,9 @@ static hipError_t prepare_gram_e() {
 #define FA_X(t, cpl, w)                                                                          \
   FA_SET(t, cpl, E, w, ROWS ? FA_MEM_ROWS : FA_MEM_WORKER, false)                                  \
   if constexpr (!ROWS && t > 1) { FA_SET(t, cpl, E, w, FA_MEM_WORKER, true) }                     \
-  if constexpr (ROWS && t == 1) { FA_SET(t, cpl, E, w, FA_MEM_SCATTER, false) }
+  if constexpr (ROWS && t == 1) { FA_SET(t, cpl, E, w, FA_MEM_SCATTER, false) }                   \
+  if constexpr (ROWS && t > 1) { FA_SET(t, cpl, E, w, FA_MEM_ROWS_LAST4, false) }                 \
+  if constexpr (ROWS && t > 1) { FA_SET(t, cpl, E, w, FA_MEM_ROWS_LAST8, false) }
   FA_GRAM_TILINGS(FA_X)
 #undef FA_X
 #undef FA_SET

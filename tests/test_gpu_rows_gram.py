@@ -80,3 +80,27 @@ def test_interleaved_gram_of_many_rows(p, pitch, dtype):
         assert np.all(np.isfinite(K)) and np.array_equal(K, W), n
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("p,pitch", [(17, 18), (19, 31), (20, 20), (20, 32), (21, 21), (24, 24), (24, 31), (25, 25),
+                                     (33, 33), (36, 36), (37, 48), (40, 40), (41, 41), (50, 50), (52, 64), (53, 53),
+                                     (56, 56), (57, 57)])
+def test_interleaved_gram_with_a_narrow_last_block(p, pitch, dtype):
+    """At most four, at most eight and more columns in the last block of sixteen, full and not, a tile's edge and
+    a round of all wavefronts.  fp64 products of fp32 values are exact; the sums differ from numpy's by at
+    most n eps of the sums of magnitudes, 2e-12 here."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("interleaved gram, narrow last block", p, pitch, dtype)
+    for n in (1, 65, 2049, 262_145 + 64):
+        x = si.random_dense(p, n, seed=p + n)
+        if dtype == "bf16":
+            x = si.f32_to_bf16_bits(x)
+        by_worker = to_device(x)
+        rows = torch.full((n, pitch), float("nan"), dtype=by_worker.dtype, device="cuda")
+        rows[:, :p] = by_worker.t()
+        a = FlagAggregator(n_max=n, p_max=p, dtype=dtype, layout="row_major")
+        K = a.fa_gram(rows[:, :p])
+        a.close()
+        y = by_worker.double().cpu().numpy()
+        assert np.all(np.abs(K - y @ y.T) <= 2e-12 * (np.abs(y) @ np.abs(y).T)), n
