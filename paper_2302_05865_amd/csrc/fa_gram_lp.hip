@@ -100,7 +100,8 @@ __device__ __forceinline__ void split3(uint32_t u0, uint32_t u1, uint32_t* h, ui
 template <int T, int CPL, int ES, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void fa_gram_lp_kernel(
     const unsigned char* __restrict__ G, int64_t ldg, int p, int64_t n, int64_t ntiles,
-    double* __restrict__ partials) {
+    double* __restrict__ partials, int* __restrict__ clear) {
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
   constexpr int EPL = 16 / ES;               // elements per 16-byte lane load
   constexpr int LPC = 64 / CPL;              // lanes per column in one load instruction
   constexpr int R = LPC * EPL;               // rows per tile
@@ -264,7 +265,7 @@ bool fa_gram_lp_applies(int p, int dtype) {
 }
 
 hipError_t fa_launch_gram_lp_partials(const void* G, int64_t ldg, int p, int64_t n, int dtype,
-                                      int max_blocks, double* partials, int* nparts,
+                                      int max_blocks, double* partials, int* nparts, int* clear,
                                       hipStream_t st, const fa_ktime* tm) {
   const int Tn = (p + 15) / 16, es = dtype == FA_F32 ? 4 : 2;
 #define FA_X(t, cpl, esz, w)                                                                    \
@@ -277,7 +278,7 @@ hipError_t fa_launch_gram_lp_partials(const void* G, int64_t ldg, int p, int64_t
     *nparts = (int)wgs;                                                                         \
     FA_LAUNCH(tm, (fa_gram_lp_kernel<t, cpl, esz, w>), dim3((unsigned)wgs), dim3(64 * w),       \
               (lp_lds_bytes<t, cpl, esz, w>()), st, (const unsigned char*)G, ldg, p, n, ntiles,  \
-              partials);                                                                        \
+              partials, clear);                                                                     \
     return hipGetLastError();                                                                   \
   }
   FA_GRAM_LP_TILINGS(FA_X)

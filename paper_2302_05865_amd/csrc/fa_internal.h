@@ -38,7 +38,7 @@ typedef struct { hipEvent_t start, stop; } fa_ktime;
 hipError_t fa_launch_gram_partials(const void* G, int64_t ldg, int p, int64_t n, int dtype,
                                    int layout, int gram_mode, int max_blocks, double* partials,
                                    int* nparts, hipStream_t st, const fa_ktime* tm,
-                                   const int* gate = nullptr);
+                                   const int* gate = nullptr, int* clear = nullptr);
 // whether that call hands the pass to the bf16 matrix-core kernel
 bool fa_gram_takes_matrix_core(int p, int64_t n, int dtype, int layout, int gram_mode);
 // K1 + K2 into Kd, with the fp64 pass standing by behind a matrix-core pass in case its fp32
@@ -51,7 +51,7 @@ hipError_t fa_launch_gram(const void* G, int64_t ldg, int p, int64_t n, int dtyp
 // column scales, where fa_gram_lp_applies (bf16 storage, or fp32 storage at p > 16).
 bool fa_gram_lp_applies(int p, int dtype);
 hipError_t fa_launch_gram_lp_partials(const void* G, int64_t ldg, int p, int64_t n, int dtype,
-                                      int max_blocks, double* partials, int* nparts,
+                                      int max_blocks, double* partials, int* nparts, int* clear,
                                       hipStream_t st, const fa_ktime* tm);
 hipError_t fa_gram_lp_prepare(void);
 // K (p x p) += over n rows, the products of every gradient in the set `then` (bit j: gradient j)
@@ -74,7 +74,7 @@ hipError_t fa_launch_zero(double* dst, int count, hipStream_t st);
 // diag(u) K diag(u), the Gram matrix of the columns scaled by u.
 hipError_t fa_launch_gram_reduce(const double* partials, int nparts, int p, double* Kd,
                                  const double* colscale, hipStream_t st, const fa_ktime* tm,
-                                 const int* gate = nullptr);
+                                 const int* gate = nullptr, int* nonfinite = nullptr);
 
 // K3: p x p solver.  Kd p*p doubles; cd p doubles out; info_d device fa_info; gws global
 // workspace of FA_GWS_DOUBLES doubles.  solver: 0 = default (matrix-core purification, with

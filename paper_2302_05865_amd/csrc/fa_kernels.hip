@@ -772,7 +772,8 @@ __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __re
                                                               const double* __restrict__ colscale,
                                                               const int* __restrict__ gate,
                                                               int last, int ldk,
-                                                              fa_gram_cols cols) {
+                                                              fa_gram_cols cols,
+                                                              int* __restrict__ nonfinite) {
   if (gate != nullptr && *gate == 0) return;   // stand-by of a pass that did not need it
   const int NTP = TM > 0 ? T * TM : last ? T : T * (T + 1) / 2;
   const int ei = threadIdx.x & 63, g = threadIdx.x >> 6;   // entry, strand 0..15
@@ -822,6 +823,7 @@ __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __re
         return;
       }
       const double v = colscale ? tot * (colscale[gi] * colscale[gj]) : tot;
+      if (nonfinite != nullptr && !(fabs(v) <= 1.79e308)) *nonfinite = 1;   // (the pass before has cleared it)
       K[gi * p + gj] = v;
       K[gj * p + gi] = v;
     }
@@ -1631,9 +1633,9 @@ bool fa_gram_takes_matrix_core(int p, int64_t n, int dtype, int layout, int gram
 hipError_t fa_launch_gram_partials(const void* G, int64_t ldg, int p, int64_t n, int dtype,
                                    int layout, int gram_mode, int max_blocks, double* partials,
                                    int* nparts, hipStream_t st, const fa_ktime* tm,
-                                   const int* gate) {
+                                   const int* gate, int* clear) {
   if (fa_gram_takes_matrix_core(p, n, dtype, layout, gram_mode))
-    return fa_launch_gram_lp_partials(G, ldg, p, n, dtype, max_blocks, partials, nparts, st, tm);
+    return fa_launch_gram_lp_partials(G, ldg, p, n, dtype, max_blocks, partials, nparts, clear, st, tm);
   const bool rows = layout == FA_ROW_MAJOR;
   if (dtype == FA_F32)
     return rows ? launch_gram_e<ElemF32, true>(G, ldg, p, n, max_blocks, partials, nparts, st, tm, gate)
@@ -1644,11 +1646,11 @@ hipError_t fa_launch_gram_partials(const void* G, int64_t ldg, int p, int64_t n,
 
 hipError_t fa_launch_gram_reduce(const double* partials, int nparts, int p, double* Kd,
                                  const double* colscale, hipStream_t st, const fa_ktime* tm,
-                                 const int* gate) {
+                                 const int* gate, int* nonfinite) {
   const int T = (p + 15) / 16;
   const int NTP = T * (T + 1) / 2;
   FA_LAUNCH(tm, fa_gram_reduce_kernel, dim3(NTP * 4), dim3(1024), 0, st, partials, nparts, T, p,
-            Kd, 0, 0, colscale, gate, 0, p, fa_gram_cols{});
+            Kd, 0, 0, colscale, gate, 0, p, fa_gram_cols{}, nonfinite);
   return hipGetLastError();
 }
 
@@ -1673,37 +1675,26 @@ hipError_t fa_launch_gram_add(const void* G, int64_t ldg, int p, int64_t n, int 
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fa_gram_reduce_kernel, dim3((last ? T : T * (T + 1) / 2) * 4), dim3(1024), 0,
                      st, (const double*)partials, nparts, T, ncols, Kd, 0, 0,
-                     (const double*)nullptr, (const int*)nullptr, last ? 1 : 0, p, cols);
+                     (const double*)nullptr, (const int*)nullptr, last ? 1 : 0, p, cols, (int*)nullptr);
   return hipGetLastError();
-}
-
-// *flag = 1 if any of the count doubles at K is NaN or infinite, else 0
-__global__ __launch_bounds__(256) void fa_nonfinite_flag_kernel(const double* __restrict__ K,
-                                                                int count, int* __restrict__ flag) {
-  bool bad = false;
-  for (int k = threadIdx.x; k < count; k += 256) bad = bad || !(fabs(K[k]) <= 1.79e308);
-  const int any = __syncthreads_or(bad ? 1 : 0);
-  if (threadIdx.x == 0) *flag = any ? 1 : 0;
 }
 
 // K1 + K2: K = G^T G into Kd.  Where the pass runs on the bf16 matrix core, whose 32-row sums
 // are fp32 and overflow for values beyond ~1e18, the fp64 pass stands by behind it: it is
 // always enqueued and returns at once unless K came out non-finite (flag_d: one int of device
-// scratch), so that large finite values - a Byzantine worker may send anything - cost a second
+// scratch, which the first pass clears and its reduction sets; as a kernel of its own that read K 3.4 of 546 us at
+// p = 60, 1.2 M rows), so that large finite values - a Byzantine worker may send anything - cost a second
 // pass instead of the result.  tm_gram / tm_reduce time the first pass and its reduction.
 hipError_t fa_launch_gram(const void* G, int64_t ldg, int p, int64_t n, int dtype, int layout,
                           int gram_mode, int max_blocks, double* partials, double* Kd,
                           int* flag_d, int* nparts, hipStream_t st, const fa_ktime* tm_gram,
                           const fa_ktime* tm_reduce) {
   hipError_t e = fa_launch_gram_partials(G, ldg, p, n, dtype, layout, gram_mode, max_blocks,
-                                         partials, nparts, st, tm_gram, nullptr);
+                                         partials, nparts, st, tm_gram, nullptr, flag_d);
   if (e != hipSuccess) return e;
-  e = fa_launch_gram_reduce(partials, *nparts, p, Kd, nullptr, st, tm_reduce, nullptr);
-  if (e != hipSuccess || !fa_gram_takes_matrix_core(p, n, dtype, layout, gram_mode)) return e;
-  hipLaunchKernelGGL(fa_nonfinite_flag_kernel, dim3(1), dim3(256), 0, st, (const double*)Kd, p * p,
-                     flag_d);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const bool matrix_core = fa_gram_takes_matrix_core(p, n, dtype, layout, gram_mode);
+  e = fa_launch_gram_reduce(partials, *nparts, p, Kd, nullptr, st, tm_reduce, nullptr, matrix_core ? flag_d : nullptr);
+  if (e != hipSuccess || !matrix_core) return e;
   int np2 = 0;
   e = fa_launch_gram_partials(G, ldg, p, n, dtype, layout, FA_GRAM_FP64, max_blocks, partials, &np2,
                               st, nullptr, flag_d);
@@ -1715,7 +1706,7 @@ hipError_t fa_launch_proj_reduce(const double* partials, int nparts, int p, int 
                                  hipStream_t st, const fa_ktime* tm) {
   const int T = (p + 15) / 16, TM = (m + 15) / 16;
   FA_LAUNCH(tm, fa_gram_reduce_kernel, dim3(T * TM * 4), dim3(1024), 0, st, partials, nparts, T,
-            p, Td, TM, m, (const double*)nullptr, (const int*)nullptr, 0, p, fa_gram_cols{});
+            p, Td, TM, m, (const double*)nullptr, (const int*)nullptr, 0, p, fa_gram_cols{}, (int*)nullptr);
   return hipGetLastError();
 }
 
@@ -1755,7 +1746,7 @@ hipError_t fa_launch_cross(const float* Y, int64_t ldy, int m, const void* G, in
   const int ncols = 16 * TMr + p;
   hipLaunchKernelGGL(fa_gram_reduce_kernel, dim3(TMr * TC * 4), dim3(1024), 0, st,
                      (const double*)partials, (int)stripes, TMr, m, Wd, TC, ncols,
-                     (const double*)nullptr, (const int*)nullptr, 0, m, fa_gram_cols{});
+                     (const double*)nullptr, (const int*)nullptr, 0, m, fa_gram_cols{}, (int*)nullptr);
   return hipGetLastError();
 }
 
