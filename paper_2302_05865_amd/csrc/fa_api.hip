@@ -128,7 +128,7 @@ extern "C" fa_status fa_create(const fa_config* cfg, fa_ctx** out_ctx) {
     if (hipEventCreate(&c->tm_r[i].start) != hipSuccess ||
         hipEventCreate(&c->tm_r[i].stop) != hipSuccess) { fa_destroy(c); return FA_ERR_DEVICE; }
   // per-function launch attributes (large dynamic LDS) on this context's device
-  if (fa_kernels_prepare() != hipSuccess || fa_irls64_prepare() != hipSuccess ||
+  if (fa_kernels_prepare(cfg->dtype, cfg->layout) != hipSuccess || fa_irls64_prepare() != hipSuccess ||
       fa_gram_lp_prepare() != hipSuccess) {
     fa_destroy(c);
     return FA_ERR_DEVICE;
@@ -266,7 +266,8 @@ static fa_status static_setup(int dev, StaticDev* out) {
     int cus = 0;
     if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        fa_kernels_prepare() != hipSuccess || fa_irls64_prepare() != hipSuccess ||
+        fa_kernels_prepare(FA_F32, FA_WORKER_MAJOR) != hipSuccess ||
+        fa_kernels_prepare(FA_BF16, FA_WORKER_MAJOR) != hipSuccess || fa_irls64_prepare() != hipSuccess ||
         fa_gram_lp_prepare() != hipSuccess) {
       st = FA_ERR_DEVICE;
     } else {

@@ -1927,34 +1927,32 @@ hipError_t fa_launch_gap(const double* mlast, int N, fa_info* info_d, hipStream_
   return hipGetLastError();
 }
 
-hipError_t fa_kernels_prepare(void) {
-  // the single-workgroup Jacobi solver's large dynamic LDS (p = 64 needs ~140 KiB)
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_irls_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  // the streaming kernels that claim a whole compute unit's LDS
-  if (e == hipSuccess) e = prepare_gram_e<ElemF32, false>();
-  if (e == hipSuccess) e = prepare_gram_e<ElemF32, true>();
-  if (e == hipSuccess) e = prepare_gram_e<ElemBF16, false>();
-  if (e == hipSuccess) e = prepare_gram_e<ElemBF16, true>();
-  if (e == hipSuccess) e = prepare_proj_e<ElemF32>();
-  if (e == hipSuccess) e = prepare_proj_e<ElemBF16>();
+template <typename E>
+static hipError_t prepare_e(int layout) {
+  if (layout != FA_ROW_MAJOR) {
+    const hipError_t e = prepare_gram_e<E, false>();
+    return e == hipSuccess ? prepare_proj_e<E>() : e;      // (the re-streaming schedule is worker-major only)
+  }
+  hipError_t e = prepare_gram_e<E, true>();
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_rows_kernel<ElemF32, 1>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_rows_kernel<E, 1>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)fa_rows_lds_bytes(FA_P_MAX, 4));
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_rows_kernel<ElemBF16, 1>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_rows_kernel<E, FA_ROWS_MULTI>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)fa_rows_lds_bytes(FA_P_MAX, 4));
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(fa_combine_rows_kernel<ElemF32, FA_ROWS_MULTI>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_rows_lds_bytes(FA_P_MAX, 4));
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(fa_combine_rows_kernel<ElemBF16, FA_ROWS_MULTI>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_rows_lds_bytes(FA_P_MAX, 4));
   return e;
+}
+
+hipError_t fa_kernels_prepare(int dtype, int layout) {
+  // the single-workgroup Jacobi solver's large dynamic LDS (p = 64 needs ~140 KiB)
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_irls_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e != hipSuccess) return e;
+  // the streaming kernels that claim a whole compute unit's LDS, of this storage only: an attribute takes a few
+  // microseconds of every fa_create
+  return dtype == FA_F32 ? prepare_e<ElemF32>(layout) : prepare_e<ElemBF16>(layout);
 }
 
 hipError_t fa_launch_combine(const void* G, int64_t ldg, int p, int64_t n, int dtype, int layout,
