@@ -202,7 +202,8 @@ struct Small {
   int gf[64], gc[64];
   double ginv[64];
   Step step[2];                    // of purification step k at [k & 1]
-  float hist[MAX_PURIFY];          // step k of this solve: a of a growth, -1 - b of a shrinking map
+  float hist[(MAX_PURIFY + 63) / 64 * 64];   // step k of this solve: a of a growth, -1 - b of a shrinking map
+                                             // (read 64 at a time, one a lane)
   int guessed;                     // this solve's first steps were planned
 };
 
@@ -587,6 +588,9 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       float hv = 0.0f;
       for (bool first = true; bk > down_to; first = false) {
         --bk;
+        // (every lane's read is inside, whichever step this is)
+        static_assert(sizeof(sm.hist) % (64 * sizeof(float)) == 0 && sizeof(sm.hist) / sizeof(float) >= MAX_PURIFY,
+                      "a lane would read past the end");
         if (first || (bk & 63) == 63) hv = sm.hist[(bk & ~63) + lane];
         const float h = lane_of(hv, bk & 63);
         const bool grow = h > 0.0f;
