@@ -76,6 +76,17 @@ hipError_t fa_launch_gram_reduce(const double* partials, int nparts, int p, doub
                                  const double* colscale, hipStream_t st, const fa_ktime* tm,
                                  const int* gate = nullptr, int* nonfinite = nullptr);
 
+// The trace of the weighted-PCA matrix M, which scales X_0, is the sum of the weights where R^T R is the Gram
+// matrix: a gradient adds its weight times |r_j|^2 / s_j, a pair its weight times |r_i - r_j|^2 / D_ij^2.  A
+// factorisation with a pivot for every gradient leaves |R^T R - K| <= c p eps sqrt(s_i s_j), so those ratios are within
+// 2 c p eps / f of 1 for pairs with D_ij^2 > f (s_i + s_j): 3e-8 at p = 64 with f = FA_CLOSE_PAIR, less than the 1e-7 that
+// X_0 is scaled down by.  One that stops short leaves out what K's entries are off by: nothing where gradients
+// depend on each other exactly, but where near copies meet the 1e-10 of the bf16 matrix core the ratio is anything up to
+// hundreds; there the solvers look at it (FA_TRACE_OFF).  With a closer pair or a ratio that is off they measure the
+// trace in every solve.
+#define FA_CLOSE_PAIR 1e-6
+#define FA_TRACE_OFF 3e-8
+
 // K3: p x p solver.  Kd p*p doubles; cd p doubles out; info_d device fa_info; gws global
 // workspace of FA_GWS_DOUBLES doubles.  solver: 0 = default (matrix-core purification, with
 // the Jacobi solvers as fallback), 1 = p <= 16 Jacobi path, 2 = any-p Jacobi kernel.

@@ -364,7 +364,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     }
     __syncthreads();
   }
-  bool bad = false, live = false;
+  bool bad = false, live = false, close = false;     // close: a pair nearer than FA_CLOSE_PAIR
 #pragma unroll
   for (int q = 0; q < EPT; ++q) {
     const int e = tid + q * NTHREADS;
@@ -378,8 +378,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       const double si = sm.s[i], sj = sm.s[j];
       live = live || (i == j && si > 0.0);
       B0[eidx<T>(i, j)] = (i == j) ? (si > 0.0 ? 1.0 : 0.0) : kv * sm.dinv[i] * sm.dinv[j];   // K~
-      double d2 = si + sj - 2.0 * kv;
-      bool livep = in && i != j && d2 > pair_tol * (si + sj);
+      double d2 = si + sj - 2.0 * kv, both = si + sj;
+      bool livep = in && i != j && d2 > pair_tol * both;
       if constexpr (GRP) {
         // D^2 between two blocks: column l of one against column l of the other; only blocks
         // of equal width have one, and it sits at the column pairs at the same place in them
@@ -387,22 +387,24 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         if (in && i != j) {
           const int fi = sm.gf[i], fj = sm.gf[j], ki = sm.gc[i];
           if (fi != fj && ki == sm.gc[j] && i - fi == j - fj) {
-            double ssum = 0.0;
+            both = 0.0;
             d2 = 0.0;
             for (int l = 0; l < ki; ++l) {
               const double sa = sm.s[fi + l], sb = sm.s[fj + l];
               d2 += sa + sb - 2.0 * Kg[(fi + l) * p + fj + l];
-              ssum += sa + sb;
+              both += sa + sb;
             }
-            livep = d2 > pair_tol * ssum;
+            livep = d2 > pair_tol * both;
           }
         }
       }
       D2I[eidx<T>(i, j)] = livep ? 1.0 / d2 : 0.0;
+      close = close || (livep && !(d2 > FA_CLOSE_PAIR * both));
     }
   }
   const int nbad = __syncthreads_or(bad ? 1 : 0);
   const int nlive = __syncthreads_or(live ? 1 : 0);
+  const int nclose = __syncthreads_or(close ? 1 : 0);
   if (nbad || !nlive) {
     const int st = nbad ? 4 : 5;
     if (tid < p) {
@@ -544,6 +546,36 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   if (it0 > 0 && tid < p) sm.w[0][tid] = sm.s[tid] > 0.0 ? rs->w[tid] : 0.0;
   double prev_obj = it0 > 0 ? rs->prev_obj : 0.0;
   __syncthreads();
+  // whether the sum of the weights is not trace M (see FA_CLOSE_PAIR)
+  bool inexact = nclose != 0;
+  if (!inexact && rank < __popcll(__ballot(sm.s[lane] > 0.0))) {
+    // R^T R (B0) against s and D^2
+    if (mt >= 0) {
+      v4d g = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+      for (int K = 0; K < T; ++K)
+        g = mma4(load_tile<T>(Rb, K, uI, lane), load_tile<T>(Rb, K, uJ, lane), g);
+      store_tile<T>(B0, uI, uJ, lane, g);
+      if (uI != uJ) store_tile_transposed<T>(B0, uI, uJ, lane, g);
+    }
+    __syncthreads();
+    bool off = false;
+    for (int e = tid; e < N * N; e += NTHREADS) {
+      const int i = e / N, j = e - i * N;
+      const double d2inv = D2I[eidx<T>(i, j)];
+      double ratio = 1.0;
+      if (i == j && sm.s[i] > 0.0) ratio = B0[eidx<T>(i, i)] * sm.dinv[i] * sm.dinv[i];
+      if (i != j && d2inv > 0.0 && coef > 0.0) {
+        const int fi = GRP ? sm.gf[i] : i, fj = GRP ? sm.gf[j] : j, k = GRP ? sm.gc[i] : 1;
+        ratio = 0.0;
+        for (int l = 0; l < k; ++l)
+          ratio += (B0[eidx<T>(fi + l, fi + l)] + B0[eidx<T>(fj + l, fj + l)] -
+                    2.0 * B0[eidx<T>(fi + l, fj + l)]) * d2inv;
+      }
+      off = off || !(fabs(ratio - 1.0) <= FA_TRACE_OFF);
+    }
+    inexact = __syncthreads_or(off ? 1 : 0) != 0;
+  }
 
   const double rs_delta = 1.0 / sqrt(delta);
   int iters_done = 0, steps = 0;
@@ -568,7 +600,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   }
 
   // Between two purifications stand four products and the residuals.  What is not on their path stays off
-  // it: the trace of M is the sum of the weights, C's diagonal is put in on the way to the first
+  // it: the trace of M is the sum of the weights (where it is, see FA_CLOSE_PAIR), C's diagonal is put in on the way to the first
   // product, M goes into X_0 from the accumulators, the steering wavefront plans the first step and takes
   // the gap's ends back beside the products, the residuals' chains overlap.  (With a phase and a barrier for
   // each of these, ten solves at p = 20 took 206 us instead of 165, fifteen at p = 32 263 instead of 207.)
@@ -638,6 +670,15 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         plan_push(pl, !sq, sq ? 0.0f : 1.0f);
       }
     };
+    const bool measure = it == 0 || inexact;
+    auto trace_of_M = [&]() {
+      __syncthreads();
+      hi = 0.0;
+#pragma unroll
+      for (int q = 0; q < NTP; ++q) hi += sm.red[q];
+    };
+    // (behind the first two solves the plan needs the trace)
+    if (wave == SW && inexact && it > 1) trace_of_M();
     if (wave == SW && mm < rank) {
       // while the others multiply: the first step's map (2000 cycles)
       const double is = scalar(__builtin_amdgcn_rcp(hi) * (1.0 - 1e-7));
@@ -674,8 +715,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         }
       }
     }
-    if (it == 0) {
-      // (later on the residuals' weights give it)
+    if (measure && !(wave == SW && inexact && it > 1)) {
+      // (otherwise the residuals' weights give it)
       if (mt >= 0) {
         double td = 0.0;
         if (uI == uJ) {
@@ -685,10 +726,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         td = wave_sum(td);
         if (lane == 0) sm.red[mt] = td;
       }
-      __syncthreads();
-      hi = 0.0;
-#pragma unroll
-      for (int q = 0; q < NTP; ++q) hi += sm.red[q];
+      trace_of_M();
     }
     cur = B0; nxt = B1;
     if (mm < rank) {
@@ -1066,7 +1104,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     }
     __syncthreads();
     double obj = 0.0;
-    hi = 0.0;         // trace M = sum of the weights: its columns are normalised
+    hi = 0.0;         // the next M's trace, unless it has to be measured
 #pragma unroll
     for (int q = 0; q < NTP; ++q) { obj += sm.red[q]; hi += sm.redw[q]; }
     if (tid == 0 && it0 + it < FA_ITERS_MAX) info->objective[it0 + it] = obj;

@@ -1,0 +1,126 @@
+"""Workers that send nearly the same vector, as colluding ones do.  A pair adds to the trace of the
+weighted-PCA matrix M its weight times |r_i - r_j|^2 / D_ij^2, and that ratio is 1 only while
+R^T R is the Gram matrix to the accuracy of D_ij^2.  With entries good to 1e-10, as the
+bf16 matrix core makes them, the factorisation of near copies stops short and the ratio is
+anything up to hundreds: the purification has to be scaled by the trace of M itself."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from gpu_util import announce, to_device
+from near_copies import irls, near_copies
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+STAND_BY = ("jacobi16", "jacobi")       # what a purification that fails is handed to, p <= 16 and above
+
+
+def compare(x, j, K, m, lam, iters):
+    """x: the library's info, j: the Jacobi solver's of the same K (which only says that x is not its answer).
+    R's last rows are good to eps / D^2, M's entries to that times their size, projectors to that over the gap;
+    a factor 4 p for the sums.  An answer that is not the leading projector is off by 1.4."""
+    assert x.status == 0 and x.iters_done == iters
+    assert x.sweeps != j.sweeps, "the stand-by's answer"
+    objective, R, P, gap, near, _ = irls(K, m, lam, iters)
+    bound = 4 * len(K) * 2.3e-16 / near / gap
+    assert bound < 0.05, "not a test"
+    U = R @ x.A
+    got = [np.max(np.abs(x.objective - objective) / objective), np.linalg.norm(U @ U.T - P),
+           np.max(np.abs(U.T @ U - np.eye(m)))]
+    print(x.rank, x.sweeps, "gap %.1e" % gap, "bound %.1e" % bound, ["%.1e" % g for g in got])
+    assert x.rank == len(R)
+    assert got[0] <= bound and got[1] <= bound and got[2] <= bound
+
+
+# in each of these the sum of the weights is off by 1.1 to 30 times in one of the five solves at least
+WIDE = [(20, 2, 4.0, 15, 1e-10), (20, 2, 4.0, 18, 1e-10), (20, 2, 1.0, 36, 1e-10), (20, 2, 4.0, 37, 5e-10),
+        (20, 2, 1.0, 38, 5e-10), (20, 2, 4.0, 39, 5e-10), (42, 1, 1.0, 3, 5e-10), (42, 1, 4.0, 8, 1e-10),
+        (42, 1, 4.0, 11, 5e-10), (42, 1, 1.0, 19, 1e-10), (60, 2, 4.0, 202, 5e-10), (60, 2, 1.0, 358, 5e-10),
+        (60, 2, 1.0, 460, 5e-10), (60, 2, 1.0, 468, 5e-10)]
+
+
+@pytest.mark.parametrize("p,m,lam,seed,noise", WIDE)
+def test_the_purification_is_scaled_by_the_trace_itself(p, m, lam, seed, noise):
+    from paper_2302_05865_amd import FlagAggregator
+    announce("near copies", p, m, lam, seed, noise)
+    K, got = near_copies(p, max(3, p // 3), 4e-6, 400, seed, noise), []
+    for solver in ("auto", STAND_BY[p > 16]):
+        agg = FlagAggregator(n_max=1 << 20, p_max=64, solver=solver)
+        agg.fa_irls(K, m, lam, 5, 0.0)
+        got.append(agg.fa_get_info())
+        agg.close()
+    compare(*got, K, m, lam, 5)
+
+
+@pytest.mark.parametrize("lam", [1.0, 100.0])
+@pytest.mark.parametrize("p,blocks", [(20, 1), (40, 1), (60, 1), (20, 2), (60, 2)])
+def test_close_pairs_of_an_exact_matrix_against_the_jacobi_solver(p, blocks, lam):
+    """K in fp64: every gradient has a pivot, and pairs closer than the solver lets the weights stand for the
+    trace.  The same K in front of both solvers; bounds as above."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("close pairs", p, blocks, lam)
+    n, m, r = 400, 5, np.random.default_rng(p + blocks)
+    x = (r.standard_normal((p, n)) * 0.5 + r.standard_normal((1, n))).astype(np.float32)
+    copies = r.permutation(p // blocks)[:p // blocks // 3]
+    for b in range(blocks):
+        v = np.float32(r.standard_normal(n))
+        for i in copies:
+            x[i * blocks + b] = v + np.float32(5e-4) * np.float32(r.standard_normal(n))
+    G, got = to_device(x), []
+    for solver in ("auto", "jacobi"):
+        agg = FlagAggregator(n_max=n, p_max=64, solver=solver)
+        if blocks > 1:
+            agg.fa_aggregate_grouped(G, [blocks] * (p // blocks), m, lam, 5, 0.0)
+        else:
+            agg.fa_aggregate(G, m, lam, 5, 0.0)
+        got.append(agg.fa_get_info())
+        agg.close()
+    a, j = got
+    s = np.diag(a.K)
+    both = s[:, None] + s[None]
+    near = np.min(((both - 2 * a.K) / both)[~np.eye(p, dtype=bool)])
+    bound = 4 * p * 2.3e-16 / near / j.eigengap
+    agree = [np.max(np.abs(a.objective - j.objective) / j.objective),
+             np.linalg.norm(a.K @ (a.c - j.c) / np.sqrt(s)) / np.linalg.norm(a.K @ j.c / np.sqrt(s))]
+    print(p, blocks, lam, a.rank, j.rank, a.sweeps, "near %.1e gap %.1e bound %.1e" % (near, j.eigengap, bound),
+          ["%.1e" % g for g in agree])
+    assert a.status == 0 and j.status == 0 and a.sweeps != j.sweeps and a.rank == j.rank == p
+    assert near < 1e-6 and max(agree) <= bound < 0.1
+
+
+@pytest.mark.parametrize("p,dtype", [(20, "f32"), (42, "f32"), (60, "f32"), (15, "bf16"), (24, "bf16")])
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_colluding_workers_take_the_fast_route(p, dtype, seed):
+    """The Gram matrix from the bf16 matrix core.  fp32: a third of the workers within 1e-6..8e-6 of one vector;
+    bf16: copies of one with a few coordinates one unit in the last place off."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("colluding", p, dtype, seed)
+    n, r = 1 << 20, np.random.default_rng(100 * p + seed)
+    x = (r.standard_normal((p, n), dtype=np.float32) * 0.5 + r.standard_normal((1, n), dtype=np.float32))
+    v = r.standard_normal(n, dtype=np.float32)
+    x = x if dtype == "f32" else si.f32_to_bf16_bits(x)
+    for i in r.permutation(p)[:p // 3]:
+        if dtype == "f32":
+            x[i] = v + np.float32(4e-6 * r.uniform(0.3, 2)) * r.standard_normal(n, dtype=np.float32)
+        else:
+            x[i] = si.f32_to_bf16_bits(v[None])[0]
+            x[i, r.integers(0, n, r.integers(3, 60))] ^= 1
+    G = to_device(x)
+    for m in (2, 5):
+        agg = FlagAggregator(n_max=n, p_max=p, dtype=dtype)
+        agg.fa_aggregate(G, m, 1.0, 5, 0.0)
+        a = agg.fa_get_info()
+        agg.close()
+        ref = FlagAggregator(n_max=n, p_max=p, dtype=dtype, solver=STAND_BY[p > 16])
+        ref.fa_irls(a.K, m, 1.0, 5, 0.0)
+        j = ref.fa_get_info()
+        ref.close()
+        assert a.status == 0 and a.sweeps != j.sweeps, m
+        objective, R, P, gap, near, _ = irls(a.K, m, 1.0, 5)
+        U, bound = R @ a.A, 4 * p * 2.3e-16 / near
+        got = np.max(np.abs(U.T @ U - np.eye(m))), np.linalg.norm(U @ U.T - P)
+        print(p, dtype, m, a.rank, a.sweeps, "gap %.1e" % gap, "bound %.1e" % bound, ["%.1e" % g for g in got])
+        assert a.rank == len(R) and got[0] <= bound
+        assert got[1] <= bound / gap or bound / gap > 0.05
