@@ -483,6 +483,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
 
   // ---- pairwise distances (registers, entry (4r+q4, c16)), normalised Gram (LDS) ---------
   double d2inv[4], kt[4];
+  bool close = false;                                  // a pair nearer than FA_CLOSE_PAIR
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = 4 * r + q4;
@@ -491,6 +492,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     const double d2 = si + sj - 2.0 * kv;
     const bool livep = i < p && c16 < p && i != c16 && d2 > pair_tol * (si + sj);
     d2inv[r] = livep ? 1.0 / d2 : 0.0;
+    close = close || (livep && !(d2 > FA_CLOSE_PAIR * (si + sj)));
     kt[r] = i == c16 ? (si > 0.0 ? 1.0 : 0.0) : kv * di * dj;
   }
   wave_fence();
@@ -519,6 +521,25 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
 #pragma unroll
   for (int r = 0; r < 4; ++r) isdiag[r] = (4 * r + q4) == c16;
   const bool livej = sj > 0.0;
+  // whether the sum of the weights is not trace M (see FA_CLOSE_PAIR)
+  bool inexact = __ballot(close) != 0ull;
+  if (!inexact && rank < __popcll(__ballot(q4 == 0 && livej))) {
+    // R^T R against s and D^2
+    const v4d g = mm16<NS>(rb, rb);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (isdiag[r]) fm.Zs[c16] = g[r];
+    wave_fence();
+    const double gj = fm.Zs[c16];
+    bool off = livej && !(fabs(gj * dj * dj - 1.0) <= FA_TRACE_OFF);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double ratio = (fm.Zs[4 * r + q4] + gj - 2.0 * g[r]) * d2inv[r];
+      off = off || (coef > 0.0 && d2inv[r] > 0.0 && !(fabs(ratio - 1.0) <= FA_TRACE_OFF));
+    }
+    inexact = __ballot(off) != 0ull;
+    wave_fence();
+  }
   double wj = livej ? 1.0 : 0.0;                      // IRLS weight of this lane's column
   double rhoj = 0.0, rsj = 0.0;
   const double rs_delta = 1.0 / sqrt(delta);          // the weight floor, as a cap on 1/sqrt(rho)
@@ -578,12 +599,12 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     mk = mm16<NS>(ra, wmat);
     if (mm < rank) {
       // Scale into [0, 1]: M is PSD, so 0 <= eigenvalues <= trace(M), which is the sum of the
-      // weights (a pair of nearly equal gradients adds its weight to 1e-4, rounding in D^2).  Any scale
-      // that keeps the eigenvalues in [0, 1] will do: the hardware reciprocal, shaded down.
-      if (it == 0) {
+      // weights unless that is inexact.  Any scale that keeps the eigenvalues in [0, 1] will do: the
+      // hardware reciprocal, shaded down by more than its error.
+      if (it == 0 || inexact) {
         hi = lane_bcast(sum_stage2(trace_stage1(mk, eye)), 0);
       }
-      const double sc = __builtin_amdgcn_rcp(hi) * (1.0 - 1e-3);
+      const double sc = __builtin_amdgcn_rcp(hi) * (1.0 - 1e-7);
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] = mk[r] * sc;
       // Steering: square when trace(X) > m, else X <- 2X - X^2.  With E = 2X - I both are
@@ -722,7 +743,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     rhoj = qjj * dj * dj;                                // 1 - v_j
     // sqrt(rho) = rho * rsqrt(rho) and max(rho, delta)^(-1/2) = min(rsqrt(rho), delta^(-1/2)):
     // one reciprocal square root per residual, no division
-    double part, wnext, wsum;                            // wsum: trace of the next M
+    double part, wnext, wsum;                            // wsum: of the next M's weights
     if (expo == 0.5) {
       // (a pair that is none has rho = 0: nothing is selected)
       rsj = rsq_nr<2>(fmax(rhoj, 1e-300));

@@ -39,9 +39,12 @@ WIDE = [(20, 2, 4.0, 15, 1e-10), (20, 2, 4.0, 18, 1e-10), (20, 2, 1.0, 36, 1e-10
         (20, 2, 1.0, 38, 5e-10), (20, 2, 4.0, 39, 5e-10), (42, 1, 1.0, 3, 5e-10), (42, 1, 4.0, 8, 1e-10),
         (42, 1, 4.0, 11, 5e-10), (42, 1, 1.0, 19, 1e-10), (60, 2, 4.0, 202, 5e-10), (60, 2, 1.0, 358, 5e-10),
         (60, 2, 1.0, 460, 5e-10), (60, 2, 1.0, 468, 5e-10)]
+NARROW = [(7, 4, 4.0, 2, 1e-10), (7, 2, 4.0, 2, 5e-10), (7, 2, 4.0, 12, 1e-10), (7, 2, 4.0, 20, 1e-10),
+          (7, 4, 4.0, 20, 5e-10), (15, 2, 4.0, 4, 5e-10), (15, 2, 4.0, 6, 5e-10), (15, 2, 4.0, 12, 5e-10),
+          (15, 2, 4.0, 16, 5e-10), (15, 2, 4.0, 18, 1e-10), (15, 2, 4.0, 21, 1e-10)]
 
 
-@pytest.mark.parametrize("p,m,lam,seed,noise", WIDE)
+@pytest.mark.parametrize("p,m,lam,seed,noise", WIDE + NARROW)
 def test_the_purification_is_scaled_by_the_trace_itself(p, m, lam, seed, noise):
     from paper_2302_05865_amd import FlagAggregator
     announce("near copies", p, m, lam, seed, noise)
@@ -55,13 +58,13 @@ def test_the_purification_is_scaled_by_the_trace_itself(p, m, lam, seed, noise):
 
 
 @pytest.mark.parametrize("lam", [1.0, 100.0])
-@pytest.mark.parametrize("p,blocks", [(20, 1), (40, 1), (60, 1), (20, 2), (60, 2)])
+@pytest.mark.parametrize("p,blocks", [(8, 1), (16, 1), (20, 1), (40, 1), (60, 1), (20, 2), (60, 2)])
 def test_close_pairs_of_an_exact_matrix_against_the_jacobi_solver(p, blocks, lam):
     """K in fp64: every gradient has a pivot, and pairs closer than the solver lets the weights stand for the
     trace.  The same K in front of both solvers; bounds as above."""
     from paper_2302_05865_amd import FlagAggregator
     announce("close pairs", p, blocks, lam)
-    n, m, r = 400, 5, np.random.default_rng(p + blocks)
+    n, m, r = 400, 5 if p > 8 else 3, np.random.default_rng(p + blocks)
     x = (r.standard_normal((p, n)) * 0.5 + r.standard_normal((1, n))).astype(np.float32)
     copies = r.permutation(p // blocks)[:p // blocks // 3]
     for b in range(blocks):
@@ -69,7 +72,7 @@ def test_close_pairs_of_an_exact_matrix_against_the_jacobi_solver(p, blocks, lam
         for i in copies:
             x[i * blocks + b] = v + np.float32(5e-4) * np.float32(r.standard_normal(n))
     G, got = to_device(x), []
-    for solver in ("auto", "jacobi"):
+    for solver in ("auto", STAND_BY[p > 16]):
         agg = FlagAggregator(n_max=n, p_max=64, solver=solver)
         if blocks > 1:
             agg.fa_aggregate_grouped(G, [blocks] * (p // blocks), m, lam, 5, 0.0)
