@@ -253,7 +253,7 @@ struct Fmem {
   double Am[16 * LDF];   // A (p x m)
   __attribute__((aligned(16))) double Zs[16 * LDZ];   // [0..15]: diag(Z^T Z), Z = (I-P) R
   double s[16], dinv[16], r1[16], beta[16], rinv[16];
-  int piv[16], rank;     // rank: 0 where there was no factorisation
+  int piv[16], rank;     // rank: negative where there was no factorisation
 };
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -474,7 +474,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     if (lane == 0) {
       info->status = st; info->p = p; info->m = m; info->rank = 0; info->iters_done = 0;
       info->sweeps = 0; info->eigengap = 0.0;
-      fm.rank = 0;
+      fm.rank = -1;
     }
     __syncthreads();
     __syncthreads();
@@ -887,7 +887,7 @@ __global__ __launch_bounds__(256, 2) void fa_irls16_kernel(const double* __restr
     } else {
       __syncthreads();
       const int rank = __builtin_amdgcn_readfirstlane(fm.rank);
-      if (tid < 128 && rank > 0) fastp::right_inverse(fm, rank, tid & 63);
+      if (tid < 128 && rank >= 0) fastp::right_inverse(fm, rank, tid & 63);
       __syncthreads();
     }
     __syncthreads();
