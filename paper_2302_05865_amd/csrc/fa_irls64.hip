@@ -88,19 +88,14 @@ __device__ __forceinline__ double wave_sum(double x) {
   x = row_sum(x);
   return ((lane_bcast(x, 0) + lane_bcast(x, 16)) + lane_bcast(x, 32)) + lane_bcast(x, 48);
 }
-// about the same in f32, ~80 instead of ~200 cycles: row totals, then along the rows into lane 63
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float add_dpp(float x) {
-  return x + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, ROWS, 0xf, false));
-}
-__device__ __forceinline__ float wave_sum_f32(float x) {
-  x = add_dpp<0x128, 0xf>(x);   // row_ror:8
-  x = add_dpp<0x124, 0xf>(x);   // row_ror:4
-  x = add_dpp<0x122, 0xf>(x);   // row_ror:2
-  x = add_dpp<0x121, 0xf>(x);   // row_ror:1
-  x = add_dpp<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
-  x = add_dpp<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
-  return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+// The same on the matrix core, 10 instructions behind x instead of 23: a 4 x 4 x 4 product of four blocks with all
+// ones sums over the lanes l, l + 16, l + 32, l + 48, a second one over the other index of a block.
+__device__ __forceinline__ double wave_sum_mfma(double x) {
+  x = __builtin_amdgcn_mfma_f64_4x4x4f64(x, 1.0, 0.0, 0, 0, 0);
+  x = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, x, 0.0, 0, 0, 0);
+  x += dpp_f64<0x128>(x);
+  x += dpp_f64<0x124>(x);
+  return lane_bcast(x, 0);
 }
 // 1/sqrt(x): hardware estimate plus two Newton steps
 __device__ __forceinline__ double rsq2(double x) {
@@ -830,11 +825,10 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         else if (nl == 3) run(std::integral_constant<int, 3>{});
         else run(std::integral_constant<int, 4>{});
       } else if (wave == SW) {
-        // Everything here is uniform, and its chain has to stay under a step's products (planned 470
-        // cycles, steered 710 at T = 2).  Three stages:
-        // planned steps; steps steered by f32 values of trace X_k and |X_k|_F^2 (which way does not
+        // Everything here is uniform, and its chain has to stay under a step's products.  Three stages:
+        // planned steps; steps steered by trace X_k and |X_k|_F^2 (which way does not
         // matter to what is right, both maps keep the eigenvalues' order); and from where all
-        // eigenvalues are near 0 or 1, with those two measured in f64, as many steps as it takes to
+        // eigenvalues are near 0 or 1, with those two measured, as many steps as it takes to
         // square what the sums of the lower ones and of the upper ones' distances from 1 leave away.
         __builtin_amdgcn_s_setprio(3);      // ahead of the matrix instructions of its SIMD
         __syncthreads();
@@ -853,81 +847,88 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
           ++k;
           __syncthreads();
         }
-        bool near = true, settled = false;
-        float t = 0.0f, F = 0.0f;           // of X_k
-        float A = 0.0f, B = 0.0f;           // the lower eigenvalues' sum, the upper ones' distance from 1
-        while (end == STEP_GO) {            // step k, whose map is a plain one
-          const double* cu = k & 1 ? B1 : B0;
-          if (!settled) {
-            double f0 = 0.0, f1 = 0.0;
-            v4d v[NTP];
+        double t = 0.0, F = 0.0;            // trace X_k, |X_k|_F^2
+        auto norm2 = [&](const double* cu) {
+          double f0 = 0.0, f1 = 0.0;
+          v4d v[NTP];
 #pragma unroll
-            for (int q = 0; q < NTP; ++q) {
-              int I, J;
-              upper_pair<T>(q, &I, &J);
-              v[q] = load_tile<T>(cu, I, J, lane);
-            }
-#pragma unroll
-            for (int q = 0; q < NTP; ++q) {
-              double& f = q < T ? f0 : f1;
-#pragma unroll
-              for (int r = 0; r < 4; ++r) f = fma(v[q][r], v[q][r], f);
-            }
-            f0 = fma(2.0, f1, f0);
-            if (!near) {
-              F = wave_sum_f32((float)f0);
-              near = t - F < 0.04f;
-            }
-            if (near) {
-            // (behind a plan, where the trace is not known, and from the first sign on)
-            const int d = lane < N ? lane : 0;
-            const double td = wave_sum(lane < N ? cu[eidx<T>(d, d)] : 0.0);
-            const double fd = wave_sum(f0);
-            t = (float)td; F = (float)fd;
-            const double s = td - fd;       // sum x (1 - x) over the eigenvalues of X_k
-            near = s < 0.04;
-            if (s < 0.02) {
-              // All eigenvalues of X_k near 0 or 1: the sums of the lower ones and of the upper ones'
-              // distance from 1 bound the ends of the gap (1.02 s stands for the s = sum x (1 - x)
-              // without the squares)
-              const double cl = 0.5 * (1.02 * s + td - dm), cu1 = 0.5 * (1.02 * s - td + dm);
-              if (bk < 0) {
-                bk = k;
-                yv = lane & 1 ? 1.0f - (float)fmin(0.5, fmax(1e-4, cu1)) : (float)fmin(0.5, fmax(1e-4, cl));
-                // (both are sums, good to 0.02 s)
-                const double zl = 0.5 * (double)(rank - mm) * Hp, zu = 0.5 * dm * (1.0 - Gp);
-                cap_in = !guessed ? 0 : (cl <= zl + 0.02 * s ? 1 : 0) | (cu1 <= zu + 0.02 * s ? 2 : 0);
-              }
-              if (fabs(td - dm) < 0.25) {
-                settled = true;
-                // where H and G are near 0 and 1 as well, the order is kept from here on
-                tracked = tracked && !(Hp < 0.1f && Gp > 0.9f);
-                A = fmaxf((float)cl, 1e-15f);
-                B = fmaxf((float)cu1, 1e-15f);
-              } else if (fabs(s) < 1e-10 || (guessed && s < 1e-3)) {
-                end = STEP_FAILED;          // nearly a projector, but with another trace
-              }
-            }
-            }
+          for (int q = 0; q < NTP; ++q) {
+            int I, J;
+            upper_pair<T>(q, &I, &J);
+            v[q] = load_tile<T>(cu, I, J, lane);
           }
-          // on to X_{k+1}
-          bool next;
-          if (settled) {
-            A = sq ? A * A : 2.0f * A;
-            B = sq ? 2.0f * B : B * B;
-            next = A > B;
-            if (fmaxf(A, B) < 1e-12f)
-              end = !tracked || (lane_of(pl.x, 1) > 0.9f && lane_of(pl.x, 0) < 0.1f) ? STEP_DONE : STEP_FAILED;
-          } else {
-            t = sq ? F : 2.0f * t - F;
-            next = t > (float)mm;
+#pragma unroll
+          for (int q = 0; q < NTP; ++q) {
+            double& f = q < T ? f0 : f1;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) f = fma(v[q][r], v[q][r], f);
           }
+          F = wave_sum_mfma(fma(2.0, f1, f0));
+        };
+        auto trace = [&](const double* cu) {
+          const int d = lane < N ? lane : 0;
+          t = wave_sum_mfma(lane < N ? cu[eidx<T>(d, d)] : 0.0);
+        };
+        // the lower eigenvalues' sum and the upper ones' distance from 1, where those are all near 0 or 1 (1.02 s stands
+        // for s = sum x (1 - x) without the squares)
+        double A = 0.0, B = 0.0;
+        auto fits = [&]() -> bool {
+          const double s = t - F, sa = 1.02 * s;
+          A = 0.5 * (sa + t - dm);
+          B = 0.5 * (sa - t + dm);
+          return s < 0.02 && fabs(t - dm) < 0.25;
+        };
+        auto advance = [&]() {              // on to X_{k+1}
           ++k;
           if (end == STEP_GO && k >= (guessed ? 64 : MAX_PURIFY - 1)) end = STEP_FAILED;
-          sq = next;
           publish(k);
-          if (settled) take_back(bk > BACK ? bk - BACK : 0);      // (there is time beside these steps)
+        };
+        bool near = true;                   // (behind a plan the trace is not known)
+        while (end == STEP_GO) {            // step k, whose map is a plain one
+          const double* cu = k & 1 ? B1 : B0;
+          norm2(cu);
+          near = near || t - F < 0.04;
+          if (near) {
+            trace(cu);
+            const double s = t - F;
+            near = s < 0.04;
+            if (s < 0.02) {
+              const bool good = fits();
+              if (bk < 0) {
+                // bounds of the ends of the gap
+                bk = k;
+                yv = lane & 1 ? 1.0f - (float)fmin(0.5, fmax(1e-4, B)) : (float)fmin(0.5, fmax(1e-4, A));
+                // (both are sums, good to 0.02 s)
+                const double zl = 0.5 * (double)(rank - mm) * Hp, zu = 0.5 * dm * (1.0 - Gp);
+                cap_in = !guessed ? 0 : (A <= zl + 0.02 * s ? 1 : 0) | (B <= zu + 0.02 * s ? 2 : 0);
+              }
+              if (good) break;
+              // nearly a projector, but with another trace
+              if (fabs(s) < 1e-10 || (guessed && s < 1e-3)) end = STEP_FAILED;
+            }
+          }
+          t = sq ? F : 2.0 * t - F;         // carried
+          sq = t > dm;
+          advance();
           __syncthreads();
+        }
+        if (end == STEP_GO) {
+          // where H and G are near 0 and 1 as well, the order is kept from here on
+          tracked = tracked && !(Hp < 0.1f && Gp > 0.9f);
+          A = fmax(A, 1e-15);
+          B = fmax(B, 1e-15);
+          for (;;) {
+            const double An = sq ? A * A : 2.0 * A, Bn = sq ? 2.0 * B : B * B;
+            if (fmax(An, Bn) < 1e-12)
+              end = !tracked || (lane_of(pl.x, 1) > 0.9f && lane_of(pl.x, 0) < 0.1f) ? STEP_DONE : STEP_FAILED;
+            A = An;
+            B = Bn;
+            sq = A > B;
+            advance();
+            take_back(bk > BACK ? bk - BACK : 0);        // (there is time beside these steps)
+            __syncthreads();
+            if (end != STEP_GO) break;
+          }
         }
         __builtin_amdgcn_s_setprio(0);
       } else {
