@@ -829,7 +829,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         // planned steps; steps steered by trace X_k and |X_k|_F^2 (which way does not
         // matter to what is right, both maps keep the eigenvalues' order); and from where all
         // eigenvalues are near 0 or 1, with those two measured, as many steps as it takes to
-        // square what the sums of the lower ones and of the upper ones' distances from 1 leave away.
+        // square what the sums of the lower ones and of the upper ones' distances from 1 leave away.  In the last of
+        // them both are measured again, and have to say the same.
         __builtin_amdgcn_s_setprio(3);      // ahead of the matrix instructions of its SIMD
         __syncthreads();
         if (planned) {
@@ -873,10 +874,10 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         // for s = sum x (1 - x) without the squares)
         double A = 0.0, B = 0.0;
         auto fits = [&]() -> bool {
-          const double s = t - F, sa = 1.02 * s;
+          const double s = t - F, sa = 1.02 * fabs(s);
           A = 0.5 * (sa + t - dm);
           B = 0.5 * (sa - t + dm);
-          return s < 0.02 && fabs(t - dm) < 0.25;
+          return s >= -1e-9 && s < 0.02 && fabs(t - dm) < 0.25;
         };
         auto advance = [&]() {              // on to X_{k+1}
           ++k;
@@ -903,8 +904,9 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
                 cap_in = !guessed ? 0 : (A <= zl + 0.02 * s ? 1 : 0) | (B <= zu + 0.02 * s ? 2 : 0);
               }
               if (good) break;
-              // nearly a projector, but with another trace
-              if (fabs(s) < 1e-10 || (guessed && s < 1e-3)) end = STEP_FAILED;
+              // nearly a projector, but with another trace; or eigenvalues outside [0, 1], where neither map keeps an
+              // order
+              if (s < 1e-10 || (guessed && s < 1e-3)) end = STEP_FAILED;
             }
           }
           t = sq ? F : 2.0 * t - F;         // carried
@@ -918,9 +920,17 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
           A = fmax(A, 1e-15);
           B = fmax(B, 1e-15);
           for (;;) {
+            const double* cu = k & 1 ? B1 : B0;
             const double An = sq ? A * A : 2.0 * A, Bn = sq ? 2.0 * B : B * B;
-            if (fmax(An, Bn) < 1e-12)
-              end = !tracked || (lane_of(pl.x, 1) > 0.9f && lane_of(pl.x, 0) < 0.1f) ? STEP_DONE : STEP_FAILED;
+            if (fmax(An, Bn) < 1e-12) {
+              // the last one: X_k as expected, up to rounding
+              const double limit = 2.0 * fmax(A, B) + 1e-12;
+              norm2(cu);
+              trace(cu);
+              end = fits() && fmax(A, B) <= limit &&
+                            (!tracked || (lane_of(pl.x, 1) > 0.9f && lane_of(pl.x, 0) < 0.1f))
+                        ? STEP_DONE : STEP_FAILED;
+            }
             A = An;
             B = Bn;
             sq = A > B;
