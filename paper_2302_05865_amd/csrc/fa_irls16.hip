@@ -265,10 +265,6 @@ __device__ __forceinline__ double dpp_f64(double x) {
   hi = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
 }
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float x) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, false));
-}
 __device__ __forceinline__ double lane_bcast(double x, int srclane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(x), srclane);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(x), srclane);
@@ -282,8 +278,9 @@ __device__ __forceinline__ double lane_bcast(double x, int srclane) {
 __device__ __forceinline__ double sum_stage1(double t) {
   return __builtin_amdgcn_mfma_f64_4x4x4f64(t, 1.0, 0.0, 0, 0, 0);
 }
-__device__ __forceinline__ double sum_stage2(double t) {
-  t = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, t, 0.0, 0, 0, 0);
+// (quarter_c: a fourth of what the sum starts from)
+__device__ __forceinline__ double sum_stage2(double t, double quarter_c = 0.0) {
+  t = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, t, quarter_c, 0, 0, 0);
   t += dpp_f64<0x128>(t);   // row_ror:8
   t += dpp_f64<0x124>(t);   // row_ror:4
   return t;
@@ -295,13 +292,6 @@ __device__ __forceinline__ double fro2_stage1(const v4d& x) {
 }
 __device__ __forceinline__ double trace_stage1(const v4d& x, const v4d& eye) {
   return sum_stage1(fma(x[3], eye[3], fma(x[2], eye[2], fma(x[1], eye[1], x[0] * eye[0]))));
-}
-// c + the sum in f32
-__device__ __forceinline__ float sum_stage2_f32(double t, double quarter_c) {
-  float v = (float)__builtin_amdgcn_mfma_f64_4x4x4f64(1.0, t, quarter_c, 0, 0, 0);
-  v += dpp_f32<0x128>(v);
-  v += dpp_f32<0x124>(v);
-  return v;
 }
 
 // NS: matrix instructions, four contraction indices each; all that is multiplied here is zero from
@@ -610,7 +600,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
       // Steering: square when trace(X) > m, else X <- 2X - X^2.  With E = 2X - I both are
       // E <- E + sigma (E^2 - I), sigma = 1/2 or -1/2: the accumulators start at -I, and four multiply-adds
       // are all that follows a product (twelve instructions with X itself, for the selects).
-      // trace(E) is carried along in f32 (E_{k+1}: trace(E_k) + sigma (|E_k|_F^2 - r); it only steers), so
+      // trace(E) is carried along (E_{k+1}: trace(E_k) + sigma (|E_k|_F^2 - r)), so
       // the only reduction per step is |E|_F^2, and its result is not needed before the end of
       // the *next* step: the reduction is split in two halves (second half for E_{k-1},
       // first half for E_k) issued beside the four matrix-core instructions of E_k^2.
@@ -636,15 +626,15 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
         tX = sum_stage2(trace_stage1(x, eye));
       }
       const double dr = (double)rank;
-      const float cut = (float)(2 * mm - rank);            // trace(E) of the projector
+      const double cut = (double)(2 * mm - rank);          // trace(E) of the projector
       // the dummies give the first step the trace it is told and "not near"
-      float tE = (float)(tX + tX - dr);
+      double tE = tX + tX - dr;
       double sg = 0.0, pend = -1.0;
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] = fma(2.0, x[r], less[r]);
       bool conv = false;
       int k_end = MAX_PURIFY;
-      float A = 0.0f, B = 0.0f;            // the lower eigenvalues' sum, the upper ones' distance from 1
+      double A = 0.0, B = 0.0;             // the lower eigenvalues' sum, the upper ones' distance from 1
       // Two loops: the steps run in an inner loop of their own until the iterate is nearly
       // idempotent, the exact test sits outside it.  (With the test inside one loop, never
       // taken until the end, every step was a quarter slower: 700 against 534 cycles.)
@@ -654,11 +644,11 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
       // A step at p = 15: 455 cycles, 264 of them the four matrix instructions (598 with X itself, a reduction
       // in f64 with DPP moves and readlanes and a way out behind either step); p = 7: 317 (506).
       const double r4 = -0.25 * dr;
-      auto one_step = [&](const v4d& xi, v4d& xo) __attribute__((always_inline)) -> float {
+      auto one_step = [&](const v4d& xi, v4d& xo) __attribute__((always_inline)) -> double {
         const v4d y = mm16_plus<NS>(xi, xi, less);
-        const float q = sum_stage2_f32(pend, r4);
+        const double q = sum_stage2(pend, r4);
         pend = fro2_stage1(xi);
-        tE = fmaf((float)sg, q, tE);                       // trace(E_k)
+        tE = fma(sg, q, tE);                               // trace(E_k)
         sg = tE > cut ? 0.5 : -0.5;
 #pragma unroll
         for (int r = 0; r < 4; ++r) xo[r] = fma(sg, y[r], xi[r]);
@@ -670,8 +660,8 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
         do {
           v4d x2;
           one_step(x, x2);
-          const float q = one_step(x2, x);
-          near = __ballot(q > (float)(-4.0 * NEAR)) != 0ull;
+          const double q = one_step(x2, x);
+          near = __ballot(q > -4.0 * NEAR) != 0ull;
           k += 2;
         } while (!near && k < MAX_PURIFY);
         if (!near) break;
@@ -685,14 +675,14 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
           // trace X - m are the sum and the difference of the lower ones' sum and the upper
           // ones' distances from 1, up to the squares (1.04).
           if (fabs(dt) < 0.25) {
-            A = fmaxf((float)(0.5 * (1.04 * s + dt)), 1e-15f);
-            B = fmaxf((float)(0.5 * (1.04 * s - dt)), 1e-15f);
+            A = fmax(0.5 * (1.04 * s + dt), 1e-15);
+            B = fmax(0.5 * (1.04 * s - dt), 1e-15);
             conv = true;
           }
           if (conv || s < 1e-12) { k_end = k; break; }
         }
         // not yet: go on from the exact trace
-        tE = (float)(2.0 * (dt + dm) - dr);
+        tE = 2.0 * (dt + dm) - dr;
         sg = 0.0;
         pend = -1.0;
       }
@@ -705,8 +695,8 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
       // 300 cycles at p = 15, 200 at p = 7.  (With 2e-12 for 2e-15 the aggregate's error doubles, to 2e-15.)
       {
         const bool sq = A > B;             // X^2 first: 2 A^2 and 4 B^2 after two steps
-        const float e = sq ? fmaxf(2.0f * A, 4.0f * B) : fmaxf(4.0f * A, 2.0f * B);
-        const int pairs = e < 4e-8f ? 1 : e < 2e-4f ? 2 : e < 1.4e-2f ? 3 : e < 0.12f ? 4 : 5;   // e^(2^pairs) < 2e-15
+        const double e = sq ? fmax(2.0 * A, 4.0 * B) : fmax(4.0 * A, 2.0 * B);
+        const int pairs = e < 4e-8 ? 1 : e < 2e-4 ? 2 : e < 1.4e-2 ? 3 : e < 0.12 ? 4 : 5;   // e^(2^pairs) < 2e-15
 #pragma unroll
         for (int r = 0; r < 4; ++r) x[r] = fma(0.5, x[r], (sq ? 0.5 : -0.5) * eye[r]);
 #pragma unroll 1
