@@ -576,6 +576,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
   double hi = 0.0;                                     // trace of M
   v4d x = {0.0, 0.0, 0.0, 0.0}, mk = {0.0, 0.0, 0.0, 0.0};
   int iters_done = 0, steps = 0;
+  double off = 0.0, cnt = 0.0;                         // sum x (1 - x) and trace of the results: this lane's part
   for (int it = 0; it < iters; ++it) {
     // C = diag(w/s) + Laplacian of the pair part;  M = R C R^T via W = C R^T, M = R W
     // (the pair part is symmetric, bit for bit: the sum of row j is the sum of column j, which
@@ -674,7 +675,8 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
           // maps are monotone, so the eigenvalue order is kept whatever the steering did); then s and
           // trace X - m are the sum and the difference of the lower ones' sum and the upper
           // ones' distances from 1, up to the squares (1.04).
-          if (fabs(dt) < 0.25) {
+          // A sum clearly below zero has eigenvalues outside [0, 1], where neither map keeps an order.
+          if (s >= -1e-9 && fabs(dt) < 0.25) {
             A = fmax(0.5 * (1.04 * s + dt), 1e-15);
             B = fmax(0.5 * (1.04 * s - dt), 1e-15);
             conv = true;
@@ -723,6 +725,11 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
 #pragma unroll
     for (int r = 0; r < 4; ++r) qm[r] = isdiag[r] ? 1.0 - x[r] : -x[r];
     const v4d z = mm16<NS>(qm, rb);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      off = fma(x[r], eye[r] - x[r], off);
+      cnt = fma(x[r], eye[r], cnt);
+    }
     // Q = Z^T Z straight from the accumulator registers (for A = tile^T the register layout
     // of Z is both operands): |z_j|^2 = q_jj is the residual of worker j, and the pair
     // residuals come from |z_i - z_j|^2 = q_ii + q_jj - 2 q_ij, entry (i, j) of Q sitting in
@@ -786,6 +793,15 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     }
     wj = livej ? wnext : 0.0;
     hi = wave_sum(wsum);
+  }
+
+  // Every result has to have been a projector of trace m, measured: a prediction said so (all solves at once, a sum over
+  // the wavefront for each took 0.14 us of it)
+  off = wave_sum(off);
+  cnt = wave_sum(cnt);
+  if (!(fabs(off) < 1e-12 * iters_done && fabs(cnt - (double)mm * iters_done) < 0.25)) {
+    __syncthreads();
+    return -3;
   }
 
   // ---- epilogue: basis of range(P), A = B U_m, c = A (U_m^T R 1) / p ---------------------
