@@ -656,9 +656,9 @@ def test_wide_problem_on_the_jacobi_kernel():
 
 @pytest.mark.parametrize("name,n", [("cfg4", 60_001), ("cfg5", 30_001)])
 def test_wide_solver_gives_up_and_the_jacobi_kernel_redoes_the_solve(name, n):
-    """A spin budget of zero makes the first wait for a steering word of the matrix-core solver
-    (16 < p <= 64) give up; every wavefront then leaves the purification at the same barrier,
-    the kernel hands over, and the Jacobi kernel enqueued behind it must return the oracle's
+    """A spin budget of zero makes the matrix-core solver (16 < p <= 64) give up before the first
+    purification step; every wavefront then leaves the purification at the same barrier, the
+    kernel hands over, and the Jacobi kernel enqueued behind it must return the oracle's
     answer.  Every kernel exits normally."""
     announce("wide solver gives up", name)
     w = si.WORKLOADS[name].with_n(n)
@@ -943,7 +943,7 @@ def test_grouped_with_single_columns_is_fa_aggregate(name, n):
 @pytest.mark.parametrize("sizes,m", [([4] * 10, 17), ([3, 3, 2, 2, 3], 6)])
 def test_grouped_stand_by_redoes_the_solve_when_the_purification_gives_up(sizes, m):
     """The block solver's hand-over: with a spin budget of zero the purification kernel gives up
-    at its first wait and the Jacobi kernel behind it answers, bit for bit what a context asking
+    before its first step and the Jacobi kernel behind it answers, bit for bit what a context asking
     for that kernel returns.  Also on the block route: a worker sent twice (its pair is dropped,
     its columns are linearly dependent), non-finite and all-zero input."""
     q, n, iters = sum(sizes), 8_009, 4

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("p", [3, 7, 12, 15, 20, 60])
 def test_a_rank_threshold_above_every_pivot_leaves_nothing(p):
     """rank_tol >= 1: no pivot is large enough, rank 0, an empty subspace and a zero aggregate.  Behind a pass over
-    NaN gradients, which leaves nothing else in the compute units' LDS: what the solver uses it has to write."""
+    NaN gradients, which leaves them in the compute units' LDS: what the solver uses it has to write."""
     from paper_2302_05865_amd import FlagAggregator
     announce("rank 0", p)
     n = 1 << 22
