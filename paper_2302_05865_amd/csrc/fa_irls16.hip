@@ -512,7 +512,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
   for (int r = 0; r < 4; ++r) isdiag[r] = (4 * r + q4) == c16;
   const bool livej = sj > 0.0;
   // whether the sum of the weights is not trace M (see FA_CLOSE_PAIR)
-  bool inexact = __ballot(close) != 0ull;
+  bool inexact = coef > 0.0 && __ballot(close) != 0ull;
   if (!inexact && rank < __popcll(__ballot(q4 == 0 && livej))) {
     // R^T R against s and D^2
     const v4d g = mm16<NS>(rb, rb);
@@ -551,7 +551,7 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
     }
     prev_obj = rs->prev_obj;
   }
-  // The first steps of a purification need no steering: trace X_0 = 1 bounds the eigenvalue m + 1 by
+  // The first steps of a purification need no steering: trace X_0 <= 1 bounds the eigenvalue m + 1 by
   // 1 / (m + 1), so 1 - (1 - a X)^2 with a = 2 / (1 + bound) may fold what lies above the bound (those
   // are at most m, and they stay above the rest); the map takes the bound along.  While it is small
   // such a step is worth up to two of the plain ones, and the trace is measured once after them.
@@ -642,8 +642,8 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
       // One step E_k (xi) -> E_{k+1} (xo); returns |E_{k-1}|_F^2 - r.  The loop
       // runs two of them per pass, from x into a second set of registers and back, which
       // spares the copies of a rotated loop and gives the scheduler two steps to interleave.
-      // A step at p = 15: 455 cycles, 264 of them the four matrix instructions (598 with X itself, a reduction
-      // in f64 with DPP moves and readlanes and a way out behind either step); p = 7: 317 (506).
+      // A step at p = 15: 467 cycles, 264 of them the four matrix instructions (598 with X itself, a reduction
+      // with DPP moves and readlanes and a way out behind either step); p = 7: 304 (506).
       const double r4 = -0.25 * dr;
       auto one_step = [&](const v4d& xi, v4d& xo) __attribute__((always_inline)) -> double {
         const v4d y = mm16_plus<NS>(xi, xi, less);

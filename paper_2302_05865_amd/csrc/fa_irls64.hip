@@ -11,7 +11,7 @@
 // N = 16 T (T = 2, 3, 4) are kept in LDS as T x T tiles of 16 x 16, each tile in the register
 // order of the matrix instruction's accumulator (entry r of lane l = element
 // (4 r + l / 16, l % 16)), so that a wavefront moves a tile between LDS and registers with
-// four conflict-free 8-byte accesses per lane and can use it directly
+// two conflict-free 16-byte accesses per lane and can use it directly
 //   * as B operand (rows of the tile are the contraction index), and
 //   * as A operand of the *transposed* tile (for a symmetric matrix: of tile (J, I)).
 // One wavefront owns one output tile of a product; symmetric results are computed for I <= J
@@ -116,8 +116,7 @@ __device__ __forceinline__ double rsq2(double x) {
 // sixteen lanes, so that a tile is two 16-byte accesses per lane, without bank conflicts; and the
 // transposed store (lane (q, c), source entry r, goes to entry c / 4 of lane 16 (c % 4) + 4 r + q)
 // touches every bank once per half wavefront: q and the parity of c / 4 stay within 32 bytes, c % 4
-// moves by 288 bytes and the half by 1152.  (Four 8-byte accesses per lane, entries 68 doubles apart:
-// 937 against 853 cycles a purification step at T = 2.)
+// moves by 288 bytes and the half by 1152.
 constexpr int FA_TILE = FA_TILE_DOUBLES, FA_HALF = FA_TILE / 2;
 typedef double v2d __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ int at(int l) { return 2 * l + 4 * (l >> 4); }
@@ -217,7 +216,8 @@ struct Small {
 // Once h and g are within 0.03 of 0 and 1 the steps go on as always.
 // Where there is no guess - the first two solves (the first weights move the gap most: guesses failed
 // there), a gap of less than a fifth or of more than 32 (where the plain steps need few), a guess that
-// failed - only the first growth steps are planned, from a bound that always holds (trace X_0 = 1).
+// failed - only the first growth steps are planned, from a bound that always holds (trace X_0 <= 1: measured, or the
+// weights' sum where that is it to 3e-8).
 // Measured, steps per call (plain -> with plans): p = 32, m = 16, 15 solves 400 -> 313; p = 64,
 // m = 32, 30 solves 764 -> 639; p = 60, m = 31, 5 solves 170 -> 161.  Where a guess from the second solve
 // on and ends that stay below a fold cost up to 1.7 times the plain steps (m = 1 or close to p, a = 4: 137
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         }
       }
       D2I[eidx<T>(i, j)] = livep ? 1.0 / d2 : 0.0;
-      close = close || (livep && !(d2 > FA_CLOSE_PAIR * both));
+      close = close || (livep && coef > 0.0 && !(d2 > FA_CLOSE_PAIR * both));
     }
   }
   const int nbad = __syncthreads_or(bad ? 1 : 0);
@@ -684,7 +684,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         plan_begin(pl, (float)(0.8 * lo), (float)fmin(1.0, 1.25 * up), (float)(1.05 * lo),
                    (float)fmin(0.99, 0.95 * up), 0.03f, lane);
       } else {
-        // no guess, but trace X_0 = 1 bounds x_{m+1} by 1 / (m + 1) (with a margin for rounding):
+        // no guess, but trace X_0 <= 1 bounds x_{m+1} by 1 / (m + 1) (with a margin for rounding):
         // growth may fold what is above that, while it is small
         const float bound = 1.0001f / (float)(mm + 1);
         plan_begin(pl, 0.0f, bound, 0.0f, bound, 0.5f, lane);
@@ -759,9 +759,10 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       //    t = trace X_k and |X_k|_F^2, which give trace X_{k+1}: X^2 where that is above m, 2X - X^2
       //    below; and that X_{k+1} is the result where X_k is a projector already;
       //  - everybody else keeps the barrier, one a step.
-      // So a step's map is there before the barrier in front of it and nobody waits for it.  A step, us at
-      // 2.4 GHz: T = 2 0.4 (512 of about 950 cycles matrix instructions), T = 4 1.6 (3072 of 3900); 0.6
-      // and 1.8 with the trace of X_k itself, published during step k and waited for behind its products.
+      // So a step's map is there before the barrier in front of it and nobody waits for it.  Cycles of a step,
+      // planned / steered / behind the measurement: p = 20 760 / 870 / 940, p = 32 905 / 1100 / 1020 (512 of them matrix
+      // instructions), p = 60 3510 / 3660 / 3290 (3072); with the trace of X_k itself, published during step k and waited
+      // for behind its products, 1580 at T = 2 and 4500 at T = 4.
       if (mt >= 0) {
         // this wavefront's tile of X_k stays in its registers: LDS holds it for the others
         double live[4];                                  // the identity's place in a diagonal tile
@@ -770,11 +771,11 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         // One step: X_k in cu, X_{k+1} into nx.  Written for fixed buffers (the loop alternates
         // two instances) so that every LDS address is loop invariant and the loads of a
         // wavefront that leaves the barrier behind older ones of its SIMD are in flight at
-        // once.  Own tile (uI, uJ) of X_k^2 = sum_K X(K, uI)^T X(K, uJ), K = uI first and K = T - 1,
-        // where NL of the four matrix instructions suffice (X is zero from index rank on; p = 20: 700
-        // cycles, p = 32: 850), last.  On the diagonal the part K = uI needs nobody else's tile: it is
-        // multiplied ahead of the barrier (853 against 937 cycles at T = 2, 3556 against 3809 at
-        // T = 4).  Returns true when the loop is over.
+        // once.  Own tile (uI, uJ) of X_k^2 = sum_K X(K, uI)^T X(K, uJ), K = uI first and K = T - 1, where NL of the
+        // four matrix instructions suffice (X is zero from index rank on), last.
+        // On the diagonal the part K = uI needs nobody else's tile: it is multiplied ahead of the barrier (calls of
+        // 8192 rows, us: p = 20 168.2 against 170.5, p = 48 389 against 401, p = 60 480 against 489).  Returns true
+        // when the loop is over.
         auto step = [&](auto kind, auto nl, const double* cu, double* nx) __attribute__((always_inline)) -> bool {
           constexpr int KIND = decltype(kind)::value, NL = decltype(nl)::value;
           constexpr bool DIAG = KIND != OFF_DIAGONAL;
@@ -972,7 +973,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       }
       __syncthreads();
     }
-    // ---- Z = (I - P) R (nxt): A operand = I - P (symmetric), B operand = R from global -------
+    // ---- Z = (I - P) R (nxt): A operand = I - P (symmetric), B operand = R ------------------
     for (int f = wave; f < TT; f += NW) {
       const int fI = f / T, fJ = f % T;
       v4d acc = {0.0, 0.0, 0.0, 0.0};
