@@ -57,39 +57,41 @@ def test_the_purification_is_scaled_by_the_trace_itself(p, m, lam, seed, noise):
     compare(*got, K, m, lam, 5)
 
 
-@pytest.mark.parametrize("lam", [1.0, 100.0])
-@pytest.mark.parametrize("p,blocks", [(8, 1), (16, 1), (20, 1), (40, 1), (60, 1), (20, 2), (60, 2)])
-def test_close_pairs_of_an_exact_matrix_against_the_jacobi_solver(p, blocks, lam):
+# (a = 4 at p >= 40 with lambda = 1 has gaps of 1e-6, where the bound says nothing)
+@pytest.mark.parametrize("p,blocks,a,lam", [(p, k, 2.0, lam) for lam in (1.0, 100.0) for p, k in (
+    (8, 1), (16, 1), (20, 1), (40, 1), (60, 1), (10, 2), (20, 2), (40, 4), (60, 2))] + [
+    (16, 1, 4.0, 1.0), (20, 1, 4.0, 1.0), (20, 1, 4.0, 100.0), (40, 1, 4.0, 100.0), (60, 1, 4.0, 100.0), (60, 2, 4.0, 100.0)])
+def test_close_pairs_of_an_exact_matrix_against_the_jacobi_solver(p, blocks, a, lam):
     """K in fp64: every gradient has a pivot, and pairs closer than the solver lets the weights stand for the
-    trace.  The same K in front of both solvers; bounds as above."""
+    trace.  Every tile count of every mode.  The same K in front of both solvers; bounds as above."""
     from paper_2302_05865_amd import FlagAggregator
-    announce("close pairs", p, blocks, lam)
-    n, m, r = 400, 5 if p > 8 else 3, np.random.default_rng(p + blocks)
-    x = (r.standard_normal((p, n)) * 0.5 + r.standard_normal((1, n))).astype(np.float32)
-    copies = r.permutation(p // blocks)[:p // blocks // 3]
+    announce("close pairs", p, blocks, a, lam)
+    n, m, r = 400, 5 if p > 10 else 3, np.random.default_rng(p + blocks)
+    G = (r.standard_normal((p, n)) * 0.5 + r.standard_normal((1, n))).astype(np.float32)
+    copies = r.permutation(p // blocks)[:max(2, p // blocks // 3)]
     for b in range(blocks):
         v = np.float32(r.standard_normal(n))
         for i in copies:
-            x[i * blocks + b] = v + np.float32(5e-4) * np.float32(r.standard_normal(n))
-    G, got = to_device(x), []
-    for solver in ("auto", STAND_BY[p > 16]):
-        agg = FlagAggregator(n_max=n, p_max=64, solver=solver)
+            G[i * blocks + b] = v + np.float32(5e-4) * np.float32(r.standard_normal(n))
+    G, got = to_device(G), []
+    for solver in ("auto", STAND_BY[p > 16 or blocks > 1]):
+        agg = FlagAggregator(n_max=n, p_max=64, exponent_a=a, solver=solver)
         if blocks > 1:
             agg.fa_aggregate_grouped(G, [blocks] * (p // blocks), m, lam, 5, 0.0)
         else:
             agg.fa_aggregate(G, m, lam, 5, 0.0)
         got.append(agg.fa_get_info())
         agg.close()
-    a, j = got
-    s = np.diag(a.K)
+    x, j = got
+    s = np.diag(x.K)
     both = s[:, None] + s[None]
-    near = np.min(((both - 2 * a.K) / both)[~np.eye(p, dtype=bool)])
+    near = np.min(((both - 2 * x.K) / both)[~np.eye(p, dtype=bool)])
     bound = 4 * p * 2.3e-16 / near / j.eigengap
-    agree = [np.max(np.abs(a.objective - j.objective) / j.objective),
-             np.linalg.norm(a.K @ (a.c - j.c) / np.sqrt(s)) / np.linalg.norm(a.K @ j.c / np.sqrt(s))]
-    print(p, blocks, lam, a.rank, j.rank, a.sweeps, "near %.1e gap %.1e bound %.1e" % (near, j.eigengap, bound),
+    agree = [np.max(np.abs(x.objective - j.objective) / j.objective),
+             np.linalg.norm(x.K @ (x.c - j.c) / np.sqrt(s)) / np.linalg.norm(x.K @ j.c / np.sqrt(s))]
+    print(p, blocks, lam, x.rank, j.rank, x.sweeps, "near %.1e gap %.1e bound %.1e" % (near, j.eigengap, bound),
           ["%.1e" % g for g in agree])
-    assert a.status == 0 and j.status == 0 and a.sweeps != j.sweeps and a.rank == j.rank == p
+    assert x.status == 0 and j.status == 0 and x.sweeps != j.sweeps and x.rank == j.rank == p
     assert near < 1e-6 and max(agree) <= bound < 0.1
 
 
