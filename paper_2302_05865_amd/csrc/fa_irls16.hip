@@ -677,8 +677,8 @@ __device__ int solve(const double* __restrict__ Kg, int p, int m, int iters, dou
           // ones' distances from 1, up to the squares (1.04).
           // A sum clearly below zero has eigenvalues outside [0, 1], where neither map keeps an order.
           if (s >= -1e-9 && fabs(dt) < 0.25) {
-            A = fmax(0.5 * (1.04 * s + dt), 1e-15);
-            B = fmax(0.5 * (1.04 * s - dt), 1e-15);
+            A = fmax(0.5 * (1.04 * fabs(s) + dt), 1e-15);
+            B = fmax(0.5 * (1.04 * fabs(s) - dt), 1e-15);
             conv = true;
           }
           if (conv || s < 1e-12) { k_end = k; break; }
