@@ -2,7 +2,8 @@
 weighted-PCA matrix M its weight times |r_i - r_j|^2 / D_ij^2, and that ratio is 1 only while
 R^T R is the Gram matrix to the accuracy of D_ij^2.  With entries good to 1e-10, as the
 bf16 matrix core makes them, the factorisation of near copies stops short and the ratio is
-anything up to hundreds: the purification has to be scaled by the trace of M itself."""
+anything up to hundreds: the purification has to be scaled by the trace of M itself.  Scaled by the weights' sum, 17 of
+the 25 chosen matrices ended in the stand-by and 5 on another projector than the leading one."""
 import numpy as np
 import pytest
 
@@ -34,7 +35,7 @@ def compare(x, j, K, m, lam, iters):
     assert got[0] <= bound and got[1] <= bound and got[2] <= bound
 
 
-# in each of these the sum of the weights is off by 1.1 to 30 times in one of the five solves at least
+# in each of these trace M is 1.5 to 9 times the sum of the weights in one of the five solves at least
 WIDE = [(20, 2, 4.0, 15, 1e-10), (20, 2, 4.0, 18, 1e-10), (20, 2, 1.0, 36, 1e-10), (20, 2, 4.0, 37, 5e-10),
         (20, 2, 1.0, 38, 5e-10), (20, 2, 4.0, 39, 5e-10), (42, 1, 1.0, 3, 5e-10), (42, 1, 4.0, 8, 1e-10),
         (42, 1, 4.0, 11, 5e-10), (42, 1, 1.0, 19, 1e-10), (60, 2, 4.0, 202, 5e-10), (60, 2, 1.0, 358, 5e-10),
