@@ -212,7 +212,7 @@ extern "C" fa_status fa_aggregate(fa_ctx* c, const void* G, int64_t ldg, int p, 
                      prof ? &c->tm[2] : nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
   // S6: out = G c
-  if (fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out, c->combine_max_blocks, st,
+  if (fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out, c->num_cus, st,
                         prof ? &c->tm[3] : nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
   if (prof) c->ev_recorded = 1;
@@ -312,7 +312,7 @@ extern "C" fa_status fa_aggregate_static(const void* G, int64_t ldg, int p, int6
                      cfg.exponent_a, cd, info_d, gws, cfg.solver, cfg.wide_spin_budget, nullptr,
                      st, nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
-  if (fa_launch_combine(G, ldg, p, n, dtype, FA_WORKER_MAJOR, cd, 1, out, 1 << 20, st,
+  if (fa_launch_combine(G, ldg, p, n, dtype, FA_WORKER_MAJOR, cd, 1, out, sd.blocks, st,
                         nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
   return FA_OK;
@@ -368,7 +368,7 @@ extern "C" fa_status fa_aggregate_restream(fa_ctx* c, const void* G, int64_t ldg
                                    c->cfg.pair_tol, c->cfg.exponent_a, c->rs_d, st) != hipSuccess)
       return FA_ERR_DEVICE;
   }
-  if (fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out, c->combine_max_blocks, st,
+  if (fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out, c->num_cus, st,
                         nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
   if (prof) c->ev_recorded_r = 1;
@@ -547,7 +547,7 @@ extern "C" fa_status fa_aggregate_arrived(fa_ctx* c, const void* G, int64_t ldg,
                      c->cfg.wide_spin_budget, nullptr, st, nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
   if (fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out,
-                        c->combine_max_blocks, st, nullptr) != hipSuccess)
+                        c->num_cus, st, nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
   c->last_nparts = 0;
   c->has_solution = 1;
@@ -591,7 +591,7 @@ extern "C" fa_status fa_combine(fa_ctx* c, const void* G, int64_t ldg, int p, in
   if (hipStreamSynchronize(c->stream) != hipSuccess) return FA_ERR_DEVICE;
   if (hipMemcpy(c->cd, c_host, sizeof(double) * p, hipMemcpyHostToDevice) != hipSuccess)
     return FA_ERR_DEVICE;
-  if (fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out, c->combine_max_blocks,
+  if (fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out, c->num_cus,
                         c->stream, nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
   return FA_OK;
@@ -641,7 +641,7 @@ extern "C" fa_status fa_aggregate_grouped(fa_ctx* c, const void* G, int64_t ldg,
                              c->cfg.wide_spin_budget, st) != hipSuccess)
     return FA_ERR_DEVICE;
   if (fa_launch_combine(G, ldg, q, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out,
-                        c->combine_max_blocks, st, nullptr) != hipSuccess)
+                        c->num_cus, st, nullptr) != hipSuccess)
     return FA_ERR_DEVICE;
   // the host array may be reused as soon as this returns
   if (hipStreamSynchronize(st) != hipSuccess) return FA_ERR_DEVICE;
@@ -673,7 +673,7 @@ extern "C" fa_status fa_multikrum(fa_ctx* c, const void* G, int64_t ldg, int p, 
   if (fa_launch_krum(c->Kd, p, f, q, c->cd, scores, selected, st) != hipSuccess)
     return FA_ERR_DEVICE;
   if (fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out,
-                        c->combine_max_blocks, st, nullptr) != hipSuccess)
+                        c->num_cus, st, nullptr, c->cd + FA_P_MAX, q) != hipSuccess)
     return FA_ERR_DEVICE;
   c->last_nparts = nparts;
   if (ask) {
@@ -734,7 +734,7 @@ extern "C" fa_status fa_enqueue_kernel(fa_ctx* c, int which, const void* G, int6
   } else {
     if (!check_matrix_args(c, G, ldg, p, n) || !out || ((uintptr_t)out & 15u) != 0)
       return FA_ERR_ARG;
-    e = fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out, c->combine_max_blocks,
+    e = fa_launch_combine(G, ldg, p, n, c->cfg.dtype, c->cfg.layout, c->cd, 1, out, c->num_cus,
                           c->stream, nullptr);
   }
   return e == hipSuccess ? FA_OK : FA_ERR_DEVICE;

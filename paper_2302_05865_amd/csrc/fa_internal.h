@@ -155,10 +155,12 @@ hipError_t fa_launch_restream_weights(const fa_info* info_d, const double* Pd, i
                                       double lambda, double delta, double pair_tol,
                                       double exponent_a, fa_resume* rs, hipStream_t st);
 
-// K4: out = sum_i c[i*cstride] g_i.
+// K4: out = sum_i c[i*cstride] g_i.  cus: compute units.  skip (device, may be null): if *skip is not 0, columns whose
+// coefficient is 0 need not be read; nonzero: how many others there are then.
 hipError_t fa_launch_combine(const void* G, int64_t ldg, int p, int64_t n, int dtype, int layout,
-                             const double* c, int cstride, float* out, int max_blocks,
-                             hipStream_t st, const fa_ktime* tm);
+                             const double* c, int cstride, float* out, int cus,
+                             hipStream_t st, const fa_ktime* tm, const double* skip = nullptr,
+                             int nonzero = 0);
 
 // Y = G A, eight columns per pass over G (either layout): column a of Y at Y + a*ldy.
 hipError_t fa_launch_combine_multi(const void* G, int64_t ldg, int p, int64_t n, int dtype,

@@ -78,12 +78,14 @@ __device__ __forceinline__ uint4 load16_stream(const void* src) {
 }
 
 typedef uint32_t fa_u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void store16_through(float* dst, float4 r) {
-  const fa_u32x4 v = {__float_as_uint(r.x), __float_as_uint(r.y), __float_as_uint(r.z),
-                      __float_as_uint(r.w)};
+__device__ __forceinline__ void store16_through(float* dst, fa_u32x4 v) {
   // the trailing s_nop covers the wait states a VALU write of the data registers needs
   // after a store wider than 64 bits (the compiler cannot see inside the asm)
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 2" ::"v"(dst), "v"(v) : "memory");
+}
+__device__ __forceinline__ void store16_through(float* dst, float4 r) {
+  store16_through(dst, fa_u32x4{__float_as_uint(r.x), __float_as_uint(r.y), __float_as_uint(r.z),
+                                __float_as_uint(r.w)});
 }
 
 // 16 bytes of column `base` starting at element row0, zero-filled past row n.
@@ -839,22 +841,62 @@ __global__ __launch_bounds__(1024) void fa_gram_reduce_kernel(const double* __re
 // sum_i |c_i g_i|).  A thread's eight outputs are 32 bytes; stored as they are, each of its two
 // stores would leave every other 16 bytes of a line to the other one, so the wavefront turns
 // its 2 KiB of outputs round through LDS and stores two gap-free KiB instead.
+template <typename E, typename acc_t>
+__device__ __forceinline__ void combine_add(acc_t (&acc)[E::EPL], acc_t cc, const uint4& v) {
+  if constexpr (E::SIZE == 4) {
+    acc[0] += cc * (double)__uint_as_float(v.x);
+    acc[1] += cc * (double)__uint_as_float(v.y);
+    acc[2] += cc * (double)__uint_as_float(v.z);
+    acc[3] += cc * (double)__uint_as_float(v.w);
+  } else {
+    acc[0] = fmaf(cc, __uint_as_float(v.x << 16), acc[0]);
+    acc[1] = fmaf(cc, __uint_as_float(v.x & 0xffff0000u), acc[1]);
+    acc[2] = fmaf(cc, __uint_as_float(v.y << 16), acc[2]);
+    acc[3] = fmaf(cc, __uint_as_float(v.y & 0xffff0000u), acc[3]);
+    acc[4] = fmaf(cc, __uint_as_float(v.z << 16), acc[4]);
+    acc[5] = fmaf(cc, __uint_as_float(v.z & 0xffff0000u), acc[5]);
+    acc[6] = fmaf(cc, __uint_as_float(v.w << 16), acc[6]);
+    acc[7] = fmaf(cc, __uint_as_float(v.w & 0xffff0000u), acc[7]);
+  }
+}
+
 #ifndef FA_COMBINE_NL
 #define FA_COMBINE_NL 8
 #endif
-template <typename E>
+// LISTED: columns whose coefficient is 0 are left out if *skip is not 0 (see fa_combine_held_kernel).
+template <typename E, bool LISTED>
 __global__ __launch_bounds__(256) void fa_combine_kernel(const unsigned char* __restrict__ G,
                                                          int64_t ldg, int p, int64_t n,
-                                                         const double* __restrict__ c,
-                                                         int cstride, float* __restrict__ out) {
+                                                         const double* __restrict__ c, int cstride,
+                                                         const double* __restrict__ skip,
+                                                         float* __restrict__ out) {
   constexpr int EPL = E::EPL;
   constexpr int NL = FA_COMBINE_NL;   // columns in flight per thread
   typedef typename std::conditional<E::SIZE == 4, double, float>::type acc_t;
   __shared__ acc_t cs[FA_P_MAX + NL];
   __shared__ __attribute__((aligned(16))) float turn[E::SIZE == 2 ? 256 * 8 : 4];
-  if (threadIdx.x < FA_P_MAX + NL)
-    cs[threadIdx.x] = (int)threadIdx.x < p ? (acc_t)c[(int64_t)threadIdx.x * cstride] : (acc_t)0;
-  __syncthreads();
+  __shared__ int place[LISTED ? FA_P_MAX : 1], ncols;
+  if constexpr (LISTED) {
+    if (threadIdx.x < 64) {
+      const int i = threadIdx.x;
+      const double ci = i < p ? c[(int64_t)i * cstride] : 0.0;
+      const bool keep = i < p && !(*skip != 0.0 && ci == 0.0);
+      const uint64_t mask = __ballot(keep);
+      const int at = __popcll(mask & (((uint64_t)1 << i) - 1)), count = __popcll(mask);
+      cs[i] = (acc_t)0;
+      if (i < NL) cs[FA_P_MAX + i] = (acc_t)0;
+      place[i] = 0;
+      wave_lds_fence();
+      if (keep) { cs[at] = (acc_t)ci; place[at] = i; }
+      if (i == 0) ncols = count;
+    }
+    __syncthreads();
+    p = ncols;
+  } else {
+    if (threadIdx.x < FA_P_MAX + NL)
+      cs[threadIdx.x] = (int)threadIdx.x < p ? (acc_t)c[(int64_t)threadIdx.x * cstride] : (acc_t)0;
+    __syncthreads();
+  }
   const int64_t ngroups = (n + EPL - 1) / EPL;
   for (int64_t gbase = (int64_t)blockIdx.x * 256; gbase < ngroups;
        gbase += (int64_t)gridDim.x * 256) {
@@ -872,34 +914,21 @@ __global__ __launch_bounds__(256) void fa_combine_kernel(const unsigned char* __
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
           // columns past p re-read column p-1; their coefficient is zero
-          const int col = c0 + u < p ? c0 + u : p - 1;
+          const int at = c0 + u < p ? c0 + u : p - 1;
+          const int col = LISTED ? place[at] : at;
           v[u] = load16_stream(src + (int64_t)col * ldg * E::SIZE);
         }
       } else {
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
-          const int col = c0 + u < p ? c0 + u : p - 1;
+          const int at = c0 + u < p ? c0 + u : p - 1;
+          const int col = LISTED ? place[at] : at;
           v[u] = load16_guarded<E>(G + (int64_t)col * ldg * E::SIZE, row0, n);
         }
       }
 #pragma unroll
       for (int u = 0; u < NL; ++u) {
-        const acc_t cc = cs[c0 + u];
-        if constexpr (E::SIZE == 4) {
-          acc[0] += cc * (double)__uint_as_float(v[u].x);
-          acc[1] += cc * (double)__uint_as_float(v[u].y);
-          acc[2] += cc * (double)__uint_as_float(v[u].z);
-          acc[3] += cc * (double)__uint_as_float(v[u].w);
-        } else {
-          acc[0] = fmaf(cc, __uint_as_float(v[u].x << 16), acc[0]);
-          acc[1] = fmaf(cc, __uint_as_float(v[u].x & 0xffff0000u), acc[1]);
-          acc[2] = fmaf(cc, __uint_as_float(v[u].y << 16), acc[2]);
-          acc[3] = fmaf(cc, __uint_as_float(v[u].y & 0xffff0000u), acc[3]);
-          acc[4] = fmaf(cc, __uint_as_float(v[u].z << 16), acc[4]);
-          acc[5] = fmaf(cc, __uint_as_float(v[u].z & 0xffff0000u), acc[5]);
-          acc[6] = fmaf(cc, __uint_as_float(v[u].w << 16), acc[6]);
-          acc[7] = fmaf(cc, __uint_as_float(v[u].w & 0xffff0000u), acc[7]);
-        }
+        combine_add<E>(acc, cs[c0 + u], v[u]);
       }
     }
     float* dst = out + row0;
@@ -931,6 +960,196 @@ __global__ __launch_bounds__(256) void fa_combine_kernel(const unsigned char* __
           if (row0 + e < n) dst[e] = acc[e];
       }
     }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// K4 for large sets: the same sums (same order, same bits), but the outputs are held back on the chip and written
+// many tiles at a time.  A read stream with writes strewn in between is what bounds the kernel above: p = 32, bf16,
+// n = 124M takes 1147 us without its stores and 1510 with them, although 0.5 GB are written in 72.  Here one
+// workgroup per compute unit walks its tiles in step with the others, so that the whole chip reads for a while and
+// then writes for a while; the more is written at a time the better (with twice the loads in flight: every tile for
+// itself 1567 us; 12 KiB a wavefront 1512, 24 1449, 36 1370; with registers beside LDS 66 KiB 1332, 98 KiB 1295).
+//
+// A wavefront takes the tiles w, w + W, ... (64 lanes x 16 bytes of every column).  Loads run ahead of the sums
+// over the ends of columns and tiles: FA_HELD_SLOTS 16-byte slots a lane, one column of one tile each, each refilled as
+// soon as it is used.  24 KiB in flight a compute unit are the right amount; with more the reads get in each other's
+// way (5 / 6 / 8 / 10 / 14 slots, us: p = 32 bf16, n = 124M 1353 / 1279 / 1297 / 1345 / 1363, 1510 with the kernel
+// above; p = 15 fp32, n = 30M 254 / 261 / 269 / 276 / 280, 295 above; p = 64 fp32, n = 8M 288 / 261 / 275 / 283 / 281, 300
+// above, but n = 50M 1826 / 1727 / 1650 / 1668 / 1666, 1830 above).  Eight wavefronts are slower than four by 3 to 7 %
+// at 3 slots and more beyond.  Workgroups of one XCD (blockIdx mod 8) take neighbouring tiles: p = 15, n = 11.2M 113 -> 110 us
+// (14 slots), the others the same.  At p = 15, n = 11.2M the pass now takes 97-103 us, 104-114 above.
+//
+// RT tiles of a batch stay in registers, LT in LDS.  p <= 16: half the registers and three quarters of the LDS, so that the
+// solver of a set on another stream fits beside a workgroup, whose tiles are nobody else's; one batch is
+// still all of p = 15, n = 11.2M.  ENDS: most tiles that can end within FA_HELD_SLOTS columns.
+// skip (device, may be null): if *skip is not 0, columns whose coefficient is 0 are not read (Multi-Krum; only where
+// no gradient holds a NaN or an infinity, which 0 times it would carry over).
+#define FA_HELD_SLOTS 6
+#define FA_HELD_WAVES 4
+#define FA_HELD_MIN_COLS 5                         // at most two tiles end within FA_HELD_SLOTS columns
+
+// N tiles of H x 16 bytes a lane, each in registers of its own (an array would be indexed, and so go to scratch memory)
+template <int N, int H, int ID = 0>
+struct fa_held_tiles {
+  static constexpr int HALF = N / 2;
+  fa_held_tiles<HALF, H, ID> lower;
+  fa_held_tiles<N - HALF, H, ID + HALF> upper;
+  __device__ __forceinline__ void put(int i, fa_u32x4 x, fa_u32x4 y) {
+    if (i < HALF) lower.put(i, x, y);
+    else upper.put(i - HALF, x, y);
+  }
+  // the first `count` of them, `step` apart
+  __device__ __forceinline__ void write(int count, float* dst, int64_t step) const {
+    lower.write(count, dst, step);
+    if (count > HALF) upper.write(count - HALF, dst + HALF * step, step);
+  }
+};
+template <int H, int ID>
+struct fa_held_tiles<1, H, ID> {
+  fa_u32x4 a, b;
+  __device__ __forceinline__ void put(int, fa_u32x4 x, fa_u32x4 y) {
+    a = x;
+    if constexpr (H == 2) b = y;
+    asm volatile("" ::"n"(ID));        // each place a branch of its own: two merged ones would be one indexed store
+  }
+  __device__ __forceinline__ void write(int count, float* dst, int64_t) const {
+    if (count <= 0) return;
+    store16_through(dst, a);
+    if constexpr (H == 2) store16_through(dst + 256, b);
+  }
+};
+
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                          __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+template <typename E, int RT, int LT, int ENDS>
+constexpr size_t fa_held_lds_bytes() { return (size_t)FA_HELD_WAVES * (LT + ENDS) * 64 * E::EPL * sizeof(float); }
+
+template <typename E, int RT, int LT, int ENDS>
+__global__ __launch_bounds__(64 * FA_HELD_WAVES, FA_HELD_WAVES / 4 * (ENDS > 1 ? 2 : 1)) void fa_combine_held_kernel(
+    const unsigned char* __restrict__ G, int64_t ldg, int p, int64_t n, const double* __restrict__ c,
+    int cstride, const double* __restrict__ skip, float* __restrict__ out) {
+  constexpr int EPL = E::EPL, ROWS = 64 * EPL, H = ROWS / 256, S = FA_HELD_SLOTS;
+  typedef typename std::conditional<E::SIZE == 4, double, float>::type acc_t;
+  extern __shared__ __attribute__((aligned(16))) float held[];
+  __shared__ acc_t lcoef[FA_P_MAX];
+  __shared__ int64_t loff[FA_P_MAX];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+  // the columns that are read, in ascending order: lane k holds the k-th one's coefficient and place
+  int ncols;
+  {
+    const double ci = lane < p ? c[(int64_t)lane * cstride] : 0.0;
+    const bool some = skip != nullptr && *skip != 0.0;
+    const bool keep = lane < p && !(some && ci == 0.0);
+    const uint64_t mask = __ballot(keep);
+    ncols = __popcll(mask);
+    if (keep && wave == 0) {
+      const int at = __popcll(mask & (((uint64_t)1 << lane) - 1));
+      lcoef[at] = (acc_t)ci;
+      loff[at] = (int64_t)lane * ldg * E::SIZE;
+    }
+  }
+  __syncthreads();
+  if (ncols == 0) return;                        // (a selection is never empty)
+  const acc_t coef = lane < ncols ? lcoef[lane] : (acc_t)0;
+  const int64_t off = loff[lane < ncols ? lane : ncols - 1];
+  const int off_lo = (int)off, off_hi = (int)(off >> 32);
+  if (ncols < FA_HELD_MIN_COLS) ncols = FA_HELD_MIN_COLS;     // the last one again, times 0
+  auto column = [&](int k) -> int64_t {
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(off_hi, k) << 32) |
+                     (uint32_t)__builtin_amdgcn_readlane(off_lo, k));
+  };
+
+  const int64_t W = (int64_t)gridDim.x * FA_HELD_WAVES;
+  const int blk = (gridDim.x & 7) == 0 ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3))
+                                       : (int)blockIdx.x;
+  const int64_t w = (int64_t)blk * FA_HELD_WAVES + wave;
+  const int64_t ntiles = n / ROWS;
+  const int mine = (int)(w < ntiles ? (ntiles - w + W - 1) / W : 0);
+  acc_t acc[EPL];
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) acc[e] = (acc_t)0;
+
+  if (mine > 0) {
+    float* const kept = held + wave * (LT + ENDS) * ROWS;   // LT tiles, then those that go on to registers
+    const unsigned char* base = G + w * (ROWS * E::SIZE) + lane * 16;
+    const int64_t step = W * (ROWS * E::SIZE), out_step = W * ROWS;
+    int lt = 0, lc = 0;                                     // the next slot to load: tile, column
+    uint4 v[S];
+    // past the end the last tile is read again (its sums are dropped)
+#define FA_HELD_LOAD(s)                                                     \
+    do {                                                                    \
+      v[s] = load16_stream(base + column(lc));                              \
+      if (++lc == ncols) { lc = 0; if (lt + 1 < mine) { ++lt; base += step; } } \
+    } while (0)
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      FA_HELD_LOAD(s);
+      __builtin_amdgcn_sched_barrier(0);                    // in the order they are waited for
+    }
+    fa_held_tiles<RT, H> regs;
+    float* dst = out + w * ROWS + lane * 4;                 // first tile of the batch
+    int cc = 0, nb = 0, done = 0;                           // column; tiles of the batch; tiles summed
+    while (done < mine) {
+      const int nb0 = nb;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        combine_add<E>(acc, lane_value(coef, cc), v[s]);
+        FA_HELD_LOAD(s);
+        if (++cc == ncols) {
+          cc = 0;
+          // row order: fp32 lanes hold four rows, bf16 lanes eight, of which a store takes four
+          float* o = kept + (nb < LT ? nb : LT + (nb - nb0)) * ROWS + lane * EPL;
+          *reinterpret_cast<float4*>(o) = make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]);
+          if constexpr (EPL == 8)
+            *reinterpret_cast<float4*>(o + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) acc[e] = (acc_t)0;
+          ++nb;
+        }
+      }
+      if (nb == nb0) continue;
+      wave_lds_fence();
+      for (int j = nb0 < LT ? LT : nb0; j < nb; ++j) {      // (the first of them can only be nb0 or LT)
+        const float* from = kept + (LT + (j - nb0)) * ROWS + lane * 4;
+        const fa_u32x4 x = *reinterpret_cast<const fa_u32x4*>(from);
+        regs.put(j - LT, x, H == 2 ? *reinterpret_cast<const fa_u32x4*>(from + (H - 1) * 256) : x);
+      }
+      done += nb - nb0;
+      if (done >= mine || nb > LT + RT - ENDS) {
+        const int here = done > mine ? nb - (done - mine) : nb;    // what came of the last tile read again is dropped
+        for (int j = 0; j < here && j < LT; ++j, dst += out_step)
+#pragma unroll
+          for (int h = 0; h < H; ++h)
+            store16_through(dst + h * 256, *reinterpret_cast<const float4*>(kept + j * ROWS + h * 256 + lane * 4));
+        if (here > LT) {
+          regs.write(here - LT, dst, out_step);
+          dst += (here - LT) * out_step;
+        }
+        nb = 0;
+      }
+      wave_lds_fence();                                     // the reads above precede the next tiles' writes
+    }
+#undef FA_HELD_LOAD
+  }
+
+  // the rows that do not fill a tile: the wavefront that would be next
+  if (ntiles * ROWS < n && w == ntiles % W) {
+    const int64_t row0 = ntiles * ROWS + lane * EPL;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[e] = (acc_t)0;
+    for (int k = 0; k < ncols; ++k)
+      combine_add<E>(acc, lane_value(coef, k), load16_guarded<E>(G + column(k), row0, n));
+    for (int e = 0; e < EPL; ++e)
+      if (row0 + e < n) out[row0 + e] = (float)acc[e];
   }
 }
 
@@ -1159,7 +1378,8 @@ __global__ __launch_bounds__(256) void fa_combine_multi_kernel(
 // coefficients of out = G c are 1/q on the selected workers.  A distance's place in its row is
 // counted, one thread per distance, and the row's thread adds the first k up in order (an insertion
 // sort by one thread per worker took 13.6 us at p = 15 and 185 at p = 64; 4.6 and 28 now).
-// p <= 64; scores and selected may be host memory the device can write.
+// p <= 64; scores and selected may be host memory the device can write.  c[FA_P_MAX]: whether the columns that were not
+// selected may be left out of the aggregate (a finite K has no NaN and no infinity in any gradient).
 __global__ __launch_bounds__(1024) void fa_krum_kernel(const double* __restrict__ K, int p, int k,
                                                        int q, double* __restrict__ c,
                                                        double* __restrict__ scores,
@@ -1170,17 +1390,20 @@ __global__ __launch_bounds__(1024) void fa_krum_kernel(const double* __restrict_
   const int tid = threadIdx.x, j = tid & 63, i0 = tid >> 6;      // entries (i0 + 16 u, j)
   double x[PER];
   int pos[PER];
+  bool ok = true;
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     const int i = i0 + 16 * u;
     x[u] = 0.0;
     if (i < p && j < p) {
+      ok = ok && fabs(K[i * p + j]) <= 1.79e308;
       const double d = K[i * p + i] + K[j * p + j] - 2.0 * K[i * p + j];
       x[u] = d > 0.0 ? d : 0.0;
       dist[i][j] = x[u];
     }
   }
-  __syncthreads();
+  const int finite = __syncthreads_and(ok ? 1 : 0);
+  if (tid == 0) c[FA_P_MAX] = finite ? 1.0 : 0.0;
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     const int i = i0 + 16 * u;
@@ -1927,10 +2150,36 @@ hipError_t fa_launch_gap(const double* mlast, int N, fa_info* info_d, hipStream_
   return hipGetLastError();
 }
 
+// fa_combine_held_kernel of this storage type: `wide` is for more than FA_HELD_SLOTS columns
+template <typename E, int RT, int LT, int ENDS>
+static hipError_t launch_held_t(const void* G, int64_t ldg, int p, int64_t n, const double* c,
+                                int cstride, const double* skip, float* out, int cus, hipStream_t st,
+                                const fa_ktime* tm) {
+  FA_LAUNCH(tm, (fa_combine_held_kernel<E, RT, LT, ENDS>), dim3((unsigned)cus), dim3(64 * FA_HELD_WAVES),
+            (fa_held_lds_bytes<E, RT, LT, ENDS>()), st, (const unsigned char*)G, ldg, p, n, c, cstride, skip, out);
+  return hipGetLastError();
+}
+#define FA_HELD_NARROW_F32 ElemF32, 30, 26, 2
+#define FA_HELD_NARROW_BF16 ElemBF16, 15, 12, 2
+#define FA_HELD_WIDE_F32 ElemF32, 66, 37, 1
+#define FA_HELD_WIDE_BF16 ElemBF16, 33, 18, 1
+template <typename E, int RT, int LT, int ENDS>
+static hipError_t prepare_held_t() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_held_kernel<E, RT, LT, ENDS>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_held_lds_bytes<E, RT, LT, ENDS>());
+}
+
 template <typename E>
 static hipError_t prepare_e(int layout) {
   if (layout != FA_ROW_MAJOR) {
-    const hipError_t e = prepare_gram_e<E, false>();
+    hipError_t e = prepare_gram_e<E, false>();
+    if constexpr (E::SIZE == 4) {
+      if (e == hipSuccess) e = prepare_held_t<FA_HELD_NARROW_F32>();
+      if (e == hipSuccess) e = prepare_held_t<FA_HELD_WIDE_F32>();
+    } else {
+      if (e == hipSuccess) e = prepare_held_t<FA_HELD_NARROW_BF16>();
+      if (e == hipSuccess) e = prepare_held_t<FA_HELD_WIDE_BF16>();
+    }
     return e == hipSuccess ? prepare_proj_e<E>() : e;      // (the re-streaming schedule is worker-major only)
   }
   hipError_t e = prepare_gram_e<E, true>();
@@ -1955,9 +2204,21 @@ hipError_t fa_kernels_prepare(int dtype, int layout) {
   return dtype == FA_F32 ? prepare_e<ElemF32>(layout) : prepare_e<ElemBF16>(layout);
 }
 
+// Whether fa_combine_held_kernel takes an aggregate pass that reads `cols` worker-major columns.  From sixteen tiles a
+// wavefront on: below, the last tiles of some wavefronts and the one write at the end cost more than the writes in between do.
+// us, the kernel for small sets / this one: fp32 p = 15, n = 2M 19.3 / 23.5, 4M 37.8 / 38.0, 6M 57.4 / 54.1, 8M 79 / 70; p = 20
+// 3M 39.5 / 44.1, 6M 76.9 / 71.5; p = 64 2M 75 / 89, 4M 155 / 137; bf16 p = 32 4M 42.5 / 46.0, 8M 89 / 79.  Few columns leave a
+// wavefront little time for a tile: fp32 p = 5 4M 16.6 / 16.8, 20M 78.5 / 73.8, p = 7 8M 40.4 / 40.0, 20M 99 / 93; bf16 p = 8 30M 89.8 /
+// 90.6, 120M 393 / 394.
+static bool fa_combine_held_applies(int cols, int64_t n, int dtype, int cus) {
+  const int64_t tiles = n / (64 * (dtype == FA_F32 ? 4 : 8)) / ((int64_t)FA_HELD_WAVES * cus);   // per wavefront
+  if (cols >= 10) return tiles >= 16;
+  return dtype == FA_F32 && cols >= FA_HELD_MIN_COLS && tiles >= 32;
+}
+
 hipError_t fa_launch_combine(const void* G, int64_t ldg, int p, int64_t n, int dtype, int layout,
-                             const double* c, int cstride, float* out, int max_blocks,
-                             hipStream_t st, const fa_ktime* tm) {
+                             const double* c, int cstride, float* out, int cus,
+                             hipStream_t st, const fa_ktime* tm, const double* skip, int nonzero) {
   if (layout == FA_ROW_MAJOR) {
     const int ldr = (int)ldg;
     const size_t lds = fa_rows_lds_bytes(ldr, dtype == FA_F32 ? 4 : 2);
@@ -1974,14 +2235,27 @@ hipError_t fa_launch_combine(const void* G, int64_t ldg, int p, int64_t n, int d
     return hipGetLastError();
   }
   const int epl = dtype == FA_F32 ? 4 : 8;
+  if (fa_combine_held_applies(skip ? nonzero : p, n, dtype, cus)) {
+    const bool wide = (skip ? nonzero : p) > 16;
+    if (dtype == FA_F32)
+      return wide ? launch_held_t<FA_HELD_WIDE_F32>(G, ldg, p, n, c, cstride, skip, out, cus, st, tm)
+                  : launch_held_t<FA_HELD_NARROW_F32>(G, ldg, p, n, c, cstride, skip, out, cus, st, tm);
+    return wide ? launch_held_t<FA_HELD_WIDE_BF16>(G, ldg, p, n, c, cstride, skip, out, cus, st, tm)
+                : launch_held_t<FA_HELD_NARROW_BF16>(G, ldg, p, n, c, cstride, skip, out, cus, st, tm);
+  }
   const int64_t ngroups = (n + epl - 1) / epl;
   int64_t blocks = (ngroups + 255) / 256;
-  if (blocks > max_blocks) blocks = max_blocks;
-  if (dtype == FA_F32)
-    FA_LAUNCH(tm, (fa_combine_kernel<ElemF32>), dim3((unsigned)blocks), dim3(256), 0, st,
-              (const unsigned char*)G, ldg, p, n, c, cstride, out);
-  else
-    FA_LAUNCH(tm, (fa_combine_kernel<ElemBF16>), dim3((unsigned)blocks), dim3(256), 0, st,
-              (const unsigned char*)G, ldg, p, n, c, cstride, out);
+  if (blocks > (1 << 20)) blocks = 1 << 20;
+#define FA_X(E, L)                                                                                 \
+  FA_LAUNCH(tm, (fa_combine_kernel<E, L>), dim3((unsigned)blocks), dim3(256), 0, st,               \
+            (const unsigned char*)G, ldg, p, n, c, cstride, skip, out)
+  if (dtype == FA_F32) {
+    if (skip) FA_X(ElemF32, true);
+    else FA_X(ElemF32, false);
+  } else {
+    if (skip) FA_X(ElemBF16, true);
+    else FA_X(ElemBF16, false);
+  }
+#undef FA_X
   return hipGetLastError();
 }

@@ -1,0 +1,92 @@
+"""The aggregate pass for large sets (outputs held back on the chip), and the passes that leave out columns."""
+import numpy as np
+import pytest
+
+from gpu_util import announce
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _gradients(p, n, dtype, seed):
+    per = 4 if dtype == "f32" else 8
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    G = torch.zeros((p, -(-n // per) * per), device="cuda",
+                    dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    for i in range(p):
+        G[i, :n] = torch.randn(n, generator=gen, device="cuda")
+    return G[:, :n]
+
+
+def _wave_tiles(dtype):
+    """Rows that give every wavefront (four per compute unit) one tile."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    return units * 4 * 64 * (4 if dtype == "f32" else 8)
+
+
+# sixteen tiles a wavefront (thirty-two below ten columns) are the rule's line; a batch is 56 tiles (fp32, p <= 16),
+# 103 (fp32), 27 (bf16, p <= 16) and 51 (bf16): one tile short of it, all of it, one more, and two
+@pytest.mark.parametrize("dtype,p,rounds", [
+    ("f32", 5, 32), ("f32", 5, 57), ("f32", 6, 55), ("f32", 7, 112), ("f32", 9, 32), ("f32", 10, 16), ("f32", 15, 56),
+    ("f32", 16, 16), ("f32", 17, 16), ("f32", 17, 102), ("f32", 18, 103), ("f32", 19, 104), ("f32", 33, 16),
+    ("f32", 64, 17), ("bf16", 10, 16), ("bf16", 11, 26), ("bf16", 12, 27), ("bf16", 16, 54), ("bf16", 17, 50),
+    ("bf16", 23, 51), ("bf16", 32, 52), ("bf16", 47, 17), ("bf16", 64, 16)])
+def test_held_aggregate_has_the_small_kernels_bits(dtype, p, rounds):
+    """The same sums in the same order: pieces of the rows through the kernel for small sets give the same bits.
+    Rows short of a tile, of a round of all wavefronts and none, against 64 bits as well: one rounding of
+    the result (fp32), (p + 2) 2^-24 of the sum of magnitudes (bf16, added in fp32)."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("held aggregate", dtype, p, rounds)
+    full = rounds * _wave_tiles(dtype)
+    rng = np.random.default_rng(p)
+    for n in (full, full + 1, full + 64 * 8 * 5 + 13):
+        G = _gradients(p, n, dtype, p + n % 97)
+        c = rng.standard_normal(p)
+        agg = FlagAggregator(n_max=n, p_max=p, dtype=dtype)
+        out = torch.full((n + 8,), float("nan"), device="cuda")
+        agg.fa_combine(G, c, out[:n])
+        assert torch.isnan(out[n:]).all()
+        step = 1 << 20
+        for a in range(0, n, step):
+            x = G[:, a:a + step]
+            assert torch.equal(out[a:a + x.shape[1]], agg.fa_combine(x, c)), (n, a)
+        a = max(0, n - (1 << 18))
+        x, cd = G[:, a:].double(), torch.from_numpy(c).cuda()
+        want, mag = cd @ x, cd.abs() @ x.abs()
+        lim = 2.0 ** -24 * (want.abs() * 1.01 if dtype == "f32" else (p + 2) * mag)
+        assert bool(((out[a:n].double() - want).abs() <= lim + 1e-30).all())
+        agg.close()
+
+
+@pytest.mark.parametrize("dtype,p,n,f,q", [
+    ("f32", 5, 40_003, 1, 1), ("f32", 15, 300_007, 3, 10), ("f32", 15, 9_000_001, 3, 5), ("f32", 15, 9_000_001, 3, 10),
+    ("f32", 16, 4_194_304, 2, 14), ("f32", 40, 4_200_005, 5, 12), ("f32", 40, 4_200_005, 5, 17), ("f32", 64, 70_001, 3, 1),
+    ("bf16", 15, 9_000_001, 3, 11), ("bf16", 32, 9_000_007, 4, 28), ("bf16", 33, 131_073, 4, 9)])
+def test_multi_krum_without_the_other_columns(dtype, p, n, f, q):
+    """Columns that were not selected are not read: the bits of the pass that reads them all, times 0."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("krum, selected columns", dtype, p, n, f, q)
+    G = _gradients(p, n, dtype, p)
+    agg = FlagAggregator(n_max=n, p_max=p, dtype=dtype)
+    out, _, sel = agg.fa_multikrum(G, f, q)
+    assert sel.sum() == q
+    assert torch.equal(out, agg.fa_combine(G, sel / q))
+    agg.close()
+
+
+@pytest.mark.parametrize("n", [30_001, 9_000_001])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_multi_krum_carries_nan_and_inf_over(n, bad):
+    """A NaN or an infinity in any gradient, selected or not, reaches its coordinate of the result."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("krum, non-finite", n, bad)
+    G = _gradients(15, n, "f32", 3)
+    agg = FlagAggregator(n_max=n, p_max=15, dtype="f32")
+    for i in (0, 7, 14):
+        x = G.clone()[:, :n]
+        x = torch.nn.functional.pad(x, (0, -n % 4))[:, :n]
+        x[i, n // 2] = bad
+        out, _, sel = agg.fa_multikrum(x, 3, 6)
+        assert not torch.isfinite(out[n // 2])
+        assert torch.isfinite(out[:n // 2]).all() and torch.isfinite(out[n // 2 + 1:]).all()
+    agg.close()
