@@ -226,7 +226,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   constexpr int NSTEP = R / 16;
   constexpr int TILE = ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : T * 16 * CS;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (a tile's place is a scalar)
   unsigned char* lds = lds_all + wave * TILE;
   const int64_t wid = (int64_t)blockIdx.x * WAVES + wave;   // global wave index
   const int64_t nwaves = (int64_t)gridDim.x * WAVES;
@@ -269,10 +269,14 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   const int gb = 4 * ldr * E::SIZE;
   const int gs = (gb & 15) ? gb : gb + ((16 * E::SIZE - gb) & 255);
   const int tb = R * ldr * E::SIZE;        // bytes of a tile's span
+  // An instruction that would reach past the span starts earlier and reads some pieces again, into the same places:
+  // a lane that is switched off for a load costs the wavefront a wait for all loads before it.
+  auto shift = [&](int cg) { return cg * 1024 + 1024 <= tb ? cg * 1024 : tb > 1024 ? tb - 1024 : 0; };
+  const int lane16 = lane * 16 < tb ? lane * 16 : tb - 16;
   int pdst[NCG], prow[NCG], pcol[NCG];     // (scattered: row and column of a piece's first element)
 #pragma unroll
   for (int cg = 0; cg < NCG; ++cg) {
-    const int b = (cg * 64 + lane) * 16;
+    const int b = ST == FA_MEM_SCATTER ? (cg * 64 + lane) * 16 : shift(cg) + lane16;
     pdst[cg] = ROWS ? b + (b / gb) * (gs - gb) : 0;
     prow[cg] = ST == FA_MEM_SCATTER ? (b / E::SIZE) / ldr : 0;
     pcol[cg] = b / E::SIZE - prow[cg] * ldr;
@@ -292,10 +296,9 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
     }
     if constexpr (ROWS) {
       if ((tl + 1) * R > n) return;        // the ragged last tile: see store_tile_lds
-      const unsigned char* base = G + tl * tb + lane * 16;
+      const unsigned char* base = G + tl * tb;
 #pragma unroll
-      for (int cg = 0; cg < NCG; ++cg)
-        if ((cg * 64 + lane) * 16 < tb) regs[cg] = load16_stream(base + cg * 1024);
+      for (int cg = 0; cg < NCG; ++cg) regs[cg] = load16_stream(base + shift(cg) + (uint32_t)lane16);
       return;
     }
     const int64_t row0 = tl * R + lrow;
@@ -321,8 +324,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
         return;
       }
 #pragma unroll
-      for (int cg = 0; cg < NCG; ++cg)
-        if ((cg * 64 + lane) * 16 < tb) *reinterpret_cast<uint4*>(lds + pdst[cg]) = regs[cg];
+      for (int cg = 0; cg < NCG; ++cg) *reinterpret_cast<uint4*>(lds + pdst[cg]) = regs[cg];
       return;
     }
     if constexpr (ST == FA_MEM_SCATTER) {
