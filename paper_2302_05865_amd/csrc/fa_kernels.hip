@@ -602,10 +602,11 @@ __global__ __launch_bounds__(64 * WAVES) void fa_proj_kernel(
   }
 }
 
-// K4 for interleaved storage (G row by row, row pitch ldr elements): a workgroup copies the
+// The materialised basis Y = G A over interleaved storage (G row by row, row pitch ldr elements): a workgroup copies the
 // contiguous span of its 256 rows to LDS as it is, 16 bytes per lane per load and per LDS
 // write (no decoding of rows and columns on the way); then thread r adds up row r (fp64) and
-// the workgroup writes 256 consecutive outputs.  Rows of 16 k elements would put a wavefront's
+// the workgroup writes 256 consecutive outputs of each of up to MB columns of Y (column a, at out + a*ldo, uses the
+// coefficients c[i*cstride + a]).  Rows of 16 k elements would put a wavefront's
 // reads of element i on a few banks only, so the copy leaves 16 bytes free after every 256:
 // byte b of the span sits at b + 16 (b / 256).
 #define FA_ROWS_MULTI 8   // columns of a materialised basis per pass over row-major G
@@ -613,8 +614,6 @@ __host__ __device__ inline size_t fa_rows_lds_bytes(int ldr, int es) {
   const size_t span = (size_t)256 * ldr * es;
   return span + (span >> 8) * 16 + 16;
 }
-// MB > 1: up to MB combinations from one pass over G (column a of the output, at out + a*ldo,
-// uses the coefficients c[i*cstride + a]): the materialised basis Y = G A of row-major storage.
 template <typename E, int MB>
 __global__ __launch_bounds__(256) void fa_combine_rows_kernel(const unsigned char* __restrict__ G,
                                                               int ldr, int p, int64_t n,
@@ -665,27 +664,164 @@ __global__ __launch_bounds__(256) void fa_combine_rows_kernel(const unsigned cha
         if constexpr (E::SIZE == 4) return (double)*reinterpret_cast<const float*>(at);
         else return (double)bf16_bits_to_f32(*reinterpret_cast<const uint16_t*>(at));
       };
-      if constexpr (MB == 1) {
-        double a0 = 0.0, a1 = 0.0;
-        int i = 0;
-        for (; i + 1 < p; i += 2) {
-          a0 = fma(cs[0][i], elem(i), a0);
-          a1 = fma(cs[0][i + 1], elem(i + 1), a1);
+      double acc[MB];
+#pragma unroll
+      for (int a = 0; a < MB; ++a) acc[a] = 0.0;
+      for (int i = 0; i < p; ++i) {
+        const double t = elem(i);
+#pragma unroll
+        for (int a = 0; a < MB; ++a) acc[a] = fma(cs[a][i], t, acc[a]);
+      }
+#pragma unroll
+      for (int a = 0; a < MB; ++a)
+        if (a < ncols) out[(int64_t)a * ldo + row_base + r] = (float)acc[a];
+    }
+  }
+}
+
+// K4 for interleaved storage, one output: every wavefront has a tile of 64 rows to itself, as it lies in memory, in LDS
+// while the next one is on its way to its registers, and a lane adds up one row (even and odd
+// elements, in fp64).  NP: 1 KiB loads a tile (ceil(ldr es / 16), rounded up; a load that would reach past the tile starts earlier).
+// WHOLE: rows are whole 16-byte pieces, read as such.  The outputs of fa_rows_held tiles, one a lane, stay in registers
+// and are written together (see fa_combine_held_kernel), but for the shortest rows, where that costs more than it gives.
+// us, one workgroup per span of 256 rows and a barrier either side of its copy to LDS / this: fp32 p = 20, n = 3M 51.2 / 39.9;
+// p = 15, 10M 108 / 103; p = 5, 4M 23.3 / 16.5; p = 28, 4M 75 / 69; p = 40, 2M 66 / 50; p = 64, 4M 217 / 170; bf16 p = 32, 8M 98 / 86;
+// p = 7, 8M 52 / 29; p = 16, 8M 64 / 47; p = 64, 2M 50 / 44 (direct stores: p = 20 43.6, bf16 p = 32 97; 64 tiles held with
+// three workgroups a compute unit bf16 p = 23 39.2 instead of 34.4; fp32 p = 32 with three 88 instead of 81; bf16 p = 48 with
+// two 83 instead of 69).
+constexpr int fa_rows_held(int np) { return np < 3 ? 0 : np < 6 ? 32 : 64; }
+// workgroups a compute unit
+constexpr int fa_rows_wgs(int es, int np) {
+  return np < 2 ? 12 : np < 3 ? 7 : np < 6 ? 4 : np < 9 && es == 2 ? 3 : 2;
+}
+template <int N, int ID = 0>
+struct fa_held_rows {
+  static constexpr int HALF = N / 2;
+  fa_held_rows<HALF, ID> lower;
+  fa_held_rows<N - HALF, ID + HALF> upper;
+  __device__ __forceinline__ void put(int i, float x) {
+    if (i < HALF) lower.put(i, x);
+    else upper.put(i - HALF, x);
+  }
+  __device__ __forceinline__ void write(int count, float* dst, int64_t step) const {
+    lower.write(count, dst, step);
+    if (count > HALF) upper.write(count - HALF, dst + HALF * step, step);
+  }
+};
+template <int ID>
+struct fa_held_rows<1, ID> {
+  float a;
+  __device__ __forceinline__ void put(int, float x) {
+    a = x;
+    asm volatile("" ::"n"(ID));        // a branch of its own (as in fa_held_tiles)
+  }
+  __device__ __forceinline__ void write(int count, float* dst, int64_t) const {
+    if (count > 0) __builtin_nontemporal_store(a, dst);
+  }
+};
+template <int ID>
+struct fa_held_rows<0, ID> {};
+template <typename E, int NP, bool WHOLE>
+__global__ __launch_bounds__(256, fa_rows_held(NP) ? fa_rows_wgs(E::SIZE, NP) : 1) void fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G,
+                                                                    int ldr, int p, int64_t n,
+                                                                    const double* __restrict__ c, int cstride,
+                                                                    float* __restrict__ out) {
+  constexpr int EPL = E::EPL;
+  extern __shared__ __attribute__((aligned(16))) unsigned char tile[];
+  __shared__ __attribute__((aligned(16))) double cs[FA_P_MAX];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (threadIdx.x < FA_P_MAX) cs[threadIdx.x] = (int)threadIdx.x < p ? c[(int64_t)threadIdx.x * cstride] : 0.0;
+  __syncthreads();
+  const int tb = 64 * ldr * E::SIZE;
+  // byte b of a tile sits at b + 16 (b / 256)
+  unsigned char* const mine = tile + wave * (NP * 1088);
+  const int lane16 = lane * 16 < tb ? lane * 16 : tb - 16;
+  auto shift = [&](int k) { return k * 1024 + 1024 <= tb ? k * 1024 : tb > 1024 ? tb - 1024 : 0; };
+  int dst[NP];
+#pragma unroll
+  for (int k = 0; k < NP; ++k) {
+    const int b = shift(k) + lane16;
+    dst[k] = b + (b >> 8) * 16;
+  }
+  const int64_t ntiles = (n + 63) / 64, nwaves = (int64_t)gridDim.x * 4;
+  int64_t t = (int64_t)blockIdx.x * 4 + wave;
+  uint4 regs[NP];
+  auto load_tile = [&](int64_t tl) {
+    const unsigned char* base = G + tl * tb;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) regs[k] = load16_stream(base + shift(k) + (uint32_t)lane16);
+  };
+  const int r0 = lane * ldr * E::SIZE;                     // first byte of this lane's row
+  constexpr int HELD = fa_rows_held(NP);
+  fa_held_rows<HELD> held;
+  int nheld = 0;
+  float* dst_out = out + t * 64 + lane;                    // first tile of those held
+  if ((t + 1) * 64 <= n) load_tile(t);
+  for (; t < ntiles; t += nwaves) {
+    const int rows_here = (int)(n - t * 64 < 64 ? n - t * 64 : 64);
+    wave_lds_fence();                                      // the previous tile has been read
+    if (rows_here == 64) {
+#pragma unroll
+      for (int k = 0; k < NP; ++k) *reinterpret_cast<uint4*>(mine + dst[k]) = regs[k];
+    } else {
+      const int lim = rows_here * ldr;                     // elements that exist
+      for (int b = lane * 16; b < tb; b += 1024)
+        *reinterpret_cast<uint4*>(mine + b + (b >> 8) * 16) = load16_guarded<E>(G + t * tb, b / E::SIZE, lim);
+    }
+    wave_lds_fence();
+    const int64_t next = t + nwaves;
+    if ((next + 1) * 64 <= n) load_tile(next);
+    double a0 = 0.0, a1 = 0.0;
+    if constexpr (WHOLE) {
+      // (elements past p are multiplied by 0 only where the row has them: left out)
+#pragma unroll 2
+      for (int i = 0; i < p; i += EPL) {
+        const int b = r0 + i * E::SIZE;
+        const uint4 v = *reinterpret_cast<const uint4*>(mine + b + (b >> 8) * 16);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < EPL; e += 2) {
+          double x0, x1;
+          if constexpr (E::SIZE == 4) {
+            x0 = (double)__uint_as_float(w[e]);
+            x1 = (double)__uint_as_float(w[e + 1]);
+          } else {
+            x0 = (double)__uint_as_float(w[e >> 1] << 16);
+            x1 = (double)__uint_as_float(w[e >> 1] & 0xffff0000u);
+          }
+          if (i + e < p) a0 = fma(cs[i + e], x0, a0);
+          if (i + e + 1 < p) a1 = fma(cs[i + e + 1], x1, a1);
         }
-        if (i < p) a0 = fma(cs[0][i], elem(i), a0);
-        out[row_base + r] = (float)(a0 + a1);
-      } else {
-        double acc[MB];
-#pragma unroll
-        for (int a = 0; a < MB; ++a) acc[a] = 0.0;
-        for (int i = 0; i < p; ++i) {
-          const double t = elem(i);
-#pragma unroll
-          for (int a = 0; a < MB; ++a) acc[a] = fma(cs[a][i], t, acc[a]);
-        }
-#pragma unroll
-        for (int a = 0; a < MB; ++a)
-          if (a < ncols) out[(int64_t)a * ldo + row_base + r] = (float)acc[a];
+      }
+    } else {
+      auto elem = [&](int i) -> double {
+        const int b = r0 + i * E::SIZE;
+        const unsigned char* at = mine + b + (b >> 8) * 16;
+        if constexpr (E::SIZE == 4) return (double)*reinterpret_cast<const float*>(at);
+        else return (double)bf16_bits_to_f32(*reinterpret_cast<const uint16_t*>(at));
+      };
+      int i = 0;
+#pragma unroll 4
+      for (; i + 1 < p; i += 2) {
+        a0 = fma(cs[i], elem(i), a0);
+        a1 = fma(cs[i + 1], elem(i + 1), a1);
+      }
+      if (i < p) a0 = fma(cs[i], elem(i), a0);
+    }
+    if constexpr (HELD == 0) {
+      if (lane < rows_here) __builtin_nontemporal_store((float)(a0 + a1), out + t * 64 + lane);
+    } else {
+      if (rows_here == 64) {
+        held.put(nheld, (float)(a0 + a1));
+        ++nheld;
+      } else if (lane < rows_here) {
+        out[t * 64 + lane] = (float)(a0 + a1);             // the ragged last tile
+      }
+      if (nheld == HELD || next >= ntiles) {
+        held.write(nheld, dst_out, nwaves * 64);
+        dst_out += (int64_t)nheld * nwaves * 64;
+        nheld = 0;
       }
     }
   }
@@ -2185,10 +2321,14 @@ static hipError_t prepare_e(int layout) {
     return e == hipSuccess ? prepare_proj_e<E>() : e;      // (the re-streaming schedule is worker-major only)
   }
   hipError_t e = prepare_gram_e<E, true>();
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_rows_kernel<E, 1>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)fa_rows_lds_bytes(FA_P_MAX, 4));
+  if constexpr (E::SIZE == 4) {
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_rows_tiles_kernel<E, 16, true>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 16 * 1088);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_rows_tiles_kernel<E, 16, false>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 16 * 1088);
+  }
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_rows_kernel<E, FA_ROWS_MULTI>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -2206,6 +2346,30 @@ hipError_t fa_kernels_prepare(int dtype, int layout) {
   return dtype == FA_F32 ? prepare_e<ElemF32>(layout) : prepare_e<ElemBF16>(layout);
 }
 
+template <typename E>
+static hipError_t launch_combine_rows(const void* G, int ldr, int p, int64_t n, const double* c, int cstride,
+                                      float* out, int cus, hipStream_t st, const fa_ktime* tm) {
+  const int need = (ldr * E::SIZE + 15) / 16;
+  const bool whole = ldr * E::SIZE % 16 == 0;
+  const int64_t ntiles = (n + 63) / 64;
+#define FA_X(np)                                                                                     \
+  if (need <= np) {                                                                                  \
+    int64_t blocks = (int64_t)cus * fa_rows_wgs(E::SIZE, np);                                         \
+    if (blocks > (ntiles + 3) / 4) blocks = (ntiles + 3) / 4;                                        \
+    if (whole)                                                                                       \
+      FA_LAUNCH(tm, (fa_combine_rows_tiles_kernel<E, np, true>), dim3((unsigned)blocks), dim3(256),  \
+                4 * np * 1088, st, (const unsigned char*)G, ldr, p, n, c, cstride, out);             \
+    else                                                                                             \
+      FA_LAUNCH(tm, (fa_combine_rows_tiles_kernel<E, np, false>), dim3((unsigned)blocks), dim3(256), \
+                4 * np * 1088, st, (const unsigned char*)G, ldr, p, n, c, cstride, out);             \
+    return hipGetLastError();                                                                        \
+  }
+  FA_X(1) FA_X(2) FA_X(3) FA_X(4) FA_X(5) FA_X(6) FA_X(7) FA_X(8)
+  if constexpr (E::SIZE == 4) { FA_X(10) FA_X(12) FA_X(14) FA_X(16) }
+#undef FA_X
+  return hipErrorInvalidValue;
+}
+
 // Whether fa_combine_held_kernel takes an aggregate pass that reads `cols` worker-major columns.  From sixteen tiles a
 // wavefront on: below, the last tiles of some wavefronts and the one write at the end cost more than the writes in between do.
 // us, the kernel for small sets / this one: fp32 p = 15, n = 2M 19.3 / 23.5, 4M 37.8 / 38.0, 6M 57.4 / 54.1, 8M 79 / 70; p = 20
@@ -2221,21 +2385,9 @@ static bool fa_combine_held_applies(int cols, int64_t n, int dtype, int cus) {
 hipError_t fa_launch_combine(const void* G, int64_t ldg, int p, int64_t n, int dtype, int layout,
                              const double* c, int cstride, float* out, int cus,
                              hipStream_t st, const fa_ktime* tm, const double* skip, int nonzero) {
-  if (layout == FA_ROW_MAJOR) {
-    const int ldr = (int)ldg;
-    const size_t lds = fa_rows_lds_bytes(ldr, dtype == FA_F32 ? 4 : 2);
-    int64_t blocks = (n + 255) / 256;
-    // one workgroup per span of 256 rows (measured at p = 15, n = 11.2M: 124 us; eight
-    // persistent workgroups per compute unit 133 us, sixty-four 121-127 us)
-    if (blocks > 0x7fffffff) blocks = 0x7fffffff;
-    if (dtype == FA_F32)
-      FA_LAUNCH(tm, (fa_combine_rows_kernel<ElemF32, 1>), dim3((unsigned)blocks), dim3(256), lds,
-                st, (const unsigned char*)G, ldr, p, n, c, cstride, 1, out, (int64_t)0);
-    else
-      FA_LAUNCH(tm, (fa_combine_rows_kernel<ElemBF16, 1>), dim3((unsigned)blocks), dim3(256), lds,
-                st, (const unsigned char*)G, ldr, p, n, c, cstride, 1, out, (int64_t)0);
-    return hipGetLastError();
-  }
+  if (layout == FA_ROW_MAJOR)
+    return dtype == FA_F32 ? launch_combine_rows<ElemF32>(G, (int)ldg, p, n, c, cstride, out, cus, st, tm)
+                           : launch_combine_rows<ElemBF16>(G, (int)ldg, p, n, c, cstride, out, cus, st, tm);
   const int epl = dtype == FA_F32 ? 4 : 8;
   if (fa_combine_held_applies(skip ? nonzero : p, n, dtype, cus)) {
     const bool wide = (skip ? nonzero : p) > 16;

@@ -1,0 +1,61 @@
+"""The aggregate pass over interleaved storage, at the edges of its tiles, pitches, types and batches."""
+import numpy as np
+import pytest
+
+from gpu_util import announce
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _check(p, pitch, n, dtype, rng):
+    """The places between the rows hold NaN and reach nothing; fp64 sums of exact values, one fp32 rounding of the
+    result (2^-24 of it, and of the sum of magnitudes at most p 2^-53 from the order of the additions)."""
+    from paper_2302_05865_amd import FlagAggregator
+    gen = torch.Generator(device="cuda").manual_seed(p + n % 1013)
+    rows = torch.full((n, pitch), float("nan"), device="cuda",
+                      dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    step = 1 << 20
+    for a in range(0, n, step):
+        k = min(step, n - a)
+        rows[a:a + k, :p] = torch.randn((k, p), generator=gen, device="cuda").to(rows.dtype)
+    c = rng.standard_normal(p)
+    agg = FlagAggregator(n_max=n, p_max=p, dtype=dtype, layout="row_major")
+    out = torch.full((n + 8,), float("nan"), device="cuda")
+    agg.fa_combine(rows[:, :p], c, out[:n])
+    agg.close()
+    assert torch.isnan(out[n:]).all()
+    cd = torch.from_numpy(c).cuda()
+    for a in range(0, n, step):
+        x = rows[a:min(a + step, n), :p].double()
+        want, mag = x @ cd, x.abs() @ cd.abs()
+        lim = 2.0 ** -24 * 1.0001 * want.abs() + p * 2.0 ** -53 * mag + 1e-45
+        assert bool(((out[a:a + x.shape[0]].double() - want).abs() <= lim).all()), (p, pitch, n, a)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("p,pitch", [(1, 1), (1, 16), (3, 3), (4, 4), (5, 5), (7, 8), (8, 8), (9, 12), (15, 15), (15, 16),
+                                     (16, 16), (17, 17), (20, 20), (21, 24), (23, 23), (24, 24), (28, 28), (31, 32),
+                                     (32, 32), (33, 33), (40, 40), (41, 47), (48, 48), (49, 49), (52, 56), (57, 57),
+                                     (63, 64), (64, 64)])
+def test_rows_around_a_tile(p, pitch, dtype):
+    """Rows of whole 16-byte pieces and others, every number of loads a tile; a row, a tile, one short and one over,
+    less than a round of all wavefronts and a few rounds."""
+    announce("rows aggregate", p, pitch, dtype)
+    rng = np.random.default_rng(p)
+    for n in (1, 63, 64, 65, 255, 1000, 300_007):
+        _check(p, pitch, n, dtype, rng)
+
+
+@pytest.mark.parametrize("dtype,p,wgs,held", [("f32", 10, 4, 32), ("f32", 16, 4, 32), ("f32", 20, 4, 32), ("f32", 24, 2, 64),
+                                              ("f32", 37, 2, 64), ("bf16", 17, 4, 32), ("bf16", 32, 4, 32),
+                                              ("bf16", 47, 3, 64)])
+def test_rows_around_a_batch(p, wgs, held, dtype):
+    """The outputs a wavefront holds back (wgs workgroups of four a compute unit, held tiles of 64 rows): one tile
+    short of all, all, and one row more."""
+    announce("rows aggregate, batches", dtype, p, wgs, held)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    full = units * wgs * 4 * 64 * held
+    rng = np.random.default_rng(p)
+    for n in (full - 64, full, full + 1):
+        _check(p, p, n, dtype, rng)
