@@ -8,6 +8,7 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -52,11 +53,12 @@ def build(verbose: bool = True) -> str:
               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
               "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]
     os.makedirs(OBJ_DIR, exist_ok=True)
-    objs = []
-    for src, extra in SOURCES.items():
-        obj = os.path.join(OBJ_DIR, src.replace(".hip", ".o"))
-        _run(common + extra + ["-c", os.path.join(CSRC, src), "-o", obj], verbose)
-        objs.append(obj)
+    objs = [os.path.join(OBJ_DIR, src.replace(".hip", ".o")) for src in SOURCES]
+    with ThreadPoolExecutor(len(SOURCES)) as pool:      # (one compiler a file)
+        done = [pool.submit(_run, common + extra + ["-c", os.path.join(CSRC, src), "-o", obj], verbose)
+                for (src, extra), obj in zip(SOURCES.items(), objs)]
+        for job in done:
+            job.result()
     _run([hipcc_path(), "--offload-arch=gfx950", "-fno-gpu-rdc", "-shared", "-fPIC"] + objs +
          ["-o", LIB_PATH], verbose)
     return LIB_PATH

@@ -4,6 +4,7 @@
 
 #include <math.h>
 #include <pthread.h>
+#include <atomic>
 #include <new>
 #include <stdlib.h>
 #include <string.h>
@@ -44,6 +45,21 @@ struct fa_ctx {
   uint64_t arr_early;           // the gradients whose pairs are worked off ahead of the others' ...
   int arr_n_early;              // ... and how many there will be (negative: nothing landed yet)
 };
+
+// Launch attributes (dynamic LDS above the default limit) of the kernels for this storage, on the current device: they
+// last as long as the library's image there, so they are set once (a context took 0.1 ms for them each time).
+static const int kMaxDevices = 64;
+static hipError_t prepare_kernels(int dev, int dtype, int layout) {
+  static std::atomic<unsigned> done[kMaxDevices];
+  const unsigned bit = 1u << (2 * dtype + layout);
+  const bool known = dev >= 0 && dev < kMaxDevices;
+  if (known && (done[dev].load(std::memory_order_acquire) & bit)) return hipSuccess;
+  hipError_t e = fa_kernels_prepare(dtype, layout);
+  if (e == hipSuccess) e = fa_irls64_prepare();
+  if (e == hipSuccess) e = fa_gram_lp_prepare();
+  if (e == hipSuccess && known) done[dev].fetch_or(bit, std::memory_order_release);
+  return e;
+}
 
 static int elem_size(int dtype) { return dtype == FA_F32 ? 4 : 2; }
 
@@ -128,8 +144,7 @@ extern "C" fa_status fa_create(const fa_config* cfg, fa_ctx** out_ctx) {
     if (hipEventCreate(&c->tm_r[i].start) != hipSuccess ||
         hipEventCreate(&c->tm_r[i].stop) != hipSuccess) { fa_destroy(c); return FA_ERR_DEVICE; }
   // per-function launch attributes (large dynamic LDS) on this context's device
-  if (fa_kernels_prepare(cfg->dtype, cfg->layout) != hipSuccess || fa_irls64_prepare() != hipSuccess ||
-      fa_gram_lp_prepare() != hipSuccess) {
+  if (prepare_kernels(c->device, cfg->dtype, cfg->layout) != hipSuccess) {
     fa_destroy(c);
     return FA_ERR_DEVICE;
   }
@@ -243,7 +258,6 @@ static_assert(kStaticUsed <= FA_STATIC_SCRATCH_BYTES, "the static workspace is t
 static_assert(kOffK % 256 == 0 && kOffC % 8 == 0 && kOffGws % 16 == 0 && kOffInfo % 8 == 0,
               "alignment of the parts of the static workspace");
 
-constexpr int kMaxDevices = 64;
 struct StaticDev {
   unsigned char* base;   // device address of `scratch` on this GPU; null until looked up
   int blocks;            // Gram workgroups: min(compute units, kStaticBlocks)
@@ -266,9 +280,8 @@ static fa_status static_setup(int dev, StaticDev* out) {
     int cus = 0;
     if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        fa_kernels_prepare(FA_F32, FA_WORKER_MAJOR) != hipSuccess ||
-        fa_kernels_prepare(FA_BF16, FA_WORKER_MAJOR) != hipSuccess || fa_irls64_prepare() != hipSuccess ||
-        fa_gram_lp_prepare() != hipSuccess) {
+        prepare_kernels(dev, FA_F32, FA_WORKER_MAJOR) != hipSuccess ||
+        prepare_kernels(dev, FA_BF16, FA_WORKER_MAJOR) != hipSuccess) {
       st = FA_ERR_DEVICE;
     } else {
       g_static_dev[dev].blocks = cus > 0 && cus < kStaticBlocks ? cus : kStaticBlocks;

@@ -105,7 +105,7 @@ hipError_t fa_launch_irls_grouped(const double* Kd, int q, int nworkers, const i
                                   fa_info* info_d, double* gws, int solver, int spin_budget,
                                   hipStream_t st);
 // Launch attributes (dynamic LDS above the default limit) of every kernel that needs them, on
-// the current device (the first: of those for that storage type and order); called by fa_create.
+// the current device (the first: of those for that storage type and order); called once per device.
 hipError_t fa_kernels_prepare(int dtype, int layout);
 hipError_t fa_irls64_prepare(void);
 // One term of the objective, residual^(1/a), and the weight the majorisation step gives it,

@@ -111,10 +111,12 @@ __device__ __forceinline__ uint4 load16_guarded(const unsigned char* base, int64
   return v;
 }
 
-// how G lies in memory and goes to LDS: worker-major; interleaved as it is; interleaved, scattered;
-// interleaved as it is with at most four, at most eight columns in the last block of sixteen
-enum { FA_MEM_WORKER, FA_MEM_ROWS, FA_MEM_SCATTER, FA_MEM_ROWS_LAST4, FA_MEM_ROWS_LAST8 };
-constexpr bool fa_mem_rows(int st) { return st == FA_MEM_ROWS || st >= FA_MEM_ROWS_LAST4; }
+// how G lies in memory and goes to LDS: worker-major; interleaved as it is; interleaved, scattered
+enum { FA_MEM_WORKER, FA_MEM_ROWS, FA_MEM_SCATTER };
+// and, added to that: at most four, at most eight columns in the last block of sixteen; at most eight in all
+enum { FA_NARROW_LAST4 = 4, FA_NARROW_LAST8 = 8, FA_NARROW_ALL8 = 12 };
+constexpr int fa_mem(int st) { return st & 3; }
+constexpr int fa_narrow(int st) { return st & 12; }
 
 // a pass over some rows of some gradients, whose sums are added to K: which gradients its columns are,
 // where they are not simply the first p
@@ -195,10 +197,14 @@ __device__ __forceinline__ void unpack4(const unsigned char* src, double* x) {
 // With few columns in the last block most of what is multiplied for it is thrown away.  v_mfma_f64_4x4x4_4b
 // multiplies four pairs of blocks of four columns at the rate of the 16 x 16 instruction (18 cycles against 64),
 // block b of an operand being columns 4 b .. 4 b + 3: sixteen columns times four, in all four blocks, are one of
-// them (FA_MEM_ROWS_LAST4), times eight, in two blocks each and in turn, two (FA_MEM_ROWS_LAST8; with twelve columns
-// nothing is left of the gain).  The order of an entry's sums, and so its bits, are those of the other instruction.
-// Multi-Krum calls over 3 M rows (this pass, the aggregate's and 12 us between them), us: fp32 p = 20 173 -> 149,
-// 24 167 -> 153, 36 292 -> 251, 40 320 -> 301, 52 512 -> 457, 56 524 -> 472; bf16 152 -> 124, 153 -> 151, 238 -> 190,
+// them (FA_NARROW_LAST4), times eight, in two blocks each and in turn, two (FA_NARROW_LAST8; with twelve columns
+// nothing is left of the gain); and all pairs of at most eight columns in all are one, of the columns (0, 0, 1, 1) with
+// themselves four lanes on (FA_NARROW_ALL8).  The order of an entry's sums, and so its bits, are those of the other
+// instruction.  Worker-major columns that the block does not have are not loaded either.
+// This pass, us: worker-major fp32 p = 7 n = 10M 85 -> 47, 50M 414 -> 232, p = 18 1M 30 -> 18, p = 23 1M 31 -> 23, p = 36 500
+// thousand 34 -> 24, p = 56 900 thousand 83 -> 70; bf16 p = 23 1M 29.6 -> 23.0, p = 50 900 thousand 92 -> 68; interleaved
+// p = 7 10M 89 -> 54, bf16 8M 82 -> 52.  With the aggregate's and 12 us between them, interleaved, 3 M rows: fp32 p = 20 173 ->
+// 149, 24 167 -> 153, 36 292 -> 251, 40 320 -> 301, 52 512 -> 457, 56 524 -> 472; bf16 152 -> 124, 153 -> 151, 238 -> 190,
 // 305 -> 265, 348 -> 292, 364 -> 332.
 // LDS bytes of a tile of r interleaved rows, whatever their pitch (at most 16 t elements):
 constexpr int fa_rows_tile_bytes(int t, int es, int r) {
@@ -214,17 +220,19 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
                                                      fa_gram_cols cols) {
   // as the stand-by of the bf16 matrix-core pass: nothing to do unless that one overflowed
   if (gate != nullptr && *gate == 0) return;
-  constexpr bool ROWS = fa_mem_rows(ST);
-  constexpr int NB = ST == FA_MEM_ROWS_LAST4 ? 4 : ST == FA_MEM_ROWS_LAST8 ? 8 : 16;   // columns of the last block
+  constexpr bool ROWS = fa_mem(ST) == FA_MEM_ROWS, SCATTER = fa_mem(ST) == FA_MEM_SCATTER;
+  constexpr bool ALL8 = fa_narrow(ST) == FA_NARROW_ALL8;
+  constexpr int NB = fa_narrow(ST) == FA_NARROW_LAST4 ? 4 : fa_narrow(ST) == FA_NARROW_LAST8 ? 8 : 16;   // columns of the last block
   constexpr int NQ = NB / 4;
   constexpr int EPL = E::EPL;
   constexpr int LPC = 64 / CPL;            // lanes per column in one load instruction
   constexpr int R = LPC * EPL;             // rows per tile
-  constexpr int NCG = T * 16 / CPL;        // load instructions per tile
+  constexpr int COLS = ROWS || SCATTER ? T * 16 : ALL8 ? 8 : T * 16 - 16 + NB;   // columns that are loaded
+  constexpr int NCG = COLS / CPL;          // load instructions per tile
   constexpr int CS = R * E::SIZE + 16;     // LDS bytes per column (+16: bank spread)
   constexpr int NTP = LAST ? T : T * (T + 1) / 2;
   constexpr int NSTEP = R / 16;
-  constexpr int TILE = ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : T * 16 * CS;
+  constexpr int TILE = ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : COLS * CS;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (a tile's place is a scalar)
   unsigned char* lds = lds_all + wave * TILE;
@@ -276,15 +284,15 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   int pdst[NCG], prow[NCG], pcol[NCG];     // (scattered: row and column of a piece's first element)
 #pragma unroll
   for (int cg = 0; cg < NCG; ++cg) {
-    const int b = ST == FA_MEM_SCATTER ? (cg * 64 + lane) * 16 : shift(cg) + lane16;
+    const int b = SCATTER ? (cg * 64 + lane) * 16 : shift(cg) + lane16;
     pdst[cg] = ROWS ? b + (b / gb) * (gs - gb) : 0;
-    prow[cg] = ST == FA_MEM_SCATTER ? (b / E::SIZE) / ldr : 0;
+    prow[cg] = SCATTER ? (b / E::SIZE) / ldr : 0;
     pcol[cg] = b / E::SIZE - prow[cg] * ldr;
   }
 
   uint4 regs[NCG];
   auto load_tile = [&](int64_t tl) {
-    if constexpr (ST == FA_MEM_SCATTER) {
+    if constexpr (SCATTER) {
       const unsigned char* base = G + tl * tb;
       const int lim = (int)(n - tl * R < R ? n - tl * R : R) * ldr;   // elements that exist
 #pragma unroll
@@ -327,7 +335,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
       for (int cg = 0; cg < NCG; ++cg) *reinterpret_cast<uint4*>(lds + pdst[cg]) = regs[cg];
       return;
     }
-    if constexpr (ST == FA_MEM_SCATTER) {
+    if constexpr (SCATTER) {
 #pragma unroll
       for (int cg = 0; cg < NCG; ++cg) {
         if ((cg * 64 + lane) * EPL >= R * ldr) continue;
@@ -356,12 +364,13 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   // a column >= p reads whatever comes next in the tile's LDS (a row has at most 16 T elements, so
   // that is never past its end); it only reaches entries of its own row and column, which the
   // reduction does not look at.
+  // (at most eight columns in all: the first four twice, the others twice)
+  const int left16 = ALL8 ? (c16 >> 3) * 4 + (c16 & 3) : c16;
   const unsigned char* src =
-      ROWS ? lds + kq * gs + c16 * E::SIZE : lds + c16 * CS + 4 * kq * E::SIZE;
+      ROWS ? lds + kq * gs + left16 * E::SIZE : lds + left16 * CS + 4 * kq * E::SIZE;
   auto operand = [&](int t, int tt, double* x) {
     if constexpr (ROWS) {
-      const unsigned char* at =
-          src + t * (4 * gs) + (tt * 16 + (NB < 16 && tt == T - 1 ? (c16 & (NB - 1)) - c16 : 0)) * E::SIZE;
+      const unsigned char* at = src + t * (4 * gs) + (tt * 16 + (NB < 16 && tt == T - 1 ? (c16 & (NB - 1)) - c16 : 0)) * E::SIZE;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if constexpr (E::SIZE == 4)
@@ -370,7 +379,7 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
           x[j] = (double)bf16_bits_to_f32(*reinterpret_cast<const uint16_t*>(at + j * ldr * 2));
       }
     } else {
-      unpack4<E>(src + tt * 16 * CS + 16 * t * E::SIZE, x);
+      unpack4<E>(src + (tt * 16 + (NB < 16 && tt == T - 1 ? (c16 & (NB - 1)) - c16 : 0)) * CS + 16 * t * E::SIZE, x);
     }
   };
 
@@ -395,6 +404,10 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
       for (int tt = 0; tt < T; ++tt) operand(tn, tt, xn[tt]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
+        if constexpr (ALL8) {
+          accl[0][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(xc[0][j], row_ror<0x124>(xc[0][j]), accl[0][0], 0, 0, 0);
+          continue;
+        }
         if constexpr (NB < 16) {
           const double y = xc[T - 1][j];
           double z = 0.0;
@@ -438,7 +451,11 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
       end += T - a;
       if (NB < 16 && tp == end) narrow = a;
     }
-    if (narrow >= 0) {
+    if constexpr (ALL8) {
+      // the same places: block b of the left operand is the columns of left16, the right one's are four lanes on
+      const int row = (c16 >> 3) * 4 + kq, from = __builtin_amdgcn_mov_dpp(c16, 0x124, 0xf, 0xf, false);
+      red[wave * 256 + (row >> 2) * 64 + (row & 3) * 16 + (from >> 3) * 4 + (from & 3)] = accl[0][0];
+    } else if (narrow >= 0) {
       // entry i of lane (i, 4 b + j) belongs to column 4 b + i of the left operand and to the right one's of
       // this lane; the places of columns that the block does not have stay as they are, nobody reads them
 #pragma unroll
@@ -1909,7 +1926,7 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
   constexpr int R = (64 / CPL) * E::EPL;
   constexpr int CS = R * E::SIZE + 16;
   constexpr size_t tile_bytes =
-      fa_mem_rows(ST) ? fa_rows_tile_bytes(T, E::SIZE, R) : (size_t)T * 16 * CS;
+      fa_mem(ST) == FA_MEM_ROWS ? fa_rows_tile_bytes(T, E::SIZE, R) : (size_t)T * 16 * CS;
   static_assert(WAVES * tile_bytes <= 160 * 1024, "LDS tiles of one workgroup must fit a CU");
   // more than half of the CU's 160 KiB, so that no second workgroup fits beside this one
   const size_t lds_bytes = WAVES * tile_bytes > 84 * 1024 ? WAVES * tile_bytes : 84 * 1024;
@@ -1932,53 +1949,51 @@ static hipError_t launch_gram_t(const void* G, int64_t ldg, int p, int64_t n, in
 
 template <typename E, bool ROWS>
 static hipError_t launch_gram_e(const void* G, int64_t ldg, int p, int64_t n, int max_blocks,
-                                double* partials, int* nparts, hipStream_t st,
+                                double* partials, int* nparts, hipStream_t st_,
                                 const fa_ktime* tm, const int* gate,
                                 const fa_gram_cols& cols = fa_gram_cols{}, bool last = false) {
+  constexpr int BASE = ROWS ? FA_MEM_ROWS : FA_MEM_WORKER;
   switch ((p + 15) / 16) {
-#define FA_X(t, cpl, w)                                                                        \
-    case t:                                                                                    \
-      if constexpr (!ROWS && t > 1)                                                            \
-        if (last)                                                                              \
-          return launch_gram_t<t, cpl, E, w, FA_MEM_WORKER, true>(G, ldg, p, n, max_blocks,     \
-                                                                 partials, nparts, st, tm,     \
-                                                                 gate, cols);                  \
-      if constexpr (ROWS && t == 1)                                                            \
-        if (n >= FA_SCATTER_MIN_ROWS)                                                          \
-          return launch_gram_t<t, cpl, E, w, FA_MEM_SCATTER>(G, ldg, p, n, max_blocks,          \
-                                                            partials, nparts, st, tm, gate,    \
-                                                            cols);                             \
-      if constexpr (ROWS && t > 1) {                                                           \
-        if (p <= 16 * t - 12)                                                                  \
-          return launch_gram_t<t, cpl, E, w, FA_MEM_ROWS_LAST4>(G, ldg, p, n, max_blocks,       \
-                                                               partials, nparts, st, tm, gate, \
-                                                               cols);                          \
-        if (p <= 16 * t - 8)                                                                   \
-          return launch_gram_t<t, cpl, E, w, FA_MEM_ROWS_LAST8>(G, ldg, p, n, max_blocks,       \
-                                                               partials, nparts, st, tm, gate, \
-                                                               cols);                          \
-      }                                                                                        \
-      return launch_gram_t<t, cpl, E, w, ROWS ? FA_MEM_ROWS : FA_MEM_WORKER>(                    \
-          G, ldg, p, n, max_blocks, partials, nparts, st, tm, gate, cols);
+#define FA_L(t, cpl, w, st, l)                                                                     \
+  return launch_gram_t<t, cpl, E, w, st, l>(G, ldg, p, n, max_blocks, partials, nparts, st_, tm, gate, cols)
+#define FA_X(t, cpl, w)                                                                            \
+    case t:                                                                                        \
+      if constexpr (t == 1) {                                                                      \
+        if (ROWS && n >= FA_SCATTER_MIN_ROWS) {                                                    \
+          if (p <= 8) FA_L(t, cpl, w, FA_MEM_SCATTER + FA_NARROW_ALL8, false);                      \
+          FA_L(t, cpl, w, FA_MEM_SCATTER, false);                                                  \
+        }                                                                                          \
+        if (p <= 8) FA_L(t, cpl, w, BASE + FA_NARROW_ALL8, false);                                  \
+      } else {                                                                                     \
+        if constexpr (!ROWS)                                                                       \
+          if (last) FA_L(t, cpl, w, BASE, true);                                                   \
+        if (p <= 16 * t - 12) FA_L(t, cpl, w, BASE + FA_NARROW_LAST4, false);                       \
+        if (p <= 16 * t - 8) FA_L(t, cpl, w, BASE + FA_NARROW_LAST8, false);                        \
+      }                                                                                            \
+      FA_L(t, cpl, w, BASE, false);
     FA_GRAM_TILINGS(FA_X)
 #undef FA_X
+#undef FA_L
   }
   return hipErrorInvalidValue;
 }
 
 template <typename E, bool ROWS>
 static hipError_t prepare_gram_e() {
+  constexpr int BASE = ROWS ? FA_MEM_ROWS : FA_MEM_WORKER;
   hipError_t e = hipSuccess;
 #define FA_SET(...)                                                                               \
   if (e == hipSuccess)                                                                           \
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(fa_gram_kernel<__VA_ARGS__>),          \
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 #define FA_X(t, cpl, w)                                                                          \
-  FA_SET(t, cpl, E, w, ROWS ? FA_MEM_ROWS : FA_MEM_WORKER, false)                                  \
-  if constexpr (!ROWS && t > 1) { FA_SET(t, cpl, E, w, FA_MEM_WORKER, true) }                     \
+  FA_SET(t, cpl, E, w, BASE, false)                                                              \
+  if constexpr (!ROWS && t > 1) { FA_SET(t, cpl, E, w, BASE, true) }                              \
+  if constexpr (t == 1) { FA_SET(t, cpl, E, w, BASE + FA_NARROW_ALL8, false) }                    \
   if constexpr (ROWS && t == 1) { FA_SET(t, cpl, E, w, FA_MEM_SCATTER, false) }                   \
-  if constexpr (ROWS && t > 1) { FA_SET(t, cpl, E, w, FA_MEM_ROWS_LAST4, false) }                 \
-  if constexpr (ROWS && t > 1) { FA_SET(t, cpl, E, w, FA_MEM_ROWS_LAST8, false) }
+  if constexpr (ROWS && t == 1) { FA_SET(t, cpl, E, w, FA_MEM_SCATTER + FA_NARROW_ALL8, false) }  \
+  if constexpr (t > 1) { FA_SET(t, cpl, E, w, BASE + FA_NARROW_LAST4, false) }                    \
+  if constexpr (t > 1) { FA_SET(t, cpl, E, w, BASE + FA_NARROW_LAST8, false) }
   FA_GRAM_TILINGS(FA_X)
 #undef FA_X
 #undef FA_SET
