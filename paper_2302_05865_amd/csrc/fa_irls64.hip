@@ -79,6 +79,11 @@ __device__ __forceinline__ double rows_sum(double t) {
   b = __builtin_amdgcn_permlane32_swap((unsigned)hi, (unsigned)hi, false, false);
   return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
 }
+// x, but computed from here on and not ahead of the loop that this stands in
+__device__ __forceinline__ int again(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -126,6 +131,18 @@ __device__ __forceinline__ v4d load_tile(const double* base, int I, int J, int l
   const v2d a = *reinterpret_cast<const v2d*>(t), b = *reinterpret_cast<const v2d*>(t + FA_HALF);
   return v4d{a[0], a[1], b[0], b[1]};
 }
+// the first NS entries of each lane only: with all four loaded, the registers of those without a use were given to
+// the next load, which then waited for this one
+template <int T, int NS>
+__device__ __forceinline__ v4d load_tile_first(const double* base, int I, int J, int lane) {
+  const double* t = base + (I * T + J) * FA_TILE + at(lane);
+  v4d v = {0.0, 0.0, 0.0, 0.0};
+  const v2d a = *reinterpret_cast<const v2d*>(t);
+  v[0] = a[0]; v[1] = a[1];
+  if constexpr (NS == 3) v[2] = t[FA_HALF];
+  if constexpr (NS == 4) { const v2d b = *reinterpret_cast<const v2d*>(t + FA_HALF); v[2] = b[0]; v[3] = b[1]; }
+  return v;
+}
 template <int T>
 __device__ __forceinline__ void store_tile(double* base, int I, int J, int lane, const v4d& v) {
   double* t = base + (I * T + J) * FA_TILE + at(lane);
@@ -142,6 +159,14 @@ __device__ __forceinline__ void store_tile_transposed(double* base, int I, int J
               at((c16 & 3) * 16 + q4);
 #pragma unroll
   for (int r = 0; r < 4; ++r) t[8 * r] = v[r];
+}
+// the tile as store_tile_transposed would have written it at (J, I), read instead of written
+template <int T>
+__device__ __forceinline__ v4d load_tile_transposed(const double* base, int I, int J, int lane) {
+  const int c16 = lane & 15, q4 = lane >> 4;
+  const double* t = base + (I * T + J) * FA_TILE + (c16 >> 3) * FA_HALF + ((c16 >> 2) & 1) +
+                    at((c16 & 3) * 16 + q4);
+  return v4d{t[0], t[8], t[16], t[24]};
 }
 // offset of entry e of lane l
 __device__ __forceinline__ int entry(int e, int l) { return (e >> 1) * FA_HALF + (e & 1) + at(l); }
@@ -583,23 +608,28 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   // matrix, if known
   double est = 0.0;
   bool have_est = false;
-  // Of this wavefront's tile: 1 / D^2 (0: no such term); in the Eq. 5 kernel with 1 / |g|^2 on the diagonal.
-  double d2i[4] = {0.0, 0.0, 0.0, 0.0};
-  if (mt >= 0) {
+  // Of this wavefront's tile: 1 / D^2 (0: no such term); in the Eq. 5 kernel with 1 / |g|^2 on the diagonal.  At T = 4
+  // they are loaded for each solve, beside a product: kept, they were spilled and came back one by one.
+  v4d d2i = {0.0, 0.0, 0.0, 0.0};
+  auto load_d2i = [&](int lane) {
+    if (coef > 0.0) d2i = load_tile<T>(D2I, uI, uJ, lane);
+    if (!GEN && uI == uJ) {
+      const double di = sm.dinv[16 * uI + (lane & 15)];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = 16 * uI + 4 * r + q4, j = 16 * uJ + c16;
-      d2i[r] = coef > 0.0 ? D2I[eidx<T>(i, j)] : 0.0;
-      if (!GEN && i == j) d2i[r] = sm.dinv[j] * sm.dinv[j];
+      for (int r = 0; r < 4; ++r) d2i[r] = isdiag[r] ? di * di : d2i[r];
     }
-  }
+  };
+  if (T < 4 && mt >= 0) load_d2i(lane);
 
   // Between two purifications stand four products and the residuals.  What is not on their path stays off
   // it: the trace of M is the sum of the weights (where it is, see FA_CLOSE_PAIR), C's diagonal is put in on the way to the first
   // product, M goes into X_0 from the accumulators, the steering wavefront plans the first step and takes
   // the gap's ends back beside the products, the residuals' chains overlap.  (With a phase and a barrier for
-  // each of these, ten solves at p = 20 took 206 us instead of 165, fifteen at p = 32 263 instead of 207.)
+  // each of these, ten solves at p = 20 took 206 us instead of 165, fifteen at p = 32 263 instead of 207; with what is
+  // said below at the residuals, the gap's ends and R, 157 and, 16 workers of two columns, 276 instead of 307.)
   for (int it = 0; it < iters; ++it) {
+    // (at T = 4 every address made of it used to be computed ahead of all solves, spilled, and waited for singly)
+    const int lane = T > 3 ? again(tid & 63) : tid & 63, c16 = lane & 15, q4 = lane >> 4;
     int k = 0, end = STEP_GO;
     // the steering wavefront's
     Plan pl;
@@ -776,7 +806,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         // On the diagonal the part K = uI needs nobody else's tile: it is multiplied ahead of the barrier (calls of
         // 8192 rows, us: p = 20 168.2 against 170.5, p = 48 389 against 401, p = 60 480 against 489).  Returns true
         // when the loop is over.
-        auto step = [&](auto kind, auto nl, const double* cu, double* nx) __attribute__((always_inline)) -> bool {
+        auto step = [&](auto kind, auto nl, const Step& st, const double* cu, double* nx) __attribute__((always_inline)) -> bool {
           constexpr int KIND = decltype(kind)::value, NL = decltype(nl)::value;
           constexpr bool DIAG = KIND != OFF_DIAGONAL;
           v4d y = {0.0, 0.0, 0.0, 0.0};
@@ -785,31 +815,44 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
             __builtin_amdgcn_sched_barrier(0);
           }
           __syncthreads();
-          const Step& st = sm.step[k & 1];
           const int e = st.end;
+          const double al = st.al, be = st.be, ga = st.ga;
+          __builtin_amdgcn_sched_barrier(0);             // ahead of the tiles: products wait for their own operands only
           v4d a[T], b[T];
 #pragma unroll
           for (int i = DIAG ? 1 : 0; i < T; ++i) {
             const int K = KIND == LAST_DIAGONAL ? i - 1 : i == T - 1 ? T - 1 : uI + i < T - 1 ? uI + i : uI + i - (T - 1);
-            a[i] = load_tile<T>(cu, K, uI, lane);
-            b[i] = DIAG ? a[i] : i == 0 ? x : load_tile<T>(cu, K, uJ, lane);
+            if (T > 2 && i == T - 1 && KIND != LAST_DIAGONAL) {
+              a[i] = load_tile_first<T, NL>(cu, K, uI, lane);
+              b[i] = DIAG ? a[i] : load_tile_first<T, NL>(cu, K, uJ, lane);
+            } else {
+              a[i] = load_tile<T>(cu, K, uI, lane);
+              b[i] = DIAG ? a[i] : i == 0 ? x : load_tile<T>(cu, K, uJ, lane);
+            }
           }
-          const double al = st.al, be = st.be, ga = st.ga;
           __builtin_amdgcn_sched_barrier(0);             // all of them ahead of the products
           end = __builtin_amdgcn_readfirstlane(e);
           if (end != STEP_GO) return true;
 #pragma unroll
           for (int i = DIAG ? 1 : 0; i < T; ++i)
             y = i == T - 1 && KIND != LAST_DIAGONAL ? mma_first<NL>(a[i], b[i], y) : mma4(a[i], b[i], y);
+          if constexpr (T < 3) {
+            // one such wavefront a SIMD: nothing of the rest in between the products (calls of 8192 rows, us: p = 20
+            // 162.0 against 165.4, p = 32 183.1 against 185.5; where wavefronts share a SIMD it takes turns from the others'
+            // products instead, p = 60 482 against 474)
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(2);
+          }
 #pragma unroll
           for (int r = 0; r < 4; ++r) x[r] = fma(be, y[r], DIAG ? fma(al, x[r], ga * live[r]) : al * x[r]);
           store_tile<T>(nx, uI, uJ, lane, x);
           if constexpr (!DIAG) store_tile_transposed<T>(nx, uI, uJ, lane, x);
+          if constexpr (T < 3) __builtin_amdgcn_s_setprio(0);
           ++k;
           return false;
         };
         auto steps_of = [&](auto kind, auto nl) __attribute__((always_inline)) {
-          while (!step(kind, nl, B0, B1) && !step(kind, nl, B1, B0)) {}
+          while (!step(kind, nl, sm.step[0], B0, B1) && !step(kind, nl, sm.step[1], B1, B0)) {}
         };
         auto run = [&](auto nl) __attribute__((always_inline)) {
           if (uI != uJ) {
@@ -973,31 +1016,32 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       }
       __syncthreads();
     }
-    // ---- Z = (I - P) R (nxt): A operand = I - P (symmetric), B operand = R ------------------
+    // ---- -Z = (P - I) R (nxt): A operand = P - I (symmetric), B operand = R (at T = 4 from RA: eight-byte reads of
+    // LDS, where sixteen-byte ones of global memory had the products wait, 7400 cycles against 4950) -----------------
     for (int f = wave; f < TT; f += NW) {
       const int fI = f / T, fJ = f % T;
       v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int K = 0; K < T; ++K) {
         v4d q = load_tile<T>(cur, K, fI, lane);
+        if (K == fI) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) q[r] = (K == fI && isdiag[r]) ? 1.0 - q[r] : -q[r];
-        acc = mma4(q, load_tile<T>(Rb, K, fJ, lane), acc);
+          for (int r = 0; r < 4; ++r) q[r] = isdiag[r] ? q[r] - 1.0 : q[r];
+        }
+        acc = mma4(q, RB_LDS ? load_tile<T>(Rb, K, fJ, lane) : load_tile_transposed<T>(RA, K, fJ, lane), acc);
       }
       store_tile<T>(nxt, fI, fJ, lane, acc);
     }
-    if (wave == SW && bk >= 0) {
-      take_back(0);
-      // an end that was folded could have come from either side of the fold: then further out
-      double e = hi * (double)yv;
-      if ((cap_in >> (lane & 1)) & 1) e = lane & 1 ? fmin(hi, fmax(e, 2.0 * est)) : fmin(e, 0.5 * est);
-      est = e;
-      have_est = true;
-    }
+    // (beside this product, the next and the residuals: all of it in front of this barrier was waited for)
+    if (wave == SW) take_back(bk > 4 ? bk - 4 : 0);
     __syncthreads();
     // ---- Gq = Z^T Z (symmetric; tile (I, J) = sum_K Z(K, I)^T Z(K, J)); its diagonal ----------
     v4d gq = {0.0, 0.0, 0.0, 0.0};
     if (mt >= 0) {
+      if constexpr (T > 3) {
+        load_d2i(lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int K = 0; K < T; ++K)
         gq = mma4(load_tile<T>(nxt, K, uI, lane), load_tile<T>(nxt, K, uJ, lane), gq);
@@ -1006,6 +1050,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         for (int r = 0; r < 4; ++r)
           if (isdiag[r]) sm.gd[16 * uI + c16] = gq[r];
       }
+    } else if (wave == SW) {
+      take_back(bk > 4 ? bk - 4 : 0);
     }
     __syncthreads();
     if constexpr (GRP) {
@@ -1021,98 +1067,148 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     double part = 0.0, wsum = 0.0;          // of the objective; of the next M's trace
     if (mt >= 0) {
       v4d cpn;
+      const int j = 16 * uJ + c16;
+      const double pair = (uI == uJ ? 1.0 : 2.0) * coef;
+      double rho[4] = {}, wv[4] = {};
       if constexpr (!GEN) {
         // |(I - P) r_j|^2 / |g_j|^2 = 1 - v_j on the diagonal, |z_i - z_j|^2 / D_ij^2 elsewhere; ordered
         // pairs: an off-diagonal tile stands for its mirror image too.  All four without a branch, so
-        // that their chains overlap.
-        const int j = 16 * uJ + c16;
-        const double gj = sm.gd[j], pair = (uI == uJ ? 1.0 : 2.0) * coef;
-        double rho[4], wv[4];
+        // that their chains overlap: what they read ahead of all of it, what they write behind (between them it
+        // cost a branch each: a solve's residuals took 2100 cycles at T = 2 and 5200 at T = 4, they take 1300 and 2950).
+        const double gj = sm.gd[j];
+        double gi[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) gi[r] = sm.gd[16 * uI + 4 * r + q4];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const bool diag = uI == uJ && isdiag[r];
-          const double num = diag ? gq[r] : fma(-2.0, gq[r], sm.gd[16 * uI + 4 * r + q4] + gj);
-          rho[r] = fmax(num, 0.0) * d2i[r];
+          const double off = fma(-2.0, gq[r], gi[r] + gj);
+          rho[r] = fmax(diag ? gq[r] : off, 0.0) * d2i[r];
           const double rsv = rsq2(rho[r] > 1e-300 ? rho[r] : 1e-300);
           const double f = d2i[r] > 0.0 ? (diag ? 1.0 : pair) : 0.0;
           wv[r] = fmin(rsv, rs_delta);
           part = fma(f, rho[r] * rsv, part);
           wsum = fma(f, wv[r], wsum);
           cpn[r] = diag ? 0.0 : -2.0 * coef * d2i[r] * wv[r];
+          wv[r] = d2i[r] > 0.0 ? wv[r] : 0.0;
+        }
+      } else if constexpr (GRP) {
+        // a block's numbers, the same at each of its columns; its term of the objective is counted at its
+        // first column (pair terms: at the blocks' first columns).  All four entries together, a wavefront goes on to its
+        // widest block (one by one, 16 blocks of two: 7450 cycles a solve, 3700 like this).
+        const int kj = sm.gc[j], fj = sm.gf[j];
+        const double gvj = sm.ginv[j];
+        int fi[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) fi[r] = sm.gf[16 * uI + 4 * r + q4];
+        double bot = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rho[r] = 0.0;
+#pragma unroll 1
+        for (int l = 0; __any(l < kj); ++l) {
+          const bool in = l < kj;
+          const int jl = fj + (in ? l : 0);
+          const double gj = sm.gd[jl];
+          double gi[4], x[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = fi[r] + (in ? l : 0), il = i < N ? i : N - 1;   // (a narrower block's neighbour: not used)
+            gi[r] = sm.gd[il];
+            x[r] = nxt[eidx<T>(il, jl)];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          bot += in ? gj : 0.0;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) rho[r] += in ? fma(-2.0, x[r], gi[r] + gj) : 0.0;
+        }
+        double tv[4];
+        bool use[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool diag = uI == uJ && isdiag[r];
+          use[r] = diag ? gvj > 0.0 : d2i[r] > 0.0;
+          const double v = diag ? bot * gvj : fmax(rho[r], 0.0) * d2i[r];
+          rho[r] = use[r] ? v : 0.0;
+        }
+        if (expo == 0.5) {
+          // Eq. 5: one reciprocal square root instead of two powers
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const double rsv = rsq2(rho[r] > 1e-300 ? rho[r] : 1e-300);
+            tv[r] = rho[r] * rsv;
+            wv[r] = rsv < rs_delta ? rsv : rs_delta;
+          }
+        } else {
+          // (rolled: once per solve, and inlined copies of pow() are long)
+#pragma unroll 1
+          for (int r = 0; r < 4; ++r) {
+            const double ro = r == 0 ? rho[0] : r == 1 ? rho[1] : r == 2 ? rho[2] : rho[3];
+            const double t = fa_term_pow(ro, expo), w = fa_weight_pow(ro, delta, expo);
+            if (r == 0) { tv[0] = t; wv[0] = w; }
+            else if (r == 1) { tv[1] = t; wv[1] = w; }
+            else if (r == 2) { tv[2] = t; wv[2] = w; }
+            else { tv[3] = t; wv[3] = w; }
+          }
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (uI == uJ && isdiag[r]) {
-            sm.rho[j] = rho[r];
-            sm.w[wi ^ 1][j] = d2i[r] > 0.0 ? wv[r] : 0.0;
-          }
+        for (int r = 0; r < 4; ++r) {
+          const bool diag = uI == uJ && isdiag[r];
+          const double f = !use[r] ? 0.0 : diag ? (j == fj ? 1.0 : 0.0) : 16 * uI + 4 * r + q4 == fi[r] ? pair : 0.0;
+          part = fma(f, tv[r], part);
+          wsum = fma(f, wv[r], wsum);
+          cpn[r] = !diag && use[r] ? -2.0 * coef * d2i[r] * wv[r] : 0.0;
+          wv[r] = use[r] ? wv[r] : 0.0;
+        }
       } else {
         // the general exponent: same places, powers instead of square roots (rolled: once per
         // solve, and inlined copies of pow() are long)
 #pragma unroll 1
         for (int r = 0; r < 4; ++r) {
-          const int i = 16 * uI + 4 * r + q4, j = 16 * uJ + c16;
+          const int i = 16 * uI + 4 * r + q4;
           const double gqr = r == 0 ? gq[0] : r == 1 ? gq[1] : r == 2 ? gq[2] : gq[3];
-          double rho = 0.0, scale = 0.0;       // residual; factor of its term in the objective
-          bool diag = i == j, use = false;
           const double di = r == 0 ? d2i[0] : r == 1 ? d2i[1] : r == 2 ? d2i[2] : d2i[3];
-          if constexpr (!GRP) {
-            if (diag) {
-              rho = gqr * sm.dinv[j] * sm.dinv[j];
-              use = sm.s[j] > 0.0;
-              scale = 1.0;
-            } else {
-              if (di > 0.0 && coef > 0.0) {
-                double num = sm.gd[i] + sm.gd[j] - 2.0 * gqr;
-                num = num > 0.0 ? num : 0.0;
-                rho = num * di;
-                use = true;
-                scale = (uI == uJ ? 1.0 : 2.0) * coef;
-              }
-            }
-          } else {
-            // the block's numbers, the same at each of its columns; its term of the objective
-            // is counted at its first column (pair terms: at the blocks' first columns)
-            const int fi = sm.gf[i], fj = sm.gf[j], kj = sm.gc[j];
-            if (diag) {
-              double bot = 0.0;
-              for (int l = 0; l < kj; ++l) bot += sm.gd[fj + l];
-              rho = bot * sm.ginv[j];
-              use = sm.ginv[j] > 0.0;
-              scale = j == fj ? 1.0 : 0.0;
-            } else {
-              if (di > 0.0 && coef > 0.0) {
-                double num = 0.0;
-                for (int l = 0; l < kj; ++l)
-                  num += sm.gd[fi + l] + sm.gd[fj + l] - 2.0 * nxt[eidx<T>(fi + l, fj + l)];
-                num = num > 0.0 ? num : 0.0;
-                rho = num * di;
-                use = true;
-                scale = i == fi ? (uI == uJ ? 1.0 : 2.0) * coef : 0.0;
-              }
-            }
+          double ro = 0.0, scale = 0.0;        // residual; factor of its term in the objective
+          bool diag = i == j, use = false;
+          if (diag) {
+            ro = gqr * sm.dinv[j] * sm.dinv[j];
+            use = sm.s[j] > 0.0;
+            scale = 1.0;
+          } else if (di > 0.0 && coef > 0.0) {
+            double num = sm.gd[i] + sm.gd[j] - 2.0 * gqr;
+            num = num > 0.0 ? num : 0.0;
+            ro = num * di;
+            use = true;
+            scale = pair;
           }
-          double tv, wv;
-          if (GRP && expo == 0.5) {
-            // Eq. 5: one reciprocal square root instead of two powers
-            const double rsv = rsq2(rho > 1e-300 ? rho : 1e-300);
-            tv = rho * rsv;
-            wv = rsv < rs_delta ? rsv : rs_delta;
-          } else {
-            tv = fa_term_pow(rho, expo);
-            wv = fa_weight_pow(rho, delta, expo);
-          }
-          if (use) { part += scale * tv; wsum += scale * wv; }
-          if (diag) { sm.rho[j] = rho; sm.w[wi ^ 1][j] = use ? wv : 0.0; }
-          const double cv = (!diag && use) ? -2.0 * coef * di * wv : 0.0;
+          const double t = fa_term_pow(ro, expo), w = fa_weight_pow(ro, delta, expo);
+          if (use) { part += scale * t; wsum += scale * w; }
+          if (diag) { sm.rho[j] = ro; sm.w[wi ^ 1][j] = use ? w : 0.0; }
+          const double cv = (!diag && use) ? -2.0 * coef * di * w : 0.0;
           if (r == 0) cpn[0] = cv; else if (r == 1) cpn[1] = cv; else if (r == 2) cpn[2] = cv; else cpn[3] = cv;
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
       store_tile<T>(B2, uI, uJ, lane, cpn);
       if (uI != uJ) store_tile_transposed<T>(B2, uI, uJ, lane, cpn);
-      part = wave_sum(part);
-      wsum = wave_sum(wsum);
+      if ((!GEN || GRP) && uI == uJ && q4 == (c16 & 3)) {
+        // this lane's diagonal entry
+        double dr = rho[0], dw = wv[0];
+#pragma unroll
+        for (int r = 1; r < 4; ++r) { dr = isdiag[r] ? rho[r] : dr; dw = isdiag[r] ? wv[r] : dw; }
+        sm.rho[j] = dr;
+        sm.w[wi ^ 1][j] = dw;
+      }
+      part = wave_sum_mfma(part);
+      wsum = wave_sum_mfma(wsum);
       if (lane == 0) { sm.red[mt] = part; sm.redw[mt] = wsum; }
+    } else if (wave == SW && bk >= 0) {
+      take_back(0);
+      // an end that was folded could have come from either side of the fold: then further out
+      double e = hi * (double)yv;
+      if ((cap_in >> (lane & 1)) & 1) e = lane & 1 ? fmin(hi, fmax(e, 2.0 * est)) : fmin(e, 0.5 * est);
+      est = e;
+      have_est = true;
     }
     __syncthreads();
     double obj = 0.0;
