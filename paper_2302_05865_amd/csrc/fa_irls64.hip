@@ -326,7 +326,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
   // R as B operand: a fifth matrix in LDS where there is room, in global memory (a second-level cache's
   // latency in front of a product) otherwise.
   constexpr bool RB_LDS = T < 4;
-  constexpr int BACK = T < 3 ? 2 : T < 4 ? 6 : 10;         // see take_back
+  constexpr int BACK = T < 3 ? 1 : T < 4 ? 6 : 10;         // see take_back
   constexpr int EPT = (N * N + NTHREADS - 1) / NTHREADS;   // matrix entries per thread
   extern __shared__ __attribute__((aligned(16))) double lds[];
   double* B0 = lds;
@@ -641,14 +641,15 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     // of the steps bk - 1, ..., 0 before that.
     float yv = 0.5f;
     int bk = -1, cap_in = 0;                // (negative: not known); bit e: end e may lie in what was folded
+    float hv = 0.0f;                        // hist[64 hb + lane]
+    int hb = -1;
     auto take_back = [&](int down_to) {
-      float hv = 0.0f;
-      for (bool first = true; bk > down_to; first = false) {
+      while (bk > down_to) {
         --bk;
         // (every lane's read is inside, whichever step this is)
         static_assert(sizeof(sm.hist) % (64 * sizeof(float)) == 0 && sizeof(sm.hist) / sizeof(float) >= MAX_PURIFY,
                       "a lane would read past the end");
-        if (first || (bk & 63) == 63) hv = sm.hist[(bk & ~63) + lane];
+        if (bk >> 6 != hb) { hb = bk >> 6; hv = sm.hist[64 * hb + lane]; }
         const float h = lane_of(hv, bk & 63);
         const bool grow = h > 0.0f;
         const float r = __builtin_amdgcn_sqrtf(fmaxf(grow ? 1.0f - yv : yv, 0.0f));
@@ -683,6 +684,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
     __syncthreads();
     // the unplanned map of step j
     bool tracked = false;                   // H and G are taken along
+    bool owed = false;                      // ... not yet through the published map
     auto publish = [&](int j) {
       pl.al = sq ? 0.0 : 2.0; pl.be = sq ? 1.0 : -1.0; pl.ga = 0.0;
       if (lane == 0) {
@@ -690,9 +692,14 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
         st.al = pl.al; st.be = pl.be; st.ga = 0.0; st.end = end;
         sm.hist[j] = sq ? -1.0f : 1.0f;
       }
-      if (tracked) {
+      owed = tracked;
+    };
+    // the ends through it: behind the next measurement's reads, not ahead of the barrier
+    auto push = [&]() {
+      if (owed) {
         Hp = lane_of(pl.x, 0); Gp = lane_of(pl.x, 1);
         plan_push(pl, !sq, sq ? 0.0f : 1.0f);
+        owed = false;
       }
     };
     const bool measure = it == 0 || inexact;
@@ -790,9 +797,11 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
       //    below; and that X_{k+1} is the result where X_k is a projector already;
       //  - everybody else keeps the barrier, one a step.
       // So a step's map is there before the barrier in front of it and nobody waits for it.  Cycles of a step,
-      // planned / steered / behind the measurement: p = 20 760 / 870 / 940, p = 32 905 / 1100 / 1020 (512 of them matrix
-      // instructions), p = 60 3510 / 3660 / 3290 (3072); with the trace of X_k itself, published during step k and waited
-      // for behind its products, 1580 at T = 2 and 4500 at T = 4.
+      // planned / steered / behind the measurement, some 70 of each for reading the clock: p = 20 790 / 920 / 910, p = 32
+      // 980 / 1080 / 1050 (512 of them matrix instructions), p = 60 3750 / 3810 / 3510 (3072); with the trace of X_k
+      // itself, published during step k and waited for behind its products, 1580 at T = 2 and 4500 at T = 4.  At T = 4
+      // the fourth SIMD has a third of the others' products; a wavefront there that makes half of the last tile of each
+      // of the others handed it over too late (569 us against 482 for a call at p = 60).
       if (mt >= 0) {
         // this wavefront's tile of X_k stays in its registers: LDS holds it for the others
         double live[4];                                  // the identity's place in a diagonal tile
@@ -902,6 +911,8 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
             upper_pair<T>(q, &I, &J);
             v[q] = load_tile<T>(cu, I, J, lane);
           }
+          __builtin_amdgcn_sched_barrier(0);
+          push();
 #pragma unroll
           for (int q = 0; q < NTP; ++q) {
             double& f = q < T ? f0 : f1;
@@ -979,6 +990,7 @@ __global__ __launch_bounds__(64 * waves_for(T)) void fa_irls64_kernel(const doub
             B = Bn;
             sq = A > B;
             advance();
+            push();
             take_back(bk > BACK ? bk - BACK : 0);        // (there is time beside these steps)
             __syncthreads();
             if (end != STEP_GO) break;
