@@ -111,6 +111,29 @@ __device__ __forceinline__ uint4 load16_guarded(const unsigned char* base, int64
   return v;
 }
 
+// The 16 bytes at element row0 <= n - 1, zero from element n on, of which some do not exist.  No load depends on a condition,
+// so that several of these wait once; element by element under conditions they are a chain of 0.3 to 0.6 us a call.
+template <typename E>
+__device__ __forceinline__ uint4 load16_end(const unsigned char* base, int64_t row0, int64_t n) {
+  const int have = (int)(n - row0 < E::EPL ? n - row0 : E::EPL);
+  uint32_t x[E::EPL];
+  if constexpr (E::SIZE == 4) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(base) + row0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = src[e < have ? e : have - 1];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = e < have ? x[e] : 0u;
+    return make_uint4(x[0], x[1], x[2], x[3]);
+  } else {
+    const uint16_t* src = reinterpret_cast<const uint16_t*>(base) + row0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = src[e < have ? e : have - 1];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = e < have ? x[e] : 0u;
+    return make_uint4(x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6] | x[7] << 16);
+  }
+}
+
 // how G lies in memory and goes to LDS: worker-major; interleaved as it is; interleaved, scattered
 enum { FA_MEM_WORKER, FA_MEM_ROWS, FA_MEM_SCATTER };
 // and, added to that: at most four, at most eight columns in the last block of sixteen; at most eight in all
@@ -761,7 +784,7 @@ __global__ __launch_bounds__(256, fa_rows_held(NP) ? fa_rows_wgs(E::SIZE, NP) : 
     const int b = shift(k) + lane16;
     dst[k] = b + (b >> 8) * 16;
   }
-  const int64_t ntiles = (n + 63) / 64, nwaves = (int64_t)gridDim.x * 4;
+  const int64_t ntiles = n / 64, nwaves = (int64_t)gridDim.x * 4;   // whole tiles
   int64_t t = (int64_t)blockIdx.x * 4 + wave;
   uint4 regs[NP];
   auto load_tile = [&](int64_t tl) {
@@ -770,25 +793,7 @@ __global__ __launch_bounds__(256, fa_rows_held(NP) ? fa_rows_wgs(E::SIZE, NP) : 
     for (int k = 0; k < NP; ++k) regs[k] = load16_stream(base + shift(k) + (uint32_t)lane16);
   };
   const int r0 = lane * ldr * E::SIZE;                     // first byte of this lane's row
-  constexpr int HELD = fa_rows_held(NP);
-  fa_held_rows<HELD> held;
-  int nheld = 0;
-  float* dst_out = out + t * 64 + lane;                    // first tile of those held
-  if ((t + 1) * 64 <= n) load_tile(t);
-  for (; t < ntiles; t += nwaves) {
-    const int rows_here = (int)(n - t * 64 < 64 ? n - t * 64 : 64);
-    wave_lds_fence();                                      // the previous tile has been read
-    if (rows_here == 64) {
-#pragma unroll
-      for (int k = 0; k < NP; ++k) *reinterpret_cast<uint4*>(mine + dst[k]) = regs[k];
-    } else {
-      const int lim = rows_here * ldr;                     // elements that exist
-      for (int b = lane * 16; b < tb; b += 1024)
-        *reinterpret_cast<uint4*>(mine + b + (b >> 8) * 16) = load16_guarded<E>(G + t * tb, b / E::SIZE, lim);
-    }
-    wave_lds_fence();
-    const int64_t next = t + nwaves;
-    if ((next + 1) * 64 <= n) load_tile(next);
+  auto row_sum = [&]() -> float {
     double a0 = 0.0, a1 = 0.0;
     if constexpr (WHOLE) {
       // (elements past p are multiplied by 0 only where the row has them: left out)
@@ -826,15 +831,26 @@ __global__ __launch_bounds__(256, fa_rows_held(NP) ? fa_rows_wgs(E::SIZE, NP) : 
       }
       if (i < p) a0 = fma(cs[i], elem(i), a0);
     }
+    return (float)(a0 + a1);
+  };
+  constexpr int HELD = fa_rows_held(NP);
+  fa_held_rows<HELD> held;
+  int nheld = 0;
+  float* dst_out = out + t * 64 + lane;                    // first tile of those held
+  if (t < ntiles) load_tile(t);
+  for (; t < ntiles; t += nwaves) {
+    wave_lds_fence();                                      // the previous tile has been read
+#pragma unroll
+    for (int k = 0; k < NP; ++k) *reinterpret_cast<uint4*>(mine + dst[k]) = regs[k];
+    wave_lds_fence();
+    const int64_t next = t + nwaves;
+    if (next < ntiles) load_tile(next);
+    const float r = row_sum();
     if constexpr (HELD == 0) {
-      if (lane < rows_here) __builtin_nontemporal_store((float)(a0 + a1), out + t * 64 + lane);
+      __builtin_nontemporal_store(r, out + t * 64 + lane);
     } else {
-      if (rows_here == 64) {
-        held.put(nheld, (float)(a0 + a1));
-        ++nheld;
-      } else if (lane < rows_here) {
-        out[t * 64 + lane] = (float)(a0 + a1);             // the ragged last tile
-      }
+      held.put(nheld, r);
+      ++nheld;
       if (nheld == HELD || next >= ntiles) {
         held.write(nheld, dst_out, nwaves * 64);
         dst_out += (int64_t)nheld * nwaves * 64;
@@ -842,6 +858,32 @@ __global__ __launch_bounds__(256, fa_rows_held(NP) ? fa_rows_wgs(E::SIZE, NP) : 
       }
     }
   }
+  if (t > ntiles || ntiles * 64 == n) return;
+
+  // The ragged last tile, all its pieces at once: a place past the last whole piece is given that piece again (no row
+  // that exists is there).  With a wait after each KiB the pass took, us, fp32 p = 32, 30 thousand rows 5.8, p = 64 9.9, 300
+  // thousand 19.8, bf16 p = 64, 30 thousand 7.0; 4.3, 6.2, 18.8 and 5.5 like this (64-row tiles of a wavefront are few there).
+  const unsigned char* base = G + ntiles * tb;
+  const int rows_here = (int)(n - ntiles * 64);
+  const int lim = rows_here * ldr, whole = lim / EPL * EPL;     // elements that exist; those in whole pieces
+  const int last = whole * E::SIZE - 16;
+  wave_lds_fence();
+  if (last >= 0) {
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      const int b = shift(k) + lane16;
+      regs[k] = load16_stream(base + (uint32_t)(b < last ? b : last));
+    }
+#pragma unroll
+    for (int k = 0; k < NP; ++k) *reinterpret_cast<uint4*>(mine + dst[k]) = regs[k];
+  }
+  if (!WHOLE && whole < lim) {
+    wave_lds_fence();                                      // (after what its place has been given above)
+    *reinterpret_cast<uint4*>(mine + whole * E::SIZE + (whole * E::SIZE >> 8) * 16) = load16_end<E>(base, whole, lim);
+  }
+  wave_lds_fence();
+  const float r = row_sum();
+  if (lane < rows_here) out[ntiles * 64 + lane] = r;
 }
 
 // The p x p solver text (any p): parallel-for phases over one workgroup.  Included here

@@ -59,3 +59,46 @@ def test_rows_around_a_batch(p, wgs, held, dtype):
     rng = np.random.default_rng(p)
     for n in (full - 64, full, full + 1):
         _check(p, p, n, dtype, rng)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("p,pitch", [(1, 1), (2, 2), (3, 3), (5, 6), (7, 7), (8, 8), (13, 13), (16, 16), (19, 20), (33, 33),
+                                     (40, 40), (55, 64), (61, 61), (64, 64)])
+def test_rows_past_the_last_tile(p, pitch, dtype):
+    """One to 63 rows past the whole tiles, with none, one and several of these: whole 16-byte pieces, less than one, and one
+    that the last row ends in.  What lies behind the last row is NaN and reaches nothing."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("rows aggregate, ragged tile", p, pitch, dtype)
+    rng = np.random.default_rng(p)
+    gen = torch.Generator(device="cuda").manual_seed(p)
+    agg = FlagAggregator(n_max=1 << 12, p_max=p, dtype=dtype, layout="row_major")
+    c = rng.standard_normal(p)
+    cd = torch.from_numpy(c).cuda()
+    for n in [64 * k + r for k in (0, 1, 5) for r in (1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 33, 63)]:
+        rows = torch.full((n + 64, pitch), float("nan"), device="cuda",
+                          dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+        rows[:n, :p] = torch.randn((n, p), generator=gen, device="cuda").to(rows.dtype)
+        out = torch.full((n + 8,), float("nan"), device="cuda")
+        agg.fa_combine(rows[:n, :p], c, out[:n])
+        assert torch.isnan(out[n:]).all()
+        x = rows[:n, :p].double()
+        lim = 2.0 ** -24 * 1.0001 * (x @ cd).abs() + p * 2.0 ** -53 * (x.abs() @ cd.abs()) + 1e-45
+        assert bool(((out[:n].double() - x @ cd).abs() <= lim).all()), n
+    agg.close()
+
+
+def test_rows_past_the_last_tile_take_no_longer():
+    """A set a few rows short of whole tiles takes as long as one that is not (the dispatch alone, the shortest of many);
+    a ragged tile read one KiB after the other took 1.6 of it."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("rows aggregate, time of a ragged tile")
+    sets = [torch.randn((n, 64), device="cuda") for n in (30_016, 30_001)]
+    agg = FlagAggregator(n_max=30_016, p_max=64, dtype="f32", layout="row_major")
+    agg.fa_set_profiling(True)
+    best = [1e9, 1e9]
+    for _ in range(40):
+        for k, G in enumerate(sets):
+            agg.fa_aggregate(G, 2, 1.0, 1, 0.0)
+            best[k] = min(best[k], float(agg.fa_get_timings()[3]))
+    agg.close()
+    assert best[1] <= 1.25 * best[0], best
