@@ -1275,6 +1275,37 @@ __global__ __launch_bounds__(64 * FA_HELD_WAVES, FA_HELD_WAVES / 4 * (ENDS > 1 ?
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = (acc_t)0;
 
+  // The rows that do not fill a tile: the wavefront that would be next, which has a tile less than those before it, ahead of
+  // its tiles and eight columns at a time.  Behind them and column by column, each waited for, they made every set of
+  // another length than whole tiles slower, 16 tiles a wavefront and no more than the kernel for small sets takes: fp32, us,
+  // 4 194 304 rows / 4 234 340 before / now (that kernel): p = 15 42.3 / 45.5 / 42.7 (46.2), p = 64 159 / 187 / 173 (189).
+  if (ntiles * ROWS < n && w == ntiles % W) {
+    const int64_t row0 = ntiles * ROWS + lane * EPL;
+    constexpr int NL = 8;                                     // columns in flight
+    if (row0 < n) {
+      for (int k0 = 0; k0 < ncols; k0 += NL) {
+        uint4 v[NL];
+        if (row0 + EPL <= n) {
+#pragma unroll
+          for (int u = 0; u < NL; ++u)
+            v[u] = load16_stream(G + column(k0 + u < ncols ? k0 + u : ncols - 1) + row0 * E::SIZE);
+        } else {
+#pragma unroll
+          for (int u = 0; u < NL; ++u)
+            v[u] = load16_end<E>(G + column(k0 + u < ncols ? k0 + u : ncols - 1), row0, n);
+        }
+#pragma unroll
+        for (int u = 0; u < NL; ++u)
+          if (k0 + u < ncols) combine_add<E>(acc, lane_value(coef, k0 + u), v[u]);
+      }
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        if (row0 + e < n) out[row0 + e] = (float)acc[e];
+        acc[e] = (acc_t)0;
+      }
+    }
+  }
+
   if (mine > 0) {
     float* const kept = held + wave * (LT + ENDS) * ROWS;   // LT tiles, then those that go on to registers
     const unsigned char* base = G + w * (ROWS * E::SIZE) + lane * 16;
@@ -1336,17 +1367,6 @@ __global__ __launch_bounds__(64 * FA_HELD_WAVES, FA_HELD_WAVES / 4 * (ENDS > 1 ?
       wave_lds_fence();                                     // the reads above precede the next tiles' writes
     }
 #undef FA_HELD_LOAD
-  }
-
-  // the rows that do not fill a tile: the wavefront that would be next
-  if (ntiles * ROWS < n && w == ntiles % W) {
-    const int64_t row0 = ntiles * ROWS + lane * EPL;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = (acc_t)0;
-    for (int k = 0; k < ncols; ++k)
-      combine_add<E>(acc, lane_value(coef, k), load16_guarded<E>(G + column(k), row0, n));
-    for (int e = 0; e < EPL; ++e)
-      if (row0 + e < n) out[row0 + e] = (float)acc[e];
   }
 }
 
