@@ -1115,12 +1115,22 @@ __global__ __launch_bounds__(256) void fa_combine_kernel(const unsigned char* __
           const int col = LISTED ? place[at] : at;
           v[u] = load16_stream(src + (int64_t)col * ldg * E::SIZE);
         }
-      } else {
+      } else if (row0 + EPL <= n) {
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
           const int at = c0 + u < p ? c0 + u : p - 1;
           const int col = LISTED ? place[at] : at;
-          v[u] = load16_guarded<E>(G + (int64_t)col * ldg * E::SIZE, row0, n);
+          v[u] = load16_stream(src + (int64_t)col * ldg * E::SIZE);
+        }
+      } else {
+        // the piece that the columns end in.  Under a condition for each element these loads were a chain, a wait for every
+        // column.  us, whole pieces / a row or three more, before / now: fp32 p = 60, 1.2 M rows 50 / 84 / 61; p = 32, 2 M 44 /
+        // 61 / 48; p = 15, 271 thousand 6.0 / 10.0 / 7.8; p = 64, 100 thousand 10 / 44 / 17; bf16 p = 23, 1 M 9.8 / 28 / 13.
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+          const int at = c0 + u < p ? c0 + u : p - 1;
+          const int col = LISTED ? place[at] : at;
+          v[u] = load16_end<E>(G + (int64_t)col * ldg * E::SIZE, row0, n);
         }
       }
 #pragma unroll
