@@ -724,15 +724,23 @@ __global__ __launch_bounds__(256) void fa_combine_rows_kernel(const unsigned cha
 // elements, in fp64).  NP: 1 KiB loads a tile (ceil(ldr es / 16), rounded up; a load that would reach past the tile starts earlier).
 // WHOLE: rows are whole 16-byte pieces, read as such.  The outputs of fa_rows_held tiles, one a lane, stay in registers
 // and are written together (see fa_combine_held_kernel), but for the shortest rows, where that costs more than it gives.
-// us, one workgroup per span of 256 rows and a barrier either side of its copy to LDS / this: fp32 p = 20, n = 3M 51.2 / 39.9;
-// p = 15, 10M 108 / 103; p = 5, 4M 23.3 / 16.5; p = 28, 4M 75 / 69; p = 40, 2M 66 / 50; p = 64, 4M 217 / 170; bf16 p = 32, 8M 98 / 86;
-// p = 7, 8M 52 / 29; p = 16, 8M 64 / 47; p = 64, 2M 50 / 44 (direct stores: p = 20 43.6, bf16 p = 32 97; 64 tiles held with
-// three workgroups a compute unit bf16 p = 23 39.2 instead of 34.4; fp32 p = 32 with three 88 instead of 81; bf16 p = 48 with
-// two 83 instead of 69).
-constexpr int fa_rows_held(int np) { return np < 3 ? 0 : np < 6 ? 32 : 64; }
+// us, one workgroup per span of 256 rows and a barrier either side of its copy to LDS / this: fp32 p = 5, 4M 24.2 / 17.7; p = 16,
+// 8M 85.7 / 80.2; p = 20, 3M 52 / 39; p = 28, 4M 77 / 71; p = 40, 3M 98 / 76; p = 64, 3M 161 / 132; bf16 p = 7, 8M 52 / 29; p = 16,
+// 8M 64 / 47; p = 32, 8M 98 / 87; p = 64, 3M 75 / 65.
+// Tiles held and workgroups a compute unit.  Where the outputs of a set are more than one batch, short batches of many workgroups
+// cost more than that kernel did, so it is 64 or 48 tiles and three workgroups for fp32 (32 tiles, four workgroups / so / that
+// kernel: p = 12, 50M 461 / 419 / 424; p = 16, 12M 134 / 121 / 128, 50M 628 / 538 / 535, 100M 1308 / 1126 / 1134; p = 18, 50M 700 /
+// 599 / 638; p = 20, 3M 42.3 / 39.0 / 52; with p = 12, 80M 763 / 707 / 692 alone above it), six instead of seven for whole rows
+// of at most 32 bytes (p = 8, 100M 664 / 614 / 626) and three instead of four for bf16 rows of 49 to 80 bytes once they are more
+// than one batch (p = 32, 8M 87 / 89 / 98, 12M 140 / 127 / 144, 60M 782 / 711 / 721; with 64 tiles p = 25, 8M 89.5 instead of 72.2).
+// Direct stores: p = 16, 50M 606, bf16 p = 32, 60M 758.
+constexpr int fa_rows_held(int es, int np, bool whole) {
+  return np < 3 ? 0 : np > 5 ? 64 : es == 2 ? 32 : np == 3 && !whole ? 48 : 64;
+}
 // workgroups a compute unit
-constexpr int fa_rows_wgs(int es, int np) {
-  return np < 2 ? 12 : np < 3 ? 7 : np < 6 ? 4 : np < 9 && es == 2 ? 3 : 2;
+constexpr int fa_rows_wgs(int es, int np, bool whole) {
+  if (np < 3) return np < 2 ? 12 : whole ? 6 : 7;
+  return np < 6 ? (es == 2 ? 4 : 3) : np < 9 && es == 2 ? 3 : 2;
 }
 template <int N, int ID = 0>
 struct fa_held_rows {
@@ -762,10 +770,9 @@ struct fa_held_rows<1, ID> {
 template <int ID>
 struct fa_held_rows<0, ID> {};
 template <typename E, int NP, bool WHOLE>
-__global__ __launch_bounds__(256, fa_rows_held(NP) ? fa_rows_wgs(E::SIZE, NP) : 1) void fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G,
-                                                                    int ldr, int p, int64_t n,
-                                                                    const double* __restrict__ c, int cstride,
-                                                                    float* __restrict__ out) {
+__global__ __launch_bounds__(256, fa_rows_held(E::SIZE, NP, WHOLE) ? fa_rows_wgs(E::SIZE, NP, WHOLE) : 1) void
+fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G, int ldr, int p, int64_t n, const double* __restrict__ c,
+                             int cstride, float* __restrict__ out) {
   constexpr int EPL = E::EPL;
   extern __shared__ __attribute__((aligned(16))) unsigned char tile[];
   __shared__ __attribute__((aligned(16))) double cs[FA_P_MAX];
@@ -833,7 +840,7 @@ __global__ __launch_bounds__(256, fa_rows_held(NP) ? fa_rows_wgs(E::SIZE, NP) : 
     }
     return (float)(a0 + a1);
   };
-  constexpr int HELD = fa_rows_held(NP);
+  constexpr int HELD = fa_rows_held(E::SIZE, NP, WHOLE);
   fa_held_rows<HELD> held;
   int nheld = 0;
   float* dst_out = out + t * 64 + lane;                    // first tile of those held
@@ -2441,7 +2448,9 @@ static hipError_t launch_combine_rows(const void* G, int ldr, int p, int64_t n, 
   const int64_t ntiles = (n + 63) / 64;
 #define FA_X(np)                                                                                     \
   if (need <= np) {                                                                                  \
-    int64_t blocks = (int64_t)cus * fa_rows_wgs(E::SIZE, np);                                         \
+    int64_t blocks = (int64_t)cus * fa_rows_wgs(E::SIZE, np, whole);                                  \
+    if (E::SIZE == 2 && np > 3 && np < 6 && ntiles > blocks * 4 * fa_rows_held(2, np, whole))        \
+      blocks = (int64_t)cus * 3;                                                                     \
     if (blocks > (ntiles + 3) / 4) blocks = (ntiles + 3) / 4;                                        \
     if (whole)                                                                                       \
       FA_LAUNCH(tm, (fa_combine_rows_tiles_kernel<E, np, true>), dim3((unsigned)blocks), dim3(256),  \
