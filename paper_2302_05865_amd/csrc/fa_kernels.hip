@@ -769,8 +769,13 @@ struct fa_held_rows<1, ID> {
 };
 template <int ID>
 struct fa_held_rows<0, ID> {};
+// Wavefronts a SIMD that the registers have to allow: those of the workgroups that are there, and no more with ten loads a tile,
+// where the compiler reads a row's elements one by one to get down to the registers of one more (p = 33 fp32, 1M 24.9 us, 23.2
+// like this; with twelve loads the same costs 3 to 5 % from four million rows on).
+constexpr int fa_rows_waves(int es, int np, bool whole) { return fa_rows_held(es, np, whole) ? fa_rows_wgs(es, np, whole) : 1; }
 template <typename E, int NP, bool WHOLE>
-__global__ __launch_bounds__(256, fa_rows_held(E::SIZE, NP, WHOLE) ? fa_rows_wgs(E::SIZE, NP, WHOLE) : 1) void
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fa_rows_waves(E::SIZE, NP, WHOLE),
+                                                                     NP == 10 ? fa_rows_waves(E::SIZE, NP, WHOLE) : 8))) void
 fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G, int ldr, int p, int64_t n, const double* __restrict__ c,
                              int cstride, float* __restrict__ out) {
   constexpr int EPL = E::EPL;
