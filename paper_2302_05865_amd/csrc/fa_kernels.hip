@@ -786,7 +786,12 @@ fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G, int ldr, int p
   if (threadIdx.x < FA_P_MAX) cs[threadIdx.x] = (int)threadIdx.x < p ? c[(int64_t)threadIdx.x * cstride] : 0.0;
   __syncthreads();
   const int tb = 64 * ldr * E::SIZE;
-  // byte b of a tile sits at b + 16 (b / 256)
+  // byte b of a tile sits at b + 16 (b / 256), so that rows of 16 k elements do not lie on a few banks only; but rows of 40, 60
+  // or 120 bytes as they are, of which that would put every sixth, fourth or second one on the same bank (us, with the
+  // places: bf16 p = 20, 4M 35.2 -> 28.9, p = 30, 16M 258 -> 173, p = 60, 16M 772 -> 338; fp32 p = 15, 12M 120 -> 115, p = 30, 12M 318 ->
+  // 225; other widths lose up to 10 % without them)
+  const int row = ldr * E::SIZE;
+  const int sh = !WHOLE && row >= 40 && 240 % row == 0 ? 31 : 8;
   unsigned char* const mine = tile + wave * (NP * 1088);
   const int lane16 = lane * 16 < tb ? lane * 16 : tb - 16;
   auto shift = [&](int k) { return k * 1024 + 1024 <= tb ? k * 1024 : tb > 1024 ? tb - 1024 : 0; };
@@ -794,7 +799,7 @@ fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G, int ldr, int p
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
     const int b = shift(k) + lane16;
-    dst[k] = b + (b >> 8) * 16;
+    dst[k] = b + (b >> sh) * 16;
   }
   const int64_t ntiles = n / 64, nwaves = (int64_t)gridDim.x * 4;   // whole tiles
   int64_t t = (int64_t)blockIdx.x * 4 + wave;
@@ -804,7 +809,7 @@ fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G, int ldr, int p
 #pragma unroll
     for (int k = 0; k < NP; ++k) regs[k] = load16_stream(base + shift(k) + (uint32_t)lane16);
   };
-  const int r0 = lane * ldr * E::SIZE;                     // first byte of this lane's row
+  const int r0 = lane * row;                               // first byte of this lane's row
   auto row_sum = [&]() -> float {
     double a0 = 0.0, a1 = 0.0;
     if constexpr (WHOLE) {
@@ -831,7 +836,7 @@ fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G, int ldr, int p
     } else {
       auto elem = [&](int i) -> double {
         const int b = r0 + i * E::SIZE;
-        const unsigned char* at = mine + b + (b >> 8) * 16;
+        const unsigned char* at = mine + b + (b >> sh) * 16;
         if constexpr (E::SIZE == 4) return (double)*reinterpret_cast<const float*>(at);
         else return (double)bf16_bits_to_f32(*reinterpret_cast<const uint16_t*>(at));
       };
@@ -891,7 +896,7 @@ fa_combine_rows_tiles_kernel(const unsigned char* __restrict__ G, int ldr, int p
   }
   if (!WHOLE && whole < lim) {
     wave_lds_fence();                                      // (after what its place has been given above)
-    *reinterpret_cast<uint4*>(mine + whole * E::SIZE + (whole * E::SIZE >> 8) * 16) = load16_end<E>(base, whole, lim);
+    *reinterpret_cast<uint4*>(mine + whole * E::SIZE + (whole * E::SIZE >> sh) * 16) = load16_end<E>(base, whole, lim);
   }
   wave_lds_fence();
   const float r = row_sum();
