@@ -301,7 +301,11 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
   const int gs = (gb & 15) ? gb : gb + ((16 * E::SIZE - gb) & 255);
   const int tb = R * ldr * E::SIZE;        // bytes of a tile's span
   // An instruction that would reach past the span starts earlier and reads some pieces again, into the same places:
-  // a lane that is switched off for a load costs the wavefront a wait for all loads before it.
+  // a lane that is switched off for a load costs the wavefront a wait for all loads before it.  One that starts past the span,
+  // which is so for all lanes, is left out with 49 to 56 columns only (us, all / so: bf16 p = 49, 300 thousand rows 43.6 / 41.5, a
+  // million 72.7 / 70.2; fp32 p = 52, a million 71 / 69; but bf16 p = 17, 300 thousand 14.1 / 15.5, p = 24 18 / 25, and with no load
+  // to leave out fp32 p = 64, 3 M 239 / 245).
+  constexpr bool LEAVE_OUT = T == 4 && NB < 16;
   auto shift = [&](int cg) { return cg * 1024 + 1024 <= tb ? cg * 1024 : tb > 1024 ? tb - 1024 : 0; };
   const int lane16 = lane * 16 < tb ? lane * 16 : tb - 16;
   int pdst[NCG], prow[NCG], pcol[NCG];     // (scattered: row and column of a piece's first element)
@@ -329,7 +333,8 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
       if ((tl + 1) * R > n) return;        // the ragged last tile: see store_tile_lds
       const unsigned char* base = G + tl * tb;
 #pragma unroll
-      for (int cg = 0; cg < NCG; ++cg) regs[cg] = load16_stream(base + shift(cg) + (uint32_t)lane16);
+      for (int cg = 0; cg < NCG; ++cg)
+        if (!LEAVE_OUT || cg * 1024 < tb) regs[cg] = load16_stream(base + shift(cg) + (uint32_t)lane16);
       return;
     }
     const int64_t row0 = tl * R + lrow;
@@ -355,7 +360,8 @@ __global__ __launch_bounds__(64 * WAVES) void fa_gram_kernel(
         return;
       }
 #pragma unroll
-      for (int cg = 0; cg < NCG; ++cg) *reinterpret_cast<uint4*>(lds + pdst[cg]) = regs[cg];
+      for (int cg = 0; cg < NCG; ++cg)
+        if (!LEAVE_OUT || cg * 1024 < tb) *reinterpret_cast<uint4*>(lds + pdst[cg]) = regs[cg];
       return;
     }
     if constexpr (SCATTER) {

@@ -11,8 +11,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("p,pitch", [(1, 16), (5, 5), (15, 16), (16, 16), (17, 17), (17, 32), (23, 23),
-                                     (32, 32), (33, 48), (47, 47), (48, 48), (49, 64), (63, 63),
-                                     (64, 64)])
+                                     (32, 32), (33, 48), (47, 47), (48, 48), (49, 49), (49, 64), (50, 52), (53, 60),
+                                     (56, 56), (63, 63), (64, 64)])
 def test_interleaved_gram_matches_worker_major(p, pitch, dtype):
     """Same tiles, same order of rows and sums as over worker-major storage: the same bits, whatever
     the pitch; the places between the rows hold NaN and reach nothing.  Sizes around one tile
@@ -36,7 +36,7 @@ def test_interleaved_gram_matches_worker_major(p, pitch, dtype):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("p,pitch,waves", [(9, 9, 12), (15, 16, 12), (17, 17, 16), (30, 32, 16),
-                                           (33, 33, 8), (45, 48, 8), (51, 51, 8), (64, 64, 8)])
+                                           (33, 33, 8), (45, 48, 8), (49, 49, 8), (51, 51, 8), (56, 58, 8), (64, 64, 8)])
 def test_interleaved_gram_in_its_steady_state(p, pitch, waves, dtype):
     """Two rounds of all wavefronts and a ragged tail: every wavefront has a full tile in LDS while the
     next full one is on its way to its registers, some have a third and one the ragged one (waves: per
