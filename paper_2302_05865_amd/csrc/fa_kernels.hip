@@ -1212,12 +1212,13 @@ __global__ __launch_bounds__(256) void fa_combine_kernel(const unsigned char* __
 //
 // RT tiles of a batch stay in registers, LT in LDS.  p <= 16: half the registers and three quarters of the LDS, so that the
 // solver of a set on another stream fits beside a workgroup, whose tiles are nobody else's; one batch is
-// still all of p = 15, n = 11.2M.  ENDS: most tiles that can end within FA_HELD_SLOTS columns.
+// still all of p = 15, n = 11.2M.  A batch is written at the end of the FA_HELD_SLOTS slots after which another ENDS tiles might not
+// fit: 55 tiles (now and then 56 of five columns) or 103 for fp32, 28 or 51 for bf16.  ENDS: most tiles that can end within
+// FA_HELD_SLOTS columns, two of five columns, which is the fewest there are (fa_combine_held_applies), one of six and more.
 // skip (device, may be null): if *skip is not 0, columns whose coefficient is 0 are not read (Multi-Krum; only where
 // no gradient holds a NaN or an infinity, which 0 times it would carry over).
 #define FA_HELD_SLOTS 6
 #define FA_HELD_WAVES 4
-#define FA_HELD_MIN_COLS 5                         // at most two tiles end within FA_HELD_SLOTS columns
 
 // N tiles of H x 16 bytes a lane, each in registers of its own (an array would be indexed, and so go to scratch memory)
 template <int N, int H, int ID = 0>
@@ -1261,8 +1262,9 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
 template <typename E, int RT, int LT, int ENDS>
 constexpr size_t fa_held_lds_bytes() { return (size_t)FA_HELD_WAVES * (LT + ENDS) * 64 * E::EPL * sizeof(float); }
 
-template <typename E, int RT, int LT, int ENDS>
-__global__ __launch_bounds__(64 * FA_HELD_WAVES, FA_HELD_WAVES / 4 * (ENDS > 1 ? 2 : 1)) void fa_combine_held_kernel(
+// WGS: workgroups a compute unit that the registers have to leave room for
+template <typename E, int RT, int LT, int ENDS, int WGS>
+__global__ __launch_bounds__(64 * FA_HELD_WAVES, FA_HELD_WAVES / 4 * WGS) void fa_combine_held_kernel(
     const unsigned char* __restrict__ G, int64_t ldg, int p, int64_t n, const double* __restrict__ c,
     int cstride, const double* __restrict__ skip, float* __restrict__ out) {
   constexpr int EPL = E::EPL, ROWS = 64 * EPL, H = ROWS / 256, S = FA_HELD_SLOTS;
@@ -1288,11 +1290,9 @@ __global__ __launch_bounds__(64 * FA_HELD_WAVES, FA_HELD_WAVES / 4 * (ENDS > 1 ?
     }
   }
   __syncthreads();
-  if (ncols == 0) return;                        // (a selection is never empty)
   const acc_t coef = lane < ncols ? lcoef[lane] : (acc_t)0;
   const int64_t off = loff[lane < ncols ? lane : ncols - 1];
   const int off_lo = (int)off, off_hi = (int)(off >> 32);
-  if (ncols < FA_HELD_MIN_COLS) ncols = FA_HELD_MIN_COLS;     // the last one again, times 0
   auto column = [&](int k) -> int64_t {
     return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(off_hi, k) << 32) |
                      (uint32_t)__builtin_amdgcn_readlane(off_lo, k));
@@ -2398,22 +2398,22 @@ hipError_t fa_launch_gap(const double* mlast, int N, fa_info* info_d, hipStream_
   return hipGetLastError();
 }
 
-// fa_combine_held_kernel of this storage type: `wide` is for more than FA_HELD_SLOTS columns
-template <typename E, int RT, int LT, int ENDS>
+// narrow: at most sixteen columns.  (bf16 never has fewer than ten, so one tile more fits in place of a second end.)
+template <typename E, int RT, int LT, int ENDS, int WGS>
 static hipError_t launch_held_t(const void* G, int64_t ldg, int p, int64_t n, const double* c,
                                 int cstride, const double* skip, float* out, int cus, hipStream_t st,
                                 const fa_ktime* tm) {
-  FA_LAUNCH(tm, (fa_combine_held_kernel<E, RT, LT, ENDS>), dim3((unsigned)cus), dim3(64 * FA_HELD_WAVES),
+  FA_LAUNCH(tm, (fa_combine_held_kernel<E, RT, LT, ENDS, WGS>), dim3((unsigned)cus), dim3(64 * FA_HELD_WAVES),
             (fa_held_lds_bytes<E, RT, LT, ENDS>()), st, (const unsigned char*)G, ldg, p, n, c, cstride, skip, out);
   return hipGetLastError();
 }
-#define FA_HELD_NARROW_F32 ElemF32, 30, 26, 2
-#define FA_HELD_NARROW_BF16 ElemBF16, 15, 12, 2
-#define FA_HELD_WIDE_F32 ElemF32, 66, 37, 1
-#define FA_HELD_WIDE_BF16 ElemBF16, 33, 18, 1
-template <typename E, int RT, int LT, int ENDS>
+#define FA_HELD_NARROW_F32 ElemF32, 30, 26, 2, 2
+#define FA_HELD_NARROW_BF16 ElemBF16, 15, 13, 1, 2
+#define FA_HELD_WIDE_F32 ElemF32, 66, 37, 1, 1
+#define FA_HELD_WIDE_BF16 ElemBF16, 33, 18, 1, 1
+template <typename E, int RT, int LT, int ENDS, int WGS>
 static hipError_t prepare_held_t() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_held_kernel<E, RT, LT, ENDS>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(fa_combine_held_kernel<E, RT, LT, ENDS, WGS>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)fa_held_lds_bytes<E, RT, LT, ENDS>());
 }
 
@@ -2491,7 +2491,7 @@ static hipError_t launch_combine_rows(const void* G, int ldr, int p, int64_t n, 
 static bool fa_combine_held_applies(int cols, int64_t n, int dtype, int cus) {
   const int64_t tiles = n / (64 * (dtype == FA_F32 ? 4 : 8)) / ((int64_t)FA_HELD_WAVES * cus);   // per wavefront
   if (cols >= 10) return tiles >= 16;
-  return dtype == FA_F32 && cols >= FA_HELD_MIN_COLS && tiles >= 32;
+  return dtype == FA_F32 && cols >= 5 && tiles >= 32;
 }
 
 hipError_t fa_launch_combine(const void* G, int64_t ldg, int p, int64_t n, int dtype, int layout,
