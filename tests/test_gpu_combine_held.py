@@ -24,12 +24,15 @@ def _wave_tiles(dtype):
     return units * 4 * 64 * (4 if dtype == "f32" else 8)
 
 
-# sixteen tiles a wavefront (thirty-two below ten columns) are the rule's line; a batch is 56 tiles (fp32, p <= 16),
-# 103 (fp32), 27 (bf16, p <= 16) and 51 (bf16): one tile short of it, all of it, one more, and two
+# sixteen tiles a wavefront (thirty-two below ten columns) are the rule's line; a batch is 55 tiles (fp32, p <= 16),
+# 103 (fp32), 28 (bf16, p <= 16) and 51 (bf16): one tile short of it, all of it, one more, and two.  280 tiles of five columns
+# are batches of 55, 55, 55, 55, 56 and 4: two tiles end within six columns and the second of them is the first in registers,
+# and the last place in registers is filled
 @pytest.mark.parametrize("dtype,p,rounds", [
-    ("f32", 5, 32), ("f32", 5, 57), ("f32", 6, 55), ("f32", 7, 112), ("f32", 9, 32), ("f32", 10, 16), ("f32", 15, 56),
+    ("f32", 5, 32), ("f32", 5, 55), ("f32", 5, 57), ("f32", 5, 280), ("f32", 6, 54), ("f32", 6, 55), ("f32", 7, 110),
+    ("f32", 7, 112), ("f32", 9, 32), ("f32", 10, 16), ("f32", 15, 55), ("f32", 15, 56),
     ("f32", 16, 16), ("f32", 17, 16), ("f32", 17, 102), ("f32", 18, 103), ("f32", 19, 104), ("f32", 33, 16),
-    ("f32", 64, 17), ("bf16", 10, 16), ("bf16", 11, 26), ("bf16", 12, 27), ("bf16", 16, 54), ("bf16", 17, 50),
+    ("f32", 64, 17), ("bf16", 10, 16), ("bf16", 11, 27), ("bf16", 12, 28), ("bf16", 13, 29), ("bf16", 16, 56), ("bf16", 17, 50),
     ("bf16", 23, 51), ("bf16", 32, 52), ("bf16", 47, 17), ("bf16", 64, 16)])
 def test_held_aggregate_has_the_small_kernels_bits(dtype, p, rounds):
     """The same sums in the same order: pieces of the rows through the kernel for small sets give the same bits.
