@@ -2482,16 +2482,19 @@ static hipError_t launch_combine_rows(const void* G, int ldr, int p, int64_t n, 
   return hipErrorInvalidValue;
 }
 
-// Whether fa_combine_held_kernel takes an aggregate pass that reads `cols` worker-major columns.  From sixteen tiles a
-// wavefront on: below, the last tiles of some wavefronts and the one write at the end cost more than the writes in between do.
-// us, the kernel for small sets / this one: fp32 p = 15, n = 2M 19.3 / 23.5, 4M 37.8 / 38.0, 6M 57.4 / 54.1, 8M 79 / 70; p = 20
-// 3M 39.5 / 44.1, 6M 76.9 / 71.5; p = 64 2M 75 / 89, 4M 155 / 137; bf16 p = 32 4M 42.5 / 46.0, 8M 89 / 79.  Few columns leave a
-// wavefront little time for a tile: fp32 p = 5 4M 16.6 / 16.8, 20M 78.5 / 73.8, p = 7 8M 40.4 / 40.0, 20M 99 / 93; bf16 p = 8 30M 89.8 /
-// 90.6, 120M 393 / 394.
+// Whether fa_combine_held_kernel takes an aggregate pass that reads `cols` worker-major columns: from ten columns on where a
+// wavefront has ten whole tiles, fp32 with five to nine where it has sixteen.  Below, which of the two is ahead changes with the width,
+// the type and how full the last round of tiles is.  us, the kernel for small sets / this one, sets of so many tiles a wavefront (262 144
+// rows each for fp32, 524 288 for bf16) that do not end on a whole piece: fp32 p = 12 4.03 14.1 / 13.7, 10.03 26.2 / 24.5, 16.2 39.4 /
+// 36.2; p = 15 4.03 15.6 / 15.5, 7.03 22.9 / 22.7, 10.03 30.3 / 28.6, 13.03 38.3 / 35.8; p = 64 7.03 88.7 / 83.3, 10.03 123 / 108, 16.03 192 /
+// 168; bf16 p = 16 7.03 25.9 / 26.9, 9.03 31.7 / 32.4, 10.03 34.7 / 34.2, 13.03 43.4 / 41.7; p = 32 7.03 48.5 / 48.2, 10.03 66.1 / 61.3; that end on a
+// tile: fp32 p = 15 4 13.4 / 13.6, 10 28.4 / 26.8; p = 64 16 177 / 158.  Few columns leave a wavefront little time for a tile: fp32 p = 6
+// 12.03 16.6 / 16.7, 16.03 21.4 / 21.1; p = 7 16.03 24.1 / 23.5, 32.03 44.6 / 41.5; bf16 p = 7 32.03 50.2 / 51.4, p = 8 16.03 31.0 / 30.7, 64.03
+// 113 / 108.
 static bool fa_combine_held_applies(int cols, int64_t n, int dtype, int cus) {
   const int64_t tiles = n / (64 * (dtype == FA_F32 ? 4 : 8)) / ((int64_t)FA_HELD_WAVES * cus);   // per wavefront
-  if (cols >= 10) return tiles >= 16;
-  return dtype == FA_F32 && cols >= 5 && tiles >= 32;
+  if (cols >= 10) return tiles >= 10;
+  return dtype == FA_F32 && cols >= 5 && tiles >= 16;
 }
 
 hipError_t fa_launch_combine(const void* G, int64_t ldg, int p, int64_t n, int dtype, int layout,
