@@ -157,3 +157,31 @@ def test_held_aggregate_takes_no_longer_where_it_begins():
             best[n] = min(best[n], float(agg.fa_get_timings()[3]))
     agg.close()
     assert best[full - 64 * 4] <= 1.06 * best[full], best
+
+
+@pytest.mark.parametrize("dtype,p,rounds", [("f32", 12, 10), ("f32", 20, 11), ("f32", 64, 12), ("bf16", 16, 10), ("bf16", 32, 10)])
+def test_held_aggregate_beside_another_sets_solver(dtype, p, rounds):
+    """Two sets in flight, a context and a stream each: the solver of one holds a compute unit whose share of the other's
+    aggregate waits for it (the wide forms fit beside no solver).  Bit for bit what the calls return alone."""
+    from paper_2302_05865_amd import FlagAggregator
+    announce("held aggregate, two sets in flight", dtype, p, rounds)
+    n = rounds * _wave_tiles(dtype) + 37
+    sets = [_gradients(p, n, dtype, p + k) for k in range(2)]
+    for G in sets:
+        G += _gradients(1, n, dtype, 7)
+    aggs = [FlagAggregator(n_max=n, p_max=p, dtype=dtype) for _ in range(2)]
+    refs = [aggs[0].fa_aggregate(G, p // 2, 1.0, 8, 0.0).clone() for G in sets]
+    outs, streams = [torch.empty_like(r) for r in refs], [torch.cuda.Stream(), torch.cuda.Stream()]
+    for rep in range(3):
+        for o in outs:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for i in range(6):
+            with torch.cuda.stream(streams[i & 1]):
+                aggs[i & 1].fa_aggregate(sets[i & 1], p // 2, 1.0, 8, 0.0, out=outs[i & 1])
+        torch.cuda.synchronize()
+        for k in range(2):
+            assert torch.equal(outs[k], refs[k]), (rep, k)
+            assert aggs[k].fa_get_info().status == 0
+    for a in aggs:
+        a.close()
