@@ -18,7 +18,8 @@ MIXED = [3, 2, 1, 5, 4, 2, 3, 1, 2, 4, 3, 3]        # 33 columns, blocks over ti
     [1] * 64, [2] * 16, MIXED, MIXED + [15], [1, 31, 32], [7] * 9 + [1], [2, 3, 2, 3, 2, 5], [17, 1, 1]],
     ids=lambda s: "%dx%d" % (len(s), sum(s)))
 def test_wide_solve(sizes, a):
-    """Aggregate, values and objective against the fp64 definition.  The solver is fp64 throughout; the aggregate is rounded
+    """Aggregate, values and objective against the fp64 definition, from the purification (the Jacobi stand-by, which would
+    give the same answer, counts other steps).  The solver is fp64 throughout; the aggregate is rounded
     to fp32 (6e-8), and 1e-6 leaves the rounding of K's eigenvectors (1e-14 times a gap's inverse, here below 1e4) far below."""
     from paper_2302_05865_amd import FlagAggregator
     p, n, iters = sum(sizes), 1_203, 4
@@ -31,12 +32,15 @@ def test_wide_solve(sizes, a):
         ref = fa_literal(as_f64_matrix(G), m, 1.0, iters, 0.0, a=a)
     else:
         ref = fa_literal_grouped(as_f64_matrix(G), sizes, m, 1.0, iters, 0.0, a=a)
-    agg = FlagAggregator(n_max=n, p_max=p, exponent_a=a)
-    dev = to_device(G)
-    out = agg.fa_aggregate(dev, m, 1.0, iters, 0.0) if single else agg.fa_aggregate_grouped(dev, sizes, m, 1.0, iters, 0.0)
-    out, info = out.cpu().numpy().astype(np.float64), agg.fa_get_info()
-    agg.close()
+    dev, steps = to_device(G), {}
+    for solver in ("jacobi", "auto"):
+        agg = FlagAggregator(n_max=n, p_max=p, exponent_a=a, solver=solver)
+        out = agg.fa_aggregate(dev, m, 1.0, iters, 0.0) if single else agg.fa_aggregate_grouped(dev, sizes, m, 1.0, iters, 0.0)
+        out, info = out.cpu().numpy().astype(np.float64), agg.fa_get_info()
+        agg.close()
+        steps[solver] = info.sweeps
     assert info.status == 0 and info.iters_done == iters
+    assert m >= info.rank or steps["auto"] != steps["jacobi"], steps
     assert np.linalg.norm(out - ref["out"]) <= 1e-6 * np.linalg.norm(ref["out"])
     first = np.concatenate([[0], np.cumsum(sizes)[:-1]])
     assert np.allclose(np.asarray(info.v)[first], ref["v"], rtol=0, atol=1e-6)
