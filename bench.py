@@ -307,15 +307,22 @@ def main() -> int:
               (w.dtype == "bf16" or w.p > 16)
     k1_name = "fa_gram_lp_kernel" if uses_lp else "fa_gram_kernel"
     k3_name = "fa_irls16_kernel" if w.p <= 16 else "fa_irls64_kernel"
+    # which aggregate kernel ran (the rule beside it in csrc/fa_kernels.hip: whole tiles a wavefront)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = w.n // (64 * 16 // es) // (4 * cus)
+    held = tiles >= 10 if w.p >= 10 else w.dtype == "f32" and w.p >= 5 and tiles >= 16
+    k4_name = "fa_combine_held_kernel" if held else "fa_combine_kernel"
     # HBM traffic per launch as measured with rocprofv3 --pmc: read from the committed summary
-    # of this workload, if there is one (never typed in here); null otherwise
+    # of this workload, if there is one (never typed in here); null otherwise.  The summary has the aggregate pass
+    # under fa_combine_kernel, whichever of the two made it
     traffic, traffic_src = read_traffic(w.name if not args.n else None)
     # the roofline entry is for the longer of the two streaming kernels
-    dom = k1_name if kms[0] >= kms[3] else "fa_combine_kernel"
+    dom = k1_name if kms[0] >= kms[3] else k4_name
     dom_gbs = gram_gbs if dom == k1_name else comb_gbs
+    dom_traffic = traffic.get(k1_name if dom == k1_name else "fa_combine_kernel")
     roofline = {"kernel": dom, "bound": "hbm", "achieved": dom_gbs, "peak": HBM_PEAK_GBS,
-                "unit": "GB/s", "frac": dom_gbs / HBM_PEAK_GBS, "traffic": traffic.get(dom),
-                "traffic_source": traffic_src if traffic.get(dom) is not None else None}
+                "unit": "GB/s", "frac": dom_gbs / HBM_PEAK_GBS, "traffic": dom_traffic,
+                "traffic_source": traffic_src if dom_traffic is not None else None}
     # the fp64 Gram pass of a wide problem is bound by the fp64 matrix core, not by HBM: price
     # it against that roof when it is the nearer one (algorithmic flops: n p (p + 1), the
     # symmetric half of G^T G, one multiply and one add per term)
@@ -334,10 +341,8 @@ def main() -> int:
         "fa_gram_reduce_kernel": {"ms_in_step": kms_in[1]},
         k3_name: {"ms_in_step": kms_in[2], "bound": "latency (one workgroup)",
                   "purification_steps": info.sweeps},
-        "fa_combine_kernel": {"ms_in_step": kms_in[3],
-                              "algorithmic_bytes": comb_bytes, "GB/s": comb_gbs,
-                              "frac_hbm_peak": comb_gbs / HBM_PEAK_GBS,
-                              "traffic": traffic.get("fa_combine_kernel")},
+        k4_name: {"ms_in_step": kms_in[3], "algorithmic_bytes": comb_bytes, "GB/s": comb_gbs,
+                  "frac_hbm_peak": comb_gbs / HBM_PEAK_GBS, "traffic": traffic.get("fa_combine_kernel")},
     }
     whole_gbs = (gram_bytes + comb_bytes) / (ms_per_step * 1e-3) / 1e9
     # what the roofline entry does not show: the share of the step spent in the kernels that
